@@ -431,198 +431,381 @@ hipError_t launch_adam(hipStream_t st, float* w, float* m, float* v, const float
 
 // ---------------------------------------------------------------------------
 // Preconditioned COCG (FP64, all columns in lock step).  Vectors are
-// n x Bc complex FP64 blocks, row-major; a workgroup owns a contiguous row
-// range and 256 columns (thread = column); per-column partial sums go to
-// part[(block * Bc + c) * NQ + q] and are summed in a fixed order.
+// n x Bc complex FP64 blocks, row-major; a lane owns one column, L lanes a row
+// and a chunk of L columns.  Per-column partial sums go to
+// part[(q * Bc + c) * NQ + u], q the row block, and are summed in a fixed order.
 namespace {
 constexpr int kPcT = 256;
+constexpr int kPcBlocks = 1024;  // workgroups of a launch: four per CU
+
+// Work split.  The operator rows come in the caller's order, so the rows a
+// gather needs are anywhere in the block: an XCD's L2 (4 MiB) serves the
+// gathers only if it holds a whole chunk of columns, n * 16 L bytes.  Chunks
+// are dealt to the XCDs (workgroup b runs on XCD b mod 8), and each chunk's
+// rows are cut into R parts so that the units (chunk, part) fill all eight.
+//   L = 16 (256 bytes a row, four rows a wave) while a chunk fits in 3 MiB,
+//   n <= 12288, or for few columns, where 64 lanes would idle;
+//   L = 64 (a wave a row, 1 KiB a gather) above, where no chunk fits and the
+//   wider gathers use memory better.
+// Measured (knn n = 8000, 128 columns): a Clenshaw step 40.8 us with 256
+// columns a workgroup over row ranges, 18.8 us with L = 16.
+struct PcMap {
+  int L = 16, nch = 1, R = 1, nrb = 1;
+  int blocks() const { return nch * R * nrb; }  // workgroups
+  int rowblocks() const { return R * nrb; }     // partials per column
+};
+
+PcMap pc_map(int64_t n, int Bc) {
+  PcMap m;
+  m.L = (n <= 12288 || Bc <= 32) ? 16 : 64;
+  m.nch = (Bc + m.L - 1) / m.L;
+  int g = 8;
+  while (m.nch % g) g /= 2;
+  m.R = 8 / g;
+  const int sweep = kPcT / m.L;  // rows of a workgroup's step
+  const int64_t most = (n + (int64_t)sweep * m.R - 1) / ((int64_t)sweep * m.R);
+  int64_t nrb = kPcBlocks / (m.nch * m.R);
+  if (nrb > most) nrb = most;
+  m.nrb = nrb < 1 ? 1 : (int)nrb;
+  return m;
+}
 
 struct PcRows {
-  int64_t r0, r1;
+  int64_t r0, r1;  // the workgroup's rows
+  int c, q;        // this lane's column, the row block
 };
-__device__ __forceinline__ PcRows pc_rows(int64_t n) {
-  const int64_t per = (n + gridDim.x - 1) / gridDim.x;
-  const int64_t r0 = (int64_t)blockIdx.x * per;
-  return {r0 < n ? r0 : n, r0 + per < n ? r0 + per : n};
+
+template <int L>
+__device__ __forceinline__ PcRows pc_rows(int64_t n, int R, int nrb) {
+  const int b = (int)blockIdx.x, x = b & 7, i = b >> 3;
+  const int unit = (i / nrb) * 8 + x;
+  PcRows p;
+  p.q = (unit % R) * nrb + i % nrb;
+  p.c = (unit / R) * L + (int)(threadIdx.x % L);
+  const int nq = R * nrb;
+  const int64_t per = (n + nq - 1) / nq;
+  p.r0 = min(n, (int64_t)p.q * per);
+  p.r1 = min(n, p.r0 + per);
+  return p;
 }
+
 __device__ __forceinline__ cpx<double> cm(cpx<double> a, cpx<double> b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
+
+// Value of lane U of this lane's group of L lanes (a 16-lane row: the DPP
+// row broadcast; the whole wave: a lane read).
+template <int L, int U>
+__device__ __forceinline__ int pc_bcast(int v) {
+  if constexpr (L == 16)
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + U, 0xF, 0xF, false);
+  else
+    return __builtin_amdgcn_readlane(v, U);
+}
+
+template <int L, int U0, int U>
+struct PcEight {
+  __device__ __forceinline__ static void run(int mc, double mv, int* j, double* a) {
+    const long long bits = __double_as_longlong(mv);
+    j[U] = pc_bcast<L, U0 + U>(mc);
+    const int lo = pc_bcast<L, U0 + U>((int)(bits & 0xffffffffLL));
+    const int hi = pc_bcast<L, U0 + U>((int)(bits >> 32));
+    a[U] = __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+    if constexpr (U + 1 < 8) PcEight<L, U0, U + 1>::run(mc, mv, j, a);
+  }
+};
+
+// Eight entries (U0 .. U0 + 7 of the group's lanes): their rows of v gathered
+// together, then added in order.
+template <int L, int U0>
+__device__ __forceinline__ void pc_eight(int mc, double mv, const cpx<double>* __restrict__ v,
+                                         int Bc, int c, cpx<double>& acc) {
+  int j[8];
+  double a[8];
+  PcEight<L, U0, 0>::run(mc, mv, j, a);
+  cpx<double> g[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) g[u] = v[(size_t)j[u] * Bc + c];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    acc.re += a[u] * g[u].re;
+    acc.im += a[u] * g[u].im;
+  }
+}
+
+// (A v)(row, c): lane t of the row's lanes holds entry t (own row, value 0,
+// past the row's end); a wave's rows run to its longest.  Every lane of the
+// wave calls it, with a row and a column in range.
+template <int L>
+__device__ __forceinline__ cpx<double> pc_row(int64_t row, bool live, int c, int Bc,
+                                              const int* __restrict__ rowptr,
+                                              const int* __restrict__ col,
+                                              const double* __restrict__ val,
+                                              const cpx<double>* __restrict__ v) {
+  const int s = rowptr[row], len = live ? rowptr[row + 1] - s : 0;
+  int longest = __builtin_amdgcn_readfirstlane(len);
+  if constexpr (L == 16) {
+#pragma unroll
+    for (int k = 16; k < 64; k += 16) longest = max(longest, __builtin_amdgcn_readlane(len, k));
+  }
+  const int sub = (int)(threadIdx.x % L);
+  cpx<double> acc{0.0, 0.0};
+  for (int base = 0; base < longest; base += L) {
+    int mc = (int)row;
+    double mv = 0.0;
+    if (base + sub < len) {
+      mc = col[s + base + sub];
+      mv = val[s + base + sub];
+    }
+    const int m = longest - base;
+    pc_eight<L, 0>(mc, mv, v, Bc, c, acc);
+    if (m > 8) pc_eight<L, 8>(mc, mv, v, Bc, c, acc);
+    if constexpr (L == 64) {
+      if (m > 16) pc_eight<L, 16>(mc, mv, v, Bc, c, acc);
+      if (m > 24) pc_eight<L, 24>(mc, mv, v, Bc, c, acc);
+      if (m > 32) pc_eight<L, 32>(mc, mv, v, Bc, c, acc);
+      if (m > 40) pc_eight<L, 40>(mc, mv, v, Bc, c, acc);
+      if (m > 48) pc_eight<L, 48>(mc, mv, v, Bc, c, acc);
+      if (m > 56) pc_eight<L, 56>(mc, mv, v, Bc, c, acc);
+    }
+  }
+  return acc;
+}
+
+// The workgroup's per-column sums of NQ values of its lanes, at
+// part[(q Bc + c) NQ]: the lanes of a column in a tree.
+template <int L, int NQ>
+__device__ __forceinline__ void pc_put(const double (&s)[NQ], int q, int c, int Bc,
+                                       double* __restrict__ part) {
+  __shared__ double sh[kPcT * NQ];
+#pragma unroll
+  for (int u = 0; u < NQ; ++u) sh[u * kPcT + threadIdx.x] = s[u];
+  __syncthreads();
+  const int t = (int)threadIdx.x;
+#pragma unroll
+  for (int o = kPcT / 2; o >= L; o >>= 1) {
+    if (t < o) {
+#pragma unroll
+      for (int u = 0; u < NQ; ++u) sh[u * kPcT + t] += sh[u * kPcT + t + o];
+    }
+    __syncthreads();
+  }
+  if (t < L && c < Bc) {
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) part[((size_t)q * Bc + c) * NQ + u] = sh[u * kPcT + t];
+  }
+}
 }  // namespace
 
-// out = coef_c r + s * (a A bk1 + b bk1) - bk2 (bk1, bk2 nullable = 0);
-// with part, partials of r^T out.
+// out = coef_c r + s (a A g + b g) - h with g = bk1 (f1 null) or f1_c bk1, and
+// h = bk2 (f2 null) or f2_c bk2, bk2 nullable (0); with part, partials of
+// r^T out.  out may be bk2 (read and written at this lane's element only).
+template <int L>
 __global__ __launch_bounds__(kPcT) void k_pc_cheb(
-    int64_t n, const int* __restrict__ rowptr, const int* __restrict__ col,
+    int64_t n, int R, int nrb, const int* __restrict__ rowptr, const int* __restrict__ col,
     const double* __restrict__ val, double a, double b, int Bc,
     const double* __restrict__ coef /*[Bc] complex*/, double sA, const cpx<double>* __restrict__ r,
-    const cpx<double>* __restrict__ bk1, const cpx<double>* __restrict__ bk2,
-    cpx<double>* __restrict__ out, double* __restrict__ part) {
-  const int c = blockIdx.y * kPcT + threadIdx.x;
-  if (c >= Bc) return;
+    const cpx<double>* __restrict__ bk1, const double* __restrict__ f1, const cpx<double>* bk2,
+    const double* __restrict__ f2, cpx<double>* out, double* __restrict__ part) {
+  const PcRows rg = pc_rows<L>(n, R, nrb);
+  const int c = min(rg.c, Bc - 1);
   const cpx<double> cf{coef[2 * c], coef[2 * c + 1]};
-  double pr = 0.0, pi = 0.0;
-  const PcRows rg = pc_rows(n);
-  for (int64_t row = rg.r0; row < rg.r1; ++row) {
+  cpx<double> g1{1.0, 0.0}, g2{1.0, 0.0};
+  if (f1) g1 = cpx<double>{f1[2 * c], f1[2 * c + 1]};
+  if (f2) g2 = cpx<double>{f2[2 * c], f2[2 * c + 1]};
+  double pr[2] = {0.0, 0.0};
+  for (int64_t r0 = rg.r0; r0 < rg.r1; r0 += kPcT / L) {
+    const int64_t row = min(r0 + (int)(threadIdx.x / L), rg.r1 - 1);
+    const bool live = r0 + (int)(threadIdx.x / L) < rg.r1;
+    const cpx<double> ag = pc_row<L>(row, live, c, Bc, rowptr, col, val, bk1);
+    if (!live || rg.c >= Bc) continue;
     const size_t o = (size_t)row * Bc + c;
-    const cpx<double> rv = r[o];
+    const cpx<double> rv = r[o], own = bk1[o];
     cpx<double> y = cm(cf, rv);
-    if (bk1) {
-      double ar = 0.0, ai = 0.0;
-      for (int t = rowptr[row]; t < rowptr[row + 1]; ++t) {
-        const cpx<double> v = bk1[(size_t)col[t] * Bc + c];
-        ar += val[t] * v.re;
-        ai += val[t] * v.im;
-      }
-      const cpx<double> own = bk1[o];
-      y.re += sA * (a * ar + b * own.re);
-      y.im += sA * (a * ai + b * own.im);
-    }
+    cpx<double> t{sA * (a * ag.re + b * own.re), sA * (a * ag.im + b * own.im)};
+    if (f1) t = cm(g1, t);
+    y.re += t.re;
+    y.im += t.im;
     if (bk2) {
-      const cpx<double> v = bk2[o];
+      cpx<double> v = bk2[o];
+      if (f2) v = cm(g2, v);
       y.re -= v.re;
       y.im -= v.im;
     }
     out[o] = y;
-    pr += rv.re * y.re - rv.im * y.im;
-    pi += rv.re * y.im + rv.im * y.re;
+    pr[0] += rv.re * y.re - rv.im * y.im;
+    pr[1] += rv.re * y.im + rv.im * y.re;
   }
-  if (part) {
-    part[((size_t)blockIdx.x * Bc + c) * 2] = pr;
-    part[((size_t)blockIdx.x * Bc + c) * 2 + 1] = pi;
+  if (part) pc_put<L, 2>(pr, rg.q, rg.c, Bc, part);
+}
+
+// p = u + beta p (beta of an iteration's start).
+template <int L>
+__global__ __launch_bounds__(kPcT) void k_pc_pupd(int64_t n, int R, int nrb, int Bc,
+                                                  const double* __restrict__ beta,
+                                                  const cpx<double>* __restrict__ u,
+                                                  cpx<double>* __restrict__ p) {
+  const PcRows rg = pc_rows<L>(n, R, nrb);
+  if (rg.c >= Bc) return;
+  const cpx<double> bt{beta[2 * rg.c], beta[2 * rg.c + 1]};
+  for (int64_t row = rg.r0 + (int)(threadIdx.x / L); row < rg.r1; row += kPcT / L) {
+    const size_t o = (size_t)row * Bc + rg.c;
+    const cpx<double> pb = cm(bt, p[o]), uv = u[o];
+    p[o] = cpx<double>{uv.re + pb.re, uv.im + pb.im};
   }
 }
 
-// p = u + beta p (own and gathered rows; pnew written), w = z p - A p,
-// partials of p^T w.
+// w = z p - A p, partials of p^T w.
+template <int L>
 __global__ __launch_bounds__(kPcT) void k_pc_spmm(
-    int64_t n, const int* __restrict__ rowptr, const int* __restrict__ col,
+    int64_t n, int R, int nrb, const int* __restrict__ rowptr, const int* __restrict__ col,
     const double* __restrict__ val, int Bc, const double* __restrict__ zc,
-    const double* __restrict__ beta, const cpx<double>* __restrict__ u,
-    const cpx<double>* __restrict__ pold, cpx<double>* __restrict__ pnew,
-    cpx<double>* __restrict__ w, double* __restrict__ part) {
-  const int c = blockIdx.y * kPcT + threadIdx.x;
-  if (c >= Bc) return;
-  const cpx<double> bt{beta[2 * c], beta[2 * c + 1]};
+    const cpx<double>* __restrict__ p, cpx<double>* __restrict__ w, double* __restrict__ part) {
+  const PcRows rg = pc_rows<L>(n, R, nrb);
+  const int c = min(rg.c, Bc - 1);
   const cpx<double> z{zc[2 * c], zc[2 * c + 1]};
-  double mr = 0.0, mi = 0.0;
-  const PcRows rg = pc_rows(n);
-  for (int64_t row = rg.r0; row < rg.r1; ++row) {
+  double mu[2] = {0.0, 0.0};
+  for (int64_t r0 = rg.r0; r0 < rg.r1; r0 += kPcT / L) {
+    const int64_t row = min(r0 + (int)(threadIdx.x / L), rg.r1 - 1);
+    const bool live = r0 + (int)(threadIdx.x / L) < rg.r1;
+    const cpx<double> ap = pc_row<L>(row, live, c, Bc, rowptr, col, val, p);
+    if (!live || rg.c >= Bc) continue;
     const size_t o = (size_t)row * Bc + c;
-    const cpx<double> pb = cm(bt, pold[o]);
-    const cpx<double> pv{u[o].re + pb.re, u[o].im + pb.im};
-    double ar = 0.0, ai = 0.0;
-    for (int t = rowptr[row]; t < rowptr[row + 1]; ++t) {
-      const size_t q = (size_t)col[t] * Bc + c;
-      const cpx<double> pq = cm(bt, pold[q]);
-      ar += val[t] * (u[q].re + pq.re);
-      ai += val[t] * (u[q].im + pq.im);
-    }
-    const cpx<double> zp = cm(z, pv);
-    const cpx<double> wv{zp.re - ar, zp.im - ai};
-    pnew[o] = pv;
+    const cpx<double> pv = p[o], zp = cm(z, pv);
+    const cpx<double> wv{zp.re - ap.re, zp.im - ap.im};
     w[o] = wv;
-    mr += pv.re * wv.re - pv.im * wv.im;
-    mi += pv.re * wv.im + pv.im * wv.re;
+    mu[0] += pv.re * wv.re - pv.im * wv.im;
+    mu[1] += pv.re * wv.im + pv.im * wv.re;
   }
-  part[((size_t)blockIdx.x * Bc + c) * 2] = mr;
-  part[((size_t)blockIdx.x * Bc + c) * 2 + 1] = mi;
+  pc_put<L, 2>(mu, rg.q, rg.c, Bc, part);
 }
 
 // x += alpha p, r -= alpha w; partials of ||r||^2 and r^T r.
-__global__ __launch_bounds__(kPcT) void k_pc_update(int64_t n, int Bc,
-                                                   const double* __restrict__ alpha,
-                                                   cpx<double>* __restrict__ x,
-                                                   cpx<double>* __restrict__ r,
-                                                   const cpx<double>* __restrict__ p,
-                                                   const cpx<double>* __restrict__ w,
-                                                   double* __restrict__ part) {
-  const int c = blockIdx.y * kPcT + threadIdx.x;
-  if (c >= Bc) return;
-  const cpx<double> al{alpha[2 * c], alpha[2 * c + 1]};
-  double s2 = 0.0, sr = 0.0, si = 0.0;
-  const PcRows rg = pc_rows(n);
-  for (int64_t row = rg.r0; row < rg.r1; ++row) {
-    const size_t o = (size_t)row * Bc + c;
-    const cpx<double> ap = cm(al, p[o]), aw = cm(al, w[o]);
-    x[o].re += ap.re;
-    x[o].im += ap.im;
-    cpx<double> rv = r[o];
-    rv.re -= aw.re;
-    rv.im -= aw.im;
-    r[o] = rv;
-    s2 += rv.re * rv.re + rv.im * rv.im;
-    sr += rv.re * rv.re - rv.im * rv.im;
-    si += 2.0 * rv.re * rv.im;
+template <int L>
+__global__ __launch_bounds__(kPcT) void k_pc_update(int64_t n, int R, int nrb, int Bc,
+                                                    const double* __restrict__ alpha,
+                                                    cpx<double>* __restrict__ x,
+                                                    cpx<double>* __restrict__ r,
+                                                    const cpx<double>* __restrict__ p,
+                                                    const cpx<double>* __restrict__ w,
+                                                    double* __restrict__ part) {
+  const PcRows rg = pc_rows<L>(n, R, nrb);
+  double s[3] = {0.0, 0.0, 0.0};
+  if (rg.c < Bc) {
+    const cpx<double> al{alpha[2 * rg.c], alpha[2 * rg.c + 1]};
+    for (int64_t row = rg.r0 + (int)(threadIdx.x / L); row < rg.r1; row += kPcT / L) {
+      const size_t o = (size_t)row * Bc + rg.c;
+      const cpx<double> ap = cm(al, p[o]), aw = cm(al, w[o]);
+      cpx<double> xv = x[o], rv = r[o];
+      xv.re += ap.re;
+      xv.im += ap.im;
+      x[o] = xv;
+      rv.re -= aw.re;
+      rv.im -= aw.im;
+      r[o] = rv;
+      s[0] += rv.re * rv.re + rv.im * rv.im;
+      s[1] += rv.re * rv.re - rv.im * rv.im;
+      s[2] += 2.0 * rv.re * rv.im;
+    }
   }
-  part[((size_t)blockIdx.x * Bc + c) * 3] = s2;
-  part[((size_t)blockIdx.x * Bc + c) * 3 + 1] = sr;
-  part[((size_t)blockIdx.x * Bc + c) * 3 + 2] = si;
+  pc_put<L, 3>(s, rg.q, rg.c, Bc, part);
 }
 
-// Start (init) or true-residual check: for columns with flag set,
-// s = b - (zI - A) x (x = 0 at the start), r = s; partials of ||s||^2 and
-// s^T s.  Column c takes B[:, c % kb].
+// Start (init): x = 0, r = b.  Else the true-residual check of the columns
+// with flag set, s = b - (zI - A) x, r = s; a workgroup none of whose columns
+// is flagged ends at once.  Partials of ||s||^2 and s^T s.  Column c takes
+// B[:, c % kb].
+template <int L>
 __global__ __launch_bounds__(kPcT) void k_pc_resid(
-    int64_t n, const int* __restrict__ rowptr, const int* __restrict__ col,
+    int64_t n, int R, int nrb, const int* __restrict__ rowptr, const int* __restrict__ col,
     const double* __restrict__ val, int Bc, const double* __restrict__ zc,
     const double* __restrict__ B, int ldb, int kb, const int* __restrict__ flag, int init,
     cpx<double>* __restrict__ x, cpx<double>* __restrict__ r, double* __restrict__ part) {
-  const int c = blockIdx.y * kPcT + threadIdx.x;
-  if (c >= Bc) return;
-  const bool on = init || flag[c] != 0;
+  const PcRows rg = pc_rows<L>(n, R, nrb);
+  const int c = min(rg.c, Bc - 1);
+  const bool on = rg.c < Bc && (init || flag[c] != 0);
+  if (__ballot(on) == 0) return;  // the same columns in every wave: uniform
   const cpx<double> z{zc[2 * c], zc[2 * c + 1]};
-  double s2 = 0.0, sr = 0.0, si = 0.0;
-  const PcRows rg = pc_rows(n);
-  for (int64_t row = rg.r0; row < rg.r1; ++row) {
-    if (!on) break;
+  double s3[3] = {0.0, 0.0, 0.0};
+  for (int64_t r0 = rg.r0; r0 < rg.r1; r0 += kPcT / L) {
+    const int64_t row = min(r0 + (int)(threadIdx.x / L), rg.r1 - 1);
+    const bool live = r0 + (int)(threadIdx.x / L) < rg.r1;
+    cpx<double> ax{0.0, 0.0};
+    if (!init) ax = pc_row<L>(row, live, c, Bc, rowptr, col, val, x);
+    if (!live || !on) continue;
     const size_t o = (size_t)row * Bc + c;
-    const double bv = B[(size_t)row * ldb + c % kb];
-    cpx<double> s{bv, 0.0};
+    cpx<double> s{B[(size_t)row * ldb + c % kb], 0.0};
     if (init) {
       x[o] = cpx<double>{0.0, 0.0};
     } else {
-      double ar = 0.0, ai = 0.0;
-      for (int t = rowptr[row]; t < rowptr[row + 1]; ++t) {
-        const cpx<double> xv = x[(size_t)col[t] * Bc + c];
-        ar += val[t] * xv.re;
-        ai += val[t] * xv.im;
-      }
       const cpx<double> zx = cm(z, x[o]);
-      s.re -= zx.re - ar;
-      s.im -= zx.im - ai;
+      s.re -= zx.re - ax.re;
+      s.im -= zx.im - ax.im;
     }
     r[o] = s;
-    s2 += s.re * s.re + s.im * s.im;
-    sr += s.re * s.re - s.im * s.im;
-    si += 2.0 * s.re * s.im;
+    s3[0] += s.re * s.re + s.im * s.im;
+    s3[1] += s.re * s.re - s.im * s.im;
+    s3[2] += 2.0 * s.re * s.im;
   }
-  part[((size_t)blockIdx.x * Bc + c) * 3] = s2;
-  part[((size_t)blockIdx.x * Bc + c) * 3 + 1] = sr;
-  part[((size_t)blockIdx.x * Bc + c) * 3 + 2] = si;
+  pc_put<L, 3>(s3, rg.q, rg.c, Bc, part);
 }
 
-// Per-column scalars (one thread per column, fixed-order sums over blocks).
+// Per-column scalars: a workgroup sums 16 columns' partials, 16 threads a
+// column (strided, then a tree).  One thread a column over all row blocks
+// was a chain of up to 3072 dependent loads: 391 us a call (knn n = 8000, 128
+// columns), three in four of the solve; now 6.6 us.
 //  mode 0 (start):  bn2 = ||b||^2; active = bn2 > 0; done columns get x = 0
 //  mode 1 (mu):     alpha = rho / mu for active columns, else 0
 //  mode 2 (resid):  it += 1 for active; pending = ||r||^2 <= tol^2 bn2 or
 //                   it >= maxit; without a preconditioner also rho_new = r^T r
-//  mode 3 (check):  for pending: res = ||s||/||b||; done if <= tol or it >= maxit
-//  mode 4 (rho):    beta = rho_new / rho, rho = rho_new for active columns
-__global__ void k_pc_fin(int mode, int Bc, int nb, const double* __restrict__ part, int nq,
-                         PcCols cols, double tol, int maxit, int precond,
-                         int* __restrict__ counts) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= Bc) return;
-  double s[3] = {0.0, 0.0, 0.0};
-  for (int bb = 0; bb < nb; ++bb)
-    for (int q = 0; q < nq; ++q) s[q] += part[((size_t)bb * Bc + c) * nq + q];
-  const bool act = cols.active[c] != 0;
+//  mode 3 (rho):    for pending columns, from the check's partials chk:
+//                   res = ||s||/||b||; done if <= tol or it >= maxit, and
+//                   without a preconditioner rho_new = s^T s; then
+//                   beta = rho_new / rho, rho = rho_new for active columns
+constexpr int kPcFinCols = 16;
+__global__ __launch_bounds__(256) void k_pc_fin(int mode, int Bc, int nb,
+                                                const double* __restrict__ part, int nq,
+                                                const double* __restrict__ chk, PcCols cols,
+                                                double tol, int maxit, int precond) {
+  __shared__ double sh[2][3][256];
+  const int t = threadIdx.x, g = t / kPcFinCols;
+  const int c = blockIdx.x * kPcFinCols + t % kPcFinCols;
+  const bool pend = c < Bc && mode == 3 && chk && cols.pending[c] != 0;
+  double s[3] = {0.0, 0.0, 0.0}, k3[3] = {0.0, 0.0, 0.0};
+  if (c < Bc && part)
+    for (int b = g; b < nb; b += 256 / kPcFinCols)
+      for (int q = 0; q < nq; ++q) s[q] += part[((size_t)b * Bc + c) * nq + q];
+  if (pend)
+    for (int b = g; b < nb; b += 256 / kPcFinCols)
+      for (int q = 0; q < 3; ++q) k3[q] += chk[((size_t)b * Bc + c) * 3 + q];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    sh[0][q][t] = s[q];
+    sh[1][q][t] = k3[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int o = 128; o >= kPcFinCols; o >>= 1) {
+    if (t < o) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        sh[0][q][t] += sh[0][q][t + o];
+        sh[1][q][t] += sh[1][q][t + o];
+      }
+    }
+    __syncthreads();
+  }
+  if (t >= kPcFinCols || c >= Bc) return;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    s[q] = sh[0][q][t];
+    k3[q] = sh[1][q][t];
+  }
+  bool act = cols.active[c] != 0;
   switch (mode) {
     case 0:
       cols.bn2[c] = s[0];
       cols.active[c] = s[0] > 0.0 ? 1 : 0;
-      if (s[0] > 0.0) atomicAdd(&counts[1], 1);
       cols.it[c] = 0;
       cols.pending[c] = 0;
       cols.res[c] = 0.0;
@@ -642,7 +825,6 @@ __global__ void k_pc_fin(int mode, int Bc, int nb, const double* __restrict__ pa
         } else {
           cols.active[c] = 0;  // breakdown: stop the column, report its residual
           cols.pending[c] = 1;
-          atomicAdd(&counts[0], 1);
         }
       }
       cols.alpha[2 * c] = ar;
@@ -652,10 +834,7 @@ __global__ void k_pc_fin(int mode, int Bc, int nb, const double* __restrict__ pa
     case 2:
       if (act) {
         cols.it[c] += 1;
-        if (s[0] <= tol * tol * cols.bn2[c] || cols.it[c] >= maxit) {
-          cols.pending[c] = 1;
-          atomicAdd(&counts[0], 1);
-        }
+        if (s[0] <= tol * tol * cols.bn2[c] || cols.it[c] >= maxit) cols.pending[c] = 1;
         if (!precond) {
           cols.rhon[2 * c] = s[1];
           cols.rhon[2 * c + 1] = s[2];
@@ -663,18 +842,18 @@ __global__ void k_pc_fin(int mode, int Bc, int nb, const double* __restrict__ pa
       }
       break;
     case 3:
-      if (cols.pending[c]) {
+      if (pend) {
         cols.pending[c] = 0;
-        cols.res[c] = sqrt(s[0] / cols.bn2[c]);
-        if (s[0] <= tol * tol * cols.bn2[c] || cols.it[c] >= maxit) cols.active[c] = 0;
+        cols.res[c] = sqrt(k3[0] / cols.bn2[c]);
+        if (k3[0] <= tol * tol * cols.bn2[c] || cols.it[c] >= maxit) {
+          cols.active[c] = 0;
+          act = false;
+        }
         if (!precond) {  // the replaced residual's r^T r
-          cols.rhon[2 * c] = s[1];
-          cols.rhon[2 * c + 1] = s[2];
+          cols.rhon[2 * c] = k3[1];
+          cols.rhon[2 * c + 1] = k3[2];
         }
       }
-      if (cols.active[c]) atomicAdd(&counts[1], 1);
-      break;
-    case 4:
       if (precond) {
         cols.rhon[2 * c] = s[0];
         cols.rhon[2 * c + 1] = s[1];
@@ -694,107 +873,117 @@ __global__ void k_pc_fin(int mode, int Bc, int nb, const double* __restrict__ pa
   }
 }
 
-int pc_blocks(int64_t n, int num_cu) {
-  int64_t nb = (int64_t)num_cu * 4;
-  if (nb > n) nb = n;
-  return nb < 1 ? 1 : (int)nb;
+// live = columns still active.
+__global__ __launch_bounds__(256) void k_pc_live(int Bc, const int* __restrict__ active,
+                                                 int* __restrict__ live) {
+  __shared__ double sh[4];
+  double a = 0.0;
+  for (int c = threadIdx.x; c < Bc; c += 256) a += active[c] ? 1.0 : 0.0;
+  a = wave_sum(a);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
+  __syncthreads();
+  if (threadIdx.x == 0) *live = (int)((sh[0] + sh[1]) + (sh[2] + sh[3]));
 }
 
-hipError_t run_pc_cocg(hipStream_t st, const PcSolve& S) {
-  const int Bc = S.Bc;
-  const int nb = pc_blocks(S.n, S.num_cu);
-  const dim3 grid(nb, (Bc + kPcT - 1) / kPcT), blk(kPcT), fg((Bc + 255) / 256), fb(256);
+size_t pc_partial_doubles(int64_t n, int Bc) {
+  return (size_t)pc_map(n, Bc).rowblocks() * Bc * 3 * 2;
+}
+
+namespace {
+template <int L>
+hipError_t run_pc_t(hipStream_t st, const PcSolve& S, const PcMap& M) {
+  const int Bc = S.Bc, nb = M.rowblocks();
+  const dim3 grid(M.blocks()), blk(kPcT), fg((Bc + kPcFinCols - 1) / kPcFinCols), fb(256);
   const bool pre = S.coef != nullptr;
-  auto fin = [&](int mode, int nq) {
-    hipLaunchKernelGGL(k_pc_fin, fg, fb, 0, st, mode, Bc, nb, S.part, nq, S.cols, S.tol, S.maxit,
-                       pre ? 1 : 0, S.counts);
+  double* part = S.part;
+  double* chk = S.part + (size_t)nb * Bc * 3;
+  hipError_t e = hipSuccess;
+#define PCL(...)                   \
+  do {                             \
+    hipLaunchKernelGGL(__VA_ARGS__); \
+    e = hipGetLastError();         \
+    if (e != hipSuccess) return e; \
+  } while (0)
+#define PCE(expr)                  \
+  do {                             \
+    e = (expr);                    \
+    if (e != hipSuccess) return e; \
+  } while (0)
+  auto fin = [&](int mode, const double* p, int nq, const double* ck) {
+    hipLaunchKernelGGL(k_pc_fin, fg, fb, 0, st, mode, Bc, nb, p, nq, ck, S.cols, S.tol, S.maxit,
+                       pre ? 1 : 0);
     return hipGetLastError();
   };
-#define PCL(...)                     \
-  do {                               \
-    hipLaunchKernelGGL(__VA_ARGS__); \
-    hipError_t _e = hipGetLastError(); \
-    if (_e != hipSuccess) return _e; \
-  } while (0)
-#define PCE(expr)                    \
-  do {                               \
-    hipError_t _e = (expr);          \
-    if (_e != hipSuccess) return _e; \
-  } while (0)
   cpx<double>* X = S.x;
   cpx<double>* R = S.r;
   cpx<double>* U = pre ? S.u : S.r;  // no preconditioner: u is r itself
-  cpx<double>* Pa = S.p0;
-  cpx<double>* Pb = S.p1;
-  cpx<double>* W = S.w;
-  // M r by Clenshaw: b_7 = c_7 r; b_k = c_k r + 2 A^ b_{k+1} - b_{k+2}
-  // (k = 6..1); u = c_0 r + A^ b_1 - b_2; partials of r^T u
+  // u = M r by Clenshaw: b_7 = c_7 r (never stored: A^ b_7 = c_7 A^ r);
+  // b_k = c_k r + 2 A^ b_{k+1} - b_{k+2} (k = 6..1, b_k over b_{k+2});
+  // u = c_0 r + A^ b_1 - b_2; partials of r^T u
   auto apply_m = [&]() -> hipError_t {
-    cpx<double>* bb[3] = {S.t0, S.t1, S.t2};  // b_{k+2}, b_{k+1}, b_k (rotating)
     const size_t cs = (size_t)Bc * 2;
-    PCL(k_pc_cheb, grid, blk, 0, st, S.n, S.rowptr, S.col, S.val, S.a, S.b, Bc, S.coef + 7 * cs,
-        0.0, R, (const cpx<double>*)nullptr, (const cpx<double>*)nullptr, bb[1], (double*)nullptr);
-    for (int k = 6; k >= 1; --k) {
-      PCL(k_pc_cheb, grid, blk, 0, st, S.n, S.rowptr, S.col, S.val, S.a, S.b, Bc,
-          S.coef + k * cs, 2.0, R, bb[1], k == 6 ? (const cpx<double>*)nullptr : bb[0], bb[2],
-          (double*)nullptr);
-      cpx<double>* t = bb[0];
-      bb[0] = bb[1];
-      bb[1] = bb[2];
-      bb[2] = t;
+    const double* c7 = S.coef + 7 * cs;
+    const double* nof = nullptr;
+    const cpx<double>* none = nullptr;
+    cpx<double>* t[2] = {S.t0, S.t1};
+    PCL(k_pc_cheb<L>, grid, blk, 0, st, S.n, M.R, M.nrb, S.rowptr, S.col, S.val, S.a, S.b, Bc,
+        S.coef + 6 * cs, 2.0, R, (const cpx<double>*)R, c7, none, nof, t[0], (double*)nullptr);
+    for (int k = 5; k >= 0; --k) {
+      const bool second = k == 5, last = k == 0;
+      const cpx<double>* h = second ? R : t[1];
+      PCL(k_pc_cheb<L>, grid, blk, 0, st, S.n, M.R, M.nrb, S.rowptr, S.col, S.val, S.a, S.b, Bc,
+          S.coef + k * cs, last ? 1.0 : 2.0, R, (const cpx<double>*)t[0], nof, h,
+          second ? c7 : nof, last ? U : t[1], last ? part : (double*)nullptr);
+      std::swap(t[0], t[1]);
     }
-    PCL(k_pc_cheb, grid, blk, 0, st, S.n, S.rowptr, S.col, S.val, S.a, S.b, Bc, S.coef, 1.0, R,
-        bb[1], bb[0], U, S.part);
     return hipSuccess;
   };
-  // start: x = 0, r = b, u = M r, rho = r^T u
-  PCE(hipMemsetAsync(S.counts, 0, 2 * sizeof(int), st));
-  PCL(k_pc_resid, grid, blk, 0, st, S.n, S.rowptr, S.col, S.val, Bc, S.zc, S.B, S.ldb, S.kb,
-      (const int*)nullptr, 1, X, R, S.part);
-  PCE(fin(0, 3));
+  auto count = [&](int& live) -> hipError_t {
+    PCL(k_pc_live, dim3(1), dim3(256), 0, st, Bc, S.cols.active, S.counts);
+    PCE(hipMemcpyAsync(&live, S.counts, sizeof(int), hipMemcpyDeviceToHost, st));
+    return hipStreamSynchronize(st);
+  };
+  // start: x = 0, r = b, u = M r, rho = r^T u, p = 0
+  PCL(k_pc_resid<L>, grid, blk, 0, st, S.n, M.R, M.nrb, S.rowptr, S.col, S.val, Bc, S.zc, S.B,
+      S.ldb, S.kb, (const int*)nullptr, 1, X, R, part);
+  PCE(fin(0, part, 3, nullptr));
   if (pre) {
     PCE(apply_m());
-    PCE(fin(4, 2));  // rho = r^T u (beta from a zero rho_old is discarded: p_old = 0)
-    PCE(hipMemsetAsync(Pa, 0, (size_t)S.n * Bc * sizeof(cpx<double>), st));
-  } else {
-    PCE(hipMemsetAsync(Pa, 0, (size_t)S.n * Bc * sizeof(cpx<double>), st));
+    PCE(fin(3, part, 2, nullptr));  // rho = r^T u (beta from a zero rho_old is discarded: p_old = 0)
   }
-  int host_counts[2] = {0, 0};
-  PCE(hipMemcpyAsync(host_counts, S.counts, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-  PCE(hipStreamSynchronize(st));
-  int live = host_counts[1];
+  PCE(hipMemsetAsync(S.p, 0, (size_t)S.n * Bc * sizeof(cpx<double>), st));
+  int live = 0;
+  PCE(count(live));
+  // The live count comes to the host every kPcChunk iterations; columns that
+  // are done keep x and r (alpha = 0), so iterations past the last one's end
+  // change nothing.
+  constexpr int kPcChunk = 8;
   for (int it = 0; it < S.maxit && live > 0; ++it) {
-    PCE(hipMemsetAsync(S.counts, 0, 2 * sizeof(int), st));
-    PCL(k_pc_spmm, grid, blk, 0, st, S.n, S.rowptr, S.col, S.val, Bc, S.zc, S.cols.beta, U, Pa,
-        Pb, W, S.part);
-    std::swap(Pa, Pb);
-    PCE(fin(1, 2));
-    PCL(k_pc_update, grid, blk, 0, st, S.n, Bc, S.cols.alpha, X, R, Pa, W, S.part);
-    PCE(fin(2, 3));
-    PCE(hipMemcpyAsync(host_counts, S.counts, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-    PCE(hipStreamSynchronize(st));
-    if (host_counts[0] > 0) {
-      PCL(k_pc_resid, grid, blk, 0, st, S.n, S.rowptr, S.col, S.val, Bc, S.zc, S.B, S.ldb, S.kb,
-          S.cols.pending, 0, X, R, S.part);
-      PCE(fin(3, 3));
-      PCE(hipMemcpyAsync(host_counts, S.counts, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-      PCE(hipStreamSynchronize(st));
-      live = host_counts[1];
-      if (live == 0) break;
-    }
-    if (S.progress && (it + 1) % 500 == 0)
+    PCL(k_pc_pupd<L>, grid, blk, 0, st, S.n, M.R, M.nrb, Bc, S.cols.beta, (const cpx<double>*)U,
+        S.p);
+    PCL(k_pc_spmm<L>, grid, blk, 0, st, S.n, M.R, M.nrb, S.rowptr, S.col, S.val, Bc, S.zc, S.p,
+        S.w, part);
+    PCE(fin(1, part, 2, nullptr));
+    PCL(k_pc_update<L>, grid, blk, 0, st, S.n, M.R, M.nrb, Bc, S.cols.alpha, X, R, S.p, S.w, part);
+    PCE(fin(2, part, 3, nullptr));
+    PCL(k_pc_resid<L>, grid, blk, 0, st, S.n, M.R, M.nrb, S.rowptr, S.col, S.val, Bc, S.zc, S.B,
+        S.ldb, S.kb, S.cols.pending, 0, X, R, chk);
+    if (pre) PCE(apply_m());
+    PCE(fin(3, pre ? part : nullptr, 2, chk));
+    if ((it + 1) % kPcChunk == 0) PCE(count(live));
+    if (S.progress && (it + 1) % 504 == 0)
       std::fprintf(stderr, "rafeast: preconditioned COCG iteration %d, %d systems left\n", it + 1,
                    live);
-    if (pre) {
-      PCE(apply_m());
-      PCE(fin(4, 2));
-    } else {
-      PCE(fin(4, 3));
-    }
   }
 #undef PCL
 #undef PCE
   return hipSuccess;
+}
+}  // namespace
+
+hipError_t run_pc_cocg(hipStream_t st, const PcSolve& S) {
+  const PcMap M = pc_map(S.n, S.Bc);
+  return M.L == 16 ? run_pc_t<16>(st, S, M) : run_pc_t<64>(st, S, M);
 }
 
 }  // namespace rafeast

@@ -452,24 +452,21 @@ struct PcSolve {
   cpx<double>* x = nullptr;        // n x Bc complex FP64 blocks
   cpx<double>* r = nullptr;
   cpx<double>* u = nullptr;
-  cpx<double>* p0 = nullptr;
-  cpx<double>* p1 = nullptr;
+  cpx<double>* p = nullptr;
   cpx<double>* w = nullptr;
   cpx<double>* t0 = nullptr;       // Clenshaw work blocks (unused without coef)
   cpx<double>* t1 = nullptr;
-  cpx<double>* t2 = nullptr;
-  double* part = nullptr;          // pc_blocks(n, num_cu) * Bc * 3 doubles
-  int* counts = nullptr;           // [2]
+  double* part = nullptr;          // pc_partial_doubles(n, Bc)
+  int* counts = nullptr;           // [1]
   PcCols cols;
   double tol = 1e-10;
   int maxit = 20000;
-  int num_cu = 256;
-  bool progress = false;           // a line on stderr every 500 iterations
+  bool progress = false;           // a line on stderr every 504 iterations
 };
-int pc_blocks(int64_t n, int num_cu);
+size_t pc_partial_doubles(int64_t n, int Bc);
 // Preconditioned COCG (coef) or plain COCG (coef null) in FP64 on all Bc
 // columns in lock step, to true residual ||b - (zI - A) x|| <= tol ||b||.
-// Synchronises st once or twice per iteration.
+// Synchronises st every eighth iteration.
 hipError_t run_pc_cocg(hipStream_t st, const PcSolve& S);
 
 }  // namespace rafeast

@@ -1072,23 +1072,20 @@ rafeast_status pc_solve_run(rafeast_plan_s* P, int nz, const double* z, int k, c
   S.kb = k;
   S.tol = tol;
   S.maxit = maxit >= 0 ? maxit : P->prm.max_cocg;
-  S.num_cu = P->num_cu;
   S.progress = verbose_log();
   const size_t blk = (size_t)n * Bc;
   S.x = (cpx<double>*)Xout;
   HIPCHK(P, buf.get(&S.r, blk));
-  HIPCHK(P, buf.get(&S.p0, blk));
-  HIPCHK(P, buf.get(&S.p1, blk));
+  HIPCHK(P, buf.get(&S.p, blk));
   HIPCHK(P, buf.get(&S.w, blk));
   if (coef) {
     HIPCHK(P, buf.get(&S.u, blk));
     HIPCHK(P, buf.get(&S.t0, blk));
     HIPCHK(P, buf.get(&S.t1, blk));
-    HIPCHK(P, buf.get(&S.t2, blk));
   }
   double *zc = nullptr, *cf = nullptr;
-  HIPCHK(P, buf.get(&S.part, (size_t)pc_blocks(n, P->num_cu) * Bc * 3));
-  HIPCHK(P, buf.get(&S.counts, 2));
+  HIPCHK(P, buf.get(&S.part, pc_partial_doubles(n, Bc)));
+  HIPCHK(P, buf.get(&S.counts, 1));
   HIPCHK(P, buf.get(&zc, 2 * (size_t)Bc));
   HIPCHK(P, buf.get(&S.cols.active, Bc));
   HIPCHK(P, buf.get(&S.cols.it, Bc));
