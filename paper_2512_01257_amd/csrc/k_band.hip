@@ -14,21 +14,25 @@
 // positive definite real and imaginary parts, Math. Comp. 1998).
 //
 // Storage: per shift an n x (b + 1) complex array W, row r holding M(r, r - d)
-// in W[r][d], d = 0..b (d = 0 the diagonal).  After the factorization
-// W[r][0] = D(r) and W[r][d] = L(r, r - d).
+// in W[r][d], d = 0..b (d = 0 the diagonal; the plan keeps b >= 31).
 //
-// Factorization: panels of nb = 32 columns, all shifts together, two
-// launches per panel.  One workgroup per shift factorizes the panel's
-// diagonal block in LDS and gives every row below it that the band reaches
-// its multipliers (a product with the block's inverse triangle); the Schur
-// complement of the b x b
-// window below the panel, W(i, j) -= sum_k l_ik d_k l_jk, is spread over
-// many workgroups per shift in 64 x 64 blocks of 4 x 4 register tiles, so a
-// factorization's time grows with the number of shifts, not only with one
-// CU's rate.  Solves: one workgroup per (shift, group of
-// right-hand sides); blocks of 32 rows, each first reduced by the solved rows
-// within the band, then solved within the block in LDS; forward with L, then
-// D, then backward with L^T.
+// Factorization: block L D L^T in block columns (panels) of 32.  With the
+// window's rows below panel c, M21 (b x 32) and the panel's own block M11 (both
+// as updated by the earlier panels), one step is
+//   W22 -= M21 M11^{-1} M21^T,
+// so a panel needs only the inverse of its 32 x 32 block: the factors kept in W
+// are M21 itself and the lower triangle of the symmetric M11^{-1}, over M11.
+// The pivots met while inverting are those of the scalar L D L^T.  One launch
+// per panel, all shifts together: workgroups own 32 x 32 tiles of the window,
+// form -M21 M11^{-1} for their rows and update their tile on the FP64 matrix
+// cores; the workgroup of the tile that holds the next panel's block inverts
+// it at once (in registers), so no launch is serial.
+// Solves: one workgroup per (shift, two right-hand sides), blocks of 32 rows:
+//   forward  y_J = b_J - sum_{I < J} M_JI v_I, v_I = M_II^{-1} y_I,
+//   backward x_J = M_JJ^{-1} (y_J - sum_{I > J} M_IJ^T x_I),
+// with no substitution inside a block: each is products with entries of W, in
+// which the rows solved more than one block ago go first, while the block
+// before finishes.
 #include "device.h"
 #include "kernels.h"
 
@@ -40,29 +44,19 @@ namespace {
 
 typedef cpx<double> zc;
 
-__device__ __forceinline__ zc cmul(zc a, zc b) {
-  return zc{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
-}
 __device__ __forceinline__ zc csub(zc a, zc b) { return zc{a.re - b.re, a.im - b.im}; }
-__device__ __forceinline__ zc cinv(zc a) {
-  // 1 / a with the larger component scaled out (Smith's method)
-  if (fabs(a.re) >= fabs(a.im)) {
-    const double r = a.im / a.re, den = a.re + a.im * r;
-    return zc{1.0 / den, -r / den};
-  }
-  const double r = a.re / a.im, den = a.re * r + a.im;
-  return zc{r / den, -1.0 / den};
+__device__ __forceinline__ void cfma(zc& s, zc a, zc x) {
+  s.re += a.re * x.re - a.im * x.im;
+  s.im += a.re * x.im + a.im * x.re;
 }
+
 __device__ __forceinline__ bool cfinite(zc a) { return isfinite(a.re) && isfinite(a.im); }
 
-constexpr int kPanelThreads = 256;
-constexpr int kPanelRows = kPanelThreads / 2;  // rows per staged chunk (two threads each)
-constexpr int kBandMaxPanel = 32;  // panel width
+constexpr int kBB = 32;                // panel width, tile and solve block
 constexpr size_t kBandSolveRingBytes = 128 * 1024;  // LDS ring of the solve
-constexpr int kSolveThreads = 256;
-constexpr int kSolveRows = 32;  // rows per solve block
-constexpr int kSolveCols = 2;   // right-hand sides per workgroup
-constexpr int kSolveSlices = kSolveThreads / kSolveRows;  // threads per block row
+constexpr int kSolveThreads = 512;
+constexpr int kSolveCols = 2;          // right-hand sides per workgroup
+constexpr int kSolveSlices = kSolveThreads / kBB;  // threads per block row
 
 // W_j: every entry zero, then z_j on the diagonal and -A(r, c) at (r, r - c)
 // for the lower entries c <= r of the reordered CSR.  Thread per row.
@@ -84,404 +78,594 @@ __global__ __launch_bounds__(256) void k_band_assemble(int n, int b, const int* 
   }
 }
 
-// Panel c of the band LDL^T of W_j (workgroup j).  The workgroup factorizes
-// the panel's diagonal block (nb x nb, in LDS: multipliers l = m / d and the
-// rank-one updates, column by column, each thread owning fixed entries) and
-// forms the inverse of its unit lower triangle L11 (by elimination on the
-// identity, likewise).  Every row i below the block that the band reaches then
-// takes its multipliers as a product with that inverse:
-//   l_ik = (sum_{q <= k} m_iq (L11^{-1})_kq) / d_k,
-// i.e. L21 = M21 L11^{-T} D^{-1}: chunks of rows staged in LDS, two threads
-// per row with nb / 2 independent sums each.
-// info[j] = 1 + the row of a vanishing or non-finite pivot (that shift's
-// factorization stops there: later panels and updates of it return at once).
-__global__ __launch_bounds__(kPanelThreads) void k_band_panel(int n, int b, int nb, int c,
-                                                              zc* __restrict__ Wall,
-                                                              size_t stride,
-                                                              int* __restrict__ info) {
-  constexpr int L = kBandMaxPanel + 1;
-  __shared__ zc Pd[kBandMaxPanel][L];  // the diagonal block, then its factors
-  __shared__ zc Li[kBandMaxPanel][L];  // Li[k][q] = (L11^{-1})_kq, q <= k
-  __shared__ zc Dinv[kBandMaxPanel];
-  __shared__ int bad;
-  const int j = blockIdx.x;
-  if (info[j] != 0) return;
-  zc* __restrict__ W = Wall + (size_t)j * stride;
-  const int ldw = b + 1;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int e = min(c + nb, n), w = e - c, rend = min(n, e + b);
-  for (int idx = tid; idx < kBandMaxPanel * kBandMaxPanel; idx += nt) {
-    const int ii = idx / kBandMaxPanel, kk = idx % kBandMaxPanel;
-    const int i = c + ii, k = c + kk;
-    Pd[ii][kk] = (ii < w && kk <= ii && i - k <= b) ? W[(size_t)i * ldw + (i - k)] : zc{0.0, 0.0};
-  }
-  if (tid == 0) bad = 0;
-  __syncthreads();
-  // the block's pivot steps: every thread owns fixed entries of the 32 x 32
-  // block (entry t + 256 u: row (t + 256 u) / 32, column (t + 256 u) % 32)
-  static_assert(kBandMaxPanel == 32, "entry indices by shifts");
-  constexpr int kOwn = kBandMaxPanel * kBandMaxPanel / kPanelThreads;
-  static_assert(kOwn * kPanelThreads == kBandMaxPanel * kBandMaxPanel, "entry ownership");
-  int fail = 0;
-  for (int kk = 0; kk < w; ++kk) {
-    const zc d = Pd[kk][kk];
-    if (!(cfinite(d) && (d.re != 0.0 || d.im != 0.0))) {
-      fail = c + kk + 1;
-      break;  // uniform: every thread read the same pivot
-    }
-    const zc inv = cinv(d);
-    if (tid == 0) Dinv[kk] = inv;
-    if (tid > kk && tid < w) Pd[tid][kk] = cmul(Pd[tid][kk], inv);  // column kk's multipliers
-    __syncthreads();
+// The panel step.  LDS planes of kBB rows kPitch doubles apart: a fragment read
+// (16 rows x 4 columns over the wave) meets each bank pair twice, the least
+// 64 eight-byte lanes can.
+constexpr int kStepThreads = 256;
+constexpr int kPitch = 36;
+
+// Entries of W through raw buffer descriptors over the rows a workgroup's step
+// can touch: an entry outside the band is asked for at an offset past the
+// descriptor and a row past n lies past it, and both read zero, so no branch
+// stands between the loads.
+constexpr int kNoEntry = 0x7ffffff0;
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_of(const zc* __restrict__ W, int first,
+                                                          int end, int ldw) {
+  const int rows = max(0, end - first);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(W + (size_t)max(0, first) * ldw), (short)0,
+                                           rows * ldw * (int)sizeof(zc), 0x00020000);
+}
+__device__ __forceinline__ zc entry(__amdgpu_buffer_rsrc_t rs, int off) {
+  return __builtin_bit_cast(zc, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+}
+struct Plane {
+  double re[kBB][kPitch], im[kBB][kPitch];
+};
+
+// acc += A B over kBB inner indices for this wave's 16 x 16 tile: A's rows
+// r0.., B's columns c0.. (BT: B(q, c) = Bm[c][q]).  Lane l holds A(l % 16,
+// l / 16) and B(l / 16, l % 16) of a step, D(l / 16 + 4 v, l % 16).
+template <bool BT>
+__device__ __forceinline__ void tile_product(const Plane& A, const Plane& Bm, int r0, int c0,
+                                             v4d& cr, v4d& ci) {
+  const int li = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
 #pragma unroll
-    for (int u = 0; u < kOwn; ++u) {
-      const int en = tid + kPanelThreads * u, ii = en >> 5, jj = en & 31;
-      if (jj > kk && jj <= ii && ii < w)
-        Pd[ii][jj] = csub(Pd[ii][jj], cmul(cmul(Pd[ii][kk], d), Pd[jj][kk]));
-    }
-    __syncthreads();
-  }
-  if (fail) {
-    if (tid == 0) {
-      bad = 1;
-      info[j] = fail;
-    }
-  } else {
-    // L11^{-1} by elimination on the identity, column q at a time:
-    // X[i][:q] -= l_iq X[q][:q] for i > q
-#pragma unroll
-    for (int u = 0; u < kOwn; ++u) {
-      const int en = tid + kPanelThreads * u, i = en >> 5, q = en & 31;
-      Li[i][q] = zc{i == q ? 1.0 : 0.0, 0.0};
-    }
-    __syncthreads();
-    for (int q = 0; q + 1 < w; ++q) {
-#pragma unroll
-      for (int u = 0; u < kOwn; ++u) {
-        const int en = tid + kPanelThreads * u, i = en >> 5, jx = en & 31;
-        if (i > q && i < w && jx <= q) Li[i][jx] = csub(Li[i][jx], cmul(Pd[i][q], Li[q][jx]));
-      }
-      __syncthreads();
-    }
-  }
-  __syncthreads();
-  if (bad) return;
-  // the block back to W: multipliers below its diagonal, pivots on it
-  for (int idx = tid; idx < w * w; idx += nt) {
-    const int ii = idx / w, kk = idx % w, i = c + ii, k = c + kk;
-    if (kk <= ii && i - k <= b) W[(size_t)i * ldw + (i - k)] = Pd[ii][kk];
-  }
-  // rows below the block, in chunks of kPanelRows staged in LDS by coalesced
-  // loads; two threads per row, one per half of the nb sums (16 each)
-  extern __shared__ zc Rs[];  // [kPanelRows][L]
-  constexpr int H = kBandMaxPanel / 2;
-  const int rr = tid % kPanelRows, h = tid / kPanelRows;
-  for (int i0 = e; i0 < rend; i0 += kPanelRows) {
-    for (int idx = tid; idx < kPanelRows * kBandMaxPanel; idx += nt) {
-      const int r = idx / kBandMaxPanel, q = idx % kBandMaxPanel, i = i0 + r;
-      Rs[r * L + q] = (i < rend && q < w && i - (c + q) <= b) ? W[(size_t)i * ldw + (i - c - q)]
-                                                              : zc{0.0, 0.0};
-    }
-    __syncthreads();
-    const int i = i0 + rr;
-    if (i < rend) {
-      zc acc[H];
-#pragma unroll
-      for (int k = 0; k < H; ++k) acc[k] = zc{0.0, 0.0};
-      const int qend = min(w, H * (h + 1));
-#pragma unroll 1
-      for (int q = 0; q < qend; ++q) {
-        const zc mq = Rs[rr * L + q];
-#pragma unroll
-        for (int k = 0; k < H; ++k) {
-          if (H * h + k >= q) {
-            const zc l = Li[H * h + k][q];
-            acc[k].re += mq.re * l.re - mq.im * l.im;
-            acc[k].im += mq.re * l.im + mq.im * l.re;
-          }
-        }
-      }
-      zc* __restrict__ row = W + (size_t)i * ldw;
-#pragma unroll
-      for (int k = 0; k < H; ++k) {
-        const int kk = H * h + k;
-        if (kk < w && i - (c + kk) <= b) row[i - c - kk] = cmul(acc[k], Dinv[kk]);
-      }
-    }
-    __syncthreads();
+  for (int q = 0; q < kBB; q += 4) {
+    const double ar = A.re[r0 + li][q + lk], ai = A.im[r0 + li][q + lk];
+    const double br = BT ? Bm.re[c0 + li][q + lk] : Bm.re[q + lk][c0 + li];
+    const double bi = BT ? Bm.im[c0 + li][q + lk] : Bm.im[q + lk][c0 + li];
+    cr = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, cr, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, ci, 0, 0, 0);
+    cr = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, bi, cr, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, br, ci, 0, 0, 0);
   }
 }
 
-// Schur complement of the window below panel c of W_j (shift blockIdx.y):
-// W(i, jc) -= sum_{k in panel} l_ik d_k l_jc,k for e <= jc <= i < rend, in
-// 64 x 64 blocks of the window's lower triangle (blockIdx.x enumerates the
-// pairs bi >= bj), each thread a 4 x 4 tile.  The panel's multipliers of the
-// block's rows and columns and the pivots are staged in LDS.
-constexpr int kSchurBlock = 64;
-__global__ __launch_bounds__(256) void k_band_schur(int n, int b, int nb, int c,
-                                                    zc* __restrict__ Wall, size_t stride,
-                                                    const int* __restrict__ info) {
-  __shared__ zc Lr[kSchurBlock][kBandMaxPanel + 1];
-  __shared__ zc Lc[kSchurBlock][kBandMaxPanel + 1];
-  __shared__ zc Dp[kBandMaxPanel];
-  const int j = blockIdx.y;
+// 1 / d: from |d|^2 where that is far from the ends of the range (one
+// reciprocal in the chain), else with the larger component scaled out.
+__device__ __forceinline__ zc crcp(zc d) {
+  const double m = d.re * d.re + d.im * d.im;
+  if (m > 0x1.0p-900 && m < 0x1.0p+900) {
+    const double x = rcp_nr(m);
+    return zc{d.re * x, -d.im * x};
+  }
+  const zd i = zdiv_fast(zd{1.0, 0.0}, zd{d.re, d.im});
+  return zc{i.re, i.im};
+}
+
+// The 32 x 32 symmetric block held in the waves' tiles (wave w: rows 16 (w /
+// 2).., columns 16 (w % 2)..) becomes minus its inverse: the sweep operator on
+// two pivots K = (k, k + 1) at a time, with P = A_KK,
+//   A_KK = -P^{-1}, A_iK = A_iK P^{-1}, A_ij -= A_iK P^{-1} A_Kj,
+// rows k and k + 1 going round through LDS, one barrier a step.  The chain
+// write - barrier - read - 1/det - update is all the time there is; one pivot a
+// step, with two dependent reciprocals, made the launch 4.4 us longer.
+// Returns 0, or 1 + the index of a vanishing or non-finite pivot (the same in
+// every thread).
+__device__ __forceinline__ int sweep_block(v4d& cr, v4d& ci, zc (*rowbuf)[2][kBB]) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r0 = 16 * (wave >> 1), c0 = 16 * (wave & 1);
+  const int li = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
+  const int col = c0 + li;
+  int fail = 0;
+#pragma unroll 1
+  for (int h = 0; h < kBB && !fail; h += 16) {
+#pragma unroll
+    for (int kk = 0; kk < 16; kk += 2) {
+      const int k = h + kk, vk = kk >> 2;
+      zc(*rows)[kBB] = rowbuf[(kk >> 1) & 1];
+      // rows k, k + 1: element kk / 4 of two of the four lane groups of the
+      // waves with r0 == h
+      const bool mine = r0 == h && (lk >> 1) == ((kk & 3) >> 1);
+      if (mine) rows[lk & 1][col] = zc{cr[vk], ci[vk]};
+      __syncthreads();
+      const zc p11 = rows[0][k], p12 = rows[0][k + 1], p22 = rows[1][k + 1];
+      const zc a0 = rows[0][col], a1 = rows[1][col];
+      zc b0[4], b1[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        b0[v] = rows[0][r0 + lk + 4 * v];
+        b1[v] = rows[1][r0 + lk + 4 * v];
+      }
+      zc det{0.0, 0.0};
+      cfma(det, p11, p22);
+      cfma(det, zc{-p12.re, -p12.im}, p12);
+      if (!fail && !(cfinite(p11) && (p11.re != 0.0 || p11.im != 0.0))) fail = k + 1;
+      if (!fail && !(cfinite(det) && (det.re != 0.0 || det.im != 0.0))) fail = k + 2;
+      const zc q = crcp(det);
+      zc i11{0.0, 0.0}, i12{0.0, 0.0}, i22{0.0, 0.0};
+      cfma(i11, p22, q);
+      cfma(i12, zc{-p12.re, -p12.im}, q);
+      cfma(i22, p11, q);
+      // t = P^{-1} A_Kj; in a column of K, -P^{-1}'s own and a = 0, so that the
+      // one update below gives A_iK P^{-1}
+      const bool ck0 = col == k, ck1 = col == k + 1;
+      zc t0{0.0, 0.0}, t1{0.0, 0.0};
+      cfma(t0, i11, a0);
+      cfma(t0, i12, a1);
+      cfma(t1, i12, a0);
+      cfma(t1, i22, a1);
+      if (ck0) {
+        t0 = zc{-i11.re, -i11.im};
+        t1 = zc{-i12.re, -i12.im};
+      }
+      if (ck1) {
+        t0 = zc{-i12.re, -i12.im};
+        t1 = zc{-i22.re, -i22.im};
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        zc a{ck0 || ck1 ? 0.0 : cr[v], ck0 || ck1 ? 0.0 : ci[v]};
+        cfma(a, zc{-b0[v].re, -b0[v].im}, t0);
+        cfma(a, zc{-b1[v].re, -b1[v].im}, t1);
+        if (v == vk && mine) a = (lk & 1) ? t1 : t0;
+        cr[v] = a.re;
+        ci[v] = a.im;
+      }
+    }
+  }
+  return fail;
+}
+
+// Writes the lower triangle of the inverse (minus the swept block) over rows
+// e.. of W, or the failure.
+__device__ __forceinline__ void store_inverse(int n, int e, int ldw, zc* __restrict__ W,
+                                              const v4d& cr, const v4d& ci, int fail, int* info) {
+  const int wave = threadIdx.x >> 6;
+  const int li = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
+  const int j = e + 16 * (wave & 1) + li;
+  if (fail) {
+    if (threadIdx.x == 0) *info = e + fail;
+    return;
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = e + 16 * (wave >> 1) + lk + 4 * v;
+    if (i < n && j <= i) W[(size_t)i * ldw + (i - j)] = zc{-cr[v], -ci[v]};
+  }
+}
+
+// The first panel's block inverted (workgroup j: shift j).
+__global__ __launch_bounds__(kStepThreads) void k_band_first(int n, int b, zc* __restrict__ Wall,
+                                                             size_t stride,
+                                                             int* __restrict__ info) {
+  __shared__ zc rowbuf[2][2][kBB];
+  zc* __restrict__ W = Wall + (size_t)blockIdx.x * stride;
+  const int ldw = b + 1, wave = threadIdx.x >> 6;
+  const int li = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
+  const int j = 16 * (wave & 1) + li;
+  v4d cr, ci;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = 16 * (wave >> 1) + lk + 4 * v, hi = max(i, j), lo = min(i, j);
+    zc w{i == j ? 1.0 : 0.0, 0.0};  // rows past n: the identity
+    if (hi < n) w = W[(size_t)hi * ldw + (hi - lo)];
+    cr[v] = w.re;
+    ci[v] = w.im;
+  }
+  const int fail = sweep_block(cr, ci, rowbuf);
+  store_inverse(n, 0, ldw, W, cr, ci, fail, info + blockIdx.x);
+}
+
+// Panel c (rows and columns c .. c + 31, its block already inverted) applied
+// to one 32 x 32 tile of the window's lower triangle, and the next panel's
+// block inverted by the workgroup of tile (0, 0).
+// What bounds it: the chain load - product - product - 32 pivots of that
+// workgroup, once per panel.  A scalar L D L^T needed two launches a panel, one
+// workgroup a shift for the block, its inverse triangle and all multipliers
+// (90 us) and the window after it (22 us); this launch takes 17.5 us
+// (knn n = 8000, band 258, 8 shifts).
+__global__ __launch_bounds__(kStepThreads) void k_band_step(int n, int b, int c, int nz,
+                                                            zc* __restrict__ Wall, size_t stride,
+                                                            int* __restrict__ info) {
+  __shared__ Plane Pi, Ri, Ci;  // Pi: the inverse, then -(rows' M21) M11^{-1}
+  __shared__ zc rowbuf[2][2][kBB];
+  const int j = (int)blockIdx.x % nz, t = (int)blockIdx.x / nz;
   if (info[j] != 0) return;
   zc* __restrict__ W = Wall + (size_t)j * stride;
-  const int ldw = b + 1;
-  const int e = min(c + nb, n), w = e - c, rend = min(n, e + b), m = rend - e;
-  const int t = blockIdx.x;
-  int bi = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+  const int ldw = b + 1, e = c + kBB, rend = min(n, e + b);
+  int bi = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
   while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
   while (bi * (bi + 1) / 2 > t) --bi;
   const int bj = t - bi * (bi + 1) / 2;
-  const int i0 = e + bi * kSchurBlock, j0 = e + bj * kSchurBlock;
-  const int tid = threadIdx.x;
-  // multipliers l(r, k) = W[r][r - k] of the block's rows and columns
-  for (int idx = tid; idx < kSchurBlock * w; idx += 256) {
-    const int r = idx / w, kk = idx % w, k = c + kk;
-    const int ri = i0 + r, rj = j0 + r;
-    Lr[r][kk] = (ri < rend && ri - k <= b) ? W[(size_t)ri * ldw + (ri - k)] : zc{0.0, 0.0};
-    Lc[r][kk] = (rj < rend && rj - k <= b) ? W[(size_t)rj * ldw + (rj - k)] : zc{0.0, 0.0};
+  const int i0 = e + bi * kBB, j0 = e + bj * kBB;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = tid & 15, lk = (tid & 63) >> 4;
+  const int r0 = 16 * (wave >> 1), c0 = 16 * (wave & 1);
+  // the panel's inverse (mirrored) and the rows' and columns' M21
+  const int lim = max(rend, min(n, e + kBB));
+  const __amdgpu_buffer_rsrc_t rs = rows_of(W, c, lim, ldw);
+  auto at = [&](int r, int q) {  // offset of M(c + r, c + q), q <= r
+    return r - q <= b ? (r * ldw + (r - q)) * (int)sizeof(zc) : kNoEntry;
+  };
+  zc p[4], mr[4], mc[4], w[4];
+  const int jc = j0 + c0 + li;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int idx = tid + kStepThreads * u, r = idx / kBB, q = idx % kBB;
+    p[u] = entry(rs, at(max(r, q), min(r, q)));
+    mr[u] = entry(rs, at(i0 - c + r, q));
+    mc[u] = entry(rs, at(j0 - c + r, q));
   }
-  if (tid < w) Dp[tid] = W[(size_t)(c + tid) * ldw];
+  // this lane's entries of the tile (mirrored in the diagonal tiles)
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = i0 + r0 + lk + 4 * v;
+    w[v] = entry(rs, at(max(i, jc) - c, min(i, jc) - c));
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int idx = tid + kStepThreads * u, r = idx / kBB, q = idx % kBB;
+    Pi.re[r][q] = p[u].re;
+    Pi.im[r][q] = p[u].im;
+    Ri.re[r][q] = mr[u].re;
+    Ri.im[r][q] = mr[u].im;
+    Ci.re[r][q] = mc[u].re;
+    Ci.im[r][q] = mc[u].im;
+  }
+  v4d cr, ci;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = i0 + r0 + lk + 4 * v;
+    // past n the next block is the identity
+    cr[v] = w[v].re + (t == 0 && i == jc && i >= n ? 1.0 : 0.0);
+    ci[v] = w[v].im;
+  }
   __syncthreads();
-  const int ti = tid / 16, tj = tid % 16;
-  if (i0 + 4 * ti >= rend || j0 + 4 * tj > i0 + 4 * ti + 3) return;  // tile outside the triangle
-  zc acc[4][4];
+  v4d tr{0.0, 0.0, 0.0, 0.0}, ti{0.0, 0.0, 0.0, 0.0};
+  tile_product<false>(Ri, Pi, r0, c0, tr, ti);
+  __syncthreads();  // the inverse has been read
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[u][v] = zc{0.0, 0.0};
-  for (int kk = 0; kk < w; ++kk) {
-    const zc dk = Dp[kk];
-    zc a[4], bv[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a[u] = cmul(Lr[4 * ti + u][kk], dk);
-      bv[u] = Lc[4 * tj + u][kk];
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        acc[u][v].re += a[u].re * bv[v].re - a[u].im * bv[v].im;
-        acc[u][v].im += a[u].re * bv[v].im + a[u].im * bv[v].re;
-      }
+  for (int v = 0; v < 4; ++v) {
+    Pi.re[r0 + lk + 4 * v][c0 + li] = -tr[v];
+    Pi.im[r0 + lk + 4 * v][c0 + li] = -ti[v];
+  }
+  __syncthreads();
+  tile_product<true>(Pi, Ci, r0, c0, cr, ci);
+  if (t == 0) {
+    const int fail = sweep_block(cr, ci, rowbuf);
+    store_inverse(n, e, ldw, W, cr, ci, fail, info + j);
+    return;
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = i0 + 4 * ti + u, jc = j0 + 4 * tj + v;
-      if (i < rend && jc <= i) {
-        zc* p = W + (size_t)i * ldw + (i - jc);
-        *p = csub(*p, acc[u][v]);
-      }
-    }
-  (void)m;
+  for (int v = 0; v < 4; ++v) {
+    const int i = i0 + r0 + lk + 4 * v;
+    if (i < rend && jc <= i) W[(size_t)i * ldw + (i - jc)] = zc{cr[v], ci[v]};
+  }
 }
 
-// X[:, j k + c] = M_j^{-1} B[:, c] for the columns of group blockIdx.x and
-// shift blockIdx.y, with the factors of W_j.  Rows of A in the engine order
-// r map to caller rows perm[r]; B (n x k, ldb) and X (n x (nz k) complex,
-// ldx) are in caller order.  The solve runs in place in X.
+// X[:, j k + c] = M_j^{-1} B[:, c] for the columns of group g and shift j
+// (workgroup g nz + j), with the factors of W_j.  Rows of A in the engine
+// order r map to caller rows perm[r]; B (n x k, ldb) and X (n x (nz k)
+// complex, ldx) are in caller order.  The solve runs in place in X.
 // LDS: a ring of the last ring_rows solved rows of the group's columns
-// (ring_rows a power of two >= b + 32), so the band terms read solved values
-// from LDS; per block the strict lower triangle and the pivots.  Band terms:
-// eight threads per block row, the row's band streamed in order by each
-// (forward), or consecutive rows of the block on consecutive threads, which
-// makes each row's band entries contiguous across the threads (backward, L^T
-// read by columns).
-__global__ __launch_bounds__(kSolveThreads) void k_band_solve(int n, int b, const zc* __restrict__ Wall,
+// (ring_rows a power of two >= b + 32).
+// Forward: sixteen threads a block row, over consecutive entries of its band
+// row (one DPP sum); backward: the block's 32 rows on consecutive threads,
+// contiguous in each row of W below, sixteen slices of rows summed through LDS.
+// The band's reads (132 KB a block at b = 258) pace it, so they are issued a
+// block ahead: entries of rows solved more than one block ago (far) are held
+// in registers, multiplied and re-issued for the next block before the chain
+// near entries - block sum - inverse runs.  Bands past 32 + 16 kFar entries
+// read the rest as they go.  A substitution inside the block with a barrier
+// per row took 11.9 us a block and direction (knn n = 8000, 8 shifts, 64
+// columns), this 3.4 us.
+constexpr int kFar = 15;
+__global__ __launch_bounds__(kSolveThreads) void k_band_solve(int n, int b, int nz,
+                                                              const zc* __restrict__ Wall,
                                                               size_t stride,
                                                               const int* __restrict__ perm,
                                                               const double* __restrict__ B, int ldb,
                                                               int k, zc* __restrict__ X,
                                                               int64_t ldx, int ring_rows) {
   extern __shared__ zc ring[];  // [ring_rows][kSolveCols]
-  __shared__ zc yb[kSolveRows][kSolveCols];
-  __shared__ zc tri[kSolveRows][kSolveRows + 1];  // tri[r][q] = L(r0 + r, r0 + q), q < r
-  __shared__ zc piv[kSolveRows];
-  __shared__ zc part[kSolveSlices][kSolveRows][kSolveCols];
-  const int j = blockIdx.y, g = blockIdx.x;
+  __shared__ zc yb[kBB][kSolveCols];
+  __shared__ zc part[kSolveThreads / 64][kBB][kSolveCols];
+  const int j = (int)blockIdx.x % nz, g = (int)blockIdx.x / nz;
   const zc* __restrict__ W = Wall + (size_t)j * stride;
   const int ldw = b + 1, mask = ring_rows - 1;
   const int c0g = g * kSolveCols, ncol = min(kSolveCols, k - c0g);
   const int tid = threadIdx.x;
-  auto xat = [&](int r, int cc) -> zc& {
-    return X[(size_t)perm[r] * ldx + (size_t)j * k + c0g + cc];
+  const int fr = tid / kSolveSlices, fs = tid % kSolveSlices;  // row, slice (forward, inverse)
+  auto zero = [](zc (&s)[kSolveCols]) {
+#pragma unroll
+    for (int cc = 0; cc < kSolveCols; ++cc) s[cc] = zc{0.0, 0.0};
   };
-  auto stage = [&](int r0, int nr) {
-    for (int idx = tid; idx < kSolveRows * kSolveRows; idx += kSolveThreads) {
-      const int r = idx / kSolveRows, q = idx % kSolveRows;
-      zc v{0.0, 0.0};
-      if (r < nr && q < r && r - q <= b) v = W[(size_t)(r0 + r) * ldw + (r - q)];
-      tri[r][q] = v;
+  auto addr = [&](zc (&s)[kSolveCols], zc w, int q) {
+#pragma unroll
+    for (int cc = 0; cc < kSolveCols; ++cc) cfma(s[cc], w, ring[(q & mask) * kSolveCols + cc]);
+  };
+  // sums over the sixteen lanes of a row, in every lane
+  auto sum16 = [](zc (&s)[kSolveCols]) {
+#pragma unroll
+    for (int st = 0; st < 4; ++st)
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) {
+        s[cc].re += dpp_f64(s[cc].re, st);
+        s[cc].im += dpp_f64(s[cc].im, st);
+      }
+  };
+  // the inverse's entries (fr, fs), (fr, fs + 16) of the block at r0 (identity past n)
+  zc iv[2];
+  auto load_inv = [&](int r0) {
+    const __amdgpu_buffer_rsrc_t rs = rows_of(W, r0, r0 < 0 ? r0 : min(n, r0 + kBB), ldw);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int q = fs + 16 * u, hi = max(fr, q), lo = min(fr, q);
+      iv[u] = entry(rs, (hi * ldw + (hi - lo)) * (int)sizeof(zc));
     }
-    if (tid < nr) piv[tid] = W[(size_t)(r0 + tid) * ldw];
   };
-  // right-hand sides into X
-  for (int idx = tid; idx < n * ncol; idx += kSolveThreads) {
-    const int r = idx / ncol, cc = idx % ncol;
-    xat(r, cc) = zc{B[(size_t)perm[r] * ldb + c0g + cc], 0.0};
-  }
-  __syncthreads();
-  const int rr = tid % kSolveRows, h = tid / kSolveRows;  // block row, slice
-  const bool lead = tid < kSolveRows * kSolveCols;        // one thread per (row, column)
-  const int lr = tid / kSolveCols, lc = tid % kSolveCols;
+  zc far[kFar], near[2];
 
-  // forward: L y = b
-  for (int r0 = 0; r0 < n; r0 += kSolveRows) {
-    const int nr = min(kSolveRows, n - r0);
-    stage(r0, nr);
+  // ---- forward ----
+  // entry t of this thread in block r0: column q = r0 - 1 - fs - 16 t
+  auto fwd_rows = [&](int r0) { return rows_of(W, r0, min(n, r0 + kBB), ldw); };
+  auto fwd_entry = [&](__amdgpu_buffer_rsrc_t rs, int r0, int t) {
+    const int back = 1 + fs + 16 * t, d = fr + back;
+    return entry(rs, d <= b && back <= r0 ? (fr * ldw + d) * (int)sizeof(zc) : kNoEntry);
+  };
+  double bv[kSolveCols];
+  size_t xo = 0;
+  // the caller's row of a block's rows, read a block before it is used (as an
+  // address: waiting for it at once would wait for every load before it)
+  int pn = perm[min(fr, n - 1)];
+  auto load_rhs = [&](int r0) {
+    const int r = r0 + fr, pr = pn;
+    pn = perm[min(r + kBB, n - 1)];
+#pragma unroll
+    for (int cc = 0; cc < kSolveCols; ++cc) bv[cc] = 0.0;
+    if (fs == 0 && r < n) {
+      xo = (size_t)pr * ldx + (size_t)j * k + c0g;
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc)
+        if (cc < ncol) bv[cc] = B[(size_t)pr * ldb + c0g + cc];
+    }
+  };
+  // rows before the first (and, backward, after the last) are zeros
+  for (int t = tid; t < ring_rows * kSolveCols; t += kSolveThreads) ring[t] = zc{0.0, 0.0};
+#pragma unroll
+  for (int t = 0; t < kFar; ++t) far[t] = zc{0.0, 0.0};
+  near[0] = near[1] = zc{0.0, 0.0};
+  load_inv(0);
+  load_rhs(0);
+  __syncthreads();
+  for (int r0 = 0; r0 < n; r0 += kBB) {
     zc s[kSolveCols];
+    zero(s);
 #pragma unroll
-    for (int cc = 0; cc < kSolveCols; ++cc) s[cc] = zc{0.0, 0.0};
-    if (rr < nr) {
-      const int r = r0 + rr;
-      const zc* __restrict__ wrow = W + (size_t)r * ldw;
-#pragma unroll 4
-      for (int q = r0 - 1 - h; q >= max(0, r - b); q -= kSolveSlices) {
-        const zc l = wrow[r - q];
+    for (int t = 0; t < kFar; ++t) addr(s, far[t], r0 - 1 - fs - 16 * (t + 2));
+    const __amdgpu_buffer_rsrc_t rc = fwd_rows(r0);
+    for (int t = kFar + 2; 16 * t < b; t += 4) {
+      zc w[4];
 #pragma unroll
-        for (int cc = 0; cc < kSolveCols; ++cc) {
-          const zc y = ring[(q & mask) * kSolveCols + cc];
-          s[cc].re += l.re * y.re - l.im * y.im;
-          s[cc].im += l.re * y.im + l.im * y.re;
-        }
-      }
-    }
+      for (int u = 0; u < 4; ++u) w[u] = fwd_entry(rc, r0, t + u);
 #pragma unroll
-    for (int cc = 0; cc < kSolveCols; ++cc) part[h][rr][cc] = s[cc];
-    __syncthreads();
-    if (lead && lr < nr && lc < ncol) {
-      zc t = xat(r0 + lr, lc);
-      for (int q = 0; q < kSolveSlices; ++q) t = csub(t, part[q][lr][lc]);
-      yb[lr][lc] = t;
+      for (int u = 0; u < 4; ++u) addr(s, w[u], r0 - 1 - fs - 16 * (t + u));
     }
-    __syncthreads();
-    for (int kk = 0; kk < nr - 1; ++kk) {
-      // rows below kk within the block take its contribution
-      if (lead && lr > kk && lr < nr && lc < ncol)
-        yb[lr][lc] = csub(yb[lr][lc], cmul(tri[lr][kk], yb[kk][lc]));
-      __syncthreads();
+    const int rn = r0 + kBB;
+    const __amdgpu_buffer_rsrc_t rx = fwd_rows(rn);
+#pragma unroll
+    for (int t = 0; t < kFar; ++t) far[t] = fwd_entry(rx, rn, t + 2);
+    __syncthreads();  // the block before is solved
+#pragma unroll
+    for (int t = 0; t < 2; ++t) addr(s, near[t], r0 - 1 - fs - 16 * t);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) near[t] = fwd_entry(rx, rn, t);
+    sum16(s);
+    const bool row = fs == 0 && r0 + fr < n;
+    zc y[kSolveCols];
+#pragma unroll
+    for (int cc = 0; cc < kSolveCols; ++cc) y[cc] = zc{bv[cc] - s[cc].re, -s[cc].im};
+    if (fs == 0) {
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) yb[fr][cc] = y[cc];
     }
-    if (lead && lr < nr) {
-      const zc v = lc < ncol ? yb[lr][lc] : zc{0.0, 0.0};
-      ring[((r0 + lr) & mask) * kSolveCols + lc] = v;
-      if (lc < ncol) xat(r0 + lr, lc) = v;
-    }
+    const size_t xw = xo;
+    load_rhs(rn);
     __syncthreads();
+    zc v[kSolveCols];
+    zero(v);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) cfma(v[cc], iv[u], yb[fs + 16 * u][cc]);
+    load_inv(rn);
+    sum16(v);
+    if (fs == 0) {
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) ring[((r0 + fr) & mask) * kSolveCols + cc] = v[cc];
+    }
+    if (row) {
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc)
+        if (cc < ncol) X[xw + cc] = y[cc];
+    }
   }
-  // backward: L^T x = D^{-1} y, blocks from the last; the ring now takes the
-  // solved x of the rows after the block
-  for (int r1 = n; r1 > 0; r1 -= kSolveRows) {
-    const int r0 = max(0, r1 - kSolveRows), nr = r1 - r0;
-    stage(r0, nr);
+
+  // ---- backward, blocks from the last; the ring takes the solved x ----
+  const int br = tid % kBB, bs = tid / kBB;  // row, slice
+  auto bwd_rows = [&](int r0) {  // none before the first block
+    return rows_of(W, r0 + kBB, r0 < 0 ? r0 : min(n, r0 + kBB + b), ldw);
+  };
+  auto bwd_entry = [&](__amdgpu_buffer_rsrc_t rs, int t) {
+    const int i = bs + kSolveSlices * t, d = kBB + i - br;  // row r0 + 32 + i
+    return entry(rs, d <= b ? (i * ldw + d) * (int)sizeof(zc) : kNoEntry);
+  };
+  zc yv[kSolveCols];
+  const int last = (n - 1) / kBB * kBB;
+  pn = perm[min(last + fr, n - 1)];
+  auto load_y = [&](int r0) {
+    const int r = r0 + fr, pr = pn;
+    pn = perm[max(0, r - kBB)];
+#pragma unroll
+    for (int cc = 0; cc < kSolveCols; ++cc) yv[cc] = zc{0.0, 0.0};
+    if (fs == 0 && r0 >= 0 && r < n) {
+      xo = (size_t)pr * ldx + (size_t)j * k + c0g;
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc)
+        if (cc < ncol) yv[cc] = X[xo + cc];
+    }
+  };
+  __syncthreads();
+  for (int t = tid; t < ring_rows * kSolveCols; t += kSolveThreads) ring[t] = zc{0.0, 0.0};
+#pragma unroll
+  for (int t = 0; t < kFar; ++t) far[t] = zc{0.0, 0.0};
+  near[0] = near[1] = zc{0.0, 0.0};
+  load_inv(last);
+  load_y(last);
+  __syncthreads();
+  for (int r0 = last; r0 >= 0; r0 -= kBB) {
     zc s[kSolveCols];
+    zero(s);
+    const int ib = r0 + kBB + bs;
 #pragma unroll
-    for (int cc = 0; cc < kSolveCols; ++cc) s[cc] = zc{0.0, 0.0};
-    if (rr < nr) {
-      const int r = r0 + rr;
-      const int hi = min(n - 1, r + b);
-#pragma unroll 4
-      for (int i = r1 + h; i <= hi; i += kSolveSlices) {
-        const zc l = W[(size_t)i * ldw + (i - r)];
+    for (int t = 0; t < kFar; ++t) addr(s, far[t], ib + kSolveSlices * (t + 2));
+    const __amdgpu_buffer_rsrc_t rc = bwd_rows(r0);
+    for (int t = kFar + 2; kSolveSlices * t < b; t += 4) {
+      zc w[4];
 #pragma unroll
-        for (int cc = 0; cc < kSolveCols; ++cc) {
-          const zc x = ring[(i & mask) * kSolveCols + cc];
-          s[cc].re += l.re * x.re - l.im * x.im;
-          s[cc].im += l.re * x.im + l.im * x.re;
-        }
+      for (int u = 0; u < 4; ++u) w[u] = bwd_entry(rc, t + u);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) addr(s, w[u], ib + kSolveSlices * (t + u));
+    }
+    const int rn = r0 - kBB;
+    const __amdgpu_buffer_rsrc_t rx = bwd_rows(rn);
+#pragma unroll
+    for (int t = 0; t < kFar; ++t) far[t] = bwd_entry(rx, t + 2);
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 2; ++t) addr(s, near[t], ib + kSolveSlices * t);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) near[t] = bwd_entry(rx, t);
+    // the wave's two slices of a row are 32 lanes apart
+#pragma unroll
+    for (int cc = 0; cc < kSolveCols; ++cc) {
+      s[cc].re += __shfl_xor(s[cc].re, 32, 64);
+      s[cc].im += __shfl_xor(s[cc].im, 32, 64);
+    }
+    if ((tid & 32) == 0) {
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) part[tid >> 6][br][cc] = s[cc];
+    }
+    __syncthreads();
+    if (fs == 0) {
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) {
+        zc y = yv[cc];
+#pragma unroll
+        for (int w = 0; w < kSolveThreads / 64; ++w) y = csub(y, part[w][fr][cc]);
+        yb[fr][cc] = y;
       }
     }
+    const bool row = fs == 0 && r0 + fr < n;
+    const size_t xw = xo;
+    load_y(rn);
+    __syncthreads();
+    zc v[kSolveCols];
+    zero(v);
 #pragma unroll
-    for (int cc = 0; cc < kSolveCols; ++cc) part[h][rr][cc] = s[cc];
-    __syncthreads();
-    if (lead && lr < nr && lc < ncol) {
-      zc t = cmul(xat(r0 + lr, lc), cinv(piv[lr]));
-      for (int q = 0; q < kSolveSlices; ++q) t = csub(t, part[q][lr][lc]);
-      yb[lr][lc] = t;
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) cfma(v[cc], iv[u], yb[fs + 16 * u][cc]);
+    load_inv(rn);
+    sum16(v);
+    if (fs == 0) {
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc) ring[((r0 + fr) & mask) * kSolveCols + cc] = v[cc];
     }
-    __syncthreads();
-    for (int kk = nr - 1; kk > 0; --kk) {
-      if (lead && lr < kk && lc < ncol)
-        yb[lr][lc] = csub(yb[lr][lc], cmul(tri[kk][lr], yb[kk][lc]));
-      __syncthreads();
+    if (row) {
+#pragma unroll
+      for (int cc = 0; cc < kSolveCols; ++cc)
+        if (cc < ncol) X[xw + cc] = v[cc];
     }
-    if (lead && lr < nr) {
-      const zc v = lc < ncol ? yb[lr][lc] : zc{0.0, 0.0};
-      ring[((r0 + lr) & mask) * kSolveCols + lc] = v;
-      if (lc < ncol) xat(r0 + lr, lc) = v;
-    }
-    __syncthreads();
   }
 }
 
-// resid[j k + c] = ||B_c - (z_j I - A) X_{j,c}|| / ||B_c|| (0 for B_c = 0),
-// in FP64 with A in caller order; one workgroup per system.
+// Partials of |b - (z_j I - A) x|^2 and |b|^2, in FP64 with A in caller order:
+// a lane per system, so a row of X is read by consecutive lanes (a workgroup
+// per system read it one column at a time: 993 us at n = 8000, 512 systems;
+// now 112 us).
 __global__ __launch_bounds__(256) void k_band_resid(int n, const int* __restrict__ rowptr,
                                                     const int* __restrict__ col,
                                                     const double* __restrict__ val,
                                                     const double* __restrict__ z,
                                                     const double* __restrict__ B, int ldb, int k,
-                                                    const zc* __restrict__ X, int64_t ldx,
-                                                    double* __restrict__ resid) {
-  const int sys = blockIdx.x, j = sys / k, c = sys % k;
+                                                    int nsys, const zc* __restrict__ X,
+                                                    int64_t ldx, double* __restrict__ part) {
+  __shared__ double red[2][256];
+  const int lane = threadIdx.x & 63, wv = wave_id();
+  const int sys = blockIdx.y * 64 + lane, sc = min(sys, nsys - 1), j = sc / k, c = sc % k;
   const double zr = z[2 * j], zi = z[2 * j + 1];
   double rr = 0.0, bb = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) {
+  for (int i = blockIdx.x * 4 + wv; i < n; i += gridDim.x * 4) {
+    const int s = rowptr[i], e = rowptr[i + 1];
     double ar = 0.0, ai = 0.0;
-    for (int t = rowptr[i]; t < rowptr[i + 1]; ++t) {
-      const zc x = X[(size_t)col[t] * ldx + sys];
-      ar += val[t] * x.re;
-      ai += val[t] * x.im;
+    for (int t = s; t < e; t += 4) {
+      zc x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = X[(size_t)col[min(t + u, e - 1)] * ldx + sc];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double a = t + u < e ? val[t + u] : 0.0;
+        ar += a * x[u].re;
+        ai += a * x[u].im;
+      }
     }
-    const zc x = X[(size_t)i * ldx + sys];
+    const zc x = X[(size_t)i * ldx + sc];
     const double bi = B[(size_t)i * ldb + c];
     const double sr = bi - (zr * x.re - zi * x.im - ar);
     const double si = -(zr * x.im + zi * x.re - ai);
     rr += sr * sr + si * si;
     bb += bi * bi;
   }
-  __shared__ double red[2][4];
-  rr = wave_sum_f64(rr);
-  bb = wave_sum_f64(bb);
-  const int wv = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    red[0][wv] = rr;
-    red[1][wv] = bb;
-  }
+  red[0][threadIdx.x] = rr;
+  red[1][threadIdx.x] = bb;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    const double r2 = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-    const double b2 = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-    resid[sys] = b2 > 0.0 ? sqrt(r2 / b2) : 0.0;
+  if (wv == 0 && sys < nsys) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      part[((size_t)blockIdx.x * nsys + sys) * 2 + q] =
+          (red[q][lane] + red[q][64 + lane]) + (red[q][128 + lane] + red[q][192 + lane]);
   }
+}
+
+// resid[j k + c] = ||B_c - (z_j I - A) X_{j,c}|| / ||B_c|| (0 for B_c = 0): a
+// workgroup sums sixteen systems' partials, sixteen threads a system.
+__global__ __launch_bounds__(256) void k_band_resid_fin(int nsys, int nb,
+                                                        const double* __restrict__ part,
+                                                        double* __restrict__ resid) {
+  __shared__ double red[2][256];
+  const int t = threadIdx.x, sys = blockIdx.x * 16 + t % 16;
+  double s[2] = {0.0, 0.0};
+  if (sys < nsys)
+    for (int b = t / 16; b < nb; b += 16)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) s[q] += part[((size_t)b * nsys + sys) * 2 + q];
+  red[0][t] = s[0];
+  red[1][t] = s[1];
+  __syncthreads();
+  if (t >= 16 || sys >= nsys) return;
+  s[0] = s[1] = 0.0;
+  for (int g = 0; g < 16; ++g) {
+    s[0] += red[0][16 * g + t];
+    s[1] += red[1][16 * g + t];
+  }
+  resid[sys] = s[1] > 0.0 ? sqrt(s[0] / s[1]) : 0.0;
 }
 
 }  // namespace
 
-int band_panel_width(int b) {
-  (void)b;
-  return kBandMaxPanel;
-}
-
-size_t band_lds_bytes(int b) {
-  (void)b;
-  // the panel kernel's dynamic LDS: a chunk of rows below the block
-  return (size_t)kPanelRows * (kBandMaxPanel + 1) * sizeof(zc);
-}
-
 int band_solve_ring_rows(int b) {
-  int rows = kSolveRows;
-  while (rows < b + kSolveRows) rows *= 2;
+  int rows = kBB;
+  while (rows < b + kBB) rows *= 2;
   return rows;
 }
 
+int band_width(int b) { return b < kBB - 1 ? kBB - 1 : b; }
+
 bool band_supported(int b) {
-  return band_lds_bytes(b) <= 160 * 1024 &&
-         (size_t)band_solve_ring_rows(b) * kSolveCols * sizeof(zc) <= kBandSolveRingBytes;
+  return (size_t)band_solve_ring_rows(b) * kSolveCols * sizeof(zc) <= kBandSolveRingBytes;
 }
 
 hipError_t band_assemble(hipStream_t st, int n, int b, const int* rowptr, const int* col,
@@ -495,25 +679,16 @@ hipError_t band_assemble(hipStream_t st, int n, int b, const int* rowptr, const 
 
 hipError_t band_factor(hipStream_t st, int n, int b, int nz, cpx<double>* W, int* info) {
   if (n <= 0 || nz <= 0) return hipSuccess;
-  const int nb = band_panel_width(b);
-  const size_t lds = band_lds_bytes(b);
-  hipError_t e = hipFuncSetAttribute((const void*)k_band_panel,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  e = hipMemsetAsync(info, 0, nz * sizeof(int), st);
+  if (b < kBB - 1) return hipErrorInvalidValue;
+  hipError_t e = hipMemsetAsync(info, 0, nz * sizeof(int), st);
   if (e != hipSuccess) return e;
   const size_t stride = (size_t)n * (b + 1);
-  // panel by panel, all shifts together: the panel (one workgroup per
-  // shift), then its window's Schur complement over many workgroups
-  for (int c = 0; c < n; c += nb) {
-    hipLaunchKernelGGL(k_band_panel, dim3(nz), dim3(kPanelThreads), lds, st, n, b, nb, c, W,
-                       stride, info);
-    const int end = std::min(c + nb, n), m = std::min(n, end + b) - end;
-    if (m > 0) {
-      const int mb = (m + kSchurBlock - 1) / kSchurBlock;
-      hipLaunchKernelGGL(k_band_schur, dim3(mb * (mb + 1) / 2, nz), dim3(256), 0, st, n, b, nb,
-                         c, W, stride, info);
-    }
+  hipLaunchKernelGGL(k_band_first, dim3(nz), dim3(kStepThreads), 0, st, n, b, W, stride, info);
+  // shift j of workgroup id % nz: with eight shifts a window stays in one XCD's L2
+  for (int c = 0; c + kBB < n; c += kBB) {
+    const int m = std::min(n, c + kBB + b) - (c + kBB), mb = (m + kBB - 1) / kBB;
+    hipLaunchKernelGGL(k_band_step, dim3(nz * (mb * (mb + 1) / 2)), dim3(kStepThreads), 0, st, n,
+                       b, c, nz, W, stride, info);
   }
   return hipGetLastError();
 }
@@ -527,18 +702,29 @@ hipError_t band_solve(hipStream_t st, int n, int b, int nz, const cpx<double>* W
   hipError_t e = hipFuncSetAttribute((const void*)k_band_solve,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  dim3 grid((k + kSolveCols - 1) / kSolveCols, nz);
-  hipLaunchKernelGGL(k_band_solve, grid, dim3(kSolveThreads), lds, st, n, b, W,
-                     (size_t)n * (b + 1), perm, B, ldb, k, X, ldx, ring);
+  hipLaunchKernelGGL(k_band_solve, dim3((k + kSolveCols - 1) / kSolveCols * nz),
+                     dim3(kSolveThreads), lds, st, n, b, nz, W, (size_t)n * (b + 1), perm, B, ldb,
+                     k, X, ldx, ring);
   return hipGetLastError();
 }
 
+namespace {
+int resid_blocks(int n) { return std::min(256, (n + 3) / 4); }
+}  // namespace
+
+size_t band_resid_doubles(int n, int nsys) { return (size_t)resid_blocks(n) * nsys * 2; }
+
 hipError_t band_resid(hipStream_t st, int n, const int* rowptr, const int* col, const double* val,
                       int nz, const double* z, const double* B, int ldb, int k,
-                      const cpx<double>* X, int64_t ldx, double* resid) {
+                      const cpx<double>* X, int64_t ldx, double* part, double* resid) {
   if (n <= 0 || nz <= 0 || k <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_band_resid, dim3(nz * k), dim3(256), 0, st, n, rowptr, col, val, z, B,
-                     ldb, k, X, ldx, resid);
+  const int nsys = nz * k, nb = resid_blocks(n);
+  hipLaunchKernelGGL(k_band_resid, dim3(nb, (nsys + 63) / 64), dim3(256), 0, st, n, rowptr, col,
+                     val, z, B, ldb, k, nsys, X, ldx, part);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_band_resid_fin, dim3((nsys + 15) / 16), dim3(256), 0, st, nsys, nb, part,
+                     resid);
   return hipGetLastError();
 }
 

@@ -1983,12 +1983,13 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
         int b = 0;
         for (int64_t r = 0; r < n; ++r)
           if (srp[r + 1] > srp[r]) b = std::max<int>(b, (int)r - scl[srp[r]]);
+        b = band_width(b);
         P->band_b = b;
         if (!band_supported(b))
           return bail(fail(P, RAFEAST_UNSUPPORTED,
                            "bandwidth " + std::to_string(b) +
                                " of the reordered matrix exceeds the direct engine's LDS "
-                               "(the factorization's panel, the solve's ring of b + 32 rows)"));
+                               "(the solve's ring of b + 32 rows)"));
         const size_t bytes = (size_t)P->nc * (size_t)n * (size_t)(b + 1) * sizeof(cpx<double>);
         size_t fr = 0, tot = 0;
         PCHK(hipMemGetInfo(&fr, &tot));
@@ -2470,8 +2471,11 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       const int n = (int)P->n, b = P->band_b;
       cpx<double>* Wb = nullptr;
       int* d_info = nullptr;
+      double* d_part = nullptr;
       e = hipMalloc(&Wb, (size_t)nz * n * (b + 1) * sizeof(cpx<double>));
       if (e == hipSuccess) e = hipMalloc(&d_info, nz * sizeof(int));
+      if (e == hipSuccess)
+        e = hipMalloc(&d_part, band_resid_doubles(n, nitems) * sizeof(double));
       if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve band workspace");
       if (s == RAFEAST_OK) {
         e = band_assemble(P->st, n, b, P->d_srow, P->d_scol, P->d_sv64, nz, d_z, Wb);
@@ -2494,12 +2498,13 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
                          static_cast<cpx<double>*>(X), (int64_t)nz * k);
         if (e == hipSuccess)
           e = band_resid(P->st, n, P->d_rowptr, P->d_col, P->d_val, nz, d_z, B, ldb, k,
-                         static_cast<const cpx<double>*>(X), (int64_t)nz * k, d_rs);
+                         static_cast<const cpx<double>*>(X), (int64_t)nz * k, d_part, d_rs);
         if (e == hipSuccess) e = hipStreamSynchronize(P->st);
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
       }
       if (Wb) (void)hipFree(Wb);
       if (d_info) (void)hipFree(d_info);
+      if (d_part) (void)hipFree(d_part);
     } else if (P->engine == RAFEAST_ENGINE_MULTISHIFT) {
       std::vector<void*> bufs;
       MsWork W;
