@@ -322,6 +322,25 @@ hipError_t launch_tiles(hipStream_t st, bool acol, bool vec, dim3 grid, int M, i
   return hipGetLastError();
 }
 
+// MFMA column tiles per wave: up to four in FP32 (128-wide blocks), up to
+// two in FP64 (64-wide blocks: half the accumulators, so two waves fit a
+// SIMD); narrow products (the few live columns at the end of a solve) take
+// one or two, so a block does not compute many columns it throws away
+int gemm_tn(bool f64, int N) {
+  const int most = f64 ? RAFEAST_GEMM_TN64 : RAFEAST_GEMM_TN32;
+  return N <= 32 ? 1 : (N <= 64 || most == 2) ? 2 : 4;
+}
+
+// Chunks of the inner dimension, given room for most of them: two workgroups
+// per CU, chunks at least 512 long.
+int gemm_chunks(bool f64, int M, int N, int K, size_t most) {
+  if (K < 1024) return 1;
+  const int BN = 32 * gemm_tn(f64, N);
+  const int tiles = ((M + kBM - 1) / kBM) * ((N + BN - 1) / BN);
+  const int want = (512 + tiles - 1) / tiles;
+  return std::max(1, std::min(want, std::min(K / 512, (int)std::min<size_t>(most, 64))));
+}
+
 // C = alpha op(A) B + beta C.  work (nullable, work_elems elements) holds the
 // chunk slabs: the inner dimension is split when the output has fewer tiles
 // than two per CU and the chunks stay at least 512 long.
@@ -330,24 +349,14 @@ hipError_t gemm(hipStream_t st, bool acol, int M, int N, int K, const T* A, int6
                 const T* B, int64_t ldb, T* C, int64_t ldc, T alpha, T beta, T* work,
                 size_t work_elems) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  // MFMA column tiles per wave: up to four in FP32 (128-wide blocks), up to
-  // two in FP64 (64-wide blocks: half the accumulators, so two waves fit a
-  // SIMD); narrow products (the few live columns at the end of a solve) take
-  // one or two, so a block does not compute many columns it throws away
-  constexpr int TNmax = sizeof(T) == 8 ? RAFEAST_GEMM_TN64 : RAFEAST_GEMM_TN32;
-  const int TN = N <= 32 ? 1 : (N <= 64 || TNmax == 2) ? 2 : 4;
+  constexpr bool f64 = sizeof(T) == 8;
+  constexpr int TNmax = f64 ? RAFEAST_GEMM_TN64 : RAFEAST_GEMM_TN32;
+  const int TN = gemm_tn(f64, N);
   const int BN = 32 * TN;
   // inner indices per LDS step (FP64: 16, so that the staging buffers leave
   // room for two workgroups per CU)
   constexpr int BK = sizeof(T) == 8 ? RAFEAST_GEMM_BK64 : RAFEAST_GEMM_BK32;
-  const int tiles = ((M + kBM - 1) / kBM) * ((N + BN - 1) / BN);
-  int S = 1;
-  if (work && K >= 1024) {
-    const int want = (512 + tiles - 1) / tiles;
-    const int by_len = K / 512;
-    const int by_room = (int)std::min<size_t>(work_elems / ((size_t)M * N), 64);
-    S = std::max(1, std::min(want, std::min(by_len, by_room)));
-  }
+  int S = work ? gemm_chunks(f64, M, N, K, work_elems / ((size_t)M * N)) : 1;
   int kc = (K + S - 1) / S;
   kc = (kc + BK - 1) / BK * BK;
   if (K <= 0) kc = BK;
@@ -423,6 +432,12 @@ hipError_t dense_axpy(hipStream_t st, int64_t count, double a, const double* x, 
   hipLaunchKernelGGL(k_axpy, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st, count, a,
                      x, y);
   return hipGetLastError();
+}
+
+size_t gemm_work_elems(bool f64, int M, int N, int K) {
+  if (M <= 0 || N <= 0 || K <= 0) return 0;
+  const int S = gemm_chunks(f64, M, N, K, 64);
+  return S > 1 ? (size_t)S * M * N : 0;
 }
 
 hipError_t launch_gemm_f64(hipStream_t st, bool acol, int M, int N, int K, const double* A,

@@ -223,6 +223,8 @@ hipError_t dense_axpy(hipStream_t st, int64_t count, double a, const double* x, 
 // C (M x N, row-major, ldc) = alpha op(A) B + beta C on the matrix cores;
 // op(A)(i, k) = A[k lda + i] when acol, else A[i lda + k]; B (K x N) by rows.
 // work (nullable): room for inner-dimension chunk slabs (work_elems elements).
+// gemm_work_elems: the elements that the launchers use for it (0: none).
+size_t gemm_work_elems(bool f64, int M, int N, int K);
 hipError_t launch_gemm_f64(hipStream_t st, bool acol, int M, int N, int K, const double* A,
                            int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc,
                            double alpha, double beta, double* work, size_t work_elems);

@@ -12,9 +12,12 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "../../include/rafeast.h"
@@ -38,6 +41,75 @@ constexpr double kSpuriousGain = 0.25;
 constexpr size_t kBatchWorkers = 8;
 
 }  // namespace
+
+// Device workspaces of finished calls, kept for the next one: hipMalloc and
+// hipFree of a step-level call's blocks cost more than its kernels (a product
+// of 8192 x 480 x 8192 in FP32: 7.1 ms, of which 0.64 ms in kernels).  A block
+// goes back only when the call that used it has waited for its work, or to a
+// caller on the same stream.  At most `most` bytes are kept, the rest is freed;
+// an allocation that fails is tried again with everything kept given back.
+class WorkCache {
+ public:
+  explicit WorkCache(size_t most) : most_(most) {}
+  ~WorkCache() { clear(); }
+  // bytes in: wanted, out: the block's size
+  hipError_t get(void** q, size_t& bytes) {
+    bytes = (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      size_t best = idle_.size();
+      for (size_t i = 0; i < idle_.size(); ++i)
+        if (idle_[i].bytes >= bytes && idle_[i].bytes <= 2 * bytes &&
+            (best == idle_.size() || idle_[i].bytes < idle_[best].bytes))
+          best = i;
+      if (best < idle_.size()) {
+        *q = idle_[best].p;
+        bytes = idle_[best].bytes;
+        held_ -= bytes;
+        idle_.erase(idle_.begin() + best);
+        return hipSuccess;
+      }
+    }
+    hipError_t e = hipMalloc(q, bytes);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      clear();
+      e = hipMalloc(q, bytes);
+    }
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      *q = nullptr;
+    }
+    return e;
+  }
+  void put(void* q, size_t bytes) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (held_ + bytes <= most_) {
+        idle_.push_back({q, bytes});
+        held_ += bytes;
+        return;
+      }
+    }
+    (void)hipFree(q);
+  }
+  void clear() {
+    std::lock_guard<std::mutex> lock(mu_);
+    for (const Block& b : idle_) (void)hipFree(b.p);
+    idle_.clear();
+    held_ = 0;
+  }
+
+ private:
+  struct Block {
+    void* p;
+    size_t bytes;
+  };
+  std::mutex mu_;
+  std::vector<Block> idle_;
+  size_t held_ = 0;
+  const size_t most_;
+};
 
 struct rafeast_plan_s {
   rafeast_params prm{};
@@ -145,6 +217,7 @@ struct rafeast_plan_s {
   std::vector<double> last_theta;
   std::string err;
   hipEvent_t ev[8] = {};
+  WorkCache cache{size_t(1) << 30};  // step-level calls' workspaces
 };
 
 // A batch: member plans sharing one stream, and the state of the shared
@@ -408,6 +481,49 @@ rafeast_status validate_csr(const rafeast_csr* A, int64_t& nnz, double& anorm, d
   return RAFEAST_OK;
 }
 
+// A call's device workspaces, given back to the plan's cache together.
+struct DevBuf {
+  WorkCache& cache;
+  std::vector<std::pair<void*, size_t>> blocks;
+  explicit DevBuf(rafeast_plan_s* P) : cache(P->cache) {}
+  explicit DevBuf(WorkCache& c) : cache(c) {}
+  DevBuf(const DevBuf&) = delete;
+  DevBuf& operator=(const DevBuf&) = delete;
+  ~DevBuf() {
+    for (const auto& b : blocks) cache.put(b.first, b.second);
+  }
+  template <typename T>
+  hipError_t get(T** p, size_t count) {
+    void* q = nullptr;
+    size_t bytes = count * sizeof(T);
+    const hipError_t e = cache.get(&q, bytes);
+    if (e == hipSuccess) blocks.emplace_back(q, bytes);
+    *p = (T*)q;
+    return e;
+  }
+};
+
+// Workspaces of rafeast_gemm, which takes no plan: per device, shared by all
+// threads (a block is one call's at a time), at most 64 MiB kept, given back
+// when the process's last plan goes.
+std::mutex g_gemm_mu;
+std::map<int, std::shared_ptr<WorkCache>> g_gemm_cache;
+int g_plans = 0;
+
+std::shared_ptr<WorkCache> gemm_cache(int dev) {
+  std::lock_guard<std::mutex> lock(g_gemm_mu);
+  std::shared_ptr<WorkCache>& c = g_gemm_cache[dev];
+  if (!c) c = std::make_shared<WorkCache>(size_t(64) << 20);
+  return c;
+}
+
+void count_plan(int d) {
+  std::lock_guard<std::mutex> lock(g_gemm_mu);
+  g_plans += d;
+  if (g_plans == 0)
+    for (auto& c : g_gemm_cache) c.second->clear();
+}
+
 template <typename T>
 rafeast_status dalloc(rafeast_plan_s* P, T** p, size_t count, const char* what) {
   if (count == 0) count = 1;
@@ -439,6 +555,7 @@ void free_plan(rafeast_plan_s* P) {
     if (e) (void)hipEventDestroy(e);
   if (P->own_stream && P->st) (void)hipStreamDestroy(P->st);
   delete P;
+  count_plan(-1);
 }
 
 // A dense operator handed to rafeast_plan_dense (kind 1: K, n x n) or
@@ -609,19 +726,26 @@ std::vector<int> rcm_order(int64_t n, const std::vector<int>& rp, const std::vec
   return order;
 }
 
+// A workspace buffer of the plan's own (freed with it), or of one call (tmp).
+rafeast_status work_alloc(rafeast_plan_s* P, DevBuf* tmp, void** ptr, size_t bytes,
+                          const char* what) {
+  const hipError_t e =
+      tmp ? tmp->get((char**)ptr, bytes) : hipMalloc(ptr, bytes ? bytes : 1);
+  if (e != hipSuccess) {
+    *ptr = nullptr;
+    return hip_fail(P, e, what);
+  }
+  if (!tmp) P->sbufs.push_back(*ptr);
+  return RAFEAST_OK;
+}
+
 // Device buffers of a streaming-engine workspace for Bp columns.
 rafeast_status alloc_stream_work(rafeast_plan_s* P, int Bp, StreamWork& W,
-                                 std::vector<void*>& bufs) {
+                                 DevBuf* tmp = nullptr) {
   const int64_t n = P->n;
   const size_t cs = P->fp32 ? 2 * sizeof(float) : 2 * sizeof(double);
-  auto get = [&](void** ptr, size_t bytes, const char* what) -> rafeast_status {
-    hipError_t e = hipMalloc(ptr, bytes ? bytes : 1);
-    if (e != hipSuccess) {
-      *ptr = nullptr;
-      return hip_fail(P, e, what);
-    }
-    bufs.push_back(*ptr);
-    return RAFEAST_OK;
+  auto get = [&](void** ptr, size_t bytes, const char* what) {
+    return work_alloc(P, tmp, ptr, bytes, what);
   };
   W = StreamWork{};
   W.Bp = Bp;
@@ -669,16 +793,10 @@ rafeast_status alloc_stream_work(rafeast_plan_s* P, int Bp, StreamWork& W,
 // shifted iterates, or (combining mode, the FEAST filter step) the block they
 // are accumulated into.
 rafeast_status alloc_ms_work(rafeast_plan_s* P, int nz, int k, MsWork& W,
-                             std::vector<void*>& bufs, bool combining = false) {
+                             bool combining, DevBuf* tmp = nullptr) {
   const int64_t n = P->n;
-  auto get = [&](void** ptr, size_t bytes, const char* what) -> rafeast_status {
-    hipError_t e = hipMalloc(ptr, bytes ? bytes : 1);
-    if (e != hipSuccess) {
-      *ptr = nullptr;
-      return hip_fail(P, e, what);
-    }
-    bufs.push_back(*ptr);
-    return RAFEAST_OK;
+  auto get = [&](void** ptr, size_t bytes, const char* what) {
+    return work_alloc(P, tmp, ptr, bytes, what);
   };
   W = MsWork{};
   W.kp = ms_padded(k);
@@ -1030,21 +1148,6 @@ int resolve_ws_op(const rafeast_plan_s* P) {
 // learned polynomial preconditioner: device buffers, spectral map, solver
 // ----------------------------------------------------------------------------
 namespace {
-struct DevBuf {  // device allocations released together
-  std::vector<void*> ptrs;
-  ~DevBuf() {
-    for (void* q : ptrs) (void)hipFree(q);
-  }
-  template <typename T>
-  hipError_t get(T** p, size_t count) {
-    void* q = nullptr;
-    const hipError_t e = hipMalloc(&q, (count ? count : 1) * sizeof(T));
-    if (e == hipSuccess) ptrs.push_back(q);
-    *p = (T*)q;
-    return e;
-  }
-};
-
 void spectral_map(const rafeast_plan_s* P, double& a, double& b) {
   a = 2.0 / (P->sig_hi - P->sig_lo);
   b = -(P->sig_hi + P->sig_lo) / (P->sig_hi - P->sig_lo);
@@ -1059,7 +1162,7 @@ rafeast_status pc_solve_run(rafeast_plan_s* P, int nz, const double* z, int k, c
                             double* resid, int maxit = -1, void* r_out = nullptr) {
   const int64_t n = P->n;
   const int Bc = nz * k;
-  DevBuf buf;
+  DevBuf buf(P);
   PcSolve S;
   S.n = n;
   S.rowptr = P->d_rowptr;
@@ -1266,7 +1369,7 @@ rafeast_status solve_learned(rafeast_plan_s* P, SolveRun& S) {
                     res.data()));
   // judge by true residual; the systems that missed the tolerance are solved
   // again by plain FP64 COCG, all misses of one node in one lock-step solve
-  DevBuf fb;
+  DevBuf fb(P);
   for (int j = 0; j < nc; ++j) {
     std::vector<int> miss;
     for (int i = 0; i < m0; ++i)
@@ -1639,6 +1742,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     return fail(nullptr, RAFEAST_DEVICE, "no HIP device available");
 
   rafeast_plan_s* P = new rafeast_plan_s();
+  count_plan(1);
   P->prm = *prm;
   P->n = n;
   P->nnz = nnz;
@@ -2064,7 +2168,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   } else if (P->engine == RAFEAST_ENGINE_DIRECT) {
     // the factors are the whole workspace
   } else if (P->engine == RAFEAST_ENGINE_MULTISHIFT) {
-    PRCHK(alloc_ms_work(P, P->nc, P->m0, P->mswork, P->sbufs, true));
+    PRCHK(alloc_ms_work(P, P->nc, P->m0, P->mswork, true));
     if (prm->rhs_form == RAFEAST_RHS_LITERAL) {  // literal form: g_{j,c} = w_j
       std::vector<double> wr(2 * (size_t)P->nc * P->m0);
       for (int j = 0; j < P->nc; ++j)
@@ -2077,7 +2181,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     }
   } else {
     const int Bp = stream_padded_columns(P->m0, P->nc * P->m0, fp32);
-    PRCHK(alloc_stream_work(P, Bp, P->swork, P->sbufs));
+    PRCHK(alloc_stream_work(P, Bp, P->swork));
     const std::vector<double> zc = stream_shifts(P->nc, P->zw.data(), P->m0, Bp);
     PCHK(hipMemcpy(P->swork.zc, zc.data(), zc.size() * sizeof(double), hipMemcpyHostToDevice));
   }
@@ -2307,12 +2411,11 @@ rafeast_status rafeast_gram(rafeast_plan_t P, int64_t n, int32_t k1, int32_t k2,
                             int32_t ldx, const double* Y, int32_t ldy, double* G, int32_t ldg) {
   if (!P || !X || !Y || !G || n < 1 || k1 < 1 || k2 < 1 || ldx < k1 || ldy < k2 || ldg < k2)
     return RAFEAST_INVALID_ARG;
+  DevBuf buf(P);
   double* part = nullptr;
-  HIPCHK(P, hipMalloc(&part, gram_partial_doubles(n, k1, k2) * sizeof(double)));
-  hipError_t e = launch_gram(P->st, n, k1, k2, X, ldx, Y, ldy, G, ldg, part);
-  if (e == hipSuccess) e = hipStreamSynchronize(P->st);
-  (void)hipFree(part);
-  HIPCHK(P, e);
+  HIPCHK(P, buf.get(&part, gram_partial_doubles(n, k1, k2)));
+  HIPCHK(P, launch_gram(P->st, n, k1, k2, X, ldx, Y, ldy, G, ldg, part));
+  HIPCHK(P, hipStreamSynchronize(P->st));
   return RAFEAST_OK;
 }
 
@@ -2389,20 +2492,25 @@ rafeast_status rafeast_gemm(void* hip_stream, int32_t precision, int32_t a_cols,
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   const bool f64 = precision == RAFEAST_FP64;
   const size_t es = f64 ? sizeof(double) : sizeof(float);
-  // room for as many chunk slabs as the launcher may choose (at most 64)
-  const size_t room = K >= 1024 ? std::min<size_t>(64, (size_t)K / 512) * M * N : 0;
-  void* work = nullptr;
+  // room for the chunk slabs the launcher will choose
+  const size_t room = gemm_work_elems(f64, M, N, K);
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm: device");
+  const std::shared_ptr<WorkCache> cache = gemm_cache(dev);
+  DevBuf buf(*cache);
+  char* work = nullptr;
   if (room) {
-    const hipError_t e = hipMalloc(&work, room * es);
+    e = buf.get(&work, room * es);
     if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm: workspace");
   }
-  hipError_t e =
+  e =
       f64 ? launch_gemm_f64(st, a_cols, M, N, K, (const double*)A, lda, (const double*)B, ldb,
                             (double*)C, ldc, alpha, beta, (double*)work, room)
           : launch_gemm_f32(st, a_cols, M, N, K, (const float*)A, lda, (const float*)B, ldb,
                             (float*)C, ldc, (float)alpha, (float)beta, (float*)work, room);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (work) (void)hipFree(work);
+  const hipError_t es2 = hipStreamSynchronize(st);  // before the workspace goes back
+  if (e == hipSuccess) e = es2;
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm");
   return RAFEAST_OK;
 }
@@ -2410,28 +2518,18 @@ rafeast_status rafeast_gemm(void* hip_stream, int32_t precision, int32_t a_cols,
 rafeast_status rafeast_cholqr2(rafeast_plan_t P, int64_t n, int32_t k, double* Y, int32_t ldy,
                                int32_t* info) {
   if (!P || !Y || n < 1 || k < 1 || k > kMaxSmallK || ldy < k || k > n) return RAFEAST_INVALID_ARG;
-  double* tmp = nullptr;
-  double* part = nullptr;
-  hipError_t e = hipMalloc(&tmp, (size_t)n * k * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&part, gram_partial_doubles(n, k, k) * sizeof(double));
-  rafeast_status s = RAFEAST_OK;
+  DevBuf buf(P);
+  double *tmp = nullptr, *part = nullptr;
+  HIPCHK(P, buf.get(&tmp, (size_t)n * k));
+  HIPCHK(P, buf.get(&part, gram_partial_doubles(n, k, k)));
   int ci = 0;
-  if (e != hipSuccess) {
-    s = hip_fail(P, e, "cholqr2 workspace");
-  } else {
-    double* keep = P->d_part;
-    P->d_part = part;
-    s = cholqr2(P, n, k, Y, ldy, &ci, tmp, k);
-    P->d_part = keep;
-    if (s == RAFEAST_OK) {
-      e = hipStreamSynchronize(P->st);
-      if (e != hipSuccess) s = hip_fail(P, e, "cholqr2");
-    }
-  }
-  if (tmp) (void)hipFree(tmp);
-  if (part) (void)hipFree(part);
+  std::swap(P->d_part, part);
+  const rafeast_status s = cholqr2(P, n, k, Y, ldy, &ci, tmp, k);
+  std::swap(P->d_part, part);
   if (info) *info = ci;
-  return s;
+  RCHK(s);
+  HIPCHK(P, hipStreamSynchronize(P->st));
+  return RAFEAST_OK;
 }
 
 rafeast_status rafeast_syev(rafeast_plan_t P, int32_t k, const double* H, double* theta,
@@ -2447,6 +2545,7 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
                                      int32_t* iters, double* resid) {
   if (!P || !z || !B || !X || nz < 1 || k < 1 || ldb < k || !(tol > 0.0) || !(tol < 1.0))
     return RAFEAST_INVALID_ARG;
+  DevBuf buf(P);
   double* d_z = nullptr;
   int* d_items = nullptr;
   int* d_it = nullptr;
@@ -2454,10 +2553,10 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
   std::vector<int> items = make_items(nz, z, k);
   const int nitems = nz * k;
   rafeast_status s = RAFEAST_OK;
-  hipError_t e = hipMalloc(&d_z, 2 * nz * sizeof(double));
-  if (e == hipSuccess) e = hipMalloc(&d_items, items.size() * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&d_it, nitems * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&d_rs, nitems * sizeof(double));
+  hipError_t e = buf.get(&d_z, 2 * (size_t)nz);
+  if (e == hipSuccess) e = buf.get(&d_items, items.size());
+  if (e == hipSuccess) e = buf.get(&d_it, nitems);
+  if (e == hipSuccess) e = buf.get(&d_rs, nitems);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d_z, z, 2 * nz * sizeof(double), hipMemcpyHostToDevice, P->st);
   if (e == hipSuccess)
@@ -2472,10 +2571,9 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       cpx<double>* Wb = nullptr;
       int* d_info = nullptr;
       double* d_part = nullptr;
-      e = hipMalloc(&Wb, (size_t)nz * n * (b + 1) * sizeof(cpx<double>));
-      if (e == hipSuccess) e = hipMalloc(&d_info, nz * sizeof(int));
-      if (e == hipSuccess)
-        e = hipMalloc(&d_part, band_resid_doubles(n, nitems) * sizeof(double));
+      e = buf.get(&Wb, (size_t)nz * n * (b + 1));
+      if (e == hipSuccess) e = buf.get(&d_info, nz);
+      if (e == hipSuccess) e = buf.get(&d_part, band_resid_doubles(n, nitems));
       if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve band workspace");
       if (s == RAFEAST_OK) {
         e = band_assemble(P->st, n, b, P->d_srow, P->d_scol, P->d_sv64, nz, d_z, Wb);
@@ -2502,11 +2600,7 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
         if (e == hipSuccess) e = hipStreamSynchronize(P->st);
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
       }
-      if (Wb) (void)hipFree(Wb);
-      if (d_info) (void)hipFree(d_info);
-      if (d_part) (void)hipFree(d_part);
     } else if (P->engine == RAFEAST_ENGINE_MULTISHIFT) {
-      std::vector<void*> bufs;
       MsWork W;
       // pi_k = R_k(z_j - s) can vanish for a real z_j inside the seed's
       // spectrum: the engine takes shifts off the real axis only
@@ -2517,23 +2611,21 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       else if (k > 192)
         s = fail(P, RAFEAST_UNSUPPORTED, "the multi-shift engine takes k <= 192");
       else
-        s = alloc_ms_work(P, nz, k, W, bufs);
+        s = alloc_ms_work(P, nz, k, W, false, &buf);
       if (s == RAFEAST_OK) s = run_ms(P, W, nz, z, k, B, ldb, X, nz * k, tol, d_it, d_rs);
       if (s == RAFEAST_OK) {
         e = hipStreamSynchronize(P->st);
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
       }
-      for (void* b : bufs) (void)hipFree(b);
     } else if (P->engine == RAFEAST_ENGINE_STREAM) {
-      // a workspace of this call's width, released below
+      // a workspace of this call's width
       const int gw = 64 * stream_cpl(k, nitems, P->fp32);
       const int Bp = stream_padded_columns(k, nitems, P->fp32);
-      std::vector<void*> bufs;
       StreamWork W;
       if (Bp / gw > kStreamMaxGroups)
         s = fail(P, RAFEAST_UNSUPPORTED, "nz * k exceeds the streaming engine's column limit");
       else
-        s = alloc_stream_work(P, Bp, W, bufs);
+        s = alloc_stream_work(P, Bp, W, &buf);
       if (s == RAFEAST_OK) {
         const std::vector<double> zc = stream_shifts(nz, z, k, Bp);
         e = hipMemcpyAsync(W.zc, zc.data(), zc.size() * sizeof(double), hipMemcpyHostToDevice,
@@ -2545,7 +2637,6 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
         e = hipStreamSynchronize(P->st);
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
       }
-      for (void* b : bufs) (void)hipFree(b);
     } else {
       s = run_cocg(P, nitems, d_items, d_z, k, B, ldb, X, nz * k, tol, d_it, d_rs);
     }
@@ -2562,10 +2653,6 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
     }
   }
-  if (d_z) (void)hipFree(d_z);
-  if (d_items) (void)hipFree(d_items);
-  if (d_it) (void)hipFree(d_it);
-  if (d_rs) (void)hipFree(d_rs);
   return s;
 }
 
@@ -2951,7 +3038,7 @@ rafeast_status rafeast_pc_samples(rafeast_plan_t P, int32_t nz, const double* z,
   const int64_t n = P->n;
   double a, b;
   spectral_map(P, a, b);
-  DevBuf buf;
+  DevBuf buf(P);
   double *T = nullptr, *part = nullptr, *dz = nullptr;
   const size_t bs = (size_t)n * k;
   const int nchunks = (int)std::max<int64_t>(1, std::min<int64_t>(256, (n + 2047) / 2048));
@@ -2974,7 +3061,7 @@ rafeast_status rafeast_pc_samples(rafeast_plan_t P, int32_t nz, const double* z,
 rafeast_status rafeast_pc_forward(rafeast_plan_t P, int32_t ns, const double* X, const float* W,
                                   float* Y) {
   if (!P || !X || !W || !Y || ns < 1) return RAFEAST_INVALID_ARG;
-  DevBuf buf;
+  DevBuf buf(P);
   float* wb = nullptr;
   HIPCHK(P, buf.get(&wb, mlp_param_count()));
   HIPCHK(P, launch_mlp_bf16(P->st, W, wb));
@@ -2987,7 +3074,7 @@ rafeast_status rafeast_pc_gradient(rafeast_plan_t P, int32_t ns, const double* X
                                    const double* h, const double* rr, const float* W, float* grad,
                                    double* loss) {
   if (!P || !X || !G || !h || !rr || !W || !grad || ns < 1) return RAFEAST_INVALID_ARG;
-  DevBuf buf;
+  DevBuf buf(P);
   float *wb = nullptr, *part = nullptr;
   double *lpart = nullptr, *dl = nullptr;
   int* idx = nullptr;
@@ -3017,7 +3104,7 @@ rafeast_status rafeast_pc_train(rafeast_plan_t P, int32_t ns, const double* X, c
     return RAFEAST_INVALID_ARG;
   for (int64_t t = 0; t < (int64_t)steps * batch; ++t)
     if (order[t] < 0 || order[t] >= ns) return fail(P, RAFEAST_INVALID_ARG, "order out of range");
-  DevBuf buf;
+  DevBuf buf(P);
   float *wb = nullptr, *part = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   double *lpart = nullptr, *dl = nullptr;
   int* idx = nullptr;
@@ -3060,7 +3147,7 @@ rafeast_status rafeast_pc_harvest(rafeast_plan_t P, int32_t nsteps, const int32_
   const int64_t n = P->n;
   const int m0 = P->m0, nc = P->nc, Bc = nc * m0;
   const double th_lo = P->last_theta.front(), th_hi = P->last_theta.back();
-  DevBuf buf;
+  DevBuf buf(P);
   cpx<double>* xs = nullptr;
   cpx<double>* rs = nullptr;
   double* split = nullptr;
