@@ -11,9 +11,9 @@
 namespace rafeast {
 
 // ============================================================================
-// SpMM, FP64 real: Y = alpha*A*X + beta*X + gamma*X2.  One wave per row; the
-// row's nonzeros are wave-uniform (scalar loads), lanes run over the columns
-// of the block, so every gathered row X[j, :] is one coalesced read.
+// SpMM, FP64 real: Y = alpha*A*X + beta*X + gamma*X2.  This form serves a
+// single column and matrices without nonzeros: one wave per row, the row's
+// nonzeros wave-uniform (scalar loads), lanes over the columns.
 // ============================================================================
 __global__ __launch_bounds__(256) void k_spmm_f64(int n, int k, const int* __restrict__ rowptr,
                                                   const int* __restrict__ col,
@@ -100,7 +100,7 @@ struct RowHead {
 // Every load of the SpMM below runs on every lane, at an index that is in
 // range whether or not its value is used (an unused row reads row 0, an
 // unused entry reads entry 0, an unused gather reads row j of entry 0 or
-// column grp * kg), and unused values are dropped where they are consumed:
+// column 0), and unused values are dropped where they are consumed:
 // with no lane-masked branch around the loads and no select right after
 // them, the compiler counts the loads in flight and waits only for the ones
 // a step needs.  The matrix has at least one nonzero (checked at launch).
@@ -115,45 +115,48 @@ template <int C>
 __device__ __forceinline__ void head_entries(RowHead& h, int sub, int t0,
                                              const int* __restrict__ col,
                                              const double* __restrict__ val) {
-  // the matrix streams past L2 (it is read once per column group), which
-  // keeps L2 for the gathered rows of X
+  // the matrix streams past L2 (it is read once), which keeps L2 for the
+  // gathered rows of X
   const int t = sub < C && t0 + sub < h.e ? t0 + sub : 0;
   h.jv = __builtin_nontemporal_load(col + t);
   h.av = __builtin_nontemporal_load(val + t);
 }
 
-// One row of Y (the columns of group grp) for the lanes of sub-index sub.
+// One row of Y for the lanes of sub-index sub.
 // h holds the row's extent and its first round of entries; later rounds and
 // later column passes load their own.
 template <int L>
-__device__ __forceinline__ void spmm_x2_row(int row, int sub, int grp, int k, int kg,
-                                            const RowHead& h, const int* __restrict__ col,
+__device__ __forceinline__ void spmm_x2_row(int row, int sub, int k, const RowHead& h,
+                                            const int* __restrict__ col,
                                             const double* __restrict__ val,
                                             const double* __restrict__ X, int ldx,
                                             double* __restrict__ Y, int ldy, double alpha,
                                             double beta, const double* __restrict__ X2, int ldx2,
                                             double gamma) {
   constexpr int C = L < 8 ? L : 8;  // nonzeros per round
+  // two consecutive columns; rows start at any multiple of 8 bytes
+  typedef double Pair __attribute__((ext_vector_type(2), aligned(8)));
   const int s = h.s, e = h.e;
-  const int cend = min(k, (grp + 1) * kg);
   // round 0 (positions s .. s + C - 1): lane u < C of the row's lanes holds
   // entry u; handed round the row's lanes once, kept for every column pass
   int j0[C];
   double a0[C];
   RoundBcast<L, 0, C>::run(h.jv, h.av, j0, a0);
-  for (int c0 = grp * kg; c0 < cend; c0 += 2 * L) {
-    const int c = c0 + 2 * sub;
-    const bool ok = c < cend;
-    const int cs = ok ? c : grp * kg;  // an in-range column for the idle lanes
-    double2 acc0 = make_double2(0.0, 0.0), acc1 = acc0;
+  for (int c0 = 0; c0 < k; c0 += 2 * L) {
+    // with k odd the last lane takes the last two columns, of which its
+    // neighbour writes the first as well (the same value)
+    const bool ok = c0 + 2 * sub < k;
+    const int c = min(c0 + 2 * sub, k - 2);
+    const int cs = ok ? c : 0;  // an in-range column for the idle lanes
+    Pair acc0{0.0, 0.0}, acc1{0.0, 0.0};
     // the gathered rows of a round are loaded together; even and odd
     // positions of the row go to two partial sums, in order (a round of one
     // entry alternates between them)
     {
-      double2 x[C];
+      Pair x[C];
 #pragma unroll
       for (int u = 0; u < C; ++u)
-        x[u] = *reinterpret_cast<const double2*>(X + (size_t)j0[u] * ldx + cs);
+        x[u] = *reinterpret_cast<const Pair*>(X + (size_t)j0[u] * ldx + cs);
 #pragma unroll
       for (int u = 0; u < C; ++u) {
         if (s + u < e) {
@@ -174,10 +177,10 @@ __device__ __forceinline__ void spmm_x2_row(int row, int sub, int grp, int k, in
       int j[C];
       double a[C];
       RoundBcast<L, 0, C>::run(r.jv, r.av, j, a);
-      double2 x[C];
+      Pair x[C];
 #pragma unroll
       for (int u = 0; u < C; ++u)
-        x[u] = *reinterpret_cast<const double2*>(X + (size_t)j[u] * ldx + cs);
+        x[u] = *reinterpret_cast<const Pair*>(X + (size_t)j[u] * ldx + cs);
 #pragma unroll
       for (int u = 0; u < C; ++u) {
         if (t0 + u < e) {
@@ -193,45 +196,43 @@ __device__ __forceinline__ void spmm_x2_row(int row, int sub, int grp, int k, in
       }
     }
     if (ok) {
-      double2 y = make_double2(alpha * (acc0.x + acc1.x), alpha * (acc0.y + acc1.y));
+      Pair y{alpha * (acc0.x + acc1.x), alpha * (acc0.y + acc1.y)};
       if (beta != 0.0) {
-        const double2 xr = *reinterpret_cast<const double2*>(X + (size_t)row * ldx + c);
+        const Pair xr = *reinterpret_cast<const Pair*>(X + (size_t)row * ldx + c);
         y.x += beta * xr.x;
         y.y += beta * xr.y;
       }
       if (X2 != nullptr) {
-        const double2 x2r = *reinterpret_cast<const double2*>(X2 + (size_t)row * ldx2 + c);
+        const Pair x2r = *reinterpret_cast<const Pair*>(X2 + (size_t)row * ldx2 + c);
         y.x += gamma * x2r.x;
         y.y += gamma * x2r.y;
       }
       // Y is not read again here: streamed past L2, which keeps the gathered rows
-      typedef double d2v __attribute__((ext_vector_type(2)));
-      d2v yv;
-      yv.x = y.x;
-      yv.y = y.y;
-      __builtin_nontemporal_store(yv, reinterpret_cast<d2v*>(Y + (size_t)row * ldy + c));
+      __builtin_nontemporal_store(y, reinterpret_cast<Pair*>(Y + (size_t)row * ldy + c));
     }
   }
 }
 
 // Two columns per lane (16-byte loads) and 64 / L rows per wave, L the
-// power of two of lanes that covers kg / 2 column pairs (k even, ld even and
-// 16-byte aligned blocks): each load instruction moves twice the bytes of the
+// power of two of lanes that covers the k >= 2 columns' pairs: each load instruction moves twice the bytes of the
 // one-column form, and a wave serves several short rows at once.  Nonzeros
 // go to two partial sums (even and odd positions) in row order.
 //
 // Placement: workgroup b runs on XCD b mod 8 (dispatch deals workgroup ids
 // to the eight XCDs in turn).  XCD x owns the x-th contiguous eighth of the
-// row blocks (rbx of them) and sweeps it once per group of kg columns, in
-// row order, so a gathered row X[j, group] is fetched into that XCD's L2
-// once and reused by the rows around j that need it, as long as the rows
-// within the matrix's span of j fit in L2 for one group (the host picks kg
-// for that).  A workgroup takes rpb consecutive row blocks of 4 * 64 / L
-// rows, one after the other, as a pipeline: while a block's gathers are in
-// flight, the next block's first entries and the extents of the block after
-// it are loaded.
+// row blocks (rbx of them) and sweeps it in row order, all columns of a row at
+// once, so a gathered row X[j] is fetched into that XCD's L2 once for the rows
+// around j that need it.  Rows farther apart than L2 holds come again from the
+// infinity cache; sweeping the columns in groups whose rows fit L2 saves those
+// reads but reads the matrix once per group and cuts rows that are not whole
+// 128-byte lines into partial ones, read and written twice: 100^3 grid, k = 30,
+// 64, 84, 148: 307, 397, 988, 1504 us in groups, 194, 393, 620, 1176 us without
+// (3D neighbour graph of 30,000 points, k = 84: 129 and 75 us).  A workgroup
+// takes rpb consecutive row blocks of 4 * 64 / L rows, one after the other, as
+// a pipeline: while a block's gathers are in flight, the next block's first
+// entries and the extents of the block after it are loaded.
 template <int L>
-__global__ __launch_bounds__(256) void k_spmm_f64_x2(int n, int k, int kg, int rbx, int rpb,
+__global__ __launch_bounds__(256) void k_spmm_f64_x2(int n, int k, int rbx, int rpb,
                                                      const int* __restrict__ rowptr,
                                                      const int* __restrict__ col,
                                                      const double* __restrict__ val,
@@ -242,10 +243,7 @@ __global__ __launch_bounds__(256) void k_spmm_f64_x2(int n, int k, int kg, int r
   constexpr int RW = 64 / L;  // rows per wave
   constexpr int C = L < 8 ? L : 8;
   const int b = (int)blockIdx.x;
-  const int i = b >> 3;
-  const int nbx = (rbx + rpb - 1) / rpb;  // workgroups per XCD and group
-  const int grp = i / nbx;
-  const int rb0 = (i - grp * nbx) * rpb;
+  const int rb0 = (b >> 3) * rpb;
   const int rb1 = min(rbx, rb0 + rpb);
   const int lane = threadIdx.x & 63;
   const int sub = lane % L;
@@ -264,7 +262,7 @@ __global__ __launch_bounds__(256) void k_spmm_f64_x2(int n, int k, int kg, int r
     RowHead nnh;
     head_bounds(nnh, nnrow, live(rbl + 2, nnrow), rowptr);
     head_entries<C>(nh, sub, nh.s, col, val);
-    spmm_x2_row<L>(row, sub, grp, k, kg, h, col, val, X, ldx, Y, ldy, alpha, beta, X2, ldx2,
+    spmm_x2_row<L>(row, sub, k, h, col, val, X, ldx, Y, ldy, alpha, beta, X2, ldx2,
                    gamma);
     h = nh;
     nh = nnh;
@@ -278,43 +276,22 @@ __global__ __launch_bounds__(256) void k_spmm_f64_x2(int n, int k, int kg, int r
 #define RAFEAST_SPMM_RPB 4
 #endif
 
-// Bytes of an XCD's L2 (4 MiB) given to the gathered rows of one column group.
-#ifndef RAFEAST_SPMM_L2_BYTES
-#define RAFEAST_SPMM_L2_BYTES (3 << 20)
-#endif
-
-int spmm_group_cols(int k, int64_t span) {
-  // the rows a gather can reach around row j span 2 * span + 1 rows of a
-  // group's kg FP64 columns: the fewest equal groups (kg even, at least 8)
-  // whose rows fit the budget
-  for (int ng = 1;; ++ng) {
-    int kg = (k + ng - 1) / ng;
-    kg += kg & 1;
-    if (kg <= 8 || (2 * span + 1) * (int64_t)kg * 8 <= (int64_t)RAFEAST_SPMM_L2_BYTES)
-      return kg < k ? kg : k;
-  }
-}
-
 hipError_t launch_spmm_f64(hipStream_t st, int n, int k, const int* rowptr, const int* col,
                            const double* val, int64_t nnz, const double* X, int ldx, double* Y,
                            int ldy, double alpha, double beta, const double* X2, int ldx2,
-                           double gamma, int64_t span) {
+                           double gamma) {
   if (n <= 0 || k <= 0) return hipSuccess;
-  auto al16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  const bool x2_ok = X2 == nullptr || (ldx2 % 2 == 0 && al16(X2));
-  if (nnz > 0 && k % 2 == 0 && ldx % 2 == 0 && ldy % 2 == 0 && al16(X) && al16(Y) && x2_ok) {
-    const int kg = span > 0 ? spmm_group_cols(k, span) : k;
-    const int ng = (k + kg - 1) / kg;
-    // lanes per row: the power of two covering kg / 2 column pairs (<= 64)
+  if (nnz > 0 && k >= 2) {
+    // lanes per row: the power of two covering the column pairs (<= 64)
     int L = 1;
-    while (L < 64 && 2 * L < kg) L *= 2;
+    while (L < 64 && 2 * L < k) L *= 2;
     const int rw = 64 / L;
     const int rblocks = (n + 4 * rw - 1) / (4 * rw);
     const int rbx = (rblocks + 7) / 8;
     const int rpb = RAFEAST_SPMM_RPB;
-    const dim3 grid((unsigned)(8 * ng * ((rbx + rpb - 1) / rpb)));
+    const dim3 grid((unsigned)(8 * ((rbx + rpb - 1) / rpb)));
 #define RAFEAST_SPMM_X2(LL)                                                                     \
-  hipLaunchKernelGGL(k_spmm_f64_x2<LL>, grid, dim3(256), 0, st, n, k, kg, rbx, rpb, rowptr, col, \
+  hipLaunchKernelGGL(k_spmm_f64_x2<LL>, grid, dim3(256), 0, st, n, k, rbx, rpb, rowptr, col,     \
                      val, X, ldx, Y, ldy, alpha, beta, X2, ldx2, gamma)
     switch (L) {
       case 1: RAFEAST_SPMM_X2(1); break;
@@ -356,8 +333,26 @@ int gram_chunks(int64_t n) {
   return (int)c;
 }
 
+// Largest k of the symmetric kernel (its tiles: 12 x 13 / 2).
+constexpr int kSymMaxK = 192;
+
+size_t gram_chunk_doubles(int k1, int k2) {
+  const size_t all = (size_t)k1 * (size_t)k2;
+  if (k1 != k2 || k1 > kSymMaxK) return all;
+  const size_t nt = (k1 + 15) / 16, tiles = nt * (nt + 1) / 2 * 256;
+  return all > tiles ? all : tiles;
+}
+
+// Row chunks of X^T Y, or of X^T X (sym), whose workgroups hold all tiles of
+// a chunk: two per CU, from chunks of 64 rows on.
+int gram_chunks_of(int64_t n, int k1, int k2, bool sym) {
+  if (!sym || k1 != k2 || k1 > kSymMaxK) return gram_chunks(n);
+  const int64_t c = (n + 63) / 64;
+  return (int)(c > 512 ? 512 : c < 1 ? 1 : c);
+}
+
 size_t gram_partial_doubles(int64_t n, int k1, int k2) {
-  return (size_t)gram_chunks(n) * (size_t)k1 * (size_t)k2;
+  return (size_t)gram_chunks_of(n, k1, k2, true) * gram_chunk_doubles(k1, k2);
 }
 
 // A workgroup owns a TA x TB block of 16 x 16 output tiles of one row chunk;
@@ -500,9 +495,164 @@ __global__ __launch_bounds__(256) void k_gram_reduce(int chunks, int k1, int k2,
     G[(size_t)(e / k2) * ldg + (e % k2)] = ((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane];
 }
 
+// ============================================================================
+// Symmetric Gram G = X^T X (CholQR): only the upper 16 x 16 tiles, each
+// workgroup all of them for its chunk of rows, so X is read once.  RS rows are
+// staged in LDS through registers (two buffers, the next stage's loads in
+// flight during this stage's MFMAs); the NW waves own TPW consecutive tiles
+// each.  A row of LDS is PK doubles, PK = 16 mod 32, so that a fragment (4 rows
+// of 16 doubles) covers the banks evenly.  The general kernel above computed all
+// tiles from global memory, reading each row for every block row of tiles
+// (n = 1e6, k = 84: 575 us; this GRAM_SYM_US us, X alone being 139 us at the
+// copy rate, and the tiles 137 us of matrix core time).
+// ============================================================================
+// Two consecutive columns of a row through a descriptor (byte offset off; in:
+// whether the first is wanted, in2: the second): one 16-byte load where rows
+// and base are 16-byte aligned and k is even (wide), else two.
+constexpr int kOutside = 0x7ffffff0;  // past every descriptor
+__device__ __forceinline__ double2 load_pair(__amdgpu_buffer_rsrc_t rs, int off, bool in, bool in2,
+                                             bool wide) {
+  if (wide)
+    return __builtin_bit_cast(double2,
+                              __builtin_amdgcn_raw_buffer_load_b128(rs, in ? off : kOutside, 0, 0));
+  double2 v;
+  v.x = __builtin_bit_cast(double,
+                           __builtin_amdgcn_raw_buffer_load_b64(rs, in ? off : kOutside, 0, 0));
+  v.y = __builtin_bit_cast(
+      double, __builtin_amdgcn_raw_buffer_load_b64(rs, in2 ? off + 8 : kOutside, 0, 0));
+  return v;
+}
+static bool wide_rows(const double* X, int ldx, int k) {
+  return k % 2 == 0 && ldx % 2 == 0 && ((uintptr_t)X & 15) == 0;
+}
+
+template <int NW, int TPW, int RS, int MT>
+__global__ __launch_bounds__(64 * NW) void k_gram_sym(int64_t n, int k, int wide,
+                                                      const double* __restrict__ X, int ldx,
+                                                      double* __restrict__ part,
+                                                      int64_t rows_per_chunk) {
+  extern __shared__ double sx[];
+  constexpr int T = 64 * NW, LPR = T / RS;       // lanes per staged row
+  constexpr int NL = (8 * MT + LPR - 1) / LPR;   // column pairs per lane (MT >= tiles per row)
+  const int nt = (k + 15) >> 4, ntiles = nt * (nt + 1) / 2;
+  const int PK = 16 * (nt | 1);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t r_begin = (int64_t)blockIdx.x * rows_per_chunk;
+  const int rows = (int)max<int64_t>(0, min<int64_t>(rows_per_chunk, n - r_begin));
+  // a column past k or a row past the chunk lies past the descriptor: zero
+  const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(X + r_begin * ldx), (short)0, rows > 0 ? ((rows - 1) * ldx + k) * 8 : 0,
+      kBufferWord3);
+  const int sr = tid / LPR, sl = tid % LPR;  // staged row, first column pair
+  double2 ld[NL];
+  auto load = [&](int r0) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int c = 2 * (sl + LPR * u);
+      const bool in = r0 + sr < rows;
+      ld[u] = load_pair(xs, ((r0 + sr) * ldx + c) * 8, in && c < k, in && c + 1 < k, wide != 0);
+    }
+  };
+  auto stage = [&](double* dst) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int c = 2 * (sl + LPR * u);
+      if (c < 16 * nt) *reinterpret_cast<double2*>(dst + sr * PK + c) = ld[u];
+    }
+  };
+  // this wave's tiles
+  int ti[TPW], tj[TPW];
+  bool on[TPW];
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) {
+    int t = wave * TPW + u, I = 0;
+    on[u] = t < ntiles;
+    t = min(t, ntiles - 1);
+    while (t >= nt - I) t -= nt - I++;
+    ti[u] = 16 * I + (lane >> 4) * PK + (lane & 15);
+    tj[u] = 16 * (I + t) + (lane >> 4) * PK + (lane & 15);
+  }
+  v4d acc[TPW];
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) acc[u] = v4d{0.0, 0.0, 0.0, 0.0};
+  const int buf = RS * PK;
+  load(0);
+  stage(sx);
+  __syncthreads();
+  for (int r0 = 0, cur = 0; r0 < rows; r0 += RS, cur ^= 1) {
+    if (r0 + RS < rows) load(r0 + RS);
+    const double* b = sx + cur * buf;
+#pragma unroll
+    for (int q = 0; q < RS / 4; ++q) {
+      double fa[TPW], fb[TPW];
+#pragma unroll
+      for (int u = 0; u < TPW; ++u) {
+        fa[u] = b[ti[u] + 4 * q * PK];
+        fb[u] = b[tj[u] + 4 * q * PK];
+      }
+#pragma unroll
+      for (int u = 0; u < TPW; ++u)
+        acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u], fb[u], acc[u], 0, 0, 0);
+    }
+    if (r0 + RS < rows) stage(sx + (cur ^ 1) * buf);
+    __syncthreads();
+  }
+  // partial tiles in tile order, accumulator v of lane l at 64 v + l
+#pragma unroll
+  for (int u = 0; u < TPW; ++u)
+    if (on[u])
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        part[((size_t)blockIdx.x * ntiles + wave * TPW + u) * 256 + 64 * v + lane] = acc[u][v];
+}
+
+// Sum of the chunks' tiles in order (eight groups of chunks, then the groups),
+// written to both triangles.
+__global__ __launch_bounds__(512) void k_gram_sym_reduce(int chunks, int k,
+                                                         const double* __restrict__ part,
+                                                         double* __restrict__ G, int ldg) {
+  __shared__ double sh[8][64];
+  const int nt = (k + 15) >> 4, ntiles = nt * (nt + 1) / 2;
+  const int g = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int e = blockIdx.x * 64 + lane;  // four blocks a tile
+  const int per = (chunks + 7) / 8, c0 = g * per, c1 = min(chunks, c0 + per);
+  double s = 0.0;
+#pragma unroll 8
+  for (int c = c0; c < c1; ++c) s += part[(size_t)c * ntiles * 256 + e];
+  sh[g][lane] = s;
+  __syncthreads();
+  if (g != 0) return;
+  s = 0.0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) s += sh[q][lane];
+  int t = e >> 8, I = 0;
+  while (t >= nt - I) t -= nt - I++;
+  const int i = 16 * I + 4 * ((e >> 6) & 3) + (lane >> 4), j = 16 * (I + t) + (lane & 15);
+  if (i < k && j < k) {
+    G[(size_t)i * ldg + j] = s;
+    if (t > 0) G[(size_t)j * ldg + i] = s;
+  }
+}
+
+template <int NW, int TPW, int RS, int MT>
+static hipError_t launch_sym(hipStream_t st, int64_t n, int k, const double* X, int ldx,
+                             double* part, int chunks, int64_t rpc) {
+  const int nt = (k + 15) / 16;
+  const size_t lds = (size_t)2 * RS * 16 * (nt | 1) * sizeof(double);
+  auto fn = k_gram_sym<NW, TPW, RS, MT>;
+  hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(fn, dim3(chunks), dim3(64 * NW), lds, st, n, k,
+                     wide_rows(X, ldx, k) ? 1 : 0, X, ldx, part, rpc);
+  return hipGetLastError();
+}
+
 hipError_t launch_gram(hipStream_t st, int64_t n, int k1, int k2, const double* X, int ldx,
                        const double* Y, int ldy, double* G, int ldg, double* part) {
-  return launch_gram_chunks(st, n, k1, k2, X, ldx, Y, ldy, G, ldg, part, gram_chunks(n));
+  return launch_gram_chunks(st, n, k1, k2, X, ldx, Y, ldy, G, ldg, part,
+                            gram_chunks_of(n, k1, k2, X == Y && ldx == ldy));
 }
 
 hipError_t launch_gram_chunks(hipStream_t st, int64_t n, int k1, int k2, const double* X,
@@ -510,12 +660,31 @@ hipError_t launch_gram_chunks(hipStream_t st, int64_t n, int k1, int k2, const d
                               int chunks) {
   if (k1 <= 0 || k2 <= 0) return hipSuccess;
   if (chunks < 1) chunks = 1;
-  if (chunks > gram_chunks(n)) chunks = gram_chunks(n);
+  const int most = gram_chunks_of(n, k1, k2, X == Y && ldx == ldy);
+  if (chunks > most) chunks = most;
   int64_t rpc = (n + chunks - 1) / chunks;
   rpc = (rpc + 3) & ~int64_t(3);
   // a chunk's rows are addressed through 32-bit buffer offsets
   if (rpc * (int64_t)(ldx > ldy ? ldx : ldy) * 8 > (int64_t)INT32_MAX) return hipErrorInvalidValue;
   const int ta_n = (k1 + 15) / 16, tb_n = (k2 + 15) / 16;
+  if (X == Y && ldx == ldy && k1 == k2 && k1 <= kSymMaxK &&
+      rpc * (int64_t)ldx * 8 < (int64_t)kOutside) {
+    // waves and tiles per wave by the tile count: 10, 21, 45, 78 at k = 64, 96,
+    // 144, 192; shorter stages where a row is long, so that two workgroups fit
+    hipError_t e;
+    if (ta_n <= 4)
+      e = launch_sym<4, 3, 32, 4>(st, n, k1, X, ldx, part, chunks, rpc);
+    else if (ta_n <= 6)
+      e = launch_sym<8, 3, 32, 6>(st, n, k1, X, ldx, part, chunks, rpc);
+    else if (ta_n <= 9)
+      e = launch_sym<8, 6, 16, 9>(st, n, k1, X, ldx, part, chunks, rpc);
+    else
+      e = launch_sym<8, 10, 16, 12>(st, n, k1, X, ldx, part, chunks, rpc);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_gram_sym_reduce, dim3(4 * (ta_n * (ta_n + 1) / 2)), dim3(512), 0, st,
+                       chunks, k1, part, G, ldg);
+    return hipGetLastError();
+  }
   // one workgroup per tile block and chunk: 3 x 3 blocks when that still
   // gives twelve or more per chunk, else 2 x 2
   auto nblk = [&](int ta, int tb) { return ((ta_n + ta - 1) / ta) * ((tb_n + tb - 1) / tb); };
@@ -677,6 +846,95 @@ hipError_t launch_tsmm(hipStream_t st, int64_t n, int k, int k2, const double* X
   dim3 grid((unsigned)((n + 63) / 64), (tb_n + TB - 1) / TB);
   hipLaunchKernelGGL(k_tsmm<TB>, grid, dim3(256), 0, st, n, k, k2, X, ldx, S, lds, Y, ldy);
   return hipGetLastError();
+}
+
+// ============================================================================
+// Y <- Y M in place for an upper triangular M (CholQR's R^{-1}), unless the
+// factorization failed (*status == 2).  The upper tiles of M are staged in LDS;
+// a wave takes 16 rows at a time, loads all their columns into registers (pairs
+// of columns, 16 bytes a lane: lane l holds row l % 16, columns 8 s + 2 (l / 16)
+// and the next, which are k-steps 2 s and 2 s + 1; M's rows are staged in that
+// order) and writes column tile t from the tiles s <= t, so a row is read once
+// and written once.  Measured at n = 1e6, k = 84: APPLY_US us; a product with
+// the square M into another block and a copy back were 522 + 251 us.
+// ============================================================================
+template <int NT, int NW>
+__global__ __launch_bounds__(64 * NW) void k_tri_apply(int64_t n, int k, int wide, double* Y,
+                                                       int ldy,
+                                                       const double* __restrict__ M, int ldm,
+                                                       const int* __restrict__ status) {
+  extern __shared__ double sm[];  // tiles (s, t), s <= t, by column t
+  if (*status == 2) return;
+  constexpr int kTiles = NT * (NT + 1) / 2;
+  for (int e = threadIdx.x; e < kTiles * 256; e += 64 * NW) {
+    int s = e >> 8, t = 0;
+    while (s > t) s -= ++t;
+    const int r = (e >> 4) & 15, c = e & 15;
+    // position r holds row 8 (r / 8) + 2 (r % 4) + (r / 4) % 2 of the tile
+    const int i = 16 * s + 8 * (r >> 3) + 2 * (r & 3) + ((r >> 2) & 1), j = 16 * t + c;
+    sm[e] = i < k && j < k ? M[(size_t)i * ldm + j] : 0.0;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t step = (int64_t)gridDim.x * NW * 16;
+  for (int64_t r0 = ((int64_t)blockIdx.x * NW + wave) * 16; r0 < n; r0 += step) {
+    const int rows = (int)min<int64_t>(16, n - r0);
+    const __amdgpu_buffer_rsrc_t ys = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(Y + r0 * ldy), (short)0, ((rows - 1) * ldy + k) * 8, kBufferWord3);
+    double a[4 * NT];
+#pragma unroll
+    for (int s = 0; s < 2 * NT; ++s) {
+      const int c = 8 * s + 2 * lk;
+      const bool in = li < rows;
+      const double2 v = load_pair(ys, (li * ldy + c) * 8, in && c < k, in && c + 1 < k, wide != 0);
+      a[2 * s] = v.x;
+      a[2 * s + 1] = v.y;
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      v4d acc{0.0, 0.0, 0.0, 0.0};
+      const double* col = sm + (t * (t + 1) / 2) * 256 + lane;
+#pragma unroll
+      for (int q = 0; q < 4 * (t + 1); ++q)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[q], col[64 * q], acc, 0, 0, 0);
+      const int c = 16 * t + li;
+      if (c < k) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (lk + 4 * v < rows) Y[(r0 + lk + 4 * v) * ldy + c] = acc[v];
+      }
+      // M's fragments of later tiles are not read ahead of this tile's: all of
+      // them at once spilled registers (888 to 2024 bytes a lane from k = 97 on)
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
+template <int NT, int NW>
+static hipError_t launch_tri(hipStream_t st, int64_t n, int k, double* Y, int ldy,
+                             const double* M, int ldm, const int* status) {
+  auto fn = k_tri_apply<NT, NW>;
+  const size_t lds = (size_t)NT * (NT + 1) / 2 * 256 * sizeof(double);
+  hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds);
+  if (e != hipSuccess) return e;
+  const int64_t want = (n + 16 * NW - 1) / (16 * NW);
+  hipLaunchKernelGGL(fn, dim3((unsigned)(want < 1024 ? want : 1024)), dim3(64 * NW), lds, st, n,
+                     k, wide_rows(Y, ldy, k) ? 1 : 0, Y, ldy, M, ldm, status);
+  return hipGetLastError();
+}
+
+hipError_t launch_tri_apply(hipStream_t st, int64_t n, int k, double* Y, int ldy, const double* M,
+                            int ldm, const int* status) {
+  if (n <= 0 || k <= 0) return hipSuccess;
+  if (k > kSymMaxK || ldy > (1 << 22)) return hipErrorInvalidValue;
+  const int nt = (k + 15) / 16;
+  if (nt <= 2) return launch_tri<2, 4>(st, n, k, Y, ldy, M, ldm, status);
+  if (nt <= 4) return launch_tri<4, 4>(st, n, k, Y, ldy, M, ldm, status);
+  if (nt <= 6) return launch_tri<6, 4>(st, n, k, Y, ldy, M, ldm, status);
+  if (nt <= 9) return launch_tri<9, 8>(st, n, k, Y, ldy, M, ldm, status);
+  return launch_tri<12, 8>(st, n, k, Y, ldy, M, ldm, status);
 }
 
 // ============================================================================
@@ -882,20 +1140,19 @@ hipError_t launch_colmajor_to_rowmajor(hipStream_t st, int64_t n, int k, const d
 }
 
 __global__ void k_copy_cols(int64_t n, int k, const double* __restrict__ src, int lds,
-                            double* __restrict__ dst, int ldd, const int* __restrict__ status) {
+                            double* __restrict__ dst, int ldd) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n * k) return;
-  if (status && *status == 2) return;  // a failed factorization: dst keeps its values
   const int64_t r = e / k;
   const int c = (int)(e % k);
   dst[r * ldd + c] = src[r * lds + c];
 }
 
 hipError_t launch_copy_cols(hipStream_t st, int64_t n, int k, const double* src, int lds,
-                            double* dst, int ldd, const int* status) {
+                            double* dst, int ldd) {
   const int64_t tot = n * k;
   hipLaunchKernelGGL(k_copy_cols, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, n, k,
-                     src, lds, dst, ldd, status);
+                     src, lds, dst, ldd);
   return hipGetLastError();
 }
 

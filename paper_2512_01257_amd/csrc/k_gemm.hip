@@ -81,11 +81,17 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
                                               const T* __restrict__ B, int64_t ldb,
                                               T* __restrict__ C, int64_t ldc, T alpha, T beta,
                                               T* __restrict__ part) {
-  // rows padded by one element: the transposing stores of a row-major A
-  // spread over the banks
+  // Rows are padded so that the four rows a fragment read touches start 16
+  // elements apart modulo the banks (every bank pair once), and by a whole
+  // number of 16-byte words, so that a panel stored along its rows is stored
+  // in vectors; a transposed A is padded by four more, which spreads its stores
+  // (eight rows of a vector's column over four banks) at two passes a read.
+  // A pad of one element cost four passes a read (FP32, 8192 x 480 x 8192, A by
+  // columns: 654 -> 640 us; FP64 the same).
   constexpr int BN = 32 * TN;                   // block tile width
-  __shared__ T As[2][BK][kBM + 1];
-  __shared__ T Bs[2][BK][BN + 1];
+  constexpr int PA = kBM + 16 + (ACOL ? 0 : sizeof(T) == 4 ? 4 : 2), PB = BN + 16;
+  __shared__ __align__(16) T As[2][BK][PA];
+  __shared__ __align__(16) T Bs[2][BK][PB];
   typedef typename Mfma<T>::Acc Acc;
   constexpr int NVA = kBM * BK / (kGT * VEC);  // vectors per thread: A panel
   constexpr int NVB = BN * BK / (kGT * VEC);   // and B panel
@@ -113,31 +119,40 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
 #pragma unroll
     for (int nt = 0; nt < TN; ++nt) acc[mt][nt] = Acc{T(0), T(0), T(0), T(0)};
 
+  typedef T LV __attribute__((ext_vector_type(VEC)));
+  auto store_row = [&](T* dst, const T (&src)[VEC]) {
+    LV v;
+#pragma unroll
+    for (int u = 0; u < VEC; ++u) v[u] = src[u];
+    *reinterpret_cast<LV*>(dst) = v;
+  };
   auto store = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < NVA; ++q) {
       const int e = (tid + q * kGT) * VEC;
       const int ca = e % CA, oa = e / CA;
+      if (ACOL) {
+        store_row(&As[buf][oa][ca], ra[q]);
+      } else {
 #pragma unroll
-      for (int u = 0; u < VEC; ++u) {
-        if (ACOL)
-          As[buf][oa][ca + u] = ra[q][u];
-        else
-          As[buf][ca + u][oa] = ra[q][u];
+        for (int u = 0; u < VEC; ++u) As[buf][ca + u][oa] = ra[q][u];
       }
     }
 #pragma unroll
     for (int q = 0; q < NVB; ++q) {
       const int e = (tid + q * kGT) * VEC;
-#pragma unroll
-      for (int u = 0; u < VEC; ++u) Bs[buf][e / BN][e % BN + u] = rb[q][u];
+      store_row(&Bs[buf][e / BN][e % BN], rb[q]);
     }
   };
   const int fr = lane >> 4, fc = lane & 15;
   // The fragments of sub-step ks + 4 are read from LDS while the MFMAs of
   // sub-step ks issue (two register sets), so LDS latency overlaps the
   // matrix work.
-  auto mfma_step = [&](int cur) {
+  // FP32 stores the next step's panels before the last sub-step's MFMAs, which
+  // cover them (8192 x 480 x 8192, A by columns: 640 -> 624 us; in FP64 4%
+  // slower, so it stores after them).
+  constexpr bool kStoreInStep = sizeof(T) == 4;
+  auto mfma_step = [&](int cur, bool next) {
     T a[2][4], b[2][TN];
     auto frag = [&](int set, int ks) {
 #pragma unroll
@@ -150,6 +165,7 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
     for (int ks = 0; ks < BK; ks += 4) {
       const int set = (ks / 4) & 1;
       if (ks + 4 < BK) frag(set ^ 1, ks + 4);
+      else if (kStoreInStep && next) store(cur ^ 1);
       // keep the look-ahead reads ahead of this sub-step's MFMAs
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -213,8 +229,8 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
     for (int t = 0; t < nk; ++t) {
       const int cur = t & 1;
       if (t + 1 < nk) load();
-      mfma_step(cur);
-      if (t + 1 < nk) store(cur ^ 1);
+      mfma_step(cur, t + 1 < nk);
+      if (!kStoreInStep && t + 1 < nk) store(cur ^ 1);
       __syncthreads();
     }
   } else {
@@ -253,8 +269,8 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
     for (int t = 0; t < nk; ++t) {
       const int cur = t & 1;
       if (t + 1 < nk) load(kbeg + (t + 1) * BK);
-      mfma_step(cur);
-      if (t + 1 < nk) store(cur ^ 1);
+      mfma_step(cur, t + 1 < nk);
+      if (!kStoreInStep && t + 1 < nk) store(cur ^ 1);
       __syncthreads();
     }
   }

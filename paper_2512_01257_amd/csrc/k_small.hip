@@ -12,46 +12,108 @@ namespace rafeast {
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallMaxK = 192;
 
-__device__ __forceinline__ int packed_index(int k, int i, int j) {  // i <= j
-  return i * k - (i * (i - 1)) / 2 + (j - i);
+// ============================================================================
+// CholQR factor: M = diag(s) R^{-1}, s_i = 1 / sqrt(g_ii), R^T R = S G S
+// (scaled, symmetric part), in 16 x 16 tiles on the FP64 matrix cores, one
+// workgroup, the upper tiles in LDS.  Step J:
+//   T_J = R_JJ^{-1} by one wave (elimination of [A_JJ | I], below);
+//   U_JK = T_J^T A_JK for K > J, and the inverse's column J,
+//   X_IJ = -(sum_{I <= t < J} X_It U_tJ) T_J for I < J (X_JJ = T_J);
+//   A_KL -= U_JK^T U_JL for J < K <= L, the next diagonal tile first, whose
+//   elimination then runs beside the other tiles' updates.
+// Every operand is a tile read along its rows: U as U(q, i), X kept transposed,
+// so that lane l reads element (l / 16, l % 16) of four rows in 512 consecutive
+// bytes; and a product's accumulator v (row l / 16 + 4 v) is fragment v of the
+// next product's right operand, so Y = sum U^T X^T feeds T^T Y in registers.
+// X_IJ overwrites U_IJ (last read for column J of the inverse), a barrier
+// after every wave has read the column.
+// A column at a time (a barrier and a pass over the trailing block for each of
+// k columns, then for each of k columns of the inverse) took 94 us at k = 64
+// and 115 us at k = 84; this CHOL64_US and CHOL84_US us.
+// ============================================================================
+constexpr int kTile = 256;  // doubles of a 16 x 16 tile
+
+__device__ __forceinline__ int tile_at(int nb, int I, int J) {  // I <= J
+  return (I * nb - I * (I - 1) / 2 + (J - I)) * kTile;
 }
 
-// Sum over an aligned group of 2^lg lanes (lg = 2, 3 or 4, inside a 16-lane
-// row), in every lane of the group: the butterfly over lanes l ^ 1, l ^ 2,
-// l ^ 4, l ^ 8 as DPP steps.  After the first two steps all lanes of a quad
-// hold the same value, so the half-row and row mirrors fetch the values the
-// l ^ 4 and l ^ 8 partners hold, and each sum is formed as in the butterfly.
-__device__ __forceinline__ double group_sum_f64(double v, int lg) {
-  v += dpp_f64(v, 0);
-  v += dpp_f64(v, 1);
-  if (lg >= 3) v += dpp_f64(v, 2);
-  if (lg >= 4) v += dpp_f64(v, 3);
-  return v;
+__device__ __forceinline__ void mm4(const double (&a)[4], const double (&b)[4], v4d& c) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[v], b[v], c, 0, 0, 0);
+}
+// element (l / 16 + 4 v, l % 16), v = 0..3, of a tile
+__device__ __forceinline__ void frag4(const double* t, double (&f)[4]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) f[v] = t[64 * v + (threadIdx.x & 63)];
+}
+__device__ __forceinline__ void put4(double* t, const v4d& d) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) t[64 * v + (threadIdx.x & 63)] = d[v];
 }
 
-// ============================================================================
-// CholQR factor.  LDS: dsc[k] (column scales) | U (packed upper, k(k+1)/2)
-// [| X = U^{-1} (packed upper) when kXInLds].  Right-looking Cholesky with
-// one barrier per column: step j reads the unscaled pivot d_j = U[j][j]
-// (every thread, so the failure test is uniform), updates the trailing block
-// by U[i][l] -= U[j][i] U[j][l] / d_j from the unscaled row j, and scales
-// row j-1 (which no thread of step j reads) by 1/sqrt(d_{j-1}).  The inverse
-// is built column by column, X[j][j] = 1/U[j][j] and
-// X[i][j] = -(sum_{t=i}^{j-1} X[i][t] U[t][j]) / U[j][j], in LDS when it fits
-// (else directly in M, global), then its rows are scaled by dsc.
-// ============================================================================
-template <bool kXInLds>
+// One wave: elimination of [A | I] for the symmetric tile A (fragments a), row
+// j of both going round through LDS (row, 32 doubles; a wave's LDS operations
+// are in order, so no barrier), leaves L^{-1} where I was and the pivots d;
+// T = L^{-T} D^{-1/2}.  Writes T^T (the inverse's own tile) over tile and T to
+// ts.  Returns false at a pivot that is not positive and finite.
+__device__ __forceinline__ bool tile_inverse(double (&a)[4], double* row, double* tile,
+                                             double* ts) {
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  double e[4], sc[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    e[v] = li == lk + 4 * v ? 1.0 : 0.0;
+    sc[v] = 0.0;
+  }
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    if (lk == (j & 3)) {
+      row[li] = a[j >> 2];
+      row[16 + li] = e[j >> 2];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const double d = row[j], aj = row[li], ej = row[16 + li];
+    double m[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) m[v] = row[lk + 4 * v];
+    ok = ok && d > 0.0 && isfinite(d);
+    const double inv = rcp_nr(d);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = lk + 4 * v;
+      if (i == j) sc[v] = rsq_nr(d);
+      const double f = i > j ? m[v] * inv : 0.0;
+      a[v] -= f * aj;
+      e[v] -= f * ej;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const double t = e[v] * sc[v];
+    tile[64 * v + lane] = t;
+    ts[16 * li + lk + 4 * v] = t;
+  }
+  return ok;
+}
+
 __global__ __launch_bounds__(kSmallThreads) void k_chol_inv(int k, double shift_unit,
-                                                            const double* __restrict__ G,
-                                                            int ldg, double* __restrict__ M,
-                                                            int ldm, int* __restrict__ flag) {
+                                                            const double* __restrict__ G, int ldg,
+                                                            double* __restrict__ M, int ldm,
+                                                            int* __restrict__ flag) {
   extern __shared__ double sm[];
-  double* dsc = sm;
-  double* U = sm + k;
-  double* X = U + (size_t)k * (k + 1) / 2;  // used when kXInLds
-  __shared__ int s_fail;
-  const int tid = threadIdx.x;
-  if (tid == 0) s_fail = 0;
+  const int nb = (k + 15) >> 4, nt = nb * (nb + 1) / 2;
+  double* A = sm;                      // upper tiles
+  double* ts = A + (size_t)nt * kTile; // T_J
+  double* row = ts + kTile;            // tile_inverse's rows
+  double* dsc = row + 32;              // column scales
+  int* bad = reinterpret_cast<int*>(dsc + k);  // [0] a scale, [1] a pivot
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int NW = kSmallThreads / 64;
+  if (tid < 2) bad[tid] = 0;
   __syncthreads();
   for (int i = tid; i < k; i += kSmallThreads) {
     const double d = G[(size_t)i * ldg + i];
@@ -59,61 +121,98 @@ __global__ __launch_bounds__(kSmallThreads) void k_chol_inv(int k, double shift_
       dsc[i] = 1.0 / sqrt(d);
     } else {
       dsc[i] = 0.0;
-      s_fail = 1;
+      bad[0] = 1;
     }
   }
   __syncthreads();
-  int status = 0;
-  if (s_fail) {
-    status = 2;
-  } else {
-    for (int attempt = 0; attempt < 2; ++attempt) {
-      const double shift = attempt == 0 ? 0.0 : shift_unit;
-      for (int e = tid; e < k * k; e += kSmallThreads) {
-        const int i = e / k, j = e % k;
-        if (j < i) continue;
-        double g = 0.5 * (G[(size_t)i * ldg + j] + G[(size_t)j * ldg + i]) * dsc[i] * dsc[j];
-        if (i == j) g = 1.0 + shift;  // unit diagonal after scaling
-        U[packed_index(k, i, j)] = g;
+  int status = bad[0] ? 2 : 0;
+  for (int attempt = 0; attempt < 2 && status != 2; ++attempt) {
+    // tile entries (I, J), J >= I, in tile order; past k the identity
+    for (int e = tid; e < nt * kTile; e += kSmallThreads) {
+      int t = e / kTile, I = 0;
+      while (t >= nb - I) t -= nb - I++;
+      const int i = 16 * I + (e % kTile) / 16, j = 16 * (I + t) + e % 16;
+      double g = i == j ? 1.0 : 0.0;
+      if (i < k && j < k && i != j)
+        g = 0.5 * (G[(size_t)i * ldg + j] + G[(size_t)j * ldg + i]) * dsc[i] * dsc[j];
+      if (i == j && i < k) g = 1.0 + (attempt == 0 ? 0.0 : shift_unit);
+      A[e] = g;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      double a[4];
+      frag4(A, a);
+      if (!tile_inverse(a, row, A, ts) && tid == 0) bad[1] = 1;
+    }
+    __syncthreads();
+    for (int J = 0; J < nb; ++J) {
+      if (bad[1]) break;  // uniform
+      // U_JK (waves 0 .. nb - 2 - J), then the inverse's X_IJ (the next J
+      // waves): at most nb - 1 <= 11 of them, one each
+      const int nu = nb - 1 - J;
+      const int K = J + 1 + wave, I = wave - nu;
+      v4d x{0.0, 0.0, 0.0, 0.0};
+      if (wave < nb - 1) {
+        double t[4], b[4];
+        frag4(ts, t);
+        if (wave < nu) {
+          double* u = A + tile_at(nb, J, K);
+          frag4(u, b);
+          mm4(t, b, x);
+          put4(u, x);
+        } else {
+          v4d y{0.0, 0.0, 0.0, 0.0};
+          for (int q = I; q < J; ++q) {
+            double u[4];
+            frag4(A + tile_at(nb, q, J), u);
+            frag4(A + tile_at(nb, I, q), b);
+            mm4(u, b, y);
+          }
+#pragma unroll
+          for (int v = 0; v < 4; ++v) b[v] = -y[v];
+          mm4(t, b, x);
+        }
       }
       __syncthreads();
-      bool ok = true;
-      for (int j = 0; j < k; ++j) {
-        const double d = U[packed_index(k, j, j)];
-        if (!(d > 0.0) || !isfinite(d)) {
-          ok = false;
-          break;
-        }
-        if (j > 0) {  // finish row j - 1
-          const int r = j - 1;
-          const double piv = sqrt(U[packed_index(k, r, r)]);
-          for (int l = r + 1 + tid; l < k; l += kSmallThreads) U[packed_index(k, r, l)] /= piv;
-        }
-        const double inv_d = 1.0 / d;
-        // trailing block rows ii, columns ll >= ii, on a 32 x 32 thread grid
-        const int rj = packed_index(k, j, j);  // U[j][c] = U[rj + c - j]
-        for (int ii = j + 1 + (tid >> 5); ii < k; ii += kSmallThreads / 32) {
-          const double a = U[rj + ii - j] * inv_d;
-          const int ri = packed_index(k, ii, ii);  // U[ii][c] = U[ri + c - ii]
-          for (int ll = ii + (tid & 31); ll < k; ll += 32) U[ri + ll - ii] -= a * U[rj + ll - j];
-        }
-        __syncthreads();
-        if (j > 0 && tid == 0) {
-          const int r = j - 1;
-          U[packed_index(k, r, r)] = sqrt(U[packed_index(k, r, r)]);
+      if (wave >= nu && wave < nb - 1) put4(A + tile_at(nb, I, J), x);
+      // trailing tiles: wave 0 the next diagonal one and its inverse, the
+      // other waves the rest in turn
+      if (nu > 0) {
+        int t = wave;
+        const int left = nu * (nu + 1) / 2;
+        while (t < left) {
+          int r = 0, c = t;
+          while (c >= nu - r) c -= nu - r++;
+          const int Kt = J + 1 + r, Lt = Kt + c;
+          double ua[4], ub[4], a[4];
+          double* dst = A + tile_at(nb, Kt, Lt);
+          frag4(A + tile_at(nb, J, Kt), ua);
+          frag4(A + tile_at(nb, J, Lt), ub);
+          frag4(dst, a);
+          v4d d{a[0], a[1], a[2], a[3]};
+#pragma unroll
+          for (int v = 0; v < 4; ++v) ua[v] = -ua[v];
+          mm4(ua, ub, d);
+          if (t == 0) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) a[v] = d[v];
+            if (!tile_inverse(a, row, dst, ts) && tid == 0) bad[1] = 1;
+            break;
+          }
+          put4(dst, d);
+          t += NW - 1;
         }
       }
-      if (ok) {
-        // last row: only its diagonal; the previous diagonal write is
-        // ordered by this barrier
-        if (tid == 0) U[packed_index(k, k - 1, k - 1)] = sqrt(U[packed_index(k, k - 1, k - 1)]);
-        __syncthreads();
-        status = attempt;
-        break;
-      }
-      status = 2;
       __syncthreads();
     }
+    if (!bad[1]) {
+      status = attempt;
+      break;
+    }
+    status = attempt == 0 ? 1 : 2;
+    __syncthreads();
+    if (tid == 0) bad[1] = 0;
+    __syncthreads();
   }
   if (status == 2) {
     for (int e = tid; e < k * k; e += kSmallThreads) {
@@ -123,49 +222,11 @@ __global__ __launch_bounds__(kSmallThreads) void k_chol_inv(int k, double shift_
     if (tid == 0) *flag = 2;
     return;
   }
-  // L lanes of one wave share row i and split the sum (L = 16 for k <= 64,
-  // 8 for k <= 128, else 4: L k <= 1024 threads).
-  const int lg = k <= 64 ? 4 : (k <= 128 ? 3 : 2);
-  const int L = 1 << lg;
-  const int i = tid >> lg, qd = tid & (L - 1);
-  if constexpr (kXInLds) {
-    for (int j = 0; j < k; ++j) {
-      const double ujj = U[packed_index(k, j, j)];
-      double part = 0.0;
-      if (i < j) {
-        for (int t = i + qd; t < j; t += L)
-          part += X[packed_index(k, i, t)] * U[packed_index(k, t, j)];
-      }
-      part = group_sum_f64(part, lg);
-      if (i < j && qd == 0) X[packed_index(k, i, j)] = -part / ujj;
-      if (tid == kSmallThreads - 1) X[packed_index(k, j, j)] = 1.0 / ujj;
-      __syncthreads();
-    }
-    for (int e = tid; e < k * k; e += kSmallThreads) {
-      const int r = e / k, c = e % k;
-      M[(size_t)r * ldm + c] = c >= r ? X[packed_index(k, r, c)] * dsc[r] : 0.0;
-    }
-  } else {
-    for (int e = tid; e < k * k; e += kSmallThreads) {
-      const int r = e / k, c = e % k;
-      if (c < r) M[(size_t)r * ldm + c] = 0.0;
-    }
-    for (int j = 0; j < k; ++j) {
-      const double ujj = U[packed_index(k, j, j)];
-      double part = 0.0;
-      if (i < j) {
-        for (int t = i + qd; t < j; t += L)
-          part += M[(size_t)i * ldm + t] * U[packed_index(k, t, j)];
-      }
-      part = group_sum_f64(part, lg);
-      if (i < j && qd == 0) M[(size_t)i * ldm + j] = -part / ujj;
-      if (tid == kSmallThreads - 1) M[(size_t)j * ldm + j] = 1.0 / ujj;
-      __syncthreads();
-    }
-    for (int e = tid; e < k * k; e += kSmallThreads) {
-      const int r = e / k, c = e % k;
-      if (c >= r) M[(size_t)r * ldm + c] *= dsc[r];
-    }
+  for (int e = tid; e < k * k; e += kSmallThreads) {
+    const int r = e / k, c = e % k;
+    double x = 0.0;
+    if (c >= r) x = A[tile_at(nb, r >> 4, c >> 4) + (c & 15) * 16 + (r & 15)] * dsc[r];
+    M[(size_t)r * ldm + c] = x;
   }
   if (tid == 0) *flag = status;
 }
@@ -181,19 +242,13 @@ hipError_t launch_chol_inv(hipStream_t st, int k, int64_t nrows, const double* G
   // s = 11 (m n + n (n+1)) u ||X||_2^2 with ||X||_2^2 <= trace(G) = k after scaling.
   const double u = 0x1.0p-53;
   const double shift = 11.0 * ((double)nrows * k + (double)k * (k + 1)) * u * (double)k;
-  const size_t base = sizeof(double) * ((size_t)k + (size_t)k * (k + 1) / 2);
-  const size_t with_x = base + sizeof(double) * (size_t)k * (k + 1) / 2;
-  const bool x_lds = with_x <= kSmallLdsMax;
-  const size_t lds = x_lds ? with_x : base;
-  const void* fn = x_lds ? (const void*)k_chol_inv<true> : (const void*)k_chol_inv<false>;
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const int nb = (k + 15) / 16;
+  const size_t lds = sizeof(double) * ((size_t)kTile * (nb * (nb + 1) / 2 + 1) + 32 + k) + 16;
+  hipError_t e = hipFuncSetAttribute((const void*)k_chol_inv,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  if (x_lds)
-    hipLaunchKernelGGL(k_chol_inv<true>, dim3(1), dim3(kSmallThreads), lds, st, k, shift, G, ldg,
-                       M, ldm, flag);
-  else
-    hipLaunchKernelGGL(k_chol_inv<false>, dim3(1), dim3(kSmallThreads), lds, st, k, shift, G, ldg,
-                       M, ldm, flag);
+  hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(kSmallThreads), lds, st, k, shift, G, ldg, M, ldm,
+                     flag);
   return hipGetLastError();
 }
 

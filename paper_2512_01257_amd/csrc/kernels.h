@@ -14,29 +14,32 @@ namespace rafeast {
 
 // ---- sparse x dense (FP64, real) ------------------------------------------
 // Y = alpha * A X + beta * X + gamma * X2 (X2 may be null), CSR A (FP64).
-// span: max |i - j| over the nonzeros a_ij (0: unknown); it sets how many
-// columns one sweep over the rows gathers (spmm_group_cols).
 hipError_t launch_spmm_f64(hipStream_t st, int n, int k, const int* rowptr, const int* col,
                            const double* val, int64_t nnz, const double* X, int ldx, double* Y,
                            int ldy, double alpha, double beta, const double* X2, int ldx2,
-                           double gamma, int64_t span);
-int spmm_group_cols(int k, int64_t span);
+                           double gamma);
 
 // ---- tall-skinny products (FP64 MFMA) ----------------------------------------
 // Number of row chunks the Gram splits n into, and the partial buffer it needs.
 int gram_chunks(int64_t n);
+int gram_chunks_of(int64_t n, int k1, int k2, bool sym);
+size_t gram_chunk_doubles(int k1, int k2);  // of one row chunk
 size_t gram_partial_doubles(int64_t n, int k1, int k2);
 // G = X^T Y; `part` holds gram_partial_doubles(n, k1, k2) doubles.
 hipError_t launch_gram(hipStream_t st, int64_t n, int k1, int k2, const double* X, int ldx,
                        const double* Y, int ldy, double* G, int ldg, double* part);
-// The same with an explicit number of row chunks (clamped to [1, gram_chunks(n)]);
-// `part` holds chunks * k1 * k2 doubles.
+// The same with an explicit number of row chunks (clamped to [1, gram_chunks_of()]);
+// `part` holds chunks * gram_chunk_doubles(k1, k2) doubles.
 hipError_t launch_gram_chunks(hipStream_t st, int64_t n, int k1, int k2, const double* X,
                               int ldx, const double* Y, int ldy, double* G, int ldg, double* part,
                               int chunks);
 // Y = X S, X n x k, S k x k2 (row-major, lds), Y n x k2.  Y must not alias X.
 hipError_t launch_tsmm(hipStream_t st, int64_t n, int k, int k2, const double* X, int ldx,
                        const double* S, int lds, double* Y, int ldy);
+// Y <- Y M in place, M upper triangular k x k, k <= 192; nothing is written when
+// *status is 2 (the failed Cholesky of a CholQR pass).
+hipError_t launch_tri_apply(hipStream_t st, int64_t n, int k, double* Y, int ldy, const double* M,
+                            int ldm, const int* status);
 
 // ---- Rayleigh-Ritz residual ---------------------------------------------------
 // R = W - Q diag(theta); res[c] = ||R_c|| / (s_win ||Q_c||); qn[c] = ||Q_c||.
@@ -68,10 +71,9 @@ hipError_t launch_colmajor_to_rowmajor(hipStream_t st, int64_t n, int k, const d
 // `part` holds 3 * cnt * gram_chunks(n) doubles + cnt ints of scratch.
 hipError_t launch_export_vectors(hipStream_t st, int64_t n, int cnt, const int* sel,
                                  const double* src, int lds, double* dst, double* part);
-// dst[:, 0..k) = src[:, 0..k); with status, nothing is written when *status
-// is 2 (the failed Cholesky of a CholQR pass).
+// dst[:, 0..k) = src[:, 0..k).
 hipError_t launch_copy_cols(hipStream_t st, int64_t n, int k, const double* src, int lds,
-                            double* dst, int ldd, const int* status = nullptr);
+                            double* dst, int ldd);
 // p[0..n) = v by a kernel (usable inside a captured graph, unlike a memset).
 hipError_t launch_fill_int(hipStream_t st, int* p, int v, int n);
 

@@ -126,7 +126,6 @@ struct rafeast_plan_s {
   int* d_rowptr = nullptr;
   int* d_col = nullptr;
   double* d_val = nullptr;
-  int64_t span = 0;  // max |i - j| over the nonzeros (sets the SpMM's column groups)
   SellMatrix sell;
   int* d_sbase = nullptr;
   int* d_perm = nullptr;
@@ -874,20 +873,20 @@ rafeast_status spmm(rafeast_plan_s* P, int k, const double* X, int ldx, double* 
     return RAFEAST_OK;
   }
   HIPCHK(P, launch_spmm_f64(P->st, (int)P->n, k, P->d_rowptr, P->d_col, P->d_val, P->nnz, X, ldx,
-                            Y, ldy, alpha, beta, X2, ldx2, gamma, P->span));
+                            Y, ldy, alpha, beta, X2, ldx2, gamma));
   return RAFEAST_OK;
 }
 
-// CholQR2 on Y (n x k, ld) in place through P->d_T; *info as in rafeast_cholqr2.
+// CholQR2 on Y (n x k, ld) in place; *info as in rafeast_cholqr2.
 // With track (k = m0), the product of the passes' transforms is formed on the
 // device in d_mtot (pass 0 copies M, later passes multiply it on the right).
-// A pass whose factorization failed writes nothing back to Y (the copy reads
+// A pass whose factorization failed writes nothing to Y (the product reads
 // the pass's status on the device), so Y keeps the last good pass; the passes
 // therefore run back to back and their statuses are read once at the end (a
 // third pass follows when the first needed the shift).  d_mtot is not kept
 // across a failure; the callers stop, or stop using it, on one.
 rafeast_status cholqr2(rafeast_plan_s* P, int64_t n, int k, double* Y, int ldy, int* info,
-                       double* tmp, int ldt, bool track = false) {
+                       bool track = false) {
   int worst = 0;
   int passes = 2, read = 0;
   int flags[3] = {0, 0, 0};
@@ -903,8 +902,7 @@ rafeast_status cholqr2(rafeast_plan_s* P, int64_t n, int k, double* Y, int ldy, 
         std::swap(P->d_mtot, P->d_mtmp);
       }
     }
-    HIPCHK(P, launch_tsmm(P->st, n, k, k, Y, ldy, P->d_M, k, tmp, ldt));
-    HIPCHK(P, launch_copy_cols(P->st, n, k, tmp, ldt, Y, ldy, P->d_flag + pass));
+    HIPCHK(P, launch_tri_apply(P->st, n, k, Y, ldy, P->d_M, k, P->d_flag + pass));
     if (pass == passes - 1) {
       HIPCHK(P, hipMemcpyAsync(flags + read, P->d_flag + read, (pass + 1 - read) * sizeof(int),
                                hipMemcpyDeviceToHost, P->st));
@@ -1274,12 +1272,12 @@ rafeast_status solve_begin(rafeast_plan_s* P, const double* Q_init, SolveRun& S)
                              hipMemcpyHostToDevice, P->st));
     HIPCHK(P, launch_colmajor_to_rowmajor(P->st, n, m0, P->d_T, P->d_Q, ld));
     int ci = 0;
-    RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci, P->d_T, ld));
+    RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci));
     if (ci == 2) return fail(P, RAFEAST_BREAKDOWN, "Q_init is rank deficient");
   } else if (!P->have_start) {
     HIPCHK(P, launch_gaussian(P->st, n, m0, P->prm.seed, P->d_Q, ld));
     int ci = 0;
-    RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci, P->d_T, ld));
+    RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci));
     if (ci == 2) return fail(P, RAFEAST_BREAKDOWN, "random start is rank deficient");
   }
   HIPCHK(P, hipMemsetAsync(P->d_stats, 0, 2 * sizeof(int), P->st));
@@ -1454,7 +1452,7 @@ rafeast_status solve_combine(rafeast_plan_s* P, SolveRun& S) {
   HIPCHK(P, hipEventRecord(P->ev[4], P->st));
   std::swap(P->d_Q, P->d_Y);
   int ci = 0;
-  RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci, P->d_T, ld, true));
+  RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci, true));
   P->have_filter = ci != 2;
   HIPCHK(P, hipEventRecord(P->ev[5], P->st));
   HIPCHK(P, hipEventSynchronize(P->ev[5]));
@@ -1872,9 +1870,6 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     std::vector<int> rp(n + 1), cl(nnz);
     for (int64_t i = 0; i <= n; ++i) rp[i] = A->rowptr[i] - base;
     for (int64_t t = 0; t < nnz; ++t) cl[t] = A->colind[t] - base;
-    for (int64_t i = 0; i < n; ++i)
-      for (int t = rp[i]; t < rp[i + 1]; ++t)
-        P->span = std::max<int64_t>(P->span, std::abs((int64_t)cl[t] - i));
     PRCHK(dalloc(P, &P->d_rowptr, n + 1, "rowptr"));
     PRCHK(dalloc(P, &P->d_col, nnz, "colind"));
     PRCHK(dalloc(P, &P->d_val, nnz, "values"));
@@ -2297,7 +2292,7 @@ rafeast_status rafeast_warmstart(rafeast_plan_t P, const double* omega, double* 
   if (op == RAFEAST_WS_NONE) {
     HIPCHK(P, launch_copy_cols(P->st, n, m0, P->d_Y, ld, P->d_Q, ld));
     int ci = 0;
-    RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci, P->d_T, ld));
+    RCHK(cholqr2(P, n, m0, P->d_Q, ld, &ci));
     if (ci == 2) return fail(P, RAFEAST_BREAKDOWN, "orthonormalisation of the sketch failed");
   } else {
     const double lmin = P->prm.lmin, lmax = P->prm.lmax;
@@ -2316,7 +2311,7 @@ rafeast_status rafeast_warmstart(rafeast_plan_t P, const double* omega, double* 
         RCHK(spmm(P, w, P->d_T, ld, P->d_W, ld, -1.0 / Rr, c0 / Rr, P->d_Y, ld, 1.0));
       }
       int ci = 0;
-      RCHK(cholqr2(P, n, w, P->d_W, ld, &ci, P->d_T, ld));
+      RCHK(cholqr2(P, n, w, P->d_W, ld, &ci));
       if (ci == 2) return fail(P, RAFEAST_BREAKDOWN, "orthonormalisation in Phase 1 failed");
       std::swap(P->d_Y, P->d_W);
     }
@@ -2473,7 +2468,9 @@ rafeast_status rafeast_gram_noalloc(void* hip_stream, int64_t n, int32_t k1, int
   hipError_t e = gram_scratch(&part);
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gram_noalloc: scratch address");
   // as many row chunks as rafeast_gram uses when they fit, fewer otherwise
-  const int chunks = (int)std::min<size_t>((size_t)gram_chunks(n), kGramScratchDoubles / tile);
+  const int chunks = (int)std::min<size_t>(
+      (size_t)gram_chunks_of(n, k1, k2, X == Y && ldx == ldy),
+      kGramScratchDoubles / gram_chunk_doubles(k1, k2));
   e = launch_gram_chunks(static_cast<hipStream_t>(hip_stream), n, k1, k2, X, ldx, Y, ldy, G, ldg,
                          part, chunks);
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gram_noalloc: launch");
@@ -2519,12 +2516,11 @@ rafeast_status rafeast_cholqr2(rafeast_plan_t P, int64_t n, int32_t k, double* Y
                                int32_t* info) {
   if (!P || !Y || n < 1 || k < 1 || k > kMaxSmallK || ldy < k || k > n) return RAFEAST_INVALID_ARG;
   DevBuf buf(P);
-  double *tmp = nullptr, *part = nullptr;
-  HIPCHK(P, buf.get(&tmp, (size_t)n * k));
+  double* part = nullptr;
   HIPCHK(P, buf.get(&part, gram_partial_doubles(n, k, k)));
   int ci = 0;
   std::swap(P->d_part, part);
-  const rafeast_status s = cholqr2(P, n, k, Y, ldy, &ci, tmp, k);
+  const rafeast_status s = cholqr2(P, n, k, Y, ldy, &ci);
   std::swap(P->d_part, part);
   if (info) *info = ci;
   RCHK(s);

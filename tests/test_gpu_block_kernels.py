@@ -1,0 +1,96 @@
+"""The block kernels at the edges of their tilings.  CholQR2 at the edges of its 16 x 16 tiles and kernel variants (1, 2, 4, 6, 9 and 12
+tiles a row), with odd widths and ragged row counts, against the QR factor with positive
+diagonal from numpy, and the symmetric Gram product against X^T X.
+
+Tolerances: for a Gaussian block (condition number below 2 sqrt(n / k) <= 40 here) both
+orthonormal factors are within a few k u kappa of the exact one; 1e-11 covers
+k u kappa = 192 * 1.1e-16 * 40 with a margin of ten.  A Gram entry is a sum of n products:
+its error is at most n u |x_i|^T |x_j|."""
+
+import numpy as np
+import pytest
+
+from workloads import grid_laplacian
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(1, 1), (17, 1), (40, 15), (33, 16), (200, 17), (129, 31), (257, 33), (500, 64),
+         (641, 65), (1000, 95), (333, 96), (1500, 97), (700, 144), (1031, 145), (900, 191),
+         (2100, 192)]
+
+
+@pytest.fixture(scope="module")
+def plan(gpu_lib):
+    with gpu_lib.Plan(grid_laplacian((6, 6), 0.1), 0.0, 0.5, 4, nc=2, q=1, p=4) as p:
+        yield p
+
+
+@pytest.mark.parametrize("n,k", SIZES)
+def test_cholqr2_tiles(plan, n, k):
+    import torch
+
+    rng = np.random.default_rng(n + k)
+    Y = rng.standard_normal((n, k)) * np.exp(rng.uniform(-3, 3, k))
+    buf = torch.full((n, k + 3), 7.0, dtype=torch.float64, device="cuda")
+    t = torch.from_numpy(Y).cuda()
+    assert plan.cholqr2(t) == 0
+    Q = t.cpu().numpy()
+    q, r = np.linalg.qr(Y)
+    q = q * np.where(np.diag(r) < 0, -1.0, 1.0)
+    if n >= 2 * k or k == 1:
+        assert np.abs(Q - q).max() <= 1e-11
+    assert np.abs(Q.T @ Q - np.eye(k)).max() <= 1e-13 * max(k, 8)
+    # a leading dimension past k: the columns between are neither read nor written
+    buf[:, :k] = torch.from_numpy(Y).cuda()
+    buf[:, k:] = float("nan")
+    import ctypes as C
+    info = C.c_int32()
+    from paper_2512_01257_amd import native
+    torch.cuda.synchronize()
+    assert native.lib().rafeast_cholqr2(plan.handle, n, k, C.c_void_p(buf.data_ptr()), k + 3,
+                                        C.byref(info)) == 0 and info.value == 0
+    out = buf.cpu().numpy()
+    assert np.abs(out[:, :k] - Q).max() <= 1e-13 and np.isnan(out[:, k:]).all()
+
+
+@pytest.mark.parametrize("n,k", SIZES)
+def test_gram_symmetric(plan, n, k):
+    import torch
+
+    rng = np.random.default_rng(n * 3 + k)
+    X = rng.standard_normal((n, k))
+    t = torch.from_numpy(X).cuda()
+    G = torch.zeros((k, k), dtype=torch.float64, device="cuda")
+    plan.gram(t, t, G)
+    g = G.cpu().numpy()
+    bound = n * 2.0 ** -53 * (np.abs(X).T @ np.abs(X)) * 2
+    assert (np.abs(g - X.T @ X) <= bound).all()
+    assert (g == g.T).all()
+
+
+@pytest.mark.parametrize("k,pad", [(1, 0), (2, 0), (2, 1), (3, 0), (5, 2), (16, 1), (31, 0), (33, 1),
+                                   (64, 0), (65, 0), (127, 1), (128, 0), (129, 0), (131, 3)])
+def test_spmm_widths(gpu_lib, k, pad):
+    # any width and leading dimension: pairs of columns per lane, odd widths
+    # ending in an overlapping pair; nothing past column k is written
+    import ctypes as C
+
+    import torch
+
+    from workloads import random_symmetric
+
+    csr = random_symmetric(211, seed=9, density=0.05)  # rows of 1 to about 40 entries
+    A = csr.to_scipy()
+    X = np.random.default_rng(k).standard_normal((csr.n, k))
+    with gpu_lib.Plan(csr, 0.0, 0.5, 4, nc=2, q=1, p=4) as p:
+        x = torch.full((csr.n, k + pad), float("nan"), dtype=torch.float64, device="cuda")
+        y = torch.full((csr.n, k + pad), 3.0, dtype=torch.float64, device="cuda")
+        x[:, :k] = torch.from_numpy(X).cuda()
+        torch.cuda.synchronize()
+        assert gpu_lib.lib().rafeast_spmm(p.handle, k, C.c_void_p(x.data_ptr()), k + pad,
+                                          C.c_void_p(y.data_ptr()), k + pad, 1.5, -0.5) == 0
+    out = y.cpu().numpy()
+    ref = 1.5 * (A @ X) - 0.5 * X
+    bound = 64 * 2.0 ** -53 * (1.5 * (abs(A) @ np.abs(X)) + 0.5 * np.abs(X))
+    assert (np.abs(out[:, :k] - ref) <= bound).all()
+    assert (out[:, k:] == 3.0).all()
