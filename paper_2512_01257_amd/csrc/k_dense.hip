@@ -498,12 +498,12 @@ __global__ __launch_bounds__(256) void k_gram_reduce(int chunks, int k1, int k2,
 // ============================================================================
 // Symmetric Gram G = X^T X (CholQR): only the upper 16 x 16 tiles, each
 // workgroup all of them for its chunk of rows, so X is read once.  RS rows are
-// staged in LDS through registers (two buffers, the next stage's loads in
-// flight during this stage's MFMAs); the NW waves own TPW consecutive tiles
+// staged in LDS through registers (two buffers, the loads of the next two
+// stages in flight during this stage's MFMAs); the NW waves own TPW consecutive tiles
 // each.  A row of LDS is PK doubles, PK = 16 mod 32, so that a fragment (4 rows
 // of 16 doubles) covers the banks evenly.  The general kernel above computed all
 // tiles from global memory, reading each row for every block row of tiles
-// (n = 1e6, k = 84: 575 us; this GRAM_SYM_US us, X alone being 139 us at the
+// (n = 1e6, k = 84: 575 us; this 230 us, X alone being 139 us at the
 // copy rate, and the tiles 137 us of matrix core time).
 // ============================================================================
 // Two consecutive columns of a row through a descriptor (byte offset off; in:
@@ -545,20 +545,20 @@ __global__ __launch_bounds__(64 * NW) void k_gram_sym(int64_t n, int k, int wide
       (void*)(X + r_begin * ldx), (short)0, rows > 0 ? ((rows - 1) * ldx + k) * 8 : 0,
       kBufferWord3);
   const int sr = tid / LPR, sl = tid % LPR;  // staged row, first column pair
-  double2 ld[NL];
-  auto load = [&](int r0) {
+  double2 ld[2][NL];  // two stages ahead
+  auto load = [&](double2 (&d)[NL], int r0) {
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
       const int c = 2 * (sl + LPR * u);
       const bool in = r0 + sr < rows;
-      ld[u] = load_pair(xs, ((r0 + sr) * ldx + c) * 8, in && c < k, in && c + 1 < k, wide != 0);
+      d[u] = load_pair(xs, ((r0 + sr) * ldx + c) * 8, in && c < k, in && c + 1 < k, wide != 0);
     }
   };
-  auto stage = [&](double* dst) {
+  auto stage = [&](double* dst, const double2 (&d)[NL]) {
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
       const int c = 2 * (sl + LPR * u);
-      if (c < 16 * nt) *reinterpret_cast<double2*>(dst + sr * PK + c) = ld[u];
+      if (c < 16 * nt) *reinterpret_cast<double2*>(dst + sr * PK + c) = d[u];
     }
   };
   // this wave's tiles
@@ -577,12 +577,11 @@ __global__ __launch_bounds__(64 * NW) void k_gram_sym(int64_t n, int k, int wide
 #pragma unroll
   for (int u = 0; u < TPW; ++u) acc[u] = v4d{0.0, 0.0, 0.0, 0.0};
   const int buf = RS * PK;
-  load(0);
-  stage(sx);
-  __syncthreads();
-  for (int r0 = 0, cur = 0; r0 < rows; r0 += RS, cur ^= 1) {
-    if (r0 + RS < rows) load(r0 + RS);
-    const double* b = sx + cur * buf;
+  // stage s at rows RS s: its MFMAs, while stage s + 1 waits in registers to be
+  // stored at their end and stage s + 2 is being loaded
+  auto step = [&](int r0, const double* b, double* next, const double2 (&d)[NL],
+                  double2 (&dl)[NL]) {
+    if (r0 + 2 * RS < rows) load(dl, r0 + 2 * RS);
 #pragma unroll
     for (int q = 0; q < RS / 4; ++q) {
       double fa[TPW], fb[TPW];
@@ -595,8 +594,16 @@ __global__ __launch_bounds__(64 * NW) void k_gram_sym(int64_t n, int k, int wide
       for (int u = 0; u < TPW; ++u)
         acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u], fb[u], acc[u], 0, 0, 0);
     }
-    if (r0 + RS < rows) stage(sx + (cur ^ 1) * buf);
+    if (r0 + RS < rows) stage(next, d);
     __syncthreads();
+  };
+  load(ld[0], 0);
+  load(ld[1], RS);
+  stage(sx, ld[0]);
+  __syncthreads();
+  for (int r0 = 0; r0 < rows; r0 += 2 * RS) {
+    step(r0, sx, sx + buf, ld[1], ld[0]);
+    if (r0 + RS < rows) step(r0 + RS, sx + buf, sx, ld[0], ld[1]);
   }
   // partial tiles in tile order, accumulator v of lane l at 64 v + l
 #pragma unroll
@@ -855,7 +862,7 @@ hipError_t launch_tsmm(hipStream_t st, int64_t n, int k, int k2, const double* X
 // of columns, 16 bytes a lane: lane l holds row l % 16, columns 8 s + 2 (l / 16)
 // and the next, which are k-steps 2 s and 2 s + 1; M's rows are staged in that
 // order) and writes column tile t from the tiles s <= t, so a row is read once
-// and written once.  Measured at n = 1e6, k = 84: APPLY_US us; a product with
+// and written once.  Measured at n = 1e6, k = 84: 280 us; a product with
 // the square M into another block and a copy back were 522 + 251 us.
 // ============================================================================
 template <int NT, int NW>

@@ -29,7 +29,7 @@ constexpr int kSmallMaxK = 192;
 // after every wave has read the column.
 // A column at a time (a barrier and a pass over the trailing block for each of
 // k columns, then for each of k columns of the inverse) took 94 us at k = 64
-// and 115 us at k = 84; this CHOL64_US and CHOL84_US us.
+// and 115 us at k = 84; this 23 and 36 us.
 // ============================================================================
 constexpr int kTile = 256;  // doubles of a 16 x 16 tile
 
@@ -231,9 +231,6 @@ __global__ __launch_bounds__(kSmallThreads) void k_chol_inv(int k, double shift_
   if (tid == 0) *flag = status;
 }
 
-// Dynamic LDS budget of the one-workgroup kernels (the static arrays of
-// k_jacobi take under 8 KB of the 160 KB).
-constexpr size_t kSmallLdsMax = 160 * 1024 - 8192;
 
 hipError_t launch_chol_inv(hipStream_t st, int k, int64_t nrows, const double* G, int ldg,
                            double* M, int ldm, int* flag) {
@@ -255,44 +252,95 @@ hipError_t launch_chol_inv(hipStream_t st, int k, int64_t nrows, const double* G
 // ============================================================================
 // Parallel cyclic Jacobi (round-robin pairing).  Each round rotates k/2
 // disjoint pairs (p, q) at once: the rotation J (J_pp = J_qq = c, J_pq = s,
-// J_qp = -s) zeroing H_pq follows Golub & Van Loan, Alg. 8.5.1.  H <- J^T H J
-// is applied per (row pair, column pair) 2x2 block, each block by one thread,
-// and V <- V J per (row, pair).  H lives in LDS for k <= 128, else in global
-// workspace; V lives in LDS too when both fit, else in global workspace.
+// J_qp = -s) zeroing H_pq follows Golub & Van Loan, Alg. 8.5.1.
+//
+// Two kernels.  k_jacobi, one workgroup, iterates H alone: the upper triangle
+// in LDS (an entry (i, j) is kept at (min, max); packed when the square does not
+// fit), H <- J^T H J per 2 x 2 block of pairs t1 <= t2, a block per thread.  A
+// round is a chain - rotation parameters by one wave, barrier, update, barrier -
+// and the update is LDS traffic, so it touches each block once: with both
+// triangles and V in the same rounds a k = 84 matrix took 2.6 us a round,
+// now 0.69 us.  The rotations go to a list in memory, and k_jacobi_vec applies
+// them to V: the rows of V are independent, so a wave per row runs them on as
+// many CUs as there are rows.
 // ============================================================================
-template <bool kHInLds, bool kVInLds>
+constexpr int kMaxSweeps = 40;
+constexpr int kJacobiPairs = kSmallMaxK / 2;
+
+// A square of kk (k rounded up to even) rows, or its packed upper triangle.
+template <bool kPacked>
+__device__ __forceinline__ int sym_at(int i, int j, int kk) {
+  const int lo = min(i, j), hi = max(i, j);
+  return kPacked ? lo * (2 * kk - lo - 1) / 2 + hi : lo * (kk | 1) + hi;
+}
+
+// (c, s) = f (e, a) with f within an ulp or two of 1 / sqrt(e^2 + a^2).  f errs the
+// same way for all the rotations of a small angle, which would scale V and H
+// by as much each round: one step back to c^2 + s^2 = 1.  1 - c is exact, of the
+// rounded c: contracted into the product before it, it would miss the rounding.
+__device__ __forceinline__ void unit_pair(double e, double a, double f, double& c, double& s) {
+#pragma clang fp contract(off)
+  c = e * f;
+  s = a * f;
+  const double g = 0.5 * fma(-s, s, (1.0 - c) * (1.0 + c));
+  c = fma(c, g, c);
+  s = fma(s, g, s);
+}
+
+// NB: blocks per thread.  With k odd the last player is a dummy: its row and
+// column are zero and its rotations the identity.
+template <int NB, bool kPacked>
 __global__ __launch_bounds__(kSmallThreads) void k_jacobi(int k, const double* __restrict__ Hin,
                                                           int ldh, double* __restrict__ theta,
-                                                          double* __restrict__ S, int lds,
-                                                          double* __restrict__ work) {
-  extern __shared__ double sh_h[];
-  __shared__ int rp[kSmallMaxK / 2 + 1], rq[kSmallMaxK / 2 + 1], perm[kSmallMaxK];
-  __shared__ double rc[kSmallMaxK / 2 + 1], rs[kSmallMaxK / 2 + 1], dg[kSmallMaxK];
+                                                          double2* __restrict__ rot,
+                                                          int* __restrict__ out) {
+  extern __shared__ double H[];
+  __shared__ double2 cs[kJacobiPairs];
+  __shared__ double dg[kSmallMaxK];
   __shared__ double red[2][kSmallThreads / 64];
-  // In LDS, H and V rows are k | 1 doubles apart (an odd stride): the rows a
-  // wave touches in one access then start in different banks.
-  const int hs = kHInLds ? (k | 1) : k, vs = kVInLds ? (k | 1) : k;
-  double* H = kHInLds ? sh_h : work;
-  double* V = kVInLds ? sh_h + (size_t)k * hs : work + (size_t)k * k;
   const int tid = threadIdx.x;
-  for (int e = tid; e < k * k; e += kSmallThreads) {
-    const int i = e / k, j = e % k;
-    H[i * hs + j] = 0.5 * (Hin[(size_t)i * ldh + j] + Hin[(size_t)j * ldh + i]);
-    V[i * vs + j] = (i == j) ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  const int kk = k + (k & 1);
-  const int np = kk / 2;
+  const int kk = k + (k & 1), np = kk / 2;
   const int players = kk - 1;  // the last player stays fixed
-  const float inv_np = 1.0f / (float)np;
-  for (int sweep = 0; sweep < 40; ++sweep) {
+  for (int e = tid; e < kk * kk; e += kSmallThreads) {
+    const int i = e / kk, j = e % kk;
+    if (j < i) continue;
+    double h = 0.0;
+    if (j < k) h = 0.5 * (Hin[(size_t)i * ldh + j] + Hin[(size_t)j * ldh + i]);
+    H[sym_at<kPacked>(i, j, kk)] = h;
+  }
+  // The last wave (two with more than 64 pairs) forms the rotations and holds
+  // no blocks; the other threads hold NB blocks (t1 <= t2), as packed row by row.
+  const int nbt = kSmallThreads - (np <= 64 ? 64 : 128), pt = tid - nbt;
+  int t1[NB], t2[NB];
+  bool on[NB];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int b = tid + nbt * u;
+    on[u] = pt < 0 && b < np * (np + 1) / 2;
+    int r = 0, c = on[u] ? b : 0;
+    while (c >= np - r) c -= np - r++;
+    t1[u] = r;
+    t2[u] = r + c;
+  }
+  // players of slot t in round r
+  auto first = [&](int r, int t) {
+    const int p = r + t;
+    return p >= players ? p - players : p;
+  };
+  auto second = [&](int r, int t) {
+    const int q = r - t;
+    return t == 0 ? kk - 1 : q < 0 ? q + players : q;
+  };
+  __syncthreads();
+  int rounds = 0;
+  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
     // convergence test on the off-diagonal mass
     double off = 0.0, tot = 0.0;
     for (int i = tid >> 5; i < k; i += kSmallThreads / 32)
-      for (int j = tid & 31; j < k; j += 32) {
-        const double h = H[i * hs + j];
-        tot += h * h;
-        if (i != j) off += h * h;
+      for (int j = i + (tid & 31); j < k; j += 32) {
+        const double h = H[sym_at<kPacked>(i, j, kk)];
+        if (i != j) off += 2.0 * h * h;
+        else tot += h * h;
       }
     off = wave_sum(off);
     tot = wave_sum(tot);
@@ -307,6 +355,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_jacobi(int k, const double* _
       off += red[0][w];
       tot += red[1][w];
     }
+    tot += off;
     __syncthreads();
     // converged once the off-diagonal mass is at the rounding floor: each
     // of the k (k - 1) off-diagonal entries is then a few units of roundoff
@@ -314,117 +363,222 @@ __global__ __launch_bounds__(kSmallThreads) void k_jacobi(int k, const double* _
     // per entry (u = 2^-53)
     if (k == 1 || off <= 64.0 * k * 0x1.0p-106 * tot) break;
     for (int r = 0; r < players; ++r) {
-      for (int t = tid; t < np; t += kSmallThreads) {
-        int p, q;
-        if (t == 0) {
-          p = r;
-          q = kk - 1;
-        } else {
-          p = (r + t) % players;
-          q = (r - t + players) % players;
-        }
+      // the blocks' entries are read while the rotations are formed: H changes
+      // only past the barrier
+      int at[NB][4];
+      double h[NB][4];
+      if (pt >= 0) {
+        __builtin_amdgcn_s_setprio(3);  // the other waves wait for this one
+        const int pi = min(pt, np - 1);
+        const int p = first(r, pi), q = second(r, pi);
+        const double hpp = H[sym_at<kPacked>(p, p, kk)], hqq = H[sym_at<kPacked>(q, q, kk)];
+        const double apq = H[sym_at<kPacked>(p, q, kk)];
         double c = 1.0, s = 0.0;
-        if (p < k && q < k) {
-          const double apq = H[p * hs + q];
-          if (fabs(apq) >= 0x1.0p-1000) {
-            // this phase is one wave's latency per round: reciprocals and
-            // square roots from Newton-refined hardware estimates (a few ulp;
-            // the rotation stays orthogonal to working precision)
-            const double tau = (H[q * hs + q] - H[p * hs + p]) * rcp_nr(2.0 * apq);
-            double tt;
-            if (fabs(tau) > 1e150) {
-              tt = 0.5 / tau;
-            } else {
-              const double w = fma(tau, tau, 1.0);
-              tt = (tau >= 0.0 ? 1.0 : -1.0) * rcp_nr(fabs(tau) + w * rsq_nr(w));
-            }
-            c = rsq_nr(fma(tt, tt, 1.0));
-            s = tt * c;
-          } else if (apq != 0.0) {
-            const double tau = (H[q * hs + q] - H[p * hs + p]) / (2.0 * apq);
-            const double tt = fabs(tau) > 1e150 ? 0.5 / tau
-                              : (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            c = 1.0 / sqrt(1.0 + tt * tt);
-            s = tt * c;
-          }
+        // t = s / c is the smaller root of t^2 + 2 tau t = 1, tau = d / (2 a),
+        // d = h_qq - h_pp, a = h_pq:  with e = |d| + sqrt(d^2 + 4 a^2),
+        // t = 2 a sgn(d) / e, c = e / sqrt(e^2 + 4 a^2), s = t c.  This phase
+        // is one wave's latency per round, so the two square roots are
+        // Newton-refined hardware estimates (a few ulp; the rotation stays
+        // orthogonal to working precision) and nothing is divided: a third
+        // fewer steps in the chain than from tau.
+        const double d = hqq - hpp, a2 = 2.0 * apq, w = fma(d, d, a2 * a2);
+        if (apq != 0.0 && w > 0x1.0p-900 && w < 0x1.0p+900) {
+          const double e = fabs(d) + w * rsq_nr(w);
+          unit_pair(e, d >= 0.0 ? a2 : -a2, rsq_nr(fma(e, e, a2 * a2)), c, s);
+        } else if (apq != 0.0) {
+          const double tau = (hqq - hpp) / (2.0 * apq);
+          const double tt = fabs(tau) > 1e150 ? 0.5 / tau
+                            : (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+          c = 1.0 / sqrt(1.0 + tt * tt);
+          s = tt * c;
         }
-        rp[t] = p;
-        rq[t] = q;
-        rc[t] = c;
-        rs[t] = s;
+        __builtin_amdgcn_s_setprio(0);
+        if (pt < np) {
+          cs[pt] = make_double2(c, s);
+          rot[(size_t)rounds * np + pt] = make_double2(c, s);
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+          const int p1 = first(r, t1[u]), q1 = second(r, t1[u]);
+          const int p2 = first(r, t2[u]), q2 = second(r, t2[u]);
+          at[u][0] = sym_at<kPacked>(p1, p2, kk);
+          at[u][1] = sym_at<kPacked>(p1, q2, kk);
+          at[u][2] = sym_at<kPacked>(q1, p2, kk);
+          at[u][3] = sym_at<kPacked>(q1, q2, kk);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) h[u][e] = H[at[u][e]];
+        }
       }
+      ++rounds;
       __syncthreads();
-      for (int b = tid; b < np * np; b += kSmallThreads) {
-        // b / np in float: exact for b, e < 2^15 and np <= 96
-        const int t1 = (int)(((float)b + 0.5f) * inv_np), t2 = b - t1 * np;
-        const int p1 = rp[t1], q1 = rq[t1], p2 = rp[t2], q2 = rq[t2];
-        const double c1 = rc[t1], s1 = rs[t1], c2 = rc[t2], s2 = rs[t2];
-        const bool v_p1 = p1 < k, v_q1 = q1 < k, v_p2 = p2 < k, v_q2 = q2 < k;
-        const double h00 = (v_p1 && v_p2) ? H[p1 * hs + p2] : 0.0;
-        const double h01 = (v_p1 && v_q2) ? H[p1 * hs + q2] : 0.0;
-        const double h10 = (v_q1 && v_p2) ? H[q1 * hs + p2] : 0.0;
-        const double h11 = (v_q1 && v_q2) ? H[q1 * hs + q2] : 0.0;
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        if (!on[u]) continue;
+        const double2 j1 = cs[t1[u]], j2 = cs[t2[u]];
         // rows: J^T
-        const double g00 = c1 * h00 - s1 * h10, g01 = c1 * h01 - s1 * h11;
-        const double g10 = s1 * h00 + c1 * h10, g11 = s1 * h01 + c1 * h11;
+        const double g00 = j1.x * h[u][0] - j1.y * h[u][2], g01 = j1.x * h[u][1] - j1.y * h[u][3];
+        const double g10 = j1.y * h[u][0] + j1.x * h[u][2], g11 = j1.y * h[u][1] + j1.x * h[u][3];
         // columns: J
-        const double f00 = c2 * g00 - s2 * g01, f01 = s2 * g00 + c2 * g01;
-        const double f10 = c2 * g10 - s2 * g11, f11 = s2 * g10 + c2 * g11;
-        if (v_p1 && v_p2) H[p1 * hs + p2] = f00;
-        if (v_p1 && v_q2) H[p1 * hs + q2] = f01;
-        if (v_q1 && v_p2) H[q1 * hs + p2] = f10;
-        if (v_q1 && v_q2) H[q1 * hs + q2] = f11;
-      }
-      for (int e = tid; e < k * np; e += kSmallThreads) {
-        const int row = (int)(((float)e + 0.5f) * inv_np), t = e - row * np;
-        const int p = rp[t], q = rq[t];
-        if (p < k && q < k) {
-          const double c = rc[t], s = rs[t];
-          const double vp = V[row * vs + p], vq = V[row * vs + q];
-          V[row * vs + p] = c * vp - s * vq;
-          V[row * vs + q] = s * vp + c * vq;
-        }
+        H[at[u][0]] = j2.x * g00 - j2.y * g01;
+        H[at[u][1]] = j2.y * g00 + j2.x * g01;
+        if (t1[u] != t2[u]) H[at[u][2]] = j2.x * g10 - j2.y * g11;
+        H[at[u][3]] = j2.y * g10 + j2.x * g11;
       }
       __syncthreads();
     }
   }
-  for (int i = tid; i < k; i += kSmallThreads) dg[i] = H[i * hs + i];
+  for (int i = tid; i < k; i += kSmallThreads) dg[i] = H[sym_at<kPacked>(i, i, kk)];
   __syncthreads();
   for (int i = tid; i < k; i += kSmallThreads) {
     const double d = dg[i];
     int rank = 0;
     for (int j = 0; j < k; ++j) rank += (dg[j] < d) || (dg[j] == d && j < i);
     theta[rank] = d;
-    perm[rank] = i;
+    out[1 + i] = rank;
   }
-  __syncthreads();
-  for (int e = tid; e < k * k; e += kSmallThreads) {
-    const int row = e / k, c = e % k;
-    S[(size_t)row * lds + c] = V[row * vs + perm[c]];
+  if (tid == 0) out[0] = rounds;
+}
+
+// Row blockIdx.x of V = J_1 J_2 ... J_rounds, its columns in the order of the
+// eigenvalues.  Lane l holds the row's entries of slots l + 64 w (first and
+// second player); after a round the first players move one slot down and the
+// second ones one slot up (slot 0's second player stays, its first becomes
+// slot 1's second, and the last slot's second player becomes its first), which
+// is the next round's pairing, and after a sweep every player is back.
+template <int NP>
+__device__ __forceinline__ void shift_slots(double (&a)[NP], double (&b)[NP], int np) {
+  const int lane = threadIdx.x;
+  double na[NP], nb[NP], x[NP];
+#pragma unroll
+  for (int w = 0; w < NP; ++w) x[w] = w == 0 && lane == 0 ? a[0] : b[w];
+  auto down = [](double v) {  // lane l <- lane l + 1
+    const long long t = __double_as_longlong(v);
+    const int lo = (int)(t & 0xffffffffLL), hi = (int)(t >> 32);
+    const int l2 = __builtin_amdgcn_update_dpp(0, lo, 0x130, 0xF, 0xF, false);
+    const int h2 = __builtin_amdgcn_update_dpp(0, hi, 0x130, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)h2 << 32) | (unsigned)l2);
+  };
+  auto up = [](double v) {  // lane l <- lane l - 1
+    const long long t = __double_as_longlong(v);
+    const int lo = (int)(t & 0xffffffffLL), hi = (int)(t >> 32);
+    const int l2 = __builtin_amdgcn_update_dpp(0, lo, 0x138, 0xF, 0xF, false);
+    const int h2 = __builtin_amdgcn_update_dpp(0, hi, 0x138, 0xF, 0xF, false);
+    return __longlong_as_double(((long long)h2 << 32) | (unsigned)l2);
+  };
+#pragma unroll
+  for (int w = 0; w < NP; ++w) {
+    na[w] = down(a[w]);
+    nb[w] = up(x[w]);
+    // the reads of another lane stand outside the lane's own condition: inside
+    // it the compiler would put this lane's value of a select for every lane's
+    if (w + 1 < NP) {
+      const double v = readlane_f64(a[w + 1 < NP ? w + 1 : w], 0);
+      na[w] = lane == 63 ? v : na[w];
+    }
+    if (w > 0) {
+      const double v = readlane_f64(x[w > 0 ? w - 1 : 0], 63);
+      nb[w] = lane == 0 ? v : nb[w];
+    }
+    if (lane + 64 * w == np - 1) na[w] = b[w];
   }
+  if (lane == 0) nb[0] = b[0];
+#pragma unroll
+  for (int w = 0; w < NP; ++w) {
+    a[w] = na[w];
+    b[w] = nb[w];
+  }
+}
+
+template <int NP>
+__global__ __launch_bounds__(64) void k_jacobi_vec(int k, const double2* __restrict__ rot,
+                                                   const int* __restrict__ out,
+                                                   double* __restrict__ S, int lds) {
+  const int row = blockIdx.x, lane = threadIdx.x;
+  const int kk = k + (k & 1), np = kk / 2, players = kk - 1;
+  const int rounds = out[0];
+  double a[NP], b[NP];
+  int pa[NP], pb[NP];
+#pragma unroll
+  for (int w = 0; w < NP; ++w) {
+    const int t = lane + 64 * w;
+    pa[w] = t;
+    pb[w] = t == 0 ? kk - 1 : players - t;
+    a[w] = t < np && pa[w] == row ? 1.0 : 0.0;
+    b[w] = t < np && pb[w] == row ? 1.0 : 0.0;
+  }
+  // the list is read kAhead rounds ahead
+  constexpr int kAhead = 8;
+  double2 c[kAhead][NP];
+  auto load = [&](double2 (&d)[NP], int r) {
+#pragma unroll
+    for (int w = 0; w < NP; ++w) {
+      const int t = min(lane + 64 * w, np - 1);
+      d[w] = rot[(size_t)min(r, max(rounds - 1, 0)) * np + t];
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) load(c[u], u);
+  for (int r = 0; r < rounds; r += kAhead) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (r + u < rounds) {
+#pragma unroll
+        for (int w = 0; w < NP; ++w) {
+          const double va = a[w], vb = b[w];
+          a[w] = c[u][w].x * va - c[u][w].y * vb;
+          b[w] = c[u][w].y * va + c[u][w].x * vb;
+        }
+        if (np > 1) shift_slots<NP>(a, b, np);
+      }
+      load(c[u], r + u + kAhead);
+    }
+  }
+#pragma unroll
+  for (int w = 0; w < NP; ++w) {
+    if (lane + 64 * w >= np) continue;
+    if (pa[w] < k) S[(size_t)row * lds + out[1 + pa[w]]] = a[w];
+    if (pb[w] < k && pb[w] != pa[w]) S[(size_t)row * lds + out[1 + pb[w]]] = b[w];
+  }
+}
+
+size_t jacobi_work_doubles(int k) {
+  const size_t kk = k + (k & 1);
+  return (size_t)kMaxSweeps * (kk - 1) * kk + kk;  // the rotations; rounds and ranks
 }
 
 hipError_t launch_jacobi(hipStream_t st, int k, const double* H, int ldh, double* theta,
                          double* S, int lds, double* work) {
   if (k < 1 || k > kSmallMaxK) return hipErrorInvalidValue;
-  // H (and V) in LDS with rows k | 1 doubles apart
-  const size_t hb = sizeof(double) * (size_t)k * (size_t)(k | 1);
-  if (2 * hb <= kSmallLdsMax) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_jacobi<true, true>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)(2 * hb));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_jacobi<true, true>), dim3(1), dim3(kSmallThreads), 2 * hb, st, k, H,
-                       ldh, theta, S, lds, work);
-  } else if (k <= 128) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_jacobi<true, false>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)hb);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_jacobi<true, false>), dim3(1), dim3(kSmallThreads), hb, st, k, H, ldh,
-                       theta, S, lds, work);
-  } else {
-    hipLaunchKernelGGL((k_jacobi<false, false>), dim3(1), dim3(kSmallThreads), 0, st, k, H, ldh,
-                       theta, S, lds, work);
-  }
+  const int kk = k + (k & 1), np = kk / 2, blocks = np * (np + 1) / 2;
+  double2* rot = reinterpret_cast<double2*>(work);
+  int* out = reinterpret_cast<int*>(rot + (size_t)kMaxSweeps * (kk - 1) * np);
+  // the square while two blocks a thread suffice (k <= 122: 118 KB of LDS),
+  // else the packed triangle
+  const size_t square = sizeof(double) * (size_t)kk * (kk | 1);
+  const int holders = kSmallThreads - 64;
+  const bool packed = blocks > 2 * holders;
+  const size_t bytes = packed ? sizeof(double) * (size_t)kk * (kk + 1) / 2 : square;
+  const void* fn = packed ? (const void*)k_jacobi<6, true>
+                   : blocks > holders ? (const void*)k_jacobi<2, false>
+                                            : (const void*)k_jacobi<1, false>;
+  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) return e;
+  if (packed)
+    hipLaunchKernelGGL((k_jacobi<6, true>), dim3(1), dim3(kSmallThreads), bytes, st, k, H, ldh,
+                       theta, rot, out);
+  else if (blocks > holders)
+    hipLaunchKernelGGL((k_jacobi<2, false>), dim3(1), dim3(kSmallThreads), bytes, st, k, H, ldh,
+                       theta, rot, out);
+  else
+    hipLaunchKernelGGL((k_jacobi<1, false>), dim3(1), dim3(kSmallThreads), bytes, st, k, H, ldh,
+                       theta, rot, out);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (np <= 64)
+    hipLaunchKernelGGL(k_jacobi_vec<1>, dim3(k), dim3(64), 0, st, k, rot, out, S, lds);
+  else
+    hipLaunchKernelGGL(k_jacobi_vec<2>, dim3(k), dim3(64), 0, st, k, rot, out, S, lds);
   return hipGetLastError();
 }
 

@@ -84,7 +84,8 @@ hipError_t launch_fill_int(hipStream_t st, int* p, int v, int n);
 hipError_t launch_chol_inv(hipStream_t st, int k, int64_t nrows, const double* G, int ldg,
                            double* M, int ldm, int* flag);
 // Parallel cyclic Jacobi: theta ascending, S row-major (column c = vector c).
-// `work` holds 2 * k * k doubles.
+// `work` holds jacobi_work_doubles(k).
+size_t jacobi_work_doubles(int k);
 hipError_t launch_jacobi(hipStream_t st, int k, const double* H, int ldh, double* theta,
                          double* S, int lds, double* work);
 // Keep the m0 of k Ritz values with the largest |phi(theta)|,

@@ -145,7 +145,7 @@ struct rafeast_plan_s {
   double* d_M = nullptr;     // kmax^2
   double* d_S = nullptr;     // kmax^2
   double* d_Ssel = nullptr;  // kmax * m0
-  double* d_jw = nullptr;    // 2 kmax^2
+  double* d_jw = nullptr;    // jacobi_work_doubles(kmax)
   double* d_theta = nullptr; // kmax
   double* d_res = nullptr;   // kmax
   double* d_qn = nullptr;    // kmax
@@ -2118,7 +2118,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   PRCHK(dalloc(P, &P->d_M, kk2, "M"));
   PRCHK(dalloc(P, &P->d_S, kk2, "S"));
   PRCHK(dalloc(P, &P->d_Ssel, (size_t)kMaxSmallK * P->m0, "Ssel"));
-  PRCHK(dalloc(P, &P->d_jw, 2 * kk2, "jacobi work"));
+  PRCHK(dalloc(P, &P->d_jw, jacobi_work_doubles(kMaxSmallK), "jacobi work"));
   PRCHK(dalloc(P, &P->d_theta, kMaxSmallK, "theta"));
   PRCHK(dalloc(P, &P->d_res, kMaxSmallK, "res"));
   PRCHK(dalloc(P, &P->d_qn, kMaxSmallK, "qn"));

@@ -94,3 +94,24 @@ def test_spmm_widths(gpu_lib, k, pad):
     bound = 64 * 2.0 ** -53 * (1.5 * (abs(A) @ np.abs(X)) + 0.5 * np.abs(X))
     assert (np.abs(out[:, :k] - ref) <= bound).all()
     assert (out[:, k:] == 3.0).all()
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 31, 63, 64, 85, 86, 87, 88, 121, 122, 123, 124, 127,
+                               128, 129, 130, 131, 191, 192])
+def test_syev_variants(plan, k):
+    # one, two and six blocks a thread, square and packed storage, one and two
+    # slots a lane, odd orders (a dummy player): Jacobi's eigenpairs are within a
+    # few k u |H| of a backward stable solver's
+    import torch
+
+    rng = np.random.default_rng(k)
+    H = rng.standard_normal((k, k))
+    H = 0.5 * (H + H.T)
+    th = torch.empty(k, dtype=torch.float64, device="cuda")
+    S = torch.empty((k, k), dtype=torch.float64, device="cuda")
+    plan.syev(torch.from_numpy(H).cuda(), th, S)
+    t, s = th.cpu().numpy(), S.cpu().numpy()
+    tol = 4 * k * 2.0 ** -53 * max(np.linalg.norm(H, 2), 1e-300) * 8
+    assert np.abs(t - np.linalg.eigvalsh(H)).max() <= tol
+    assert np.abs(s.T @ s - np.eye(k)).max() <= 32 * k * 2.0 ** -53
+    assert np.abs(H @ s - s * t).max() <= tol
