@@ -27,9 +27,14 @@
 //
 // Combining mode (the filter step of FEAST): only the weighted sum
 // sum_j Re(g_j d_j) of the solutions is needed, so the engine accumulates it
-// into one real block as the iterates advance and never stores them: per
-// iteration a shift then moves its direction only (32 B per row and column
-// instead of 64).
+// into one real block as the iterates advance and never stores them: a shift
+// then moves its direction only (32 B per row and column instead of 64).
+//
+// The seed needs nothing of the shifted systems, so their directions and
+// iterates follow it kMsDefer iterations at a time: the seed residuals and the
+// scalars of those iterations are kept, and one pass over the directions
+// applies them all, in the same order and with the same results as a pass per
+// iteration at a quarter of its traffic.
 //
 // Layout: engine rows in the streaming engine's reverse Cuthill-McKee order,
 // blocks n x kp row-major (kp = 64 CPL, column c of lane c / CPL); the seed
@@ -71,7 +76,7 @@ __device__ __forceinline__ Rows my_rows(int n) {
 }
 
 // Sum the four waves' per-lane values and store the workgroup's partial of
-// each column at part[blockIdx.x * kp + c].
+// each column at part[c * gridDim.x + blockIdx.x] (a column's partials together).
 template <int CPL>
 __device__ __forceinline__ void put_partial(const double (&acc)[CPL], double* __restrict__ part,
                                             int kp) {
@@ -84,30 +89,24 @@ __device__ __forceinline__ void put_partial(const double (&acc)[CPL], double* __
     double s = 0.0;
 #pragma unroll
     for (int w = 0; w < kMW; ++w) s += sh[w * 64 * CPL + e];
-    part[(size_t)blockIdx.x * kp + e] = s;
+    part[(size_t)e * gridDim.x + blockIdx.x] = s;
   }
 }
 
 constexpr int kFT = 256;  // threads of a finaliser workgroup (one per column)
 
 // Fixed-order sum of column c's partials over nb workgroups by the kFT
-// threads of the calling workgroup (strided partial sums, then a tree); every
-// thread must call it and receives the total.
-__device__ __forceinline__ double col_total(const double* __restrict__ part, int nb, int kp,
-                                            int c) {
-  __shared__ double sh[kFT];
+// threads of the calling workgroup; every thread must call it and receives the
+// total.
+__device__ __forceinline__ double col_total(const double* __restrict__ part, int nb, int c) {
+  __shared__ double sh[kFT / 64];
   const int t = threadIdx.x;
   double s = 0.0;
-  for (int b = t; b < nb; b += kFT) s += part[(size_t)b * kp + c];
-  sh[t] = s;
+  for (int b = t; b < nb; b += kFT) s += part[(size_t)c * nb + b];
+  s = wave_sum_f64(s);
+  if ((t & 63) == 0) sh[t >> 6] = s;
   __syncthreads();
-  for (int o = kFT / 2; o > 0; o >>= 1) {
-    if (t < o) sh[t] += sh[t + o];
-    __syncthreads();
-  }
-  const double tot = sh[0];
-  __syncthreads();
-  return tot;
+  return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 __device__ __forceinline__ zd zinv(zd a) { return zdiv(zd{1.0, 0.0}, a); }
@@ -154,35 +153,29 @@ __global__ __launch_bounds__(kMT) void k_ms_init(int n, int k, int kp, int nz,
 
 // Column state after the start: |b|, r^T r, the seed scalars and every
 // shift's pi; a system with b = 0 is done at once (x = 0).
-__global__ __launch_bounds__(kFT) void k_ms_fin0(int k, int kp, int nz, int nb,
-                                                 const double* __restrict__ part, MsCols cols,
-                                                 int* __restrict__ count) {
+__global__ __launch_bounds__(kFT) void k_ms_fin0(int k, int nz, int nb, int kp,
+                                                 const double* __restrict__ part, MsCols cols) {
   const int c = blockIdx.x;
-  const double tot = col_total(part, nb, kp, c);
-  if (threadIdx.x != 0) return;
+  const double tot = col_total(part, nb, c);
   const double rr = c < k ? tot : 0.0;
+  const int lv = rr > 0.0 ? 1 : 0;
+  for (int j = threadIdx.x; j < nz; j += kFT) {
+    const int e = j * kp + c;
+    cols.pi[e] = cpx<double>{1.0, 0.0};
+    cols.pi_prev[e] = cpx<double>{1.0, 0.0};
+    cols.bs[e] = cpx<double>{0.0, 0.0};
+    cols.live[e] = lv;
+    cols.its[e] = 0;
+    cols.est[e] = 0.0;
+  }
+  if (threadIdx.x != 0) return;
   cols.rr[c] = rr;
   cols.bn[c] = sqrt(rr);
   cols.alpha[c] = 0.0;
   cols.alpha_prev[c] = 1.0;
   cols.beta_prev[c] = 0.0;
   cols.scale[c] = 1.0;
-  int nl = 0;
-  for (int j = 0; j < nz; ++j) {
-    const int e = j * kp + c;
-    cols.pi[e] = cpx<double>{1.0, 0.0};
-    cols.pi_prev[e] = cpx<double>{1.0, 0.0};
-    cols.ipi[e] = cpx<double>{1.0, 0.0};
-    cols.bs[e] = cpx<double>{0.0, 0.0};
-    cols.as[e] = cpx<double>{0.0, 0.0};
-    const int lv = rr > 0.0 ? 1 : 0;
-    cols.live[e] = lv;
-    cols.its[e] = 0;
-    cols.est[e] = 0.0;
-    nl += lv;
-  }
-  cols.colive[c] = nl > 0 ? 1 : 0;
-  if (nl) atomicAdd(count, nl);
+  cols.colive[c] = lv;
 }
 
 // Seed search direction p = s (r + beta p) for the live columns; with a
@@ -280,330 +273,262 @@ __global__ __launch_bounds__(kMT) void k_ms_spmv(int n, int kp, const int* __res
   put_partial<CPL>(acc, part, kp);
 }
 
-// alpha_k of every live column, then for each live shift pi_{k+1},
-// alpha^s_k = alpha_k pi_k / pi_{k+1} and 1 / pi_k for the update kernel.
-__global__ __launch_bounds__(kFT) void k_ms_fin_alpha(int kp, int k, int nz, int nb,
+// What a shift's thread of a finaliser reads (nothing past the last shift).
+struct ShiftState {
+  cpx<double> pi{}, pi_prev{}, bs{};
+  int live = 0;
+};
+__device__ __forceinline__ ShiftState load_shift(const MsCols& cols, int j, int nz, int kp,
+                                                 int c) {
+  ShiftState v;
+  if (j < nz) {
+    const int e = j * kp + c;
+    v.pi = cols.pi[e];
+    v.pi_prev = cols.pi_prev[e];
+    v.bs = cols.bs[e];
+    v.live = cols.live[e];
+  }
+  return v;
+}
+
+// alpha_k of every live column, then for each shift (a thread each) pi_{k+1}
+// and the scalars of iteration k's shifted update, kept in their slot:
+// 1 / pi_k, beta^s_{k-1} and alpha^s_k = alpha_k pi_k / pi_{k+1}.
+__global__ __launch_bounds__(kFT) void k_ms_fin_alpha(int kp, int k, int nz, int nb, int slot,
                                                       const double* __restrict__ part,
                                                       const cpx<double>* __restrict__ sig,
                                                       const double* __restrict__ g,
                                                       MsCols cols) {
   const int c = blockIdx.x;
-  if (!cols.colive[c]) {  // uniform over the workgroup
-    if (threadIdx.x == 0) cols.scale[c] = 1.0;
-    return;
-  }
-  const double pw = col_total(part, nb, kp, c);
-  if (threadIdx.x != 0) return;
-  cols.scale[c] = 1.0;  // a rescale has been applied by the direction update
-  const double alpha = pw != 0.0 ? cols.rr[c] / pw : 0.0;
-  cols.alpha[c] = alpha;
-  const double cc = cols.beta_prev[c] * alpha / cols.alpha_prev[c];
-  for (int j = 0; j < nz; ++j) {
+  // everything that does not wait for the sum is loaded with its terms: a chain
+  // of dependent loads is what such a small kernel spends its time on
+  const int alive = cols.colive[c];
+  const double rr = cols.rr[c], beta_prev = cols.beta_prev[c], alpha_prev = cols.alpha_prev[c];
+  ShiftState v = load_shift(cols, threadIdx.x, nz, kp, c);
+  const double pw = col_total(part, nb, c);
+  const double alpha = pw != 0.0 ? rr / pw : 0.0;
+  const double cc = beta_prev * alpha / alpha_prev;
+  for (int j = threadIdx.x; j < nz; j += kFT) {
+    if (j >= kFT) v = load_shift(cols, j, nz, kp, c);
     const int e = j * kp + c;
-    if (!cols.live[e]) continue;
-    const zd pk{cols.pi[e].re, cols.pi[e].im}, pm{cols.pi_prev[e].re, cols.pi_prev[e].im};
+    const bool lv = alive && v.live;
+    cpx<double>* sc = cols.sc + (size_t)((slot * nz + j) * 3) * kp + c;
+    cols.on[(slot * nz + j) * kp + c] = lv ? 1 : 0;
+    if (!lv) continue;
+    const zd pk{v.pi.re, v.pi.im}, pm{v.pi_prev.re, v.pi_prev.im};
     const zd f{1.0 + cc + alpha * sig[j].re, alpha * sig[j].im};
     const zd fp = zmul(f, pk);
     const zd pn{fp.re - cc * pm.re, fp.im - cc * pm.im};
     cols.pi_next[e] = cpx<double>{pn.re, pn.im};
     const zd q = zdiv(pk, pn);
-    cols.as[e] = cpx<double>{alpha * q.re, alpha * q.im};
     const zd ip = zinv(pk);
-    cols.ipi[e] = cpx<double>{ip.re, ip.im};
-    if (g) {  // combining mode: the weight of this step's update of x^s
-      const zd gw = zmul(zd{g[2 * (j * k + c)], g[2 * (j * k + c) + 1]},
-                         zd{alpha * q.re, alpha * q.im});
-      cols.gas[e] = cpx<double>{gw.re, gw.im};
-    }
+    zd as{alpha * q.re, alpha * q.im};
+    // combining mode: the weight of this step's update of x^s
+    if (g) as = zmul(zd{g[2 * (j * k + c)], g[2 * (j * k + c) + 1]}, as);
+    sc[0] = cpx<double>{ip.re, ip.im};
+    sc[kp] = v.bs;
+    sc[2 * kp] = cpx<double>{as.re, as.im};
+  }
+  if (threadIdx.x == 0) {
+    cols.scale[c] = 1.0;  // a rescale has been applied by the direction update
+    if (alive) cols.alpha[c] = alpha;
   }
 }
 
-// r <- r - alpha w (partials of the new r^T r); for every live shift, with
-// the old r: p^s = r / pi_k + beta^s p^s, x^s += alpha^s p^s.
+// r_{k+1} = r_k - alpha w into the next slot, partials of its r^T r.
 template <int CPL>
-__global__ __launch_bounds__(kMT) void k_ms_update(int n, int kp, int nz, MsCols cols,
-                                                   double* __restrict__ r,
-                                                   const double* __restrict__ w,
-                                                   cpx<double>* __restrict__ X,
-                                                   cpx<double>* __restrict__ Ps,
-                                                   double* __restrict__ part) {
-  const int lane = threadIdx.x & 63;
-  const int cl = lane * CPL;
-  double alpha[CPL];
+__global__ __launch_bounds__(kMT) void k_ms_rupd(int n, int kp, MsCols cols,
+                                                 const double* __restrict__ r,
+                                                 double* __restrict__ rnext,
+                                                 const double* __restrict__ w,
+                                                 double* __restrict__ part) {
+  const int cl = (threadIdx.x & 63) * CPL;
+  double alpha[CPL], acc[CPL];
   bool on[CPL];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) {
     on[q] = cols.colive[cl + q] != 0;
     alpha[q] = cols.alpha[cl + q];
+    acc[q] = 0.0;
   }
-  double acc[CPL];
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) acc[q] = 0.0;
   const Rows rw = my_rows(n);
-  const size_t blk = (size_t)n * kp;
   for (int t = 0; t < rw.count; ++t) {
     const size_t o = (size_t)(rw.first + rw.stride * t) * kp + cl;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
       if (!on[q]) continue;
-      const double ro = r[o + q];
-      const double rn = ro - alpha[q] * w[o + q];
-      r[o + q] = rn;
+      const double rn = r[o + q] - alpha[q] * w[o + q];
+      rnext[o + q] = rn;
       acc[q] += rn * rn;
-      for (int j = 0; j < nz; ++j) {
-        const int e = j * kp + cl + q;
-        if (!cols.live[e]) continue;
-        const cpx<double> ip = cols.ipi[e], b = cols.bs[e], a = cols.as[e];
-        const cpx<double> po = Ps[j * blk + o + q];
-        const double pr = ro * ip.re + (b.re * po.re - b.im * po.im);
-        const double pi = ro * ip.im + (b.re * po.im + b.im * po.re);
-        Ps[j * blk + o + q] = cpx<double>{pr, pi};
-        cpx<double> x = X[j * blk + o + q];
-        x.re += a.re * pr - a.im * pi;
-        x.im += a.re * pi + a.im * pr;
-        X[j * blk + o + q] = x;
-      }
     }
   }
   put_partial<CPL>(acc, part, kp);
 }
 
-// The same update with the per-shift scalars of this lane's columns held in
-// registers (NZ >= nz shifts, NZ * CPL <= 8) and every live shift's loads of
-// a row issued before any of its arithmetic, so that a wave keeps 2 NZ CPL
-// loads in flight instead of two.
-template <int CPL, int NZ>
-__global__ __launch_bounds__(kMT) void k_ms_update_r(int n, int kp, int nz, MsCols cols,
-                                                     double* __restrict__ r,
-                                                     const double* __restrict__ w,
-                                                     cpx<double>* __restrict__ X,
-                                                     cpx<double>* __restrict__ Ps,
-                                                     double* __restrict__ part) {
-  const int lane = threadIdx.x & 63;
-  const int cl = lane * CPL;
-  double alpha[CPL];
-  bool on[CPL], lv[CPL][NZ];
-  zd ip[CPL][NZ], bs[CPL][NZ], as[CPL][NZ];
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    on[q] = cols.colive[cl + q] != 0;
-    alpha[q] = cols.alpha[cl + q];
-#pragma unroll
-    for (int j = 0; j < NZ; ++j) {
-      const int e = j * kp + cl + q;
-      lv[q][j] = j < nz && cols.live[e] != 0;
-      ip[q][j] = lv[q][j] ? zd{cols.ipi[e].re, cols.ipi[e].im} : zd{0.0, 0.0};
-      bs[q][j] = lv[q][j] ? zd{cols.bs[e].re, cols.bs[e].im} : zd{0.0, 0.0};
-      as[q][j] = lv[q][j] ? zd{cols.as[e].re, cols.as[e].im} : zd{0.0, 0.0};
-    }
+// The shifted updates of ns deferred iterations, in order, for shifts j0 ..
+// j0 + NZ - 1 (those below nz): with r_s the residual in slot s,
+//   p = r_s / pi + beta^s p,  then y += Re(g alpha^s p) (COMB) or x += alpha^s p.
+// A wave takes kSR rows of 64 columns at a time, all their loads together; the
+// scalars come from LDS once for the kSR rows.  What bounds it is memory (the
+// directions, 32 bytes a row, column and shift for ns iterations); one pass
+// per iteration took 27 us on 30,000 rows, 64 columns and 4 shifts, this
+// 50 us for four (6.6 TB/s).
+constexpr int kSW = 8;   // waves
+constexpr int kSR = 4;   // rows of a wave's step
+template <int NZ, bool COMB>
+__global__ __launch_bounds__(64 * kSW) void k_ms_shift(int n, int kp, int nz, int j0, int ns,
+                                                       MsCols cols, const double* __restrict__ r,
+                                                       double* __restrict__ y,
+                                                       cpx<double>* __restrict__ X,
+                                                       cpx<double>* __restrict__ P) {
+  extern __shared__ cpx<double> sc[];  // [slot][shift][3][64]
+  const int lane = threadIdx.x & 63, c = blockIdx.y * 64 + lane;
+  const int wave = wave_id();
+  for (int e = threadIdx.x; e < ns * NZ * 3 * 64; e += 64 * kSW) {
+    const int l = e & 63, q = (e >> 6) % 3, j = (e >> 6) / 3 % NZ, s = (e >> 6) / (3 * NZ);
+    cpx<double> v{0.0, 0.0};
+    if (j0 + j < nz)
+      v = cols.sc[(size_t)((s * nz + j0 + j) * 3 + q) * kp + blockIdx.y * 64 + l];
+    sc[e] = v;
   }
-  double acc[CPL];
+  // bit j of live[s]: shift j0 + j iterated in slot s (it never starts again)
+  int live[kMsDefer];
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) acc[q] = 0.0;
-  const Rows rw = my_rows(n);
+  for (int s = 0; s < kMsDefer; ++s) {
+    live[s] = 0;
+    for (int j = 0; j < NZ && s < ns && j0 + j < nz; ++j)
+      live[s] |= (cols.on[(s * nz + j0 + j) * kp + c] != 0) << j;
+  }
+  const bool any = live[0] != 0;
+  __syncthreads();
+  if (__ballot(any) == 0) return;  // the same columns in every wave
   const size_t blk = (size_t)n * kp;
-  for (int t = 0; t < rw.count; ++t) {
-    const size_t o = (size_t)(rw.first + rw.stride * t) * kp + cl;
-    double ro[CPL];
-    cpx<double> po[CPL][NZ], xo[CPL][NZ];
+  // rows: contiguous stripes, one per XCD, swept by its workgroups side by side
+  const int x = blockIdx.x & 7, per_x = gridDim.x >> 3, stripe = (n + 7) / 8;
+  const int hi = min(n, (x + 1) * stripe);
+  for (int row0 = x * stripe + ((blockIdx.x >> 3) * kSW + wave) * kSR; row0 < hi;
+       row0 += per_x * kSW * kSR) {
+    double rv[kMsDefer][kSR], yv[kSR];
+    cpx<double> p[NZ][kSR], xv[COMB ? 1 : NZ][kSR];
+    size_t o[kSR];
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      ro[q] = on[q] ? r[o + q] : 0.0;
+    for (int i = 0; i < kSR; ++i) o[i] = (size_t)min(row0 + i, hi - 1) * kp + c;
 #pragma unroll
-      for (int j = 0; j < NZ; ++j)
-        if (lv[q][j]) {
-          po[q][j] = Ps[j * blk + o + q];
-          xo[q][j] = X[j * blk + o + q];
+    for (int i = 0; i < kSR; ++i) {
+#pragma unroll
+      for (int s = 0; s < kMsDefer; ++s) rv[s][i] = live[s] ? r[s * blk + o[i]] : 0.0;
+      yv[i] = COMB && any ? y[o[i]] : 0.0;
+#pragma unroll
+      for (int j = 0; j < NZ; ++j) {
+        p[j][i] = cpx<double>{0.0, 0.0};
+        if (!COMB) xv[COMB ? 0 : j][i] = cpx<double>{0.0, 0.0};
+        if (live[0] >> j & 1) {
+          p[j][i] = P[(j0 + j) * blk + o[i]];
+          if (!COMB) xv[COMB ? 0 : j][i] = X[(j0 + j) * blk + o[i]];
         }
+      }
     }
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      if (!on[q]) continue;
-      const double rn = ro[q] - alpha[q] * w[o + q];
-      r[o + q] = rn;
-      acc[q] += rn * rn;
+    for (int s = 0; s < kMsDefer; ++s) {
+      if (s >= ns) break;
 #pragma unroll
       for (int j = 0; j < NZ; ++j) {
-        if (!lv[q][j]) continue;
-        const zd b = bs[q][j], a = as[q][j];
-        const double pr = ro[q] * ip[q][j].re + (b.re * po[q][j].re - b.im * po[q][j].im);
-        const double pi = ro[q] * ip[q][j].im + (b.re * po[q][j].im + b.im * po[q][j].re);
-        Ps[j * blk + o + q] = cpx<double>{pr, pi};
-        X[j * blk + o + q] =
-            cpx<double>{xo[q][j].re + (a.re * pr - a.im * pi), xo[q][j].im + (a.re * pi + a.im * pr)};
+        if (!(live[s] >> j & 1)) continue;
+        const cpx<double>* q = sc + ((s * NZ + j) * 3) * 64 + lane;
+        const cpx<double> ip = q[0], b = q[64], a = q[128];
+#pragma unroll
+        for (int i = 0; i < kSR; ++i) {
+          const cpx<double> po = p[j][i];
+          const double pr = rv[s][i] * ip.re + (b.re * po.re - b.im * po.im);
+          const double pi = rv[s][i] * ip.im + (b.re * po.im + b.im * po.re);
+          p[j][i] = cpx<double>{pr, pi};
+          if (COMB) {
+            yv[i] += a.re * pr - a.im * pi;
+          } else {
+            xv[COMB ? 0 : j][i].re += a.re * pr - a.im * pi;
+            xv[COMB ? 0 : j][i].im += a.re * pi + a.im * pr;
+          }
+        }
       }
     }
-  }
-  put_partial<CPL>(acc, part, kp);
-}
-
-// Combining mode of the update: the shifted directions as in k_ms_update_r,
-// and instead of every shift's iterate the one real block
-// y += sum_j Re(g_{j,c} alpha^s_k p^s_k) (the weighted sum of the iterates).
-template <int CPL, int NZ>
-__global__ __launch_bounds__(kMT) void k_ms_update_y(int n, int kp, int nz, MsCols cols,
-                                                     double* __restrict__ r,
-                                                     const double* __restrict__ w,
-                                                     double* __restrict__ y,
-                                                     cpx<double>* __restrict__ Ps,
-                                                     double* __restrict__ part) {
-  const int lane = threadIdx.x & 63;
-  const int cl = lane * CPL;
-  double alpha[CPL];
-  bool on[CPL], lv[CPL][NZ];
-  zd ip[CPL][NZ], bs[CPL][NZ], ga[CPL][NZ];
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    on[q] = cols.colive[cl + q] != 0;
-    alpha[q] = cols.alpha[cl + q];
-#pragma unroll
-    for (int j = 0; j < NZ; ++j) {
-      const int e = j * kp + cl + q;
-      lv[q][j] = j < nz && cols.live[e] != 0;
-      ip[q][j] = lv[q][j] ? zd{cols.ipi[e].re, cols.ipi[e].im} : zd{0.0, 0.0};
-      bs[q][j] = lv[q][j] ? zd{cols.bs[e].re, cols.bs[e].im} : zd{0.0, 0.0};
-      ga[q][j] = lv[q][j] ? zd{cols.gas[e].re, cols.gas[e].im} : zd{0.0, 0.0};
-    }
-  }
-  double acc[CPL];
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) acc[q] = 0.0;
-  const Rows rw = my_rows(n);
-  const size_t blk = (size_t)n * kp;
-  for (int t = 0; t < rw.count; ++t) {
-    const size_t o = (size_t)(rw.first + rw.stride * t) * kp + cl;
-    double ro[CPL], yo[CPL];
-    cpx<double> po[CPL][NZ];
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      ro[q] = on[q] ? r[o + q] : 0.0;
-      yo[q] = on[q] ? y[o + q] : 0.0;
-#pragma unroll
-      for (int j = 0; j < NZ; ++j)
-        if (lv[q][j]) po[q][j] = Ps[j * blk + o + q];
-    }
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      if (!on[q]) continue;
-      const double rn = ro[q] - alpha[q] * w[o + q];
-      r[o + q] = rn;
-      acc[q] += rn * rn;
-      double yv = yo[q];
+    for (int i = 0; i < kSR; ++i) {
+      if (row0 + i >= hi) break;
+      if (COMB && any) y[o[i]] = yv[i];
 #pragma unroll
       for (int j = 0; j < NZ; ++j) {
-        if (!lv[q][j]) continue;
-        const zd b = bs[q][j];
-        const double pr = ro[q] * ip[q][j].re + (b.re * po[q][j].re - b.im * po[q][j].im);
-        const double pi = ro[q] * ip[q][j].im + (b.re * po[q][j].im + b.im * po[q][j].re);
-        Ps[j * blk + o + q] = cpx<double>{pr, pi};
-        yv += ga[q][j].re * pr - ga[q][j].im * pi;
+        if (!(live[0] >> j & 1)) continue;
+        P[(j0 + j) * blk + o[i]] = p[j][i];
+        if (!COMB) X[(j0 + j) * blk + o[i]] = xv[COMB ? 0 : j][i];
       }
-      y[o + q] = yv;
     }
   }
-  put_partial<CPL>(acc, part, kp);
-}
-
-// Combining mode, generic shift count: as k_ms_update with y in place of the
-// iterates.
-template <int CPL>
-__global__ __launch_bounds__(kMT) void k_ms_update_yg(int n, int kp, int nz, MsCols cols,
-                                                      double* __restrict__ r,
-                                                      const double* __restrict__ w,
-                                                      double* __restrict__ y,
-                                                      cpx<double>* __restrict__ Ps,
-                                                      double* __restrict__ part) {
-  const int lane = threadIdx.x & 63;
-  const int cl = lane * CPL;
-  double alpha[CPL];
-  bool on[CPL];
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    on[q] = cols.colive[cl + q] != 0;
-    alpha[q] = cols.alpha[cl + q];
-  }
-  double acc[CPL];
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) acc[q] = 0.0;
-  const Rows rw = my_rows(n);
-  const size_t blk = (size_t)n * kp;
-  for (int t = 0; t < rw.count; ++t) {
-    const size_t o = (size_t)(rw.first + rw.stride * t) * kp + cl;
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      if (!on[q]) continue;
-      const double ro = r[o + q];
-      const double rn = ro - alpha[q] * w[o + q];
-      r[o + q] = rn;
-      acc[q] += rn * rn;
-      double yv = y[o + q];
-      for (int j = 0; j < nz; ++j) {
-        const int e = j * kp + cl + q;
-        if (!cols.live[e]) continue;
-        const cpx<double> ip = cols.ipi[e], b = cols.bs[e], ga = cols.gas[e];
-        const cpx<double> po = Ps[j * blk + o + q];
-        const double pr = ro * ip.re + (b.re * po.re - b.im * po.im);
-        const double pi = ro * ip.im + (b.re * po.im + b.im * po.re);
-        Ps[j * blk + o + q] = cpx<double>{pr, pi};
-        yv += ga.re * pr - ga.im * pi;
-      }
-      y[o + q] = yv;
-    }
-  }
-  put_partial<CPL>(acc, part, kp);
 }
 
 // beta_k, beta^s_k = beta_k (pi_k / pi_{k+1})^2, the pi shift, the
-// convergence test |r_{k+1}| / |pi_{k+1}| <= tol |b| (or the iteration cap),
-// the live counts, and the rescale of a column whose seed residual has
+// convergence test |r_{k+1}| / |pi_{k+1}| <= tol |b| (or the iteration cap), a
+// shift to a thread, and the rescale of a column whose seed residual has
 // fallen below 1e-100 |b|.
 __global__ __launch_bounds__(kFT) void k_ms_fin_beta(int kp, int nz, int nb,
                                                      const double* __restrict__ part, double tol,
-                                                     int maxit, MsCols cols,
-                                                     int* __restrict__ count) {
+                                                     int maxit, MsCols cols) {
+  __shared__ int left;
   const int c = blockIdx.x;
-  if (!cols.colive[c]) return;  // uniform over the workgroup
-  const double rn = col_total(part, nb, kp, c);
-  if (threadIdx.x != 0) return;
-  const double rr = cols.rr[c];
+  const int alive = cols.colive[c];
+  const double rr = cols.rr[c], bn = cols.bn[c], alpha = cols.alpha[c];
+  const int j0 = threadIdx.x, e0 = j0 * kp + c;
+  cpx<double> pi0{}, pn0{};
+  int live0 = 0, its0 = 0;
+  if (j0 < nz) {
+    pi0 = cols.pi[e0];
+    pn0 = cols.pi_next[e0];
+    live0 = cols.live[e0];
+    its0 = cols.its[e0];
+  }
+  if (threadIdx.x == 0) left = 0;
+  const double rn = col_total(part, nb, c);  // a barrier inside
+  if (!alive) return;  // uniform over the workgroup
   const double beta = rr > 0.0 ? rn / rr : 0.0;
-  const double bn = cols.bn[c];
   const double rnorm = sqrt(rn);
-  int nl = 0;
-  for (int j = 0; j < nz; ++j) {
+  for (int j = threadIdx.x; j < nz; j += kFT) {
     const int e = j * kp + c;
-    if (!cols.live[e]) continue;
-    const zd pk{cols.pi[e].re, cols.pi[e].im}, pn{cols.pi_next[e].re, cols.pi_next[e].im};
+    if (j >= kFT) {
+      pi0 = cols.pi[e];
+      pn0 = cols.pi_next[e];
+      live0 = cols.live[e];
+      its0 = cols.its[e];
+    }
+    if (!live0) continue;
+    const zd pk{pi0.re, pi0.im}, pn{pn0.re, pn0.im};
     const zd q = zdiv(pk, pn);
     const zd q2 = zmul(q, q);
     cols.bs[e] = cpx<double>{beta * q2.re, beta * q2.im};
-    cols.pi_prev[e] = cols.pi[e];
-    cols.pi[e] = cols.pi_next[e];
-    const int it = cols.its[e] + 1;
-    cols.its[e] = it;
+    cols.pi_prev[e] = pi0;
+    cols.pi[e] = pn0;
+    cols.its[e] = its0 + 1;
     const double est = rnorm / sqrt(pn.re * pn.re + pn.im * pn.im);
     cols.est[e] = bn > 0.0 ? est / bn : 0.0;
-    if (est <= tol * bn || it >= maxit) {
+    if (est <= tol * bn || its0 + 1 >= maxit)
       cols.live[e] = 0;
-    } else {
-      ++nl;
-    }
+    else
+      left = 1;
   }
-  cols.alpha_prev[c] = cols.alpha[c];
-  cols.beta_prev[c] = beta;
-  cols.rr[c] = rn;
-  cols.colive[c] = nl > 0 ? 1 : 0;
-  if (nl > 0 && rn > 0.0 && rn < 1e-200 * bn * bn) {
-    const double s = 1e100;
-    cols.scale[c] = s;
-    cols.rr[c] = rn * s * s;
-    for (int j = 0; j < nz; ++j) {
+  __syncthreads();
+  const bool go = left != 0;
+  const bool rescale = go && rn > 0.0 && rn < 1e-200 * bn * bn;
+  const double s = 1e100;
+  if (rescale)
+    for (int j = threadIdx.x; j < nz; j += kFT) {
       const int e = j * kp + c;
       cols.pi[e] = cpx<double>{cols.pi[e].re * s, cols.pi[e].im * s};
       cols.pi_prev[e] = cpx<double>{cols.pi_prev[e].re * s, cols.pi_prev[e].im * s};
     }
-  }
-  if (nl) atomicAdd(count, nl);
+  if (threadIdx.x != 0) return;
+  cols.alpha_prev[c] = alpha;
+  cols.beta_prev[c] = beta;
+  cols.rr[c] = rescale ? rn * s * s : rn;
+  if (rescale) cols.scale[c] = s;
+  cols.colive[c] = go ? 1 : 0;
 }
 
 // True residual of shift j: partials of |b - (z_j I - A) d|^2 with d = -x^s_j,
@@ -669,7 +594,7 @@ __global__ __launch_bounds__(kFT) void k_ms_fin_true(int k, int kp, int j, int n
                                                      const double* __restrict__ bn,
                                                      double* __restrict__ resid) {
   const int c = blockIdx.x;
-  const double s2 = col_total(part, nb, kp, c);
+  const double s2 = col_total(part, nb, c);
   if (threadIdx.x != 0 || c >= k) return;
   resid[(size_t)j * k + c] = bn[c] > 0.0 ? sqrt(s2) / bn[c] : 0.0;
 }
@@ -753,11 +678,57 @@ int ms_blocks(int n, int num_cu) {
 
 namespace {
 
+// The deferred iterations (ns of them) applied to all shifts, a launch for each
+// few (what a lane's registers and the scalars' LDS hold).
+template <int NZ, bool COMB>
+hipError_t launch_shift(hipStream_t st, int n, int ns, const MsWork& W, int nz, int j0) {
+  const size_t lds = (size_t)kMsDefer * NZ * 3 * 64 * sizeof(cpx<double>);
+  auto fn = k_ms_shift<NZ, COMB>;
+  hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds);
+  if (e != hipSuccess) return e;
+  // as many workgroups as are resident at once, a multiple of the eight XCDs
+  const int most = W.num_cu * (NZ <= 4 ? 2 : 1);
+  const int need = (n + kSR * kSW - 1) / (kSR * kSW);
+  const int nb = need < most ? (need + 7) / 8 * 8 : most;
+  hipLaunchKernelGGL(fn, dim3(nb, W.kp / 64), dim3(64 * kSW), lds, st, n, W.kp, nz, j0, ns, W.cols,
+                     W.r, W.y, W.X, W.P);
+  return hipGetLastError();
+}
+
+hipError_t shift_pass(hipStream_t st, int n, int ns, const MsWork& W, int nz, bool comb) {
+  for (int j0 = 0; j0 < nz;) {
+    const int left = nz - j0;
+    hipError_t e;
+    if (comb) {
+      if (left > 4) {
+        e = launch_shift<8, true>(st, n, ns, W, nz, j0);
+        j0 += 8;
+      } else if (left > 2) {
+        e = launch_shift<4, true>(st, n, ns, W, nz, j0);
+        j0 += 4;
+      } else {
+        e = launch_shift<2, true>(st, n, ns, W, nz, j0);
+        j0 += 2;
+      }
+    } else if (left > 2) {
+      e = launch_shift<4, false>(st, n, ns, W, nz, j0);
+      j0 += 4;
+    } else {
+      e = launch_shift<2, false>(st, n, ns, W, nz, j0);
+      j0 += 2;
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <int CPL>
 hipError_t run_ms_t(hipStream_t st, const StreamMatrix& A, const MsWork& W, const MsLaunch& L) {
   const int n = A.n, k = L.k, kp = W.kp, nz = L.nz;
   const int nb = W.nb;
   const dim3 grid(nb), blk(kMT), fg(kp), fb(kFT);
+  const size_t rblk = (size_t)n * kp;
 #define MCHK(expr)                   \
   do {                               \
     hipError_t _e = (expr);          \
@@ -772,55 +743,38 @@ hipError_t run_ms_t(hipStream_t st, const StreamMatrix& A, const MsWork& W, cons
   std::vector<cpx<double>> sg(nz);
   for (int j = 0; j < nz; ++j) sg[j] = cpx<double>{L.seed - L.z[2 * j], -L.z[2 * j + 1]};
   MCHK(hipMemcpyAsync(W.sig, sg.data(), nz * sizeof(cpx<double>), hipMemcpyHostToDevice, st));
-  MCHK(hipMemsetAsync(W.count, 0, sizeof(int), st));
   const bool comb = L.g != nullptr;
   double* yb = comb ? W.y : nullptr;
   MLAUNCH((k_ms_init<CPL>), grid, blk, 0, st, n, k, kp, nz, A.perm, L.B, L.ldb, W.r, W.p, W.X,
           W.P, yb, W.part);
-  MLAUNCH(k_ms_fin0, fg, fb, 0, st, k, kp, nz, nb, W.part, W.cols, W.count);
-  int live = 0;
-  MCHK(hipMemcpyAsync(&live, W.count, sizeof(int), hipMemcpyDeviceToHost, st));
-  MCHK(hipStreamSynchronize(st));
-  for (int it = 0; it < L.maxit && live > 0; ++it) {
-    MLAUNCH((k_ms_pupd<CPL>), grid, blk, 0, st, n, kp, W.cols, W.r, W.p);
+  MLAUNCH(k_ms_fin0, fg, fb, 0, st, k, nz, nb, kp, W.part, W.cols);
+  std::vector<int> colive(kp);
+  auto census = [&](int& live) -> hipError_t {
+    MCHK(hipMemcpyAsync(colive.data(), W.cols.colive, kp * sizeof(int), hipMemcpyDeviceToHost,
+                        st));
+    MCHK(hipStreamSynchronize(st));
+    live = 0;
+    for (int c = 0; c < kp; ++c) live += colive[c];
+    return hipSuccess;
+  };
+  int live = 0, it = 0;
+  MCHK(census(live));
+  // seed residual r_k in slot k mod kMsDefer of W.r
+  for (; it < L.maxit && live > 0; ++it) {
+    const int slot = it % kMsDefer;
+    double* r = W.r + slot * rblk;
+    MLAUNCH((k_ms_pupd<CPL>), grid, blk, 0, st, n, kp, W.cols, r, W.p);
     MLAUNCH((k_ms_spmv<CPL>), grid, blk, 0, st, n, kp, A.rowptr, A.col, A.val64, L.seed,
             W.cols.colive, W.p, W.w, W.part);
-    MLAUNCH(k_ms_fin_alpha, fg, fb, 0, st, kp, k, nz, nb, W.part, W.sig, L.g, W.cols);
-    if (comb) {
-      if (nz * CPL <= 2)
-        MLAUNCH((k_ms_update_y<CPL, (2 / CPL > 0 ? 2 / CPL : 1)>), grid, blk, 0, st, n, kp, nz,
-                W.cols, W.r, W.w, yb, W.P, W.part);
-      else if (nz * CPL <= 4)
-        MLAUNCH((k_ms_update_y<CPL, (4 / CPL > 0 ? 4 / CPL : 1)>), grid, blk, 0, st, n, kp, nz,
-                W.cols, W.r, W.w, yb, W.P, W.part);
-      else if (nz * CPL <= 8)
-        MLAUNCH((k_ms_update_y<CPL, (8 / CPL > 0 ? 8 / CPL : 1)>), grid, blk, 0, st, n, kp, nz,
-                W.cols, W.r, W.w, yb, W.P, W.part);
-      else
-        MLAUNCH((k_ms_update_yg<CPL>), grid, blk, 0, st, n, kp, nz, W.cols, W.r, W.w, yb, W.P,
-                W.part);
-    } else if (nz * CPL <= 1)
-      MLAUNCH((k_ms_update_r<CPL, 1>), grid, blk, 0, st, n, kp, nz, W.cols, W.r, W.w, W.X, W.P,
-              W.part);
-    else if (nz * CPL <= 2)
-      MLAUNCH((k_ms_update_r<CPL, (2 / CPL > 0 ? 2 / CPL : 1)>), grid, blk, 0, st, n, kp, nz,
-              W.cols, W.r, W.w, W.X, W.P, W.part);
-    else if (nz * CPL <= 4)
-      MLAUNCH((k_ms_update_r<CPL, (4 / CPL > 0 ? 4 / CPL : 1)>), grid, blk, 0, st, n, kp, nz,
-              W.cols, W.r, W.w, W.X, W.P, W.part);
-    else if (nz * CPL <= 8)
-      MLAUNCH((k_ms_update_r<CPL, (8 / CPL > 0 ? 8 / CPL : 1)>), grid, blk, 0, st, n, kp, nz,
-              W.cols, W.r, W.w, W.X, W.P, W.part);
-    else
-      MLAUNCH((k_ms_update<CPL>), grid, blk, 0, st, n, kp, nz, W.cols, W.r, W.w, W.X, W.P,
-              W.part);
-    MCHK(hipMemsetAsync(W.count, 0, sizeof(int), st));
-    MLAUNCH(k_ms_fin_beta, fg, fb, 0, st, kp, nz, nb, W.part, L.tol, L.maxit, W.cols, W.count);
-    if ((it + 1) % L.chunk == 0 || it + 1 == L.maxit) {
-      MCHK(hipMemcpyAsync(&live, W.count, sizeof(int), hipMemcpyDeviceToHost, st));
-      MCHK(hipStreamSynchronize(st));
-    }
+    MLAUNCH(k_ms_fin_alpha, fg, fb, 0, st, kp, k, nz, nb, slot, W.part, W.sig, L.g, W.cols);
+    if (slot == kMsDefer - 1) MCHK(shift_pass(st, n, kMsDefer, W, nz, comb));
+    MLAUNCH((k_ms_rupd<CPL>), grid, blk, 0, st, n, kp, W.cols, r,
+            W.r + (it + 1) % kMsDefer * rblk, W.w, W.part);
+    MLAUNCH(k_ms_fin_beta, fg, fb, 0, st, kp, nz, nb, W.part, L.tol, L.maxit, W.cols);
+    if ((it + 1) % L.chunk == 0 || it + 1 == L.maxit) MCHK(census(live));
   }
+  // iterations since the last pass: their residuals are still in slots 0, 1, ...
+  if (it % kMsDefer) MCHK(shift_pass(st, n, it % kMsDefer, W, nz, comb));
   if (comb) {
     MLAUNCH((k_ms_out_y<CPL>), grid, blk, 0, st, n, k, kp, nz, A.perm, yb, L.g, L.Qin, L.ldqin,
             L.Qt, L.ldq);
@@ -853,7 +807,7 @@ hipError_t run_mshift(hipStream_t st, const StreamMatrix& A, const MsWork& W, co
   if (L.k < 1 || L.nz < 1 || L.k > W.kp || W.kp != ms_padded(L.k) || L.nz > W.nz || !A.val64 ||
       W.nb != ms_blocks(A.n, W.num_cu) || L.chunk < 1)
     return hipErrorInvalidValue;
-  if (L.g ? (!W.y || !W.cols.gas || !L.Qt || L.ldq < L.k || (L.Qin && L.ldqin < L.k))
+  if (L.g ? (!W.y || !L.Qt || L.ldq < L.k || (L.Qin && L.ldqin < L.k))
           : (!W.X || !L.D || L.ldd < L.nz * L.k))
     return hipErrorInvalidValue;
   switch (ms_cpl(L.k)) {

@@ -345,26 +345,30 @@ struct MsCols {                  // per column kp entries; per (j, c) nz x kp en
   cpx<double>* pi = nullptr;     // pi_k of each shift
   cpx<double>* pi_prev = nullptr;
   cpx<double>* pi_next = nullptr;
-  cpx<double>* ipi = nullptr;    // 1 / pi_k
-  cpx<double>* as = nullptr;     // alpha^s_k
   cpx<double>* bs = nullptr;     // beta^s_{k-1}
   int* live = nullptr;           // the shifted system still iterates
   int* its = nullptr;            // its iterations
   double* est = nullptr;         // its estimated relative residual |r_k| / (|pi_k| |b|)
-  cpx<double>* gas = nullptr;    // combining mode: g_{j,c} alpha^s_k
+  // of the iterations whose shifted updates are still to come (slot = iteration
+  // mod kMsDefer): 1 / pi_k, beta^s_{k-1} and the step, alpha^s_k (times g_{j,c}
+  // in the combining mode), at ((slot nz + j) 3 + q) kp + c, and whether the
+  // system iterated, at (slot nz + j) kp + c
+  cpx<double>* sc = nullptr;
+  int* on = nullptr;
 };
+// Seed iterations whose shifted updates are applied in one pass.
+constexpr int kMsDefer = 4;
 struct MsWork {
   int kp = 0, nz = 0, nb = 0, num_cu = 0;  // nz: the most shifts this workspace holds
-  double* r = nullptr;           // n x kp seed blocks
-  double* p = nullptr;
+  double* r = nullptr;           // kMsDefer n x kp blocks: the last seed residuals
+  double* p = nullptr;           // n x kp seed blocks
   double* w = nullptr;
   cpx<double>* X = nullptr;      // nz blocks n x kp: shifted iterates
   cpx<double>* P = nullptr;      // nz blocks n x kp: shifted search directions
-  double* part = nullptr;        // nb x kp partial sums
+  double* part = nullptr;        // kp x nb partial sums
   double* y = nullptr;           // nullable n x kp: the filtered block accumulated in the
                                  //   combining mode (then X is not used)
   cpx<double>* sig = nullptr;    // [nz] sigma_j = s - z_j
-  int* count = nullptr;          // [1] live systems
   MsCols cols;
 };
 struct MsLaunch {

@@ -803,7 +803,7 @@ rafeast_status alloc_ms_work(rafeast_plan_s* P, int nz, int k, MsWork& W,
   W.num_cu = P->num_cu;
   W.nb = ms_blocks((int)n, P->num_cu);
   const size_t blk = (size_t)n * W.kp, cs = (size_t)nz * W.kp;
-  RCHK(get((void**)&W.r, blk * sizeof(double), "multi-shift r"));
+  RCHK(get((void**)&W.r, kMsDefer * blk * sizeof(double), "multi-shift r"));
   RCHK(get((void**)&W.p, blk * sizeof(double), "multi-shift p"));
   RCHK(get((void**)&W.w, blk * sizeof(double), "multi-shift w"));
   if (combining)
@@ -813,7 +813,6 @@ rafeast_status alloc_ms_work(rafeast_plan_s* P, int nz, int k, MsWork& W,
   RCHK(get((void**)&W.P, nz * blk * sizeof(cpx<double>), "multi-shift p^s"));
   RCHK(get((void**)&W.part, (size_t)W.nb * W.kp * sizeof(double), "multi-shift partials"));
   RCHK(get((void**)&W.sig, nz * sizeof(cpx<double>), "multi-shift sigma"));
-  RCHK(get((void**)&W.count, sizeof(int), "multi-shift count"));
   MsCols& c = W.cols;
   RCHK(get((void**)&c.rr, W.kp * sizeof(double), "ms rr"));
   RCHK(get((void**)&c.bn, W.kp * sizeof(double), "ms bn"));
@@ -825,13 +824,12 @@ rafeast_status alloc_ms_work(rafeast_plan_s* P, int nz, int k, MsWork& W,
   RCHK(get((void**)&c.pi, cs * sizeof(cpx<double>), "ms pi"));
   RCHK(get((void**)&c.pi_prev, cs * sizeof(cpx<double>), "ms pi_prev"));
   RCHK(get((void**)&c.pi_next, cs * sizeof(cpx<double>), "ms pi_next"));
-  RCHK(get((void**)&c.ipi, cs * sizeof(cpx<double>), "ms 1/pi"));
-  RCHK(get((void**)&c.as, cs * sizeof(cpx<double>), "ms alpha^s"));
   RCHK(get((void**)&c.bs, cs * sizeof(cpx<double>), "ms beta^s"));
   RCHK(get((void**)&c.live, cs * sizeof(int), "ms live"));
   RCHK(get((void**)&c.its, cs * sizeof(int), "ms its"));
   RCHK(get((void**)&c.est, cs * sizeof(double), "ms est"));
-  if (combining) RCHK(get((void**)&c.gas, cs * sizeof(cpx<double>), "ms g alpha^s"));
+  RCHK(get((void**)&c.sc, 3 * kMsDefer * cs * sizeof(cpx<double>), "ms deferred scalars"));
+  RCHK(get((void**)&c.on, kMsDefer * cs * sizeof(int), "ms deferred flags"));
   return RAFEAST_OK;
 }
 
