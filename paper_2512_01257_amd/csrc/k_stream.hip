@@ -26,25 +26,35 @@
 //   2  solved (true residual <= tol) or given up (iteration or update
 //      budget spent, repeated breakdown); frozen
 // Columns that are not in state 1 keep their vectors unchanged while the
-// others iterate (the p update copies them, alpha = 0).  Checks run between
-// chunks of iterations.  The columns are cut into groups of
-// 64 * CPL; a group with no iterating column is skipped by the row kernels
-// (the host passes the list of live groups by value), so shifts that
-// converge early stop costing bandwidth.  Group order follows the column
-// order c = j * k + i.
+// others iterate.  Checks run between chunks of iterations.
 //
-// An iteration: K1 forms p = r + beta p on the rows each wave owns, K2 the
-// SpMV w = (zI - A) p gathering only p (a fused form that gathered r and the
-// old p and formed p on the fly read twice the neighbour bytes, 20% slower),
-// the finalisers turn partials into alpha, K3 updates x and r.
+// Slots: x, r, p and w hold the columns that are not done side by side, in
+// slots (slot u holds column slots.col[u]); x_hi keeps all columns in their
+// order.  When so many columns are done that a unit of slots (the columns of
+// kSL lanes) is left over, the others move together (k_s_move), with a row
+// stride of what is left: shifts that converge early stop costing anything,
+// and the slowest shift's few columns stay dense in memory.
+//
+// An iteration: K1 x += alpha p (the last iteration's) and p = r + beta p, K2
+// the SpMV w = (zI - A) p gathering only p (a fused form that gathered r and
+// the old p and formed p on the fly read twice the neighbour bytes, 20%
+// slower), the finalisers turn partials into alpha and beta, K3 updates r.
 // Row kernels: 256 threads (4 waves).  Each XCD sweeps one contiguous eighth
-// of the rows with all its waves side by side (see wave_rows), keeping the
-// neighbour gathers in that XCD's L2.  A wave takes one row at a time; its 64
-// lanes hold CPL consecutive complex columns each.  The
-// matrix row (column indices and values) is wave-uniform and comes through
-// the scalar cache.  Reductions are per-workgroup partials, summed in a fixed
-// order by one-column-per-lane finaliser kernels, so results are
-// deterministic.
+// of the rows with all its waves side by side (see row_steps), keeping the
+// neighbour gathers in that XCD's L2.  A wave takes eight rows at a time, 8
+// lanes each; a lane holds 16 bytes of a row: two FP32 complex columns or one
+// FP64 complex column (the per-CU rate from L2 is set by load instructions).
+// Reductions are per-workgroup partials, summed in a fixed order by a wave per
+// column, so results are deterministic.
+//
+// What bounds it (random geometric graph of 16,000 points, 67 entries a row, 40
+// right-hand sides, 4 shifts of 102 to 530 iterations, FP32): the SpMM 64 us
+// with all 160 columns, 24 us with the last shift's 40, from the bytes its
+// gathers move from L2 to the CUs (10 TB/s; more waves or rows in flight change
+// nothing); the updates 17 and 6 us, memory; the finalisers 5 us each.  The
+// whole solve 73.7 ms with groups of 128 columns skipped only when all of them
+// were done, 42.1 ms with slots.  Units of 16 lanes (32 FP32 columns) are as
+// fast on full blocks and 0-5% slower on the others.
 #include <utility>
 
 #include "device.h"
@@ -56,43 +66,63 @@ namespace {
 
 constexpr int kST = 256;             // threads of a row kernel
 constexpr int kSW = kST / 64;        // waves of a row kernel
-constexpr int kFinThreads = 1024;    // finaliser: 16 columns x 64 partial groups
-constexpr int kFinCols = 16;
-constexpr int kFinGroups = kFinThreads / kFinCols;
+constexpr int kSL = 8;               // lanes of a row
+constexpr int kSR = 64 / kSL;        // rows of a wave's step
+constexpr int kFinCols = kST / 64;   // slots of a finaliser workgroup, a wave each
+
+// Columns of a lane: 16 bytes.
+template <typename T>
+constexpr int lane_cols() { return 16 / (int)sizeof(cpx<T>); }
+template <typename T>
+constexpr int unit_cols() { return kSL * lane_cols<T>(); }
 
 // Rows of a wave.  The rows are cut into 8 contiguous stripes, one per XCD
 // (dispatch round-robins workgroup ids over the 8 XCDs, so workgroup b runs
 // on XCD b mod 8); inside a stripe the XCD's waves take consecutive rows and
 // sweep the stripe together, so the rows in flight on an XCD form a window of
-// about (waves per XCD) rows and the neighbour rows a gather needs were
-// loaded recently into the same L2.  Row k of this wave is
-// first + k * stride, k < count.
-struct WaveRows {
-  int first, stride, count;
+// about (8 waves per XCD) rows and the neighbour rows a gather needs were
+// loaded recently into the same L2.  Step k of this wave takes the rows
+// first + k * stride .. + kSR - 1 below hi, k < count.
+struct RowSteps {
+  int first, stride, count, hi;
 };
 
-__device__ __forceinline__ WaveRows wave_rows(int n) {
-  const int nb = gridDim.x;
-  int x = 0, i = (int)blockIdx.x, per_x = nb, lo = 0, hi = n;
-  if (nb % 8 == 0) {
-    x = (int)(blockIdx.x % 8);
-    i = (int)(blockIdx.x / 8);
-    per_x = nb / 8;
-    const int stripe = (n + 7) / 8;
-    lo = min(n, x * stripe);
-    hi = min(n, lo + stripe);
-  }
-  const int stride = per_x * kSW;
-  const int first = lo + i * kSW + wave_id();
-  return {first, stride, first < hi ? (hi - first + stride - 1) / stride : 0};
+__device__ __forceinline__ RowSteps row_steps(int n) {
+  const int nb = gridDim.x;  // a multiple of 8
+  const int x = (int)(blockIdx.x % 8), i = (int)(blockIdx.x / 8), per_x = nb / 8;
+  const int stripe = (n + 7) / 8;
+  const int lo = min(n, x * stripe), hi = min(n, lo + stripe);
+  const int stride = per_x * kSW * kSR;
+  const int first = lo + (i * kSW + wave_id()) * kSR;
+  return {first, stride, first < hi ? (hi - first + stride - 1) / stride : 0, hi};
 }
 
 __device__ __forceinline__ bool waiting(int st) { return st == 0 || st == 3; }
 
-__device__ __forceinline__ float lane_bcast(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+// Value of lane U of this lane's group of kSL (all lanes active): the LDS
+// crossbar (no memory), since the vector unit is nearly as busy as the gathers.
+template <int U>
+__device__ __forceinline__ int row_bcast(int v) {
+  static_assert(kSL == 8);
+  return __builtin_amdgcn_ds_swizzle(v, (U << 5) | 0x18);
 }
-__device__ __forceinline__ double lane_bcast(double v, int l) { return readlane_f64(v, l); }
+template <int U>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(row_bcast<U>(__float_as_int(v)));
+}
+template <int U>
+__device__ __forceinline__ double row_bcast(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = row_bcast<U>((int)(b & 0xffffffffLL)), hi = row_bcast<U>((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// The kSL entries that each row's lanes hold: indices and values.
+template <typename T, int... U>
+__device__ __forceinline__ void entries_of(int mc, T mv, int (&j)[kSL], T (&a)[kSL],
+                                           std::integer_sequence<int, U...>) {
+  ((j[U] = row_bcast<U>(mc), a[U] = row_bcast<U>(mv)), ...);
+}
 
 template <typename T, int CPL>
 struct Chunk {
@@ -125,259 +155,270 @@ __device__ __forceinline__ void st_nt(cpx<T>* __restrict__ p, const Chunk<T, CPL
   }
 }
 
-// Sum the 4 waves' per-lane partials and store the workgroup's partials at
-// part[(blockIdx.x * Bp + c) * NQ + u].
+// Sum the workgroup's per-lane values (4 waves of kSR rows) and store its
+// partials at part[((slot) * NQ + u) * gridDim.x + blockIdx.x], the unit's
+// first slot being blockIdx.y * kSL * CPL.
 template <int CPL, int NQ>
-__device__ __forceinline__ void put_partials(const double (&acc)[CPL][NQ], double* __restrict__ part,
-                                             int Bp, int c0, double* sh) {
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr int kPer = 64 * CPL * NQ;
+__device__ __forceinline__ void put_partials(const double (&acc)[CPL][NQ],
+                                             double* __restrict__ part) {
+  constexpr int kRow = kSL * CPL * NQ;  // values of a row's lanes
+  __shared__ double sh[kSW * kSR * kRow];
+  const int g = threadIdx.x / kSL, l = threadIdx.x % kSL;
 #pragma unroll
   for (int q = 0; q < CPL; ++q)
 #pragma unroll
-    for (int u = 0; u < NQ; ++u) sh[wv * kPer + (lane * CPL + q) * NQ + u] = acc[q][u];
+    for (int u = 0; u < NQ; ++u) sh[g * kRow + (l * CPL + q) * NQ + u] = acc[q][u];
   __syncthreads();
-  for (int e = threadIdx.x; e < kPer; e += kST) {
+  for (int e = threadIdx.x; e < kRow; e += kST) {
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < kSW; ++w) s += sh[w * kPer + e];
-    part[((size_t)blockIdx.x * Bp + c0) * NQ + e] = s;
+    for (int w = 0; w < kSW * kSR; ++w) s += sh[w * kRow + e];
+    part[((size_t)blockIdx.y * kRow + e) * gridDim.x + blockIdx.x] = s;
   }
 }
 
-// Column of finaliser thread t (16 columns per block; thread t and t + 16k
-// share a column).
-__device__ __forceinline__ int fin_col() { return blockIdx.x * kFinCols + (threadIdx.x % kFinCols); }
+// Slot of a finaliser's wave.
+__device__ __forceinline__ int fin_slot() { return blockIdx.x * kFinCols + wave_id(); }
 
-// Fixed-order column sums of the partials of nb workgroups, for the 16
-// columns of this finaliser block: 64 interleaved partial groups, then a
-// fixed combination.  Result valid in threads 0..15 (column fin_col()).
-// `want` must be the same in all threads of a column.
+// Fixed-order sums of slot s's partials over nb workgroups, in every lane.
 template <int NQ>
-__device__ __forceinline__ void col_sums(const double* __restrict__ part, int nb, int Bp,
-                                         bool want, double (&out)[NQ]) {
-  __shared__ double sh[kFinThreads * NQ];
-  const int t = threadIdx.x, g = t / kFinCols;
-  const int c = fin_col();
-  double s[NQ];
+__device__ __forceinline__ void slot_sums(const double* __restrict__ part, int nb, int s,
+                                          double (&out)[NQ]) {
 #pragma unroll
-  for (int u = 0; u < NQ; ++u) s[u] = 0.0;
-  if (want && c < Bp)
-    for (int b = g; b < nb; b += kFinGroups)
+  for (int u = 0; u < NQ; ++u) out[u] = 0.0;
+  for (int b = threadIdx.x & 63; b < nb; b += 64)
 #pragma unroll
-      for (int u = 0; u < NQ; ++u) s[u] += part[((size_t)b * Bp + c) * NQ + u];
+    for (int u = 0; u < NQ; ++u) out[u] += part[((size_t)s * NQ + u) * nb + b];
 #pragma unroll
-  for (int u = 0; u < NQ; ++u) sh[t * NQ + u] = s[u];
-  __syncthreads();
-  if (t < kFinCols) {
-#pragma unroll
-    for (int u = 0; u < NQ; ++u) {
-      double a = 0.0;
-      for (int gg = 0; gg < kFinGroups; ++gg) a += sh[(gg * kFinCols + t) * NQ + u];
-      out[u] = a;
-    }
-  }
+  for (int u = 0; u < NQ; ++u) out[u] = wave_sum_f64(out[u]);
+}
+
+// This lane's place: its row of the step and its first slot.
+__device__ __forceinline__ int lane_row() { return (threadIdx.x & 63) / kSL; }
+template <int CPL>
+__device__ __forceinline__ int lane_slot() {
+  return ((int)blockIdx.y * kSL + (int)(threadIdx.x % kSL)) * CPL;
 }
 
 }  // namespace
 
-// K1: the new search direction of the group's live columns, p = r + beta p
-// (frozen columns keep p), written to the other p buffer; own rows only, so
-// the SpMV after it gathers a single vector.
+// K1: for the iterating columns x += alpha p with the last iteration's alpha
+// (whose p is read here anyway), then the new direction p = r + beta p.
 template <typename T, int CPL>
-__global__ __launch_bounds__(kST) void k_s_pupd(int n, int Bp, StreamGroups grp,
-                                                const double* __restrict__ beta,
-                                                const int* __restrict__ state,
+__global__ __launch_bounds__(kST) void k_s_pupd(int n, int S, StreamSlots sl,
                                                 const cpx<T>* __restrict__ r,
-                                                cpx<T>* __restrict__ pa, cpx<T>* __restrict__ pb) {
-  const int lane = threadIdx.x & 63;
-  const int c0 = grp.g[blockIdx.y] * 64 * CPL;
-  const cpx<T>* __restrict__ pold = grp.par[blockIdx.y] ? pb : pa;
-  cpx<T>* __restrict__ pnew = grp.par[blockIdx.y] ? pa : pb;
-  const int cl = c0 + lane * CPL;
-  T bre[CPL], bim[CPL];
-  bool live[CPL];
+                                                cpx<T>* __restrict__ x, cpx<T>* __restrict__ p) {
+  const int s0 = lane_slot<CPL>();
+  T are[CPL], aim[CPL], bre[CPL], bim[CPL];
+  bool live[CPL], any = false;
 #pragma unroll
   for (int q = 0; q < CPL; ++q) {
-    bre[q] = T(beta[2 * (cl + q)]);
-    bim[q] = T(beta[2 * (cl + q) + 1]);
-    live[q] = state[cl + q] == 1;
+    are[q] = T(sl.alpha[2 * (s0 + q)]);
+    aim[q] = T(sl.alpha[2 * (s0 + q) + 1]);
+    bre[q] = T(sl.beta[2 * (s0 + q)]);
+    bim[q] = T(sl.beta[2 * (s0 + q) + 1]);
+    live[q] = sl.state[s0 + q] == 1;
+    any = any || live[q];
   }
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const size_t ro = (size_t)(wr.first + wr.stride * k) * Bp + cl;
+  if (!any) return;
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    const size_t ro = (size_t)row * S + s0;
     const Chunk<T, CPL> r0 = ld<T, CPL>(r + ro);
-    const Chunk<T, CPL> p0 = ld<T, CPL>(pold + ro);
-    Chunk<T, CPL> pn;
+    Chunk<T, CPL> p0 = ld<T, CPL>(p + ro), x0 = ld<T, CPL>(x + ro);
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
-      if (live[q]) {
-        pn.v[q].re = r0.v[q].re + bre[q] * p0.v[q].re - bim[q] * p0.v[q].im;
-        pn.v[q].im = r0.v[q].im + bre[q] * p0.v[q].im + bim[q] * p0.v[q].re;
-      } else {
-        pn.v[q] = p0.v[q];
-      }
+      if (!live[q]) continue;
+      const cpx<T> po = p0.v[q];
+      x0.v[q].re += are[q] * po.re - aim[q] * po.im;
+      x0.v[q].im += are[q] * po.im + aim[q] * po.re;
+      p0.v[q].re = r0.v[q].re + bre[q] * po.re - bim[q] * po.im;
+      p0.v[q].im = r0.v[q].im + bre[q] * po.im + bim[q] * po.re;
     }
-    st<T, CPL>(pnew + ro, pn);
+    st<T, CPL>(x + ro, x0);
+    st<T, CPL>(p + ro, p0);
   }
 }
 
-// K2: w = (z I - A) p over the group's columns (p the current buffer, frozen
-// columns give w = 0) and the partials of mu = p^T w.  A wave takes one row
-// at a time; the row's entries come lane-parallel (lane l holds entry l) and
-// are broadcast with readlane, the next row's entries in flight during this
-// row's gathers; each gather is one 16-byte load per lane.
+// kSL entries of each of the wave's rows: their rows of p gathered together,
+// then added in order.
 template <typename T, int CPL>
-__global__ __launch_bounds__(kST) void k_s_spmm(int n, const int* __restrict__ rowptr,
+__device__ __forceinline__ void gather(int mc, T mv, const cpx<T>* __restrict__ p, int S,
+                                       T (&ar)[CPL], T (&ai)[CPL]) {
+  int j[kSL];
+  T a[kSL];
+  entries_of(mc, mv, j, a, std::make_integer_sequence<int, kSL>{});
+  Chunk<T, CPL> pj[kSL];
+#pragma unroll
+  for (int u = 0; u < kSL; ++u) pj[u] = ld<T, CPL>(p + (size_t)j[u] * S);
+#pragma unroll
+  for (int u = 0; u < kSL; ++u)
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      ar[q] += a[u] * pj[u].v[q].re;
+      ai[q] += a[u] * pj[u].v[q].im;
+    }
+}
+
+// Walks the entries of the wave's rows, kSR rows side by side: a row's entries
+// are held kSL at a time by its lanes (its own index with value 0 past its
+// end), the next ones or the next step's first in flight while these are used.
+template <typename V, class Begin, class Use, class End>
+__device__ __forceinline__ void walk_rows(int n, const int* __restrict__ rowptr,
+                                          const int* __restrict__ col,
+                                          const V* __restrict__ val, Begin begin, Use use,
+                                          End end) {
+  const RowSteps rs = row_steps(n);
+  const int l = threadIdx.x % kSL;
+  auto bounds = [&](int k, int& row, bool& valid, int& s, int& len) {
+    row = rs.first + rs.stride * k + lane_row();
+    valid = k < rs.count && row < rs.hi;
+    if (!valid) row = 0;
+    s = rowptr[row];
+    len = valid ? rowptr[row + 1] - s : 0;
+  };
+  auto entries = [&](int row, int s, int len, int base, int& mc, V& mv) {
+    mc = row;
+    mv = V(0);
+    if (base + l < len) {
+      mc = col[s + base + l];
+      mv = val[s + base + l];
+    }
+  };
+  if (rs.count == 0) return;
+  int row, s, len, mc;
+  bool valid;
+  V mv;
+  bounds(0, row, valid, s, len);
+  entries(row, s, len, 0, mc, mv);
+  for (int k = 0; k < rs.count; ++k) {
+    int lm = 0;
+#pragma unroll
+    for (int g = 0; g < kSR; ++g) lm = max(lm, __builtin_amdgcn_readlane(len, g * kSL));
+    int row_n, s_n, len_n;
+    bool valid_n;
+    bounds(k + 1, row_n, valid_n, s_n, len_n);
+    begin(row, valid);
+    for (int base = 0;; base += kSL) {
+      const bool last = base + kSL >= lm;
+      int mc_n;
+      V mv_n;
+      if (last)
+        entries(row_n, s_n, len_n, 0, mc_n, mv_n);
+      else
+        entries(row, s, len, base + kSL, mc_n, mv_n);
+      if (lm > base) use(mc, mv);
+      mc = mc_n;
+      mv = mv_n;
+      if (last) break;
+    }
+    end(row, valid);
+    row = row_n;
+    s = s_n;
+    len = len_n;
+    valid = valid_n;
+  }
+}
+
+// K2: w = (z I - A) p over the iterating columns (frozen ones give w = 0) and
+// the partials of mu = p^T w.  Lanes of frozen columns gather a live column's
+// bytes of the same row, which costs nothing, so that no lane is switched off
+// while entries are broadcast.
+template <typename T, int CPL>
+__global__ __launch_bounds__(kST) void k_s_spmm(int n, int S, const int* __restrict__ rowptr,
                                                 const int* __restrict__ col,
-                                                const T* __restrict__ val, int Bp,
-                                                StreamGroups grp, const double* __restrict__ zc,
-                                                const int* __restrict__ state,
-                                                const cpx<T>* __restrict__ pa,
-                                                const cpx<T>* __restrict__ pb,
+                                                const T* __restrict__ val, StreamSlots sl,
+                                                const cpx<T>* __restrict__ p,
                                                 cpx<T>* __restrict__ w,
                                                 double* __restrict__ part) {
-  extern __shared__ double sh[];
-  const int lane = threadIdx.x & 63;
-  const int c0 = grp.g[blockIdx.y] * 64 * CPL;
-  const cpx<T>* __restrict__ p = grp.par[blockIdx.y] ? pb : pa;
-  const int cl = c0 + lane * CPL;
+  const int s0 = lane_slot<CPL>();
   T zre[CPL], zim[CPL];
-  bool live[CPL];
+  bool live[CPL], any = false;
 #pragma unroll
   for (int q = 0; q < CPL; ++q) {
-    zre[q] = T(zc[2 * (cl + q)]);
-    zim[q] = T(zc[2 * (cl + q) + 1]);
-    live[q] = state[cl + q] == 1;
+    zre[q] = T(sl.zc[2 * (s0 + q)]);
+    zim[q] = T(sl.zc[2 * (s0 + q) + 1]);
+    live[q] = sl.state[s0 + q] == 1;
+    any = any || live[q];
   }
+  const unsigned long long who = __ballot(any);  // the unit's lanes, once per row
+  if (who == 0) return;
+  const int some = ((int)blockIdx.y * kSL + __builtin_ctzll(who) % kSL) * CPL;
+  const cpx<T>* __restrict__ pg = p + (any ? s0 : some);
   double acc[CPL][2];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q][0] = acc[q][1] = 0.0;
-  const WaveRows wr = wave_rows(n);
-  int win = -64, rs = 0, re = 0;  // row-pointer window: lane l holds row (win + l)
-  auto span = [&](int k, int& s, int& e) {
-    if (k - win >= 64) {
-      win = k;
-      const int kr = k + lane;
-      const int rl = wr.first + wr.stride * kr;
-      rs = kr < wr.count ? rowptr[rl] : 0;
-      re = kr < wr.count ? rowptr[rl + 1] : 0;
-    }
-    s = __builtin_amdgcn_readlane(rs, k - win);
-    e = __builtin_amdgcn_readlane(re, k - win);
-  };
-  // lane l <- entry l of a row (own row with value 0 beyond the row's end)
-  auto entries = [&](int row, int s, int len, int& mc, T& mv) {
-    mc = row;
-    mv = T(0);
-    if (lane < len) {
-      mc = col[s + lane];
-      mv = val[s + lane];
-    }
-  };
-  int s = 0, e = 0, mc = 0;
-  T mv = T(0);
-  if (wr.count > 0) {
-    span(0, s, e);
-    entries(wr.first, s, e - s, mc, mv);
-  }
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + wr.stride * k;
-    const int len = e - s;
-    const size_t ro = (size_t)row * Bp + cl;
-    const Chunk<T, CPL> p0 = ld<T, CPL>(p + ro);
-    // next row's entries, in flight during this row's gathers
-    int s2 = 0, e2 = 0, mc2 = 0;
-    T mv2 = T(0);
-    if (k + 1 < wr.count) {
-      span(k + 1, s2, e2);
-      entries(row + wr.stride, s2, e2 - s2, mc2, mv2);
-    }
-    T ar[CPL], ai[CPL];
+  Chunk<T, CPL> p0;
+  T ar[CPL], ai[CPL];
+  walk_rows<T>(
+      n, rowptr, col, val,
+      [&](int row, bool) {
+        p0 = ld<T, CPL>(pg + (size_t)row * S);
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) ar[q] = ai[q] = T(0);
-    for (int base = 0; base < len; base += 64) {
-      int cc = mc;
-      T cv = mv;
-      if (base > 0) entries(row, s + base, len - base, cc, cv);  // rows longer than 64
-      const int m = min(64, len - base);
-      constexpr int NB = 8;  // entries per batch
-      for (int t0 = 0; t0 < m; t0 += NB) {
-        int j[NB];
-        T a[NB];
+        for (int q = 0; q < CPL; ++q) ar[q] = ai[q] = T(0);
+      },
+      [&](int mc, T mv) { gather<T, CPL>(mc, mv, pg, S, ar, ai); },
+      [&](int row, bool valid) {
+        if (!valid || !any) return;
+        Chunk<T, CPL> ww;
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-          j[u] = __builtin_amdgcn_readlane(cc, t0 + u);
-          a[u] = lane_bcast(cv, t0 + u);
-        }
-        Chunk<T, CPL> pj[NB];
-#pragma unroll
-        for (int u = 0; u < NB; ++u) pj[u] = ld<T, CPL>(p + (size_t)j[u] * Bp + cl);
-#pragma unroll
-        for (int u = 0; u < NB; ++u)
-#pragma unroll
-          for (int q = 0; q < CPL; ++q) {
-            ar[q] += a[u] * pj[u].v[q].re;
-            ai[q] += a[u] * pj[u].v[q].im;
+        for (int q = 0; q < CPL; ++q) {
+          if (live[q]) {
+            ww.v[q].re = zre[q] * p0.v[q].re - zim[q] * p0.v[q].im - ar[q];
+            ww.v[q].im = zre[q] * p0.v[q].im + zim[q] * p0.v[q].re - ai[q];
+          } else {
+            ww.v[q] = cpx<T>{T(0), T(0)};
           }
-      }
-    }
-    Chunk<T, CPL> ww;
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      if (live[q]) {
-        ww.v[q].re = zre[q] * p0.v[q].re - zim[q] * p0.v[q].im - ar[q];
-        ww.v[q].im = zre[q] * p0.v[q].im + zim[q] * p0.v[q].re - ai[q];
-      } else {
-        ww.v[q] = cpx<T>{T(0), T(0)};
-      }
-      const double pr = p0.v[q].re, pi = p0.v[q].im, wr_ = ww.v[q].re, wi = ww.v[q].im;
-      acc[q][0] += pr * wr_ - pi * wi;
-      acc[q][1] += pr * wi + pi * wr_;
-    }
-    st_nt<T, CPL>(w + ro, ww);  // read by the update kernel, not by this sweep
-    s = s2;
-    e = e2;
-    mc = mc2;
-    mv = mv2;
-  }
-  put_partials<CPL, 2>(acc, part, Bp, c0, sh);
+          const double pr = p0.v[q].re, pi = p0.v[q].im, wr_ = ww.v[q].re, wi = ww.v[q].im;
+          acc[q][0] += pr * wr_ - pi * wi;
+          acc[q][1] += pr * wi + pi * wr_;
+        }
+        // read by the update kernel, not by this sweep
+        st_nt<T, CPL>(w + (size_t)row * S + s0, ww);
+      });
+  put_partials<CPL, 2>(acc, part);
 }
 
-// K3: x += alpha p, r -= alpha w; partials of r^T r (complex) and ||r||^2.
-template <typename T, int CPL>
-__global__ __launch_bounds__(kST) void k_s_update(int n, int Bp, StreamGroups grp,
-                                                  const double* __restrict__ alpha,
-                                                  cpx<T>* __restrict__ x, cpx<T>* __restrict__ r,
-                                                  const cpx<T>* __restrict__ pa,
-                                                  const cpx<T>* __restrict__ pb,
+// K3: r -= alpha w; partials of r^T r (complex) and ||r||^2.  With a dense
+// operator w holds A p, and w = z p - A p is formed here.
+template <typename T, int CPL, bool DENSE>
+__global__ __launch_bounds__(kST) void k_s_update(int n, int S, StreamSlots sl,
+                                                  cpx<T>* __restrict__ r,
+                                                  const cpx<T>* __restrict__ p,
                                                   const cpx<T>* __restrict__ w,
                                                   double* __restrict__ part) {
-  extern __shared__ double sh[];
-  const int c0 = grp.g[blockIdx.y] * 64 * CPL;
-  const cpx<T>* __restrict__ p = grp.par[blockIdx.y] ? pb : pa;
-  const int cl = c0 + (threadIdx.x & 63) * CPL;
-  T are[CPL], aim[CPL];
+  const int s0 = lane_slot<CPL>();
+  T are[CPL], aim[CPL], zre[CPL], zim[CPL];
+  bool live[CPL], any = false;
 #pragma unroll
   for (int q = 0; q < CPL; ++q) {
-    are[q] = T(alpha[2 * (cl + q)]);
-    aim[q] = T(alpha[2 * (cl + q) + 1]);
+    are[q] = T(sl.alpha[2 * (s0 + q)]);
+    aim[q] = T(sl.alpha[2 * (s0 + q) + 1]);
+    zre[q] = DENSE ? T(sl.zc[2 * (s0 + q)]) : T(0);
+    zim[q] = DENSE ? T(sl.zc[2 * (s0 + q) + 1]) : T(0);
+    live[q] = sl.state[s0 + q] == 1;
+    any = any || live[q];
   }
+  if (__ballot(any) == 0) return;
   double acc[CPL][3];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q][0] = acc[q][1] = acc[q][2] = 0.0;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + k * wr.stride;
-    const size_t ro = (size_t)row * Bp + cl;
-    Chunk<T, CPL> xx = ld<T, CPL>(x + ro);
-    Chunk<T, CPL> rr = ld<T, CPL>(r + ro);
-    const Chunk<T, CPL> pp = ld<T, CPL>(p + ro);
-    const Chunk<T, CPL> ww = ld<T, CPL>(w + ro);
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; any && k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    const size_t ro = (size_t)row * S + s0;
+    Chunk<T, CPL> rr = ld<T, CPL>(r + ro), ww = ld<T, CPL>(w + ro), pp{};
+    if (DENSE) pp = ld<T, CPL>(p + ro);
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
-      xx.v[q].re += are[q] * pp.v[q].re - aim[q] * pp.v[q].im;
-      xx.v[q].im += are[q] * pp.v[q].im + aim[q] * pp.v[q].re;
+      if (!live[q]) continue;
+      if (DENSE) {
+        ww.v[q].re = zre[q] * pp.v[q].re - zim[q] * pp.v[q].im - ww.v[q].re;
+        ww.v[q].im = zre[q] * pp.v[q].im + zim[q] * pp.v[q].re - ww.v[q].im;
+      }
       rr.v[q].re -= are[q] * ww.v[q].re - aim[q] * ww.v[q].im;
       rr.v[q].im -= are[q] * ww.v[q].im + aim[q] * ww.v[q].re;
       const double a = rr.v[q].re, b = rr.v[q].im;
@@ -385,301 +426,322 @@ __global__ __launch_bounds__(kST) void k_s_update(int n, int Bp, StreamGroups gr
       acc[q][1] += 2.0 * a * b;
       acc[q][2] += a * a + b * b;
     }
-    st<T, CPL>(x + ro, xx);
     st<T, CPL>(r + ro, rr);
   }
-  put_partials<CPL, 3>(acc, part, Bp, c0, sh);
+  put_partials<CPL, 3>(acc, part);
 }
 
 // alpha = rho / mu for iterating columns; a breakdown (mu = 0 or alpha not
-// finite) sends the column to a restart check.
-__global__ __launch_bounds__(kFinThreads) void k_s_fin_mu(int Bp, int nb,
-                                                          const double* __restrict__ part,
-                                                          StreamCols cols) {
-  const int c = fin_col();
-  const bool want = c < Bp && cols.state[c] == 1;
+// finite) sends the column to a restart check.  The other columns keep theirs:
+// a check still has to add alpha p to x.
+__global__ __launch_bounds__(kST) void k_s_fin_mu(int ns, int nb, const double* __restrict__ part,
+                                                  StreamSlots sl, StreamCols cols) {
+  const int s = fin_slot();
+  if (s >= ns || sl.state[s] != 1) return;
+  const int c = sl.col[s];
+  const zd rho{cols.rho[2 * c], cols.rho[2 * c + 1]};
   double m[2];
-  col_sums<2>(part, nb, Bp, want, m);
-  if (threadIdx.x >= kFinCols || c >= Bp) return;
-  double ar = 0.0, ai = 0.0;
-  if (want) {
-    const zd a = zdiv(zd{cols.rho[2 * c], cols.rho[2 * c + 1]}, zd{m[0], m[1]});
-    if ((m[0] == 0.0 && m[1] == 0.0) || !isfinite(a.re) || !isfinite(a.im)) {
-      cols.state[c] = 3;
-      cols.nbd[c] += 1;
-    } else {
-      ar = a.re;
-      ai = a.im;
-    }
+  slot_sums<2>(part, nb, s, m);
+  if ((threadIdx.x & 63) != 0) return;
+  zd a = zdiv(rho, zd{m[0], m[1]});
+  if ((m[0] == 0.0 && m[1] == 0.0) || !isfinite(a.re) || !isfinite(a.im)) {
+    cols.state[c] = 3;
+    sl.state[s] = 3;
+    cols.nbd[c] += 1;
+    a = zd{0.0, 0.0};
   }
-  cols.alpha[2 * c] = ar;
-  cols.alpha[2 * c + 1] = ai;
+  sl.alpha[2 * s] = cols.alpha[2 * c] = a.re;
+  sl.alpha[2 * s + 1] = cols.alpha[2 * c + 1] = a.im;
 }
 
 // beta = rho_new / rho; a column whose recursive residual reached its check
 // threshold, or whose iteration count reached the cap, waits for a check
 // (rho keeps the previous value, which the check's beta needs).
-__global__ __launch_bounds__(kFinThreads) void k_s_fin_rho(int Bp, int nb,
-                                                           const double* __restrict__ part,
-                                                           StreamCols cols, int maxit) {
-  const int c = fin_col();
-  const bool want = c < Bp && cols.state[c] == 1;
+__global__ __launch_bounds__(kST) void k_s_fin_rho(int ns, int nb, const double* __restrict__ part,
+                                                   StreamSlots sl, StreamCols cols, int maxit) {
+  const int sidx = fin_slot();
+  if (sidx >= ns || sl.state[sidx] != 1) return;
+  const int c = sl.col[sidx];
+  const zd rho{cols.rho[2 * c], cols.rho[2 * c + 1]};
+  const int it = cols.it[c] + 1, sp = cols.span[c], lastit = cols.lastit[c];
+  const int span0 = cols.span0[c];
+  const double ctol2 = cols.ctol2[c];
   double s[3];
-  col_sums<3>(part, nb, Bp, want, s);
-  if (threadIdx.x >= kFinCols || c >= Bp) return;
+  slot_sums<3>(part, nb, sidx, s);
+  if ((threadIdx.x & 63) != 0) return;
   double br = 0.0, bi = 0.0;
-  if (want) {
-    const int it = cols.it[c] + 1;
-    cols.it[c] = it;
-    const int sp = cols.span[c];
-    const bool stall = sp > 0 && it - cols.lastit[c] > max(max(4 * sp, 2 * cols.span0[c]), 256);
-    if (s[2] <= cols.ctol2[c] || it >= maxit || !isfinite(s[2]) || stall) {
-      cols.state[c] = 0;
-    } else {
-      const zd bt = zdiv(zd{s[0], s[1]}, zd{cols.rho[2 * c], cols.rho[2 * c + 1]});
-      br = bt.re;
-      bi = bt.im;
-      cols.rho[2 * c] = s[0];
-      cols.rho[2 * c + 1] = s[1];
-    }
+  cols.it[c] = it;
+  const bool stall = sp > 0 && it - lastit > max(max(4 * sp, 2 * span0), 256);
+  if (s[2] <= ctol2 || it >= maxit || !isfinite(s[2]) || stall) {
+    cols.state[c] = 0;
+    sl.state[sidx] = 0;
+  } else {
+    const zd bt = zdiv(zd{s[0], s[1]}, rho);
+    br = bt.re;
+    bi = bt.im;
+    cols.rho[2 * c] = s[0];
+    cols.rho[2 * c + 1] = s[1];
   }
-  cols.beta[2 * c] = br;
-  cols.beta[2 * c + 1] = bi;
+  sl.beta[2 * sidx] = cols.beta[2 * c] = br;
+  sl.beta[2 * sidx + 1] = cols.beta[2 * c + 1] = bi;
 }
 
-// Group census (one wave per group): cnt[g] = columns of group g in state 1,
-// cnt[gridDim.x + g] = columns waiting for a check (state 0 or 3).
-__global__ __launch_bounds__(64) void k_s_count(int Bp, int gw, StreamCols cols,
-                                                int* __restrict__ cnt) {
-  const int g = blockIdx.x;
-  double a = 0.0, wt = 0.0;
-  for (int c = g * gw + (int)threadIdx.x; c < (g + 1) * gw && c < Bp; c += 64) {
-    a += cols.state[c] == 1 ? 1.0 : 0.0;
-    wt += waiting(cols.state[c]) ? 1.0 : 0.0;
-  }
-  a = wave_sum(a);
-  wt = wave_sum(wt);
-  if (threadIdx.x == 0) {
-    cnt[g] = (int)a;
-    cnt[gridDim.x + g] = (int)wt;
+// The scalars of the columns in slots 0 .. ns - 1 (col[u] < 0: none).
+__global__ __launch_bounds__(kST) void k_s_slots(int ns, const double* __restrict__ zc,
+                                                 StreamCols cols, StreamSlots sl) {
+  const int u = blockIdx.x * kST + threadIdx.x;
+  if (u >= ns) return;
+  const int c = sl.col[u];
+  sl.state[u] = c >= 0 ? cols.state[c] : 2;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    sl.zc[2 * u + h] = c >= 0 ? zc[2 * c + h] : 0.0;
+    sl.alpha[2 * u + h] = c >= 0 ? cols.alpha[2 * c + h] : 0.0;
+    sl.beta[2 * u + h] = c >= 0 ? cols.beta[2 * c + h] : 0.0;
   }
 }
 
-// Check, step 1: x_hi += x (FP64) and x = 0 for waiting columns.
+// Slots move together: new slot u of a block with row stride S_new takes old
+// slot from[u] (-1: zero) of one with stride S.
+template <typename T>
+__global__ __launch_bounds__(kST) void k_s_move(int n, int S, int S_new,
+                                                const int* __restrict__ from,
+                                                const cpx<T>* __restrict__ src,
+                                                cpx<T>* __restrict__ dst) {
+  const int u = blockIdx.y * kSL + (int)(threadIdx.x % kSL);
+  const int f = from[u];
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    dst[(size_t)row * S_new + u] = f >= 0 ? src[(size_t)row * S + f] : cpx<T>{T(0), T(0)};
+  }
+}
+
+// Check, step 1: x_hi += x + alpha p (FP64; x as it stands after the last
+// iteration), x = 0 for waiting columns.
 template <typename T, int CPL>
-__global__ __launch_bounds__(kST) void k_s_xhi(int n, int Bp, StreamGroups grp,
-                                               const int* __restrict__ state,
+__global__ __launch_bounds__(kST) void k_s_xhi(int n, int S, int Bp, StreamSlots sl,
+                                               const cpx<T>* __restrict__ p,
                                                cpx<T>* __restrict__ x,
                                                cpx<double>* __restrict__ xh) {
-  const int cl = grp.g[blockIdx.y] * 64 * CPL + (threadIdx.x & 63) * CPL;
-  bool on[CPL];
+  const int s0 = lane_slot<CPL>();
+  bool on[CPL], any = false;
+  int c[CPL];
+  T are[CPL], aim[CPL];
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) on[q] = waiting(state[cl + q]);
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + k * wr.stride;
-    const size_t ro = (size_t)row * Bp + cl;
+  for (int q = 0; q < CPL; ++q) {
+    on[q] = waiting(sl.state[s0 + q]);
+    c[q] = sl.col[s0 + q];
+    are[q] = T(sl.alpha[2 * (s0 + q)]);
+    aim[q] = T(sl.alpha[2 * (s0 + q) + 1]);
+    any = any || on[q];
+  }
+  if (!any) return;
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    const size_t ro = (size_t)row * S + s0;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
       if (!on[q]) continue;
-      const cpx<T> xv = x[ro + q];
-      cpx<double> h = xh[ro + q];
-      h.re += (double)xv.re;
-      h.im += (double)xv.im;
-      xh[ro + q] = h;
+      cpx<T> xv = x[ro + q];
+      const cpx<T> po = p[ro + q];
+      xv.re += are[q] * po.re - aim[q] * po.im;
+      xv.im += are[q] * po.im + aim[q] * po.re;
+      cpx<double>* hp = xh + (size_t)row * Bp + c[q];
+      hp->re += (double)xv.re;
+      hp->im += (double)xv.im;
       x[ro + q] = cpx<T>{T(0), T(0)};
     }
   }
 }
 
+// What a lane of a check's step 2 needs of its columns.
+template <int CPL>
+struct CheckCols {
+  double zre[CPL], zim[CPL], scl[CPL];
+  bool on[CPL], rst[CPL], any = false;
+  int c[CPL], ci[CPL];
+  __device__ __forceinline__ CheckCols(const StreamSlots& sl, int s0,
+                                       const double* __restrict__ scale, int kcols) {
+#pragma unroll
+    for (int q = 0; q < CPL; ++q) {
+      zre[q] = sl.zc[2 * (s0 + q)];
+      zim[q] = sl.zc[2 * (s0 + q) + 1];
+      on[q] = waiting(sl.state[s0 + q]);
+      rst[q] = sl.state[s0 + q] == 3;
+      c[q] = sl.col[s0 + q];
+      ci[q] = on[q] ? c[q] % kcols : 0;
+      scl[q] = on[q] ? scale[c[q]] : 0.0;
+      any = any || on[q];
+    }
+  }
+  // s = b / ||b|| - (z x - A x) of column q at a row, r = s (p = s after a
+  // breakdown), its products to acc
+  template <typename T>
+  __device__ __forceinline__ void put(int q, double bv, cpx<double> x, double axr, double axi,
+                                      cpx<T>* __restrict__ r, cpx<T>* __restrict__ p,
+                                      double (&acc)[3]) const {
+    const double b = scl[q] != 0.0 ? bv * scl[q] : 0.0;
+    const double sr = b - (zre[q] * x.re - zim[q] * x.im - axr);
+    const double si = -(zre[q] * x.im + zim[q] * x.re - axi);
+    *r = cpx<T>{T(sr), T(si)};
+    if (rst[q]) *p = cpx<T>{T(sr), T(si)};
+    acc[0] += sr * sr - si * si;
+    acc[1] += 2.0 * sr * si;
+    acc[2] += sr * sr + si * si;
+  }
+};
+
 // Check, step 2: s = b/||b|| - (z x_hi - A x_hi) in FP64 with the FP64
 // values of A; r = s (and p = s after a breakdown); partials of s^T s and
-// ||s||^2.
+// ||s||^2.  Gathers as k_s_spmm, of the waiting columns (few: 16 bytes each).
 template <typename T, int CPL>
 __global__ __launch_bounds__(kST) void k_s_resid64(
-    int n, const int* __restrict__ rowptr, const int* __restrict__ col,
-    const double* __restrict__ val, int Bp, StreamGroups grp, const double* __restrict__ zc,
-    const int* __restrict__ state, const double* __restrict__ B, int ldb, int kcols,
-    const double* __restrict__ scale, const int* __restrict__ perm,
-    const cpx<double>* __restrict__ xh, cpx<T>* __restrict__ r, cpx<T>* __restrict__ pa,
-    cpx<T>* __restrict__ pb, double* __restrict__ part) {
-  extern __shared__ double sh[];
-  const int c0 = grp.g[blockIdx.y] * 64 * CPL;
-  cpx<T>* __restrict__ p = grp.par[blockIdx.y] ? pb : pa;
-  const int cl = c0 + (threadIdx.x & 63) * CPL;
-  double zre[CPL], zim[CPL], scl[CPL];
-  bool on[CPL], rst[CPL];
-  int ci[CPL];
+    int n, int S, const int* __restrict__ rowptr, const int* __restrict__ col,
+    const double* __restrict__ val, int Bp, StreamSlots sl, const double* __restrict__ B, int ldb,
+    int kcols, const double* __restrict__ scale, const int* __restrict__ perm,
+    const cpx<double>* __restrict__ xh, cpx<T>* __restrict__ r, cpx<T>* __restrict__ p,
+    double* __restrict__ part) {
+  const int s0 = lane_slot<CPL>();
+  const CheckCols<CPL> cc(sl, s0, scale, kcols);
+  const unsigned long long who = __ballot(cc.any);
+  if (who == 0) return;
+  int mine = 0;
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    zre[q] = zc[2 * (cl + q)];
-    zim[q] = zc[2 * (cl + q) + 1];
-    on[q] = waiting(state[cl + q]);
-    rst[q] = state[cl + q] == 3;
-    ci[q] = (cl + q) % kcols;
-    scl[q] = scale[cl + q];
-  }
+  for (int q = CPL - 1; q >= 0; --q)
+    if (cc.on[q]) mine = cc.c[q];
+  const int some = __builtin_amdgcn_readlane(mine, __builtin_ctzll(who));
+  const cpx<double>* __restrict__ xg[CPL];
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) xg[q] = xh + (cc.on[q] ? cc.c[q] : cc.any ? mine : some);
   double acc[CPL][3];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q][0] = acc[q][1] = acc[q][2] = 0.0;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + k * wr.stride;
-    const size_t ro = (size_t)row * Bp + cl;
-    double ar[CPL], ai[CPL];
+  double ar[CPL], ai[CPL];
+  walk_rows<double>(
+      n, rowptr, col, val,
+      [&](int, bool) {
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) ar[q] = ai[q] = 0.0;
-    const int s = rowptr[row], e = rowptr[row + 1];
-    for (int t = s; t < e; ++t) {
-      const int j = col[t];
-      const double a = val[t];
-      const size_t jo = (size_t)j * Bp + cl;
+        for (int q = 0; q < CPL; ++q) ar[q] = ai[q] = 0.0;
+      },
+      [&](int mc, double mv) {
+        int j[kSL];
+        double a[kSL];
+        entries_of(mc, mv, j, a, std::make_integer_sequence<int, kSL>{});
+        cpx<double> xj[kSL][CPL];
 #pragma unroll
-      for (int q = 0; q < CPL; ++q) {
-        if (!on[q]) continue;
-        const cpx<double> xj = xh[jo + q];
-        ar[q] += a * xj.re;
-        ai[q] += a * xj.im;
-      }
-    }
-    const size_t orow = (size_t)perm[row];
+        for (int u = 0; u < kSL; ++u)
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      if (!on[q]) continue;
-      const cpx<double> xr = xh[ro + q];
-      const double b = scl[q] != 0.0 ? B[orow * ldb + ci[q]] * scl[q] : 0.0;
-      const double sr = b - (zre[q] * xr.re - zim[q] * xr.im - ar[q]);
-      const double si = -(zre[q] * xr.im + zim[q] * xr.re - ai[q]);
-      r[ro + q] = cpx<T>{T(sr), T(si)};
-      if (rst[q]) p[ro + q] = cpx<T>{T(sr), T(si)};
-      acc[q][0] += sr * sr - si * si;
-      acc[q][1] += 2.0 * sr * si;
-      acc[q][2] += sr * sr + si * si;
-    }
-  }
-  put_partials<CPL, 3>(acc, part, Bp, c0, sh);
+          for (int q = 0; q < CPL; ++q) xj[u][q] = xg[q][(size_t)j[u] * Bp];
+#pragma unroll
+        for (int u = 0; u < kSL; ++u)
+#pragma unroll
+          for (int q = 0; q < CPL; ++q) {
+            ar[q] += a[u] * xj[u][q].re;
+            ai[q] += a[u] * xj[u][q].im;
+          }
+      },
+      [&](int row, bool valid) {
+        if (!valid) return;
+        const size_t orow = (size_t)perm[row], ro = (size_t)row * S + s0;
+#pragma unroll
+        for (int q = 0; q < CPL; ++q)
+          if (cc.on[q])
+            cc.template put<T>(q, B[orow * ldb + cc.ci[q]], xg[q][(size_t)row * Bp], ar[q], ai[q],
+                               r + ro + q, p + ro + q, acc[q]);
+      });
+  put_partials<CPL, 3>(acc, part);
 }
 
-// Dense operator: the iterating columns of the current p packed side by side
-// (packed column u holds column cidx[u] & 0xfffffff, read from the p buffer
-// of parity ((cidx[u] >> 30) & 1) ^ flip), so the GEMM multiplies only the
-// columns that iterate, not whole column groups.
-template <typename T>
-__global__ __launch_bounds__(kST) void k_s_pack(int n, int Bp, int nl,
-                                                const int* __restrict__ cidx, int flip,
-                                                const cpx<T>* __restrict__ pa,
-                                                const cpx<T>* __restrict__ pb,
-                                                cpx<T>* __restrict__ pc) {
-  const int u = blockIdx.y * 64 + (threadIdx.x & 63);
-  if (u >= nl) return;
-  const int code = cidx[u];
-  const int c = code & 0xfffffff;
-  const cpx<T>* __restrict__ src = (((code >> 30) & 1) ^ flip) ? pb : pa;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const size_t r = (size_t)(wr.first + wr.stride * k) * Bp;
-    pc[r + u] = src[r + c];
+// Dense operator: waiting columns (packed column u: column cidx[u]) of x_hi side by
+// side, so that the check's product multiplies them alone.
+__global__ __launch_bounds__(kST) void k_s_pack(int n, int Bp, int nw, int ld,
+                                                const int* __restrict__ cidx,
+                                                const cpx<double>* __restrict__ xh,
+                                                cpx<double>* __restrict__ out) {
+  const int u = blockIdx.y * kSL + (int)(threadIdx.x % kSL);
+  if (u >= nw) return;
+  const int c = cidx[u];
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    out[(size_t)row * ld + u] = xh[(size_t)row * Bp + c];
   }
 }
 
-// Dense operator, K2 after the packed product: w = z p - A p for iterating
-// columns (A p of column c at packed column cmap[c] of apc), 0 for frozen
-// ones, and the partials of mu = p^T w, as k_s_spmm.
+// Dense operator, K2 after the product (w holds A p): the partials of
+// mu = p^T (z p - A p).
 template <typename T, int CPL>
-__global__ __launch_bounds__(kST) void k_s_shiftw_packed(int n, int Bp, StreamGroups grp,
-                                                         const double* __restrict__ zc,
-                                                         const int* __restrict__ state,
-                                                         const int* __restrict__ cmap,
-                                                         const cpx<T>* __restrict__ pa,
-                                                         const cpx<T>* __restrict__ pb,
-                                                         const cpx<T>* __restrict__ apc,
-                                                         cpx<T>* __restrict__ w,
-                                                         double* __restrict__ part) {
-  extern __shared__ double sh[];
-  const int c0 = grp.g[blockIdx.y] * 64 * CPL;
-  const cpx<T>* __restrict__ p = grp.par[blockIdx.y] ? pb : pa;
-  const int cl = c0 + (threadIdx.x & 63) * CPL;
+__global__ __launch_bounds__(kST) void k_s_mu(int n, int S, StreamSlots sl,
+                                              const cpx<T>* __restrict__ p,
+                                              const cpx<T>* __restrict__ w,
+                                              double* __restrict__ part) {
+  const int s0 = lane_slot<CPL>();
   T zre[CPL], zim[CPL];
-  int pk[CPL];
+  bool any = false;
 #pragma unroll
   for (int q = 0; q < CPL; ++q) {
-    zre[q] = T(zc[2 * (cl + q)]);
-    zim[q] = T(zc[2 * (cl + q) + 1]);
-    pk[q] = state[cl + q] == 1 ? cmap[cl + q] : -1;
+    zre[q] = T(sl.zc[2 * (s0 + q)]);
+    zim[q] = T(sl.zc[2 * (s0 + q) + 1]);
+    any = any || sl.state[s0 + q] == 1;
   }
+  if (__ballot(any) == 0) return;
   double acc[CPL][2];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q][0] = acc[q][1] = 0.0;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const size_t rb = (size_t)(wr.first + wr.stride * k) * Bp;
-    const Chunk<T, CPL> p0 = ld<T, CPL>(p + rb + cl);
-    Chunk<T, CPL> ww;
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; any && k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    const size_t ro = (size_t)row * S + s0;
+    const Chunk<T, CPL> p0 = ld<T, CPL>(p + ro), a = ld<T, CPL>(w + ro);
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
-      if (pk[q] >= 0) {
-        const cpx<T> a = apc[rb + pk[q]];
-        ww.v[q].re = zre[q] * p0.v[q].re - zim[q] * p0.v[q].im - a.re;
-        ww.v[q].im = zre[q] * p0.v[q].im + zim[q] * p0.v[q].re - a.im;
-      } else {
-        ww.v[q] = cpx<T>{T(0), T(0)};
-      }
-      const double pr = p0.v[q].re, pi = p0.v[q].im, wr_ = ww.v[q].re, wi = ww.v[q].im;
+      const T wre = zre[q] * p0.v[q].re - zim[q] * p0.v[q].im - a.v[q].re;
+      const T wim = zre[q] * p0.v[q].im + zim[q] * p0.v[q].re - a.v[q].im;
+      const double pr = p0.v[q].re, pi = p0.v[q].im, wr_ = wre, wi = wim;
       acc[q][0] += pr * wr_ - pi * wi;
       acc[q][1] += pr * wi + pi * wr_;
     }
-    st<T, CPL>(w + rb + cl, ww);
   }
-  put_partials<CPL, 2>(acc, part, Bp, c0, sh);
+  put_partials<CPL, 2>(acc, part);
 }
 
-// Dense operator, check step 2 after the product: ax holds A x_hi (FP64,
-// from a GEMM); the rest as k_s_resid64.
+// Dense operator, check step 2 after the product: column c's A x_hi (FP64) in
+// packed column from[slot] of ax; the rest as k_s_resid64.
 template <typename T, int CPL>
 __global__ __launch_bounds__(kST) void k_s_resid64d(
-    int n, int Bp, StreamGroups grp, const double* __restrict__ zc,
-    const int* __restrict__ state, const double* __restrict__ B, int ldb, int kcols,
+    int n, int S, int Bp, StreamSlots sl, const double* __restrict__ B, int ldb, int kcols,
     const double* __restrict__ scale, const cpx<double>* __restrict__ xh,
-    const cpx<double>* __restrict__ ax, cpx<T>* __restrict__ r, cpx<T>* __restrict__ pa,
-    cpx<T>* __restrict__ pb, double* __restrict__ part) {
-  extern __shared__ double sh[];
-  const int c0 = grp.g[blockIdx.y] * 64 * CPL;
-  cpx<T>* __restrict__ p = grp.par[blockIdx.y] ? pb : pa;
-  const int cl = c0 + (threadIdx.x & 63) * CPL;
-  double zre[CPL], zim[CPL], scl[CPL];
-  bool on[CPL], rst[CPL];
-  int ci[CPL];
+    const cpx<double>* __restrict__ ax, cpx<T>* __restrict__ r, cpx<T>* __restrict__ p,
+    double* __restrict__ part) {
+  const int s0 = lane_slot<CPL>();
+  const CheckCols<CPL> cc(sl, s0, scale, kcols);
+  if (__ballot(cc.any) == 0) return;
+  int u[CPL];
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) {
-    zre[q] = zc[2 * (cl + q)];
-    zim[q] = zc[2 * (cl + q) + 1];
-    on[q] = waiting(state[cl + q]);
-    rst[q] = state[cl + q] == 3;
-    ci[q] = (cl + q) % kcols;
-    scl[q] = scale[cl + q];
-  }
+  for (int q = 0; q < CPL; ++q) u[q] = sl.from[s0 + q];
   double acc[CPL][3];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q][0] = acc[q][1] = acc[q][2] = 0.0;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + k * wr.stride;
-    const size_t ro = (size_t)row * Bp + cl;
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    const size_t ro = (size_t)row * S + s0, rb = (size_t)row * Bp;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
-      if (!on[q]) continue;
-      const cpx<double> xr = xh[ro + q], a = ax[ro + q];
-      const double b = scl[q] != 0.0 ? B[(size_t)row * ldb + ci[q]] * scl[q] : 0.0;
-      const double sr = b - (zre[q] * xr.re - zim[q] * xr.im - a.re);
-      const double si = -(zre[q] * xr.im + zim[q] * xr.re - a.im);
-      r[ro + q] = cpx<T>{T(sr), T(si)};
-      if (rst[q]) p[ro + q] = cpx<T>{T(sr), T(si)};
-      acc[q][0] += sr * sr - si * si;
-      acc[q][1] += 2.0 * sr * si;
-      acc[q][2] += sr * sr + si * si;
+      if (!cc.on[q]) continue;
+      const cpx<double> a = ax[rb + u[q]];
+      cc.template put<T>(q, B[(size_t)row * ldb + cc.ci[q]], xh[rb + cc.c[q]], a.re, a.im,
+                         r + ro + q, p + ro + q, acc[q]);
     }
   }
-  put_partials<CPL, 3>(acc, part, Bp, c0, sh);
+  put_partials<CPL, 3>(acc, part);
 }
 
 // Check, step 3: accept (true residual <= tol), give up (update, iteration
@@ -688,21 +750,25 @@ __global__ __launch_bounds__(kST) void k_s_resid64d(
 // r = s (after a breakdown, or when ||s|| is not at most half the previous
 // check's).  The next check comes when the recursive residual has dropped by
 // delta from ||s|| (or reaches tol), or at a stall.
-__global__ __launch_bounds__(kFinThreads) void k_s_fin_verify(int Bp, int nb,
-                                                              const double* __restrict__ part,
-                                                              StreamCols cols, double tol,
-                                                              double delta, int maxit,
-                                                              int max_updates) {
-  const int c = fin_col();
-  const int st0 = c < Bp ? cols.state[c] : 2;
-  const bool want = waiting(st0);
+__global__ __launch_bounds__(kST) void k_s_fin_verify(int ns, int nb,
+                                                      const double* __restrict__ part,
+                                                      StreamSlots sl, StreamCols cols, double tol,
+                                                      double delta, int maxit, int max_updates) {
+  const int sidx = fin_slot();
+  if (sidx >= ns) return;
+  const int st0 = sl.state[sidx];
+  if (!waiting(st0)) return;
+  const int c = sl.col[sidx];
   double s[3];
-  col_sums<3>(part, nb, Bp, want, s);
-  if (threadIdx.x >= kFinCols || !want) return;
+  slot_sums<3>(part, nb, sidx, s);
+  if ((threadIdx.x & 63) != 0) return;
   cols.res[c] = sqrt(s[2]);
+  // the check has added alpha p to x
+  sl.alpha[2 * sidx] = sl.alpha[2 * sidx + 1] = cols.alpha[2 * c] = cols.alpha[2 * c + 1] = 0.0;
   if (s[2] <= tol * tol || !isfinite(s[2]) || cols.nref[c] >= max_updates ||
       cols.it[c] >= maxit || cols.nbd[c] > 3) {
     cols.state[c] = 2;
+    sl.state[sidx] = 2;
     return;
   }
   cols.nref[c] += 1;
@@ -722,26 +788,27 @@ __global__ __launch_bounds__(kFinThreads) void k_s_fin_verify(int Bp, int nb,
   cols.sprev[c] = s[2];
   cols.rho[2 * c] = s[0];
   cols.rho[2 * c + 1] = s[1];
-  cols.beta[2 * c] = br;
-  cols.beta[2 * c + 1] = bi;
+  sl.beta[2 * sidx] = cols.beta[2 * c] = br;
+  sl.beta[2 * sidx + 1] = cols.beta[2 * c + 1] = bi;
   cols.ctol2[c] = fmax(tol * tol, delta * delta * s[2]);
   cols.state[c] = 1;
+  sl.state[sidx] = 1;
 }
 
-// Start, step 1: partials of ||b_c||^2 (column c takes RHS column c % kcols).
+// Start, step 1: partials of ||b_c||^2 (column c, in slot c, takes RHS column
+// c % kcols).
 template <int CPL>
-__global__ __launch_bounds__(kST) void k_s_bnorm(int n, int Bp, const double* __restrict__ B,
-                                                 int ldb, int kcols, int ncols,
+__global__ __launch_bounds__(kST) void k_s_bnorm(int n, const double* __restrict__ B, int ldb,
+                                                 int kcols, int ncols,
                                                  double* __restrict__ part) {
-  extern __shared__ double sh[];
-  const int c0 = blockIdx.y * 64 * CPL;
-  const int cl = c0 + (threadIdx.x & 63) * CPL;
+  const int cl = lane_slot<CPL>();
   double acc[CPL][1];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q][0] = 0.0;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + k * wr.stride;
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
       if (cl + q >= ncols) continue;
@@ -749,19 +816,21 @@ __global__ __launch_bounds__(kST) void k_s_bnorm(int n, int Bp, const double* __
       acc[q][0] += b * b;
     }
   }
-  put_partials<CPL, 1>(acc, part, Bp, c0, sh);
+  put_partials<CPL, 1>(acc, part);
 }
 
-// Start, step 2: per-column set-up; zero and padding columns are solved at once.
-__global__ __launch_bounds__(kFinThreads) void k_s_fin_bnorm(int Bp, int nb,
-                                                             const double* __restrict__ part,
-                                                             int ncols, double* __restrict__ scale,
-                                                             StreamCols cols, double tol,
-                                                             double delta) {
-  const int c = fin_col();
-  double s[1];
-  col_sums<1>(part, nb, Bp, c < ncols, s);
-  if (threadIdx.x >= kFinCols || c >= Bp) return;
+// Start, step 2: per-column set-up; zero columns are solved at once.  Column c
+// starts in slot c (S slots).
+__global__ __launch_bounds__(kST) void k_s_fin_bnorm(int S, int nb,
+                                                     const double* __restrict__ part, int ncols,
+                                                     double* __restrict__ scale, StreamCols cols,
+                                                     StreamSlots sl, double tol, double delta) {
+  const int c = fin_slot();
+  if (c >= S) return;
+  double s[1] = {0.0};
+  if (c < ncols) slot_sums<1>(part, nb, c, s);
+  if ((threadIdx.x & 63) != 0) return;
+  sl.col[c] = c < ncols ? c : -1;
   cols.it[c] = 0;
   cols.nref[c] = 0;
   cols.nbd[c] = 0;
@@ -788,27 +857,26 @@ __global__ __launch_bounds__(kFinThreads) void k_s_fin_bnorm(int Bp, int nb,
 
 // Start, step 3: r = p = b / ||b|| (engine row order), x = x_hi = 0; partials of r^T r.
 template <typename T, int CPL>
-__global__ __launch_bounds__(kST) void k_s_start(int n, int Bp, const double* __restrict__ B,
-                                                 int ldb, int kcols,
+__global__ __launch_bounds__(kST) void k_s_start(int n, int S, int Bp,
+                                                 const double* __restrict__ B, int ldb, int kcols,
                                                  const double* __restrict__ scale,
                                                  const int* __restrict__ perm,
                                                  cpx<T>* __restrict__ x, cpx<T>* __restrict__ r,
                                                  cpx<T>* __restrict__ p,
                                                  cpx<double>* __restrict__ xh,
                                                  double* __restrict__ part) {
-  extern __shared__ double sh[];
-  const int c0 = blockIdx.y * 64 * CPL;
-  const int cl = c0 + (threadIdx.x & 63) * CPL;
+  const int cl = lane_slot<CPL>();
   double scl[CPL];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) scl[q] = scale[cl + q];
   double acc[CPL][1];
 #pragma unroll
   for (int q = 0; q < CPL; ++q) acc[q][0] = 0.0;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + k * wr.stride;
-    const size_t ro = (size_t)row * Bp + cl;
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
+    const size_t ro = (size_t)row * S + cl, rh = (size_t)row * Bp + cl;
     const size_t orow = (size_t)perm[row];
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
@@ -817,21 +885,21 @@ __global__ __launch_bounds__(kST) void k_s_start(int n, int Bp, const double* __
       r[ro + q] = v;
       p[ro + q] = v;
       x[ro + q] = cpx<T>{T(0), T(0)};
-      xh[ro + q] = cpx<double>{0.0, 0.0};
+      xh[rh + q] = cpx<double>{0.0, 0.0};
       acc[q][0] += (double)v.re * (double)v.re;
     }
   }
-  put_partials<CPL, 1>(acc, part, Bp, c0, sh);
+  put_partials<CPL, 1>(acc, part);
 }
 
-__global__ __launch_bounds__(kFinThreads) void k_s_fin_start(int Bp, int nb,
-                                                             const double* __restrict__ part,
-                                                             StreamCols cols) {
-  const int c = fin_col();
-  const bool want = c < Bp && cols.state[c] == 1;
+__global__ __launch_bounds__(kST) void k_s_fin_start(int S, int nb,
+                                                     const double* __restrict__ part,
+                                                     StreamCols cols) {
+  const int c = fin_slot();  // column c is in slot c
+  if (c >= S || cols.state[c] != 1) return;
   double s[1];
-  col_sums<1>(part, nb, Bp, want, s);
-  if (threadIdx.x >= kFinCols || !want) return;
+  slot_sums<1>(part, nb, c, s);
+  if ((threadIdx.x & 63) != 0) return;
   cols.rho[2 * c] = s[0];
   cols.rho[2 * c + 1] = 0.0;
 }
@@ -843,10 +911,11 @@ __global__ __launch_bounds__(kST) void k_s_out(int n, int Bp, int ncols,
                                                const int* __restrict__ perm,
                                                const cpx<double>* __restrict__ xh,
                                                cpx<T>* __restrict__ D, int ldd) {
-  const int cl = blockIdx.y * 64 * CPL + (threadIdx.x & 63) * CPL;
-  const WaveRows wr = wave_rows(n);
-  for (int k = 0; k < wr.count; ++k) {
-    const int row = wr.first + k * wr.stride;
+  const int cl = lane_slot<CPL>();
+  const RowSteps rs = row_steps(n);
+  for (int k = 0; k < rs.count; ++k) {
+    const int row = rs.first + rs.stride * k + lane_row();
+    if (row >= rs.hi) break;
     const size_t ro = (size_t)row * Bp + cl;
     const size_t orow = (size_t)perm[row];
 #pragma unroll
@@ -877,10 +946,7 @@ __global__ void k_s_report(int ncols, StreamCols cols, int* __restrict__ iters,
 // ---------------------------------------------------------------------------
 // host side
 int stream_cpl(int k, int ncols, bool fp32) {
-  // A lane moves 16 bytes per load: two FP32 complex columns, or one FP64
-  // complex column.  The per-CU rate from L2 is set by load instructions, so
-  // 8-byte lanes would halve the gather bandwidth.  Narrow FP32 solves (under
-  // 128 columns) use one column per lane.
+  // columns are padded to 128 (FP32 blocks of at least that many) or 64
   (void)k;
   return (fp32 && ncols >= 128) ? 2 : 1;
 }
@@ -891,11 +957,12 @@ int stream_padded_columns(int k, int ncols, bool fp32) {
 }
 
 int stream_blocks(int n, int num_cu) {
-  // eight workgroups per CU for large n; four up to 2^17 rows, where the
-  // finalisers' partial sums (one per workgroup and column) cost more than
-  // the extra occupancy gives (measured 3-5% on n of 10^4 to 6 10^4)
-  int nb = num_cu * (n <= (1 << 17) ? 4 : 8);
-  const int need = (n + kSW - 1) / kSW;
+  // row blocks of a unit of slots, the grid's second dimension running over
+  // the units: two per CU up to 2^17 rows, where the finalisers' partial sums
+  // (one per row block and column) cost more than the extra occupancy gives,
+  // four above
+  int nb = num_cu * (n <= (1 << 17) ? 2 : 4) / 8 * 8;
+  const int need = (n + kSW * kSR - 1) / (kSW * kSR);
   if (nb > need) nb = (need + 7) / 8 * 8;
   return nb < 8 ? 8 : nb;
 }
@@ -904,25 +971,24 @@ size_t stream_partial_doubles(int n, int Bp, int num_cu) {
   return (size_t)stream_blocks(n, num_cu) * Bp * 3;
 }
 
-template <typename T, int CPL>
+template <typename T>
 static hipError_t run_stream_t(hipStream_t stm, const StreamMatrix& A, const StreamWork& W,
                                const StreamLaunch& L) {
+  constexpr int CPL = lane_cols<T>(), UC = unit_cols<T>();
   const int n = A.n, Bp = W.Bp;
-  const int gw = 64 * CPL, ng = Bp / gw;
   const int nb = stream_blocks(n, W.num_cu);
-  const dim3 blk(kST), fgrid((Bp + kFinCols - 1) / kFinCols), fblk(kFinThreads);
-  auto shm = [](int nq) { return (size_t)kSW * 64 * CPL * nq * sizeof(double); };
+  const dim3 blk(kST);
   // check spacing: FP32 storage drifts by about kappa * 6e-8 of the residual
   // per check interval, so checks come every decade; FP64 rarely needs one
   const double delta = sizeof(T) == 4 ? 0.1 : 1e-4;
   const T* val = sizeof(T) == 4 ? (const T*)(const void*)A.val32 : (const T*)(const void*)A.val64;
   cpx<T>* X = (cpx<T>*)W.x;
   cpx<T>* R = (cpx<T>*)W.r;
-  cpx<T>* Pa = (cpx<T>*)W.p0;
-  cpx<T>* Pb = (cpx<T>*)W.p1;
-  std::vector<int> parity(ng, 0);  // current p of group g: parity[g] ? Pb : Pa
+  cpx<T>* P = (cpx<T>*)W.p0;
+  cpx<T>* spare = (cpx<T>*)W.p1;
   cpx<T>* Wv = (cpx<T>*)W.w;
   cpx<double>* XH = (cpx<double>*)W.xh;
+  const StreamSlots& sl = W.slots;
   hipError_t e = hipSuccess;
 #define SLAUNCH(...)                      \
   do {                                    \
@@ -930,145 +996,166 @@ static hipError_t run_stream_t(hipStream_t stm, const StreamMatrix& A, const Str
     e = hipGetLastError();                \
     if (e != hipSuccess) return e;        \
   } while (0)
-  // Dense operator: the check products over runs of consecutive waiting
-  // groups, as real row-major blocks (a complex column is two real ones).
-  auto dense_check_product = [&](const StreamGroups& grp) -> hipError_t {
-    for (int a = 0; a < grp.count;) {
-      int b = a + 1;
-      while (b < grp.count && grp.g[b] == grp.g[b - 1] + 1) ++b;
-      const size_t c0 = (size_t)grp.g[a] * gw;
-      const hipError_t e2 =
-          dense_apply_f64(*A.dense, stm, 2 * gw * (b - a), (const double*)(XH + c0), 2 * Bp,
-                          (double*)((cpx<double>*)W.axh + c0), 2 * Bp, 1.0, 0.0);
+  auto padded = [&](int cols) { return (cols + UC - 1) / UC * UC; };
+  // slot u < ns holds column hcol[u] (-1: none); row stride S of the slot blocks
+  int ns = L.ncols, S = padded(L.ncols);
+  std::vector<int> hcol(S, -1), hstate(Bp), hidx(Bp), hfrom(Bp);
+  for (int c = 0; c < ns; ++c) hcol[c] = c;
+  auto units = [&](int nrb) { return dim3(nrb, S / UC); };
+  auto fins = [&] { return dim3((S + kFinCols - 1) / kFinCols); };
+  SLAUNCH(k_s_bnorm<CPL>, units(nb), blk, 0, stm, n, L.B, L.ldb, L.k, L.ncols, W.part);
+  SLAUNCH(k_s_fin_bnorm, fins(), blk, 0, stm, S, nb, W.part, L.ncols, W.scale, W.cols, sl, L.tol,
+          delta);
+  SLAUNCH((k_s_start<T, CPL>), units(nb), blk, 0, stm, n, S, Bp, L.B, L.ldb, L.k, W.scale, A.perm,
+          X, R, P, XH, W.part);
+  SLAUNCH(k_s_fin_start, fins(), blk, 0, stm, S, nb, W.part, W.cols);
+  SLAUNCH(k_s_slots, dim3((S + kST - 1) / kST), blk, 0, stm, S, W.zc, W.cols, sl);
+  int live = 0, wait = 0;
+  auto census = [&]() -> hipError_t {
+    hipError_t e2 = hipMemcpyAsync(hstate.data(), W.cols.state, L.ncols * sizeof(int),
+                                   hipMemcpyDeviceToHost, stm);
+    if (e2 == hipSuccess) e2 = hipStreamSynchronize(stm);
+    live = wait = 0;
+    for (int c = 0; c < L.ncols; ++c) {
+      live += hstate[c] == 1;
+      wait += hstate[c] == 0 || hstate[c] == 3;
+    }
+    return e2;
+  };
+  // Columns that are done leave their slots when that frees a unit (a dense
+  // operator's product, which multiplies slots 0 .. ns - 1, from eight columns
+  // on: 4 us of product each per pass on n = 4096 against 15 us for the move).
+  auto compact = [&]() -> hipError_t {
+    const int left = live + wait;
+    if (left == 0 || !(padded(left) < S || (A.dense && ns - left >= 8))) return hipSuccess;
+    const int Sn = padded(left);
+    int m = 0;
+    for (int u = 0; u < ns; ++u)
+      if (hcol[u] >= 0 && hstate[hcol[u]] != 2) {
+        hidx[m] = hcol[u];
+        hfrom[m++] = u;
+      }
+    for (int u = m; u < Sn; ++u) hidx[u] = hfrom[u] = -1;
+    hcol.assign(hidx.begin(), hidx.begin() + Sn);
+    hipError_t e2 =
+        hipMemcpyAsync(sl.col, hidx.data(), Sn * sizeof(int), hipMemcpyHostToDevice, stm);
+    if (e2 == hipSuccess)
+      e2 = hipMemcpyAsync(sl.from, hfrom.data(), Sn * sizeof(int), hipMemcpyHostToDevice, stm);
+    if (e2 != hipSuccess) return e2;
+    // X -> spare, R -> the old X, P -> the old R; the old P is the next spare
+    cpx<T>* const old[3] = {X, R, P};
+    cpx<T>* const to[3] = {spare, X, R};
+    for (int i = 0; i < 3; ++i) {
+      hipLaunchKernelGGL((k_s_move<T>), dim3(nb, Sn / kSL), blk, 0, stm, n, S, Sn, sl.from, old[i],
+                         to[i]);
+      e2 = hipGetLastError();
       if (e2 != hipSuccess) return e2;
-      a = b;
+    }
+    X = to[0];
+    R = to[1];
+    P = to[2];
+    spare = old[2];
+    S = Sn;
+    ns = m;
+    hipLaunchKernelGGL(k_s_slots, dim3((S + kST - 1) / kST), blk, 0, stm, S, W.zc, W.cols, sl);
+    return hipGetLastError();
+  };
+  // Dense operator: A x_hi of the waiting columns, packed (the update's w is
+  // free here and holds the packed x_hi, as many columns of it as fit).
+  auto dense_check_product = [&]() -> hipError_t {
+    int nw = 0;
+    for (int u = 0; u < S; ++u) {
+      const bool on = hcol[u] >= 0 && (hstate[hcol[u]] == 0 || hstate[hcol[u]] == 3);
+      hfrom[u] = on ? nw : -1;
+      if (on) hidx[nw++] = hcol[u];
+    }
+    hipError_t e2 =
+        hipMemcpyAsync(sl.from, hfrom.data(), S * sizeof(int), hipMemcpyHostToDevice, stm);
+    if (e2 != hipSuccess) return e2;
+    cpx<double>* pk = (cpx<double>*)W.w;
+    const int room = (int)((size_t)Bp * sizeof(cpx<T>) / sizeof(cpx<double>));
+    for (int u0 = 0; u0 < nw; u0 += room) {
+      const int m = nw - u0 < room ? nw - u0 : room;
+      e2 = hipMemcpyAsync(sl.list, hidx.data() + u0, m * sizeof(int), hipMemcpyHostToDevice, stm);
+      if (e2 != hipSuccess) return e2;
+      hipLaunchKernelGGL(k_s_pack, dim3(nb, (m + kSL - 1) / kSL), blk, 0, stm, n, Bp, m, room,
+                         sl.list, XH, pk);
+      e2 = hipGetLastError();
+      if (e2 == hipSuccess)
+        e2 = dense_apply_f64(*A.dense, stm, 2 * m, (const double*)pk, 2 * room,
+                             (double*)((cpx<double>*)W.axh + u0), 2 * Bp, 1.0, 0.0);
+      if (e2 != hipSuccess) return e2;
     }
     return hipSuccess;
   };
-  const dim3 gall(nb, ng);
-  SLAUNCH(k_s_bnorm<CPL>, gall, blk, shm(1), stm, n, Bp, L.B, L.ldb, L.k, L.ncols, W.part);
-  SLAUNCH(k_s_fin_bnorm, fgrid, fblk, 0, stm, Bp, nb, W.part, L.ncols, W.scale, W.cols, L.tol,
-          delta);
-  SLAUNCH((k_s_start<T, CPL>), gall, blk, shm(1), stm, n, Bp, L.B, L.ldb, L.k, W.scale, A.perm, X,
-          R, Pa, XH, W.part);
-  SLAUNCH(k_s_fin_start, fgrid, fblk, 0, stm, Bp, nb, W.part, W.cols);
-  std::vector<int> cnt(2 * ng);
-  std::vector<int> hstate(A.dense ? Bp : 0), hidx, hmap;
-  auto census = [&]() -> hipError_t {
-    hipLaunchKernelGGL(k_s_count, dim3(ng), dim3(64), 0, stm, Bp, gw, W.cols, W.cnt);
-    hipError_t e2 = hipGetLastError();
-    if (e2 != hipSuccess) return e2;
-    e2 = hipMemcpyAsync(cnt.data(), W.cnt, 2 * ng * sizeof(int), hipMemcpyDeviceToHost, stm);
-    if (e2 != hipSuccess) return e2;
+  auto check = [&]() -> hipError_t {
+    const dim3 g = units(nb);
+    SLAUNCH((k_s_xhi<T, CPL>), g, blk, 0, stm, n, S, Bp, sl, P, X, XH);
     if (A.dense) {
-      e2 = hipMemcpyAsync(hstate.data(), W.cols.state, Bp * sizeof(int), hipMemcpyDeviceToHost,
-                          stm);
-      if (e2 != hipSuccess) return e2;
+      e = dense_check_product();
+      if (e != hipSuccess) return e;
+      SLAUNCH((k_s_resid64d<T, CPL>), g, blk, 0, stm, n, S, Bp, sl, L.B, L.ldb, L.k, W.scale, XH,
+              (const cpx<double>*)W.axh, R, P, W.part);
+    } else {
+      SLAUNCH((k_s_resid64<T, CPL>), g, blk, 0, stm, n, S, A.rowptr, A.col, A.val64, Bp, sl, L.B,
+              L.ldb, L.k, W.scale, A.perm, XH, R, P, W.part);
     }
-    return hipStreamSynchronize(stm);
-  };
-  // Dense operator: the packed list of the iterating columns, each with its
-  // group's p parity at the start of the chunk, and the column -> packed map.
-  int nl = 0;
-  auto pack_list = [&]() -> hipError_t {
-    hidx.clear();
-    hmap.assign(Bp, -1);
-    for (int c = 0; c < Bp; ++c)
-      if (hstate[c] == 1) {
-        hmap[c] = (int)hidx.size();
-        hidx.push_back(c | (parity[c / gw] << 30));
-      }
-    nl = (int)hidx.size();
-    hipError_t e2 = hipSuccess;
-    if (nl > 0)
-      e2 = hipMemcpyAsync(W.cidx, hidx.data(), nl * sizeof(int), hipMemcpyHostToDevice, stm);
-    if (e2 == hipSuccess)
-      e2 = hipMemcpyAsync(W.cmap, hmap.data(), Bp * sizeof(int), hipMemcpyHostToDevice, stm);
-    return e2;
+    SLAUNCH(k_s_fin_verify, fins(), blk, 0, stm, S, nb, W.part, sl, W.cols, L.tol, delta, L.maxit,
+            L.max_updates);
+    return hipSuccess;
   };
   e = census();
   if (e != hipSuccess) return e;
   const int chunk = L.chunk > 0 ? L.chunk : 8;
+  // FP32 columns are checked in nearly every pass, so the check follows a
+  // pass's iterations at once, without asking whether a column waits (it ends
+  // early where none does), and the host reads the states once per pass.  A
+  // dense operator's product needs the list of them, and FP64 columns wait
+  // once in several passes: there the host looks first.
+  const bool always = sizeof(T) == 4 && !A.dense;
   // Every column stays live or waiting from the start until it is done, and
   // each pass gives each live column at least one iteration and checks each
   // waiting one, so no column outlasts maxit + 2 * max_updates + 2 passes.
   const long guard = (long)L.maxit + 2L * L.max_updates + 8;
-  for (long pass = 0; pass < guard; ++pass) {
-    // group lists with each group's current p buffer
-    auto list = [&](int off) {
-      StreamGroups gl;
-      gl.count = 0;
-      for (int g = 0; g < ng; ++g)
-        if (cnt[off + g] > 0) {
-          gl.par[gl.count] = parity[g];
-          gl.g[gl.count++] = g;
-        }
-      return gl;
-    };
-    StreamGroups live = list(0), wait = list(ng);
-    if (live.count == 0 && wait.count == 0) break;
-    if (live.count > 0) {
-      const dim3 gl(nb, live.count);
-      if (A.dense) {
-        e = pack_list();
-        if (e != hipSuccess) return e;
-      }
-      for (int k = 0; k < chunk; ++k) {
-        SLAUNCH((k_s_pupd<T, CPL>), gl, blk, 0, stm, n, Bp, live, W.cols.beta, W.cols.state, R,
-                Pa, Pb);
-        for (int i = 0; i < live.count; ++i) {  // the new p is now current
-          live.par[i] ^= 1;
-          parity[live.g[i]] ^= 1;
-        }
-        if (A.dense) {
-          // the packed columns' p (parity flipped once per iteration so far),
-          // their product, then the shift
-          cpx<T>* Pc = (cpx<T>*)W.pc;
-          cpx<T>* APc = (cpx<T>*)W.apc;
-          if (nl > 0)
-            SLAUNCH((k_s_pack<T>), dim3(nb, (nl + 63) / 64), blk, 0, stm, n, Bp, nl, W.cidx,
-                    (k + 1) & 1, Pa, Pb, Pc);
-          if constexpr (sizeof(T) == 4)
-            e = dense_apply_f32(*A.dense, stm, 2 * nl, (const float*)Pc, 2 * Bp, (float*)APc,
-                                2 * Bp);
-          else
-            e = dense_apply_f64(*A.dense, stm, 2 * nl, (const double*)Pc, 2 * Bp,
-                                (double*)APc, 2 * Bp, 1.0, 0.0);
-          if (e != hipSuccess) return e;
-          SLAUNCH((k_s_shiftw_packed<T, CPL>), gl, blk, shm(2), stm, n, Bp, live, W.zc,
-                  W.cols.state, W.cmap, Pa, Pb, APc, Wv, W.part);
-        } else {
-          SLAUNCH((k_s_spmm<T, CPL>), gl, blk, shm(2), stm, n, A.rowptr, A.col, val, Bp, live,
-                  W.zc, W.cols.state, Pa, Pb, Wv, W.part);
-        }
-        SLAUNCH(k_s_fin_mu, fgrid, fblk, 0, stm, Bp, nb, W.part, W.cols);
-        SLAUNCH((k_s_update<T, CPL>), gl, blk, shm(3), stm, n, Bp, live, W.cols.alpha, X, R, Pa,
-                Pb, Wv, W.part);
-        SLAUNCH(k_s_fin_rho, fgrid, fblk, 0, stm, Bp, nb, W.part, W.cols, L.maxit);
-      }
-      e = census();
+  for (long pass = 0; pass < guard && live + wait > 0; ++pass) {
+    if (live > 0) {
+      e = compact();
       if (e != hipSuccess) return e;
-      wait = list(ng);
-    }
-    if (wait.count > 0) {
-      const dim3 gw2(nb, wait.count);
-      SLAUNCH((k_s_xhi<T, CPL>), gw2, blk, 0, stm, n, Bp, wait, W.cols.state, X, XH);
-      if (A.dense) {
-        e = dense_check_product(wait);
-        if (e != hipSuccess) return e;
-        SLAUNCH((k_s_resid64d<T, CPL>), gw2, blk, shm(3), stm, n, Bp, wait, W.zc, W.cols.state,
-                L.B, L.ldb, L.k, W.scale, XH, (const cpx<double>*)W.axh, R, Pa, Pb, W.part);
-      } else {
-        SLAUNCH((k_s_resid64<T, CPL>), gw2, blk, shm(3), stm, n, A.rowptr, A.col, A.val64, Bp,
-                wait, W.zc, W.cols.state, L.B, L.ldb, L.k, W.scale, A.perm, XH, R, Pa, Pb, W.part);
+      const dim3 g = units(nb);
+      for (int k = 0; k < chunk; ++k) {
+        SLAUNCH((k_s_pupd<T, CPL>), g, blk, 0, stm, n, S, sl, R, X, P);
+        if (A.dense) {
+          if constexpr (sizeof(T) == 4)
+            e = dense_apply_f32(*A.dense, stm, 2 * ns, (const float*)P, 2 * S, (float*)Wv, 2 * S);
+          else
+            e = dense_apply_f64(*A.dense, stm, 2 * ns, (const double*)P, 2 * S, (double*)Wv,
+                                2 * S, 1.0, 0.0);
+          if (e != hipSuccess) return e;
+          SLAUNCH((k_s_mu<T, CPL>), g, blk, 0, stm, n, S, sl, P, Wv, W.part);
+        } else {
+          SLAUNCH((k_s_spmm<T, CPL>), g, blk, 0, stm, n, S, A.rowptr, A.col, val, sl, P, Wv,
+                  W.part);
+        }
+        SLAUNCH(k_s_fin_mu, fins(), blk, 0, stm, S, nb, W.part, sl, W.cols);
+        if (A.dense)
+          SLAUNCH((k_s_update<T, CPL, true>), g, blk, 0, stm, n, S, sl, R, P, Wv, W.part);
+        else
+          SLAUNCH((k_s_update<T, CPL, false>), g, blk, 0, stm, n, S, sl, R, P, Wv, W.part);
+        SLAUNCH(k_s_fin_rho, fins(), blk, 0, stm, S, nb, W.part, sl, W.cols, L.maxit);
       }
-      SLAUNCH(k_s_fin_verify, fgrid, fblk, 0, stm, Bp, nb, W.part, W.cols, L.tol, delta,
-              L.maxit, L.max_updates);
-      e = census();
+      if (!always) {
+        e = census();
+        if (e != hipSuccess) return e;
+      }
+    }
+    if (always || wait > 0) {
+      e = check();
+      if (e == hipSuccess) e = census();
       if (e != hipSuccess) return e;
     }
   }
-  SLAUNCH((k_s_out<T, CPL>), gall, blk, 0, stm, n, Bp, L.ncols, W.cols.bn, A.perm, XH,
+  S = padded(L.ncols);
+  SLAUNCH((k_s_out<T, CPL>), units(nb), blk, 0, stm, n, Bp, L.ncols, W.cols.bn, A.perm, XH,
           (cpx<T>*)L.D, L.ldd);
   SLAUNCH(k_s_report, dim3((L.ncols + 255) / 256), dim3(256), 0, stm, L.ncols, W.cols, L.iters,
           L.resid, L.stats);
@@ -1078,18 +1165,10 @@ static hipError_t run_stream_t(hipStream_t stm, const StreamMatrix& A, const Str
 
 hipError_t run_stream_cocg(hipStream_t st, const StreamMatrix& A, const StreamWork& W,
                            const StreamLaunch& L, bool fp32) {
-  const int cpl = stream_cpl(L.k, L.ncols, fp32);
-  if (W.Bp % (64 * cpl) != 0 || W.Bp < L.ncols || W.Bp / (64 * cpl) > kStreamMaxGroups)
+  const int gw = 64 * stream_cpl(L.k, L.ncols, fp32);
+  if (W.Bp % gw != 0 || W.Bp < L.ncols || W.Bp / gw > kStreamMaxGroups)
     return hipErrorInvalidValue;
-  if (fp32) {
-    switch (cpl) {
-      case 1: return run_stream_t<float, 1>(st, A, W, L);
-      case 2: return run_stream_t<float, 2>(st, A, W, L);
-    }
-  } else if (cpl == 1) {
-    return run_stream_t<double, 1>(st, A, W, L);
-  }
-  return hipErrorInvalidValue;
+  return fp32 ? run_stream_t<float>(st, A, W, L) : run_stream_t<double>(st, A, W, L);
 }
 
 }  // namespace rafeast

@@ -189,15 +189,9 @@ hipError_t launch_cocg_resident(hipStream_t st, const ResGraph* g0, const ResGra
 // ---- streaming COCG engine (any n) ------------------------------------------
 // All columns c < ncols solve (zc[c] I - A) d_c = b_{c mod k} in lock step;
 // vectors are n x Bp complex blocks, row-major, in the engine's row order
-// (engine row r is caller row perm[r]).  Columns are handled in groups of
-// 64 * stream_cpl(k, ncols, fp32) (CPL complex columns per lane); at most
-// kStreamMaxGroups groups.
+// (engine row r is caller row perm[r]).  Columns are padded to groups of
+// 64 * stream_cpl(k, ncols, fp32); at most kStreamMaxGroups groups.
 constexpr int kStreamMaxGroups = 128;
-struct StreamGroups {
-  int count;
-  int g[kStreamMaxGroups];    // group of blockIdx.y
-  int par[kStreamMaxGroups];  // which of the two p buffers holds the group's current p
-};
 // Dense symmetric operator of the statistical workloads: A = K (kind 1,
 // n x n) or A = scale X^T X (kind 2, X rows x n).  Device matrices are
 // column-major (leading dimension n for K, rows for X); the products run on
@@ -284,25 +278,30 @@ struct StreamCols {                // per-column state, Bp entries (complex: 2 B
   int* rstart = nullptr;           // iteration count at the last (re)start
   double* sprev = nullptr;         // ||s||^2 at the last check (1 at the start)
 };
+struct StreamSlots {               // per slot, Bp entries (complex: 2 Bp)
+  int* col = nullptr;              // the column it holds (-1: none)
+  int* from = nullptr;             // scratch: old slot of a move, packed column of a check
+  int* list = nullptr;             // scratch: columns of a check's product
+  int* state = nullptr;            // copies of the column's, read by the row kernels
+  double* zc = nullptr;
+  double* alpha = nullptr;         // of the last iteration: its x += alpha p is still to come
+  double* beta = nullptr;
+};
 struct StreamWork {
   int Bp = 0;                      // stream_padded_columns(k, ncols, fp32)
   int num_cu = 0;
   void* x = nullptr;               // n x Bp complex (engine precision) each
   void* r = nullptr;
   void* p0 = nullptr;
-  void* p1 = nullptr;
+  void* p1 = nullptr;              // spare block of a move
   void* w = nullptr;
   void* xh = nullptr;              // n x Bp complex FP64
   void* axh = nullptr;             // dense operator only: n x Bp complex FP64, A x_hi
-  void* pc = nullptr;              // dense only: n x Bp complex, the iterating columns of p
-  void* apc = nullptr;             //   packed side by side, and A times them
-  int* cidx = nullptr;             // dense only: [Bp] packed column -> column (+ parity bit 30)
-  int* cmap = nullptr;             // dense only: [Bp] column -> packed column (-1: none)
   double* part = nullptr;          // stream_partial_doubles(n, Bp, num_cu)
   double* zc = nullptr;            // [2 Bp] shift of each column (padding: any finite value)
   double* scale = nullptr;         // [Bp]
-  int* cnt = nullptr;              // [2 * kStreamMaxGroups]
   StreamCols cols;
+  StreamSlots slots;
 };
 struct StreamLaunch {
   const double* B = nullptr;       // n x k RHS (FP64, caller row order), ldb

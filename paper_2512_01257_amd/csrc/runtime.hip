@@ -760,16 +760,18 @@ rafeast_status alloc_stream_work(rafeast_plan_s* P, int Bp, StreamWork& W,
     if (P->dop.kind == 2 && 2 * (int64_t)Bp > P->dop.tcols)
       return fail(P, RAFEAST_UNSUPPORTED, "more columns than the covariance scratch holds");
     RCHK(get(&W.axh, blk * 2 * sizeof(double), "stream A x_hi"));
-    RCHK(get(&W.pc, blk * cs, "stream packed p"));
-    RCHK(get(&W.apc, blk * cs, "stream packed A p"));
-    RCHK(get((void**)&W.cidx, (size_t)Bp * sizeof(int), "stream packed index"));
-    RCHK(get((void**)&W.cmap, (size_t)Bp * sizeof(int), "stream packed map"));
   }
   RCHK(get((void**)&W.part, stream_partial_doubles((int)n, Bp, P->num_cu) * sizeof(double),
            "stream partials"));
   RCHK(get((void**)&W.zc, 2 * (size_t)Bp * sizeof(double), "stream shifts"));
   RCHK(get((void**)&W.scale, (size_t)Bp * sizeof(double), "stream scale"));
-  RCHK(get((void**)&W.cnt, 2 * kStreamMaxGroups * sizeof(int), "stream census"));
+  RCHK(get((void**)&W.slots.col, (size_t)Bp * sizeof(int), "stream slots"));
+  RCHK(get((void**)&W.slots.from, (size_t)Bp * sizeof(int), "stream slot moves"));
+  RCHK(get((void**)&W.slots.list, (size_t)Bp * sizeof(int), "stream check list"));
+  RCHK(get((void**)&W.slots.state, (size_t)Bp * sizeof(int), "stream slot states"));
+  RCHK(get((void**)&W.slots.zc, 2 * (size_t)Bp * sizeof(double), "stream slot shifts"));
+  RCHK(get((void**)&W.slots.alpha, 2 * (size_t)Bp * sizeof(double), "stream slot alpha"));
+  RCHK(get((void**)&W.slots.beta, 2 * (size_t)Bp * sizeof(double), "stream slot beta"));
   RCHK(get((void**)&W.cols.state, (size_t)Bp * sizeof(int), "stream state"));
   RCHK(get((void**)&W.cols.it, (size_t)Bp * sizeof(int), "stream it"));
   RCHK(get((void**)&W.cols.nref, (size_t)Bp * sizeof(int), "stream nref"));
