@@ -12,8 +12,9 @@ namespace rafeast {
 
 // ============================================================================
 // SpMM, FP64 real: Y = alpha*A*X + beta*X + gamma*X2.  This form serves a
-// single column and matrices without nonzeros: one wave per row, the row's
-// nonzeros wave-uniform (scalar loads), lanes over the columns.
+// single column, some odd widths (launch_spmm_f64) and matrices without nonzeros:
+// one wave per row, the row's nonzeros wave-uniform (scalar loads), lanes over
+// the columns.
 // ============================================================================
 __global__ __launch_bounds__(256) void k_spmm_f64(int n, int k, const int* __restrict__ rowptr,
                                                   const int* __restrict__ col,
@@ -144,10 +145,10 @@ __device__ __forceinline__ void spmm_x2_row(int row, int sub, int k, const RowHe
   RoundBcast<L, 0, C>::run(h.jv, h.av, j0, a0);
   for (int c0 = 0; c0 < k; c0 += 2 * L) {
     // with k odd the last lane takes the last two columns, of which its
-    // neighbour writes the first as well (the same value)
+    // neighbour writes the first as well (the same value); idle lanes read
+    // the last two columns with them
     const bool ok = c0 + 2 * sub < k;
     const int c = min(c0 + 2 * sub, k - 2);
-    const int cs = ok ? c : 0;  // an in-range column for the idle lanes
     Pair acc0{0.0, 0.0}, acc1{0.0, 0.0};
     // the gathered rows of a round are loaded together; even and odd
     // positions of the row go to two partial sums, in order (a round of one
@@ -156,7 +157,7 @@ __device__ __forceinline__ void spmm_x2_row(int row, int sub, int k, const RowHe
       Pair x[C];
 #pragma unroll
       for (int u = 0; u < C; ++u)
-        x[u] = *reinterpret_cast<const Pair*>(X + (size_t)j0[u] * ldx + cs);
+        x[u] = *reinterpret_cast<const Pair*>(X + (size_t)j0[u] * ldx + c);
 #pragma unroll
       for (int u = 0; u < C; ++u) {
         if (s + u < e) {
@@ -180,7 +181,7 @@ __device__ __forceinline__ void spmm_x2_row(int row, int sub, int k, const RowHe
       Pair x[C];
 #pragma unroll
       for (int u = 0; u < C; ++u)
-        x[u] = *reinterpret_cast<const Pair*>(X + (size_t)j[u] * ldx + cs);
+        x[u] = *reinterpret_cast<const Pair*>(X + (size_t)j[u] * ldx + c);
 #pragma unroll
       for (int u = 0; u < C; ++u) {
         if (t0 + u < e) {
@@ -271,24 +272,32 @@ __global__ __launch_bounds__(256) void k_spmm_f64_x2(int n, int k, int rbx, int 
   }
 }
 
-// Row blocks a workgroup of the two-column SpMM sweeps.
-#ifndef RAFEAST_SPMM_RPB
-#define RAFEAST_SPMM_RPB 4
-#endif
-
 hipError_t launch_spmm_f64(hipStream_t st, int n, int k, const int* rowptr, const int* col,
                            const double* val, int64_t nnz, const double* X, int ldx, double* Y,
                            int ldy, double alpha, double beta, const double* X2, int ldx2,
                            double gamma) {
   if (n <= 0 || k <= 0) return hipSuccess;
-  if (nnz > 0 && k >= 2) {
+  // Odd widths of 33 to 63, and above 128 on few rows: a pass over column pairs
+  // has half its lanes or more idle, and the rows start between 16-byte
+  // boundaries; one column per lane is as fast or faster (us, pairs and single
+  // columns: 3D neighbour graph of 9,402 points, k = 63: 28.7, 26.1; k = 147:
+  // 47.3, 45.3; of 50,000, k = 33: 60.8, 56.3; 2D of 30,000, k = 63: 44.3, 43.0;
+  // 40^3 grid, k = 33: 37.5, 39.1; but 2D of 30,000, k = 147: 84.6, 90.4, and 3D
+  // of 50,000: 200, 211).
+  const bool single = k % 2 == 1 && ((k > 32 && k < 64) || (k > 128 && n < 16384));
+  if (nnz > 0 && k >= 2 && !single) {
     // lanes per row: the power of two covering the column pairs (<= 64)
     int L = 1;
     while (L < 64 && 2 * L < k) L *= 2;
     const int rw = 64 / L;
     const int rblocks = (n + 4 * rw - 1) / (4 * rw);
     const int rbx = (rblocks + 7) / 8;
-    const int rpb = RAFEAST_SPMM_RPB;
+    // Few row blocks: one to a workgroup, so that the chip is full; many: the
+    // pipeline over several saves the start of each.  us with 1, 2 and 4 row
+    // blocks: 2,000 points of a 3D neighbour graph, k = 64: 19.4, 20.9, 24.5;
+    // 30,000 of a 2D one, k = 147: 87, 89, 93; 40^3 grid, k = 147 (16,000 row
+    // blocks): 78, 76, 79.
+    const int rpb = rblocks >= (1 << 16) ? 4 : rblocks >= (1 << 13) ? 2 : 1;
     const dim3 grid((unsigned)(8 * ((rbx + rpb - 1) / rpb)));
 #define RAFEAST_SPMM_X2(LL)                                                                     \
   hipLaunchKernelGGL(k_spmm_f64_x2<LL>, grid, dim3(256), 0, st, n, k, rbx, rpb, rowptr, col,     \

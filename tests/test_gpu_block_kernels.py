@@ -115,3 +115,27 @@ def test_syev_variants(plan, k):
     assert np.abs(t - np.linalg.eigvalsh(H)).max() <= tol
     assert np.abs(s.T @ s - np.eye(k)).max() <= 32 * k * 2.0 ** -53
     assert np.abs(H @ s - s * t).max() <= tol
+
+
+@pytest.mark.parametrize("n,k", [(40_000, 70), (40_001, 9), (262_150, 66)])
+def test_spmm_row_blocks(gpu_lib, n, k):
+    # two and four row blocks to a workgroup (one on small matrices), the last
+    # ones cut short
+    import ctypes as C
+
+    import torch
+
+    from workloads import grid_laplacian
+
+    csr = grid_laplacian((n, 1), 0.01)
+    A = csr.to_scipy()
+    X = np.random.default_rng(k).standard_normal((n, k))
+    with gpu_lib.Plan(csr, 0.0, 0.5, 4, nc=2, q=1, p=4, precision="fp64", engine="stream") as p:
+        x = torch.from_numpy(X).cuda()
+        y = torch.full((n, k), 3.0, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        assert gpu_lib.lib().rafeast_spmm(p.handle, k, C.c_void_p(x.data_ptr()), k,
+                                          C.c_void_p(y.data_ptr()), k, 1.5, -0.5) == 0
+    ref = 1.5 * (A @ X) - 0.5 * X
+    bound = 64 * 2.0 ** -53 * (1.5 * (abs(A) @ np.abs(X)) + 0.5 * np.abs(X))
+    assert (np.abs(y.cpu().numpy() - ref) <= bound).all()
