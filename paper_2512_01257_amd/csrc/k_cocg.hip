@@ -41,6 +41,8 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <complex>
+#include <functional>
 #include <vector>
 
 namespace rafeast {
@@ -214,6 +216,86 @@ __device__ __forceinline__ E load_entry(const E* __restrict__ base, unsigned idx
                                      idx * (unsigned)sizeof(E));
 }
 
+// acc += the entries of NS slots (first entry bse, width wde; widths do not
+// increase) times the p they gather from LDS.  FP32: few wide loads (the load
+// instruction count, not the bytes, sets the pace): per lane and slot, eight
+// entries take three 16-byte loads (eight values, eight 16-bit LDS offsets)
+// and a trailing four take two; slots go in pairs so that the loads of two
+// slots are in flight together; slots past their width load nothing
+// (wave-uniform bounds).
+template <int NS>
+__device__ __forceinline__ void spmv_f32(const float* __restrict__ vals,
+                                         const unsigned short* __restrict__ offs,
+                                         const int (&bse)[NS], const int (&wde)[NS], int ln,
+                                         float (&acc_re)[NS], float (&acc_im)[NS]) {
+#pragma unroll
+  for (int t = 0; t < NS; t += 2) {
+    const int ta = t, tb = t + 1 < NS ? t + 1 : t;
+    const int na = wde[ta] >> 3, nb = tb != ta ? wde[tb] >> 3 : 0;
+    for (int o = 0; o < na; ++o) {
+      const int ba = bse[ta] + o * 512;
+      const float4 va0 = load_entry(reinterpret_cast<const float4*>(vals + ba), (unsigned)ln);
+      const float4 va1 =
+          load_entry(reinterpret_cast<const float4*>(vals + ba + 256), (unsigned)ln);
+      const uint4 oa = load_entry(reinterpret_cast<const uint4*>(offs + ba), (unsigned)ln);
+      float4 vb0 = make_float4(0.f, 0.f, 0.f, 0.f), vb1 = vb0;
+      uint4 ob = make_uint4(0u, 0u, 0u, 0u);
+      const bool hb = o < nb;
+      if (hb) {
+        const int bb = bse[tb] + o * 512;
+        vb0 = load_entry(reinterpret_cast<const float4*>(vals + bb), (unsigned)ln);
+        vb1 = load_entry(reinterpret_cast<const float4*>(vals + bb + 256), (unsigned)ln);
+        ob = load_entry(reinterpret_cast<const uint4*>(offs + bb), (unsigned)ln);
+      }
+      const float va[8] = {va0.x, va0.y, va0.z, va0.w, va1.x, va1.y, va1.z, va1.w};
+      const unsigned oaw[4] = {oa.x, oa.y, oa.z, oa.w};
+      cpx<float> ga[8];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        ga[2 * u] = lds_gather<float>((int)(oaw[u] & 0xffffu));
+        ga[2 * u + 1] = lds_gather<float>((int)(oaw[u] >> 16));
+      }
+      if (hb) {
+        const float vbv[8] = {vb0.x, vb0.y, vb0.z, vb0.w, vb1.x, vb1.y, vb1.z, vb1.w};
+        const unsigned obw[4] = {ob.x, ob.y, ob.z, ob.w};
+        cpx<float> gb[8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          gb[2 * u] = lds_gather<float>((int)(obw[u] & 0xffffu));
+          gb[2 * u + 1] = lds_gather<float>((int)(obw[u] >> 16));
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          acc_re[tb] += vbv[u] * gb[u].re;
+          acc_im[tb] += vbv[u] * gb[u].im;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        acc_re[ta] += va[u] * ga[u].re;
+        acc_im[ta] += va[u] * ga[u].im;
+      }
+    }
+    // remaining octs of slot tb cannot exist (widths are non-increasing
+    // within a wave); trailing quads of both slots
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int tq = q == 0 ? ta : tb;
+      if ((q == 0 || tb != ta) && (wde[tq] & 4)) {
+        const int bq = bse[tq] + (wde[tq] >> 3) * 512;
+        const float4 v = load_entry(reinterpret_cast<const float4*>(vals + bq), (unsigned)ln);
+        const uint2 oq = load_entry(reinterpret_cast<const uint2*>(offs + bq), (unsigned)ln);
+        const cpx<float> g0 = lds_gather<float>((int)(oq.x & 0xffffu));
+        const cpx<float> g1 = lds_gather<float>((int)(oq.x >> 16));
+        const cpx<float> g2 = lds_gather<float>((int)(oq.y & 0xffffu));
+        const cpx<float> g3 = lds_gather<float>((int)(oq.y >> 16));
+        acc_re[tq] += v.x * g0.re + v.y * g1.re + v.z * g2.re + v.w * g3.re;
+        acc_im[tq] += v.x * g0.im + v.y * g1.im + v.z * g2.im + v.w * g3.im;
+      }
+    }
+  }
+}
+
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef const __attribute__((address_space(4))) ResGraph ConstGraph;
 __device__ __forceinline__ ConstGraph* const_graph(const ResGraph* graphs, int g) {
@@ -225,11 +307,481 @@ __device__ __forceinline__ const ResGraph* const_graph(const ResGraph* graphs, i
 }
 #endif
 
+// ---------------------------------------------------------------------------
+// Teams.  A launch ends with its slowest systems: of four shifts the hardest
+// takes four times the iterations of the others, and three quarters of the
+// CUs have nothing left to do.  The systems that the host expects to be left
+// (cocg_plan_teams) stop at an iteration given to the launch and leave their
+// state in memory; a second launch continues them, four workgroups to a system.
+// Member m owns the slots m and RPT - 1 - m of every wave and keeps all of p in
+// its LDS; a step's sums are exchanged through global memory, and with the
+// second one the new residual, from which every member forms the whole next p.
+//
+// Exchange: a double is sent as two 8-byte words, each half its bits and half
+// the number of the sum, written and polled with agent-scope atomics, so a
+// word is its own flag; the words of successive sums alternate between two
+// sets (a member writes set s again only after a sum that needed all members
+// to have read it).  Vectors are written with agent-scope stores, which have
+// arrived (vmcnt) before the next sum's words are written.  Only one wave of a
+// member polls (flags polled by all sixteen took longer than they saved).  The
+// members' workgroup numbers are 8 apart, so they run on one XCD, where an
+// exchange takes half the time; the result does not depend on it.
+//
+// Every wait ends: a member waits for the words of its three fellows only,
+// whose workgroups are at most 24 numbers away; workgroups start in the order
+// of their numbers, so at most eight teams (24 workgroups) can be waiting for
+// fellows that have not started, which leaves CUs for those to start on.  The
+// members' sums and decisions are the same bits, so they take the same steps.
+//
+// What bounds it is the latency of the exchanges (of about 14,000 clocks an
+// iteration, 3,000 for each sum and 3,000 for the residuals).  knn n = 8000,
+// FP32: an iteration takes 6.5 us of four workgroups, 9.6 us of one; 64
+// systems of 4 shifts 14.8 -> 12.0 ms.  With four slots a thread (n = 3000) it
+// takes 5.4 us of four workgroups and 4.6 us of one, so those have no teams.
+typedef unsigned long long u64;
+constexpr int kTeamStride = 80;   // words of a team's ctl: two sets of kTeamSize * 8, then
+constexpr int kTeamLeft = 64;     //   1: its system was left to it
+constexpr int kTeamHead = 18;     // words of a team's buffer before p, r and x
+
+__device__ __forceinline__ u64 agent_get(const u64* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_put(u64* p, u64 v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u64 bits_of(cpx<float> v) {
+  return ((u64)(unsigned)__float_as_int(v.im) << 32) | (unsigned)__float_as_int(v.re);
+}
+__device__ __forceinline__ cpx<float> cpx_of(u64 b) {
+  return cpx<float>{__int_as_float((int)(b & 0xffffffffull)), __int_as_float((int)(b >> 32))};
+}
+__device__ __forceinline__ void agent_put(cpx<double>* p, cpx<double> v) {
+  agent_put(reinterpret_cast<u64*>(p), (u64)__double_as_longlong(v.re));
+  agent_put(reinterpret_cast<u64*>(p) + 1, (u64)__double_as_longlong(v.im));
+}
+__device__ __forceinline__ cpx<double> agent_get(const cpx<double>* p) {
+  return cpx<double>{__longlong_as_double((long long)agent_get(reinterpret_cast<const u64*>(p))),
+                     __longlong_as_double((long long)agent_get(reinterpret_cast<const u64*>(p) + 1))};
+}
+__device__ __forceinline__ u64* team_ctl(const CocgTeams& T, int t) {
+  return T.ctl + (size_t)t * kTeamStride;
+}
+__device__ __forceinline__ u64* team_buf(const CocgTeams& T, int t, int npad) {
+  return T.buf + (size_t)t * (kTeamHead + 3 * (size_t)npad);
+}
+
+// A system's state, as in the solve of one workgroup.
+struct TeamState {
+  int it, nref, nbd, lastit, rstart, span, span0, first_cycle;
+  double rho_re, rho_im, cyc_tol2, sprev, scale, bn;
+  int j, ci, owner;  // the item; the workgroup whose x_hi buffer it uses
+};
+
+// Slot h of member m: the widest with the narrowest.
+template <int RPT>
+__device__ __forceinline__ int team_slot(int m, int h) {
+  return h ? RPT - 1 - m : m;
+}
+
+// Polls (lanes with want) until the word's low half is seq.
+__device__ __forceinline__ u64 team_poll(const u64* word, bool want, unsigned seq) {
+  u64 w = 0;
+  bool ok = !want;
+  do {
+    if (!ok) {
+      w = agent_get(word);
+      ok = (unsigned)w == seq;
+    }
+  } while (__ballot(!ok) != 0);
+  return w;
+}
+
+// block_sum_fin over the team: every member receives the same fin(totals).
+// A wave's earlier stores have arrived before the sum's words are written.
+template <int NV, int NO, typename A, typename F>
+__device__ __forceinline__ void team_sum_fin(const A (&part)[NV], double (&o)[NO],
+                                             double (*red)[kResWaves][4], u64* W, int m,
+                                             unsigned& seq, F fin) {
+  const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+  ++seq;
+  const int set = seq & 1;
+  double ws[NV];
+  wave_sums(part, ws);
+  if (ln == 0) {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) red[set][wv][q] = ws[q];
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  double* flat = &red[set][0][0];
+  if (wv == 0) {
+    double x[NV], t[NV], r[NO];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) x[q] = red[set][ln & (kResWaves - 1)][q];
+    row0_sums_f64(x);
+    u64* S = W + set * (kTeamSize * 8);
+    unsigned half = 0;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const u64 b = (u64)__double_as_longlong(x[q]);
+      if (ln == 2 * q) half = (unsigned)b;
+      if (ln == 2 * q + 1) half = (unsigned)(b >> 32);
+    }
+    if (ln < 2 * NV) agent_put(S + m * 8 + ln, ((u64)half << 32) | seq);
+    const u64 w = team_poll(S + ln, ln < kTeamSize * 8 && (ln & 7) < 2 * NV, seq);
+    const int got = (int)(w >> 32);
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      double a = 0.0;
+#pragma unroll
+      for (int k = 0; k < kTeamSize; ++k) {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readlane(got, k * 8 + 2 * q);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readlane(got, k * 8 + 2 * q + 1);
+        a += __longlong_as_double((long long)(((u64)hi << 32) | lo));
+      }
+      t[q] = a;
+    }
+    fin(t, r);
+    if (ln == 0) {
+#pragma unroll
+      for (int q = 0; q < NO; ++q) flat[q] = r[q];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NO; ++q) o[q] = flat[q];
+}
+
+// Element i of a uniform base, by a 32-bit byte offset.
+template <typename E>
+__device__ __forceinline__ E* at32(E* base, unsigned i) {
+  return reinterpret_cast<E*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(E));
+}
+
+// Leaves a system to its team: scalars, p, r, x (x_hi is in the workgroup's
+// global buffer).
+template <int RPT>
+__device__ __forceinline__ void team_leave(const CocgTeams& T, int team, int npad,
+                                           const TeamState& ts, const cpx<float>* P,
+                                           const cpx<float>* R, const cpx<float> (&xr)[RPT],
+                                           const int (&slc)[RPT], int lane) {
+  u64* buf = team_buf(T, team, npad);
+  cpx<float>* v = reinterpret_cast<cpx<float>*>(buf + kTeamHead);
+#pragma unroll
+  for (int t = 0; t < RPT; ++t)
+    if (slc[t] >= 0) {
+      const int s = slc[t] * 64 + lane;
+      *at32(v, s) = P[s];
+      *at32(v + npad, s) = R[s];
+      *at32(v + 2 * npad, s) = xr[t];
+    }
+  if (threadIdx.x == 0) {
+    *reinterpret_cast<TeamState*>(buf) = ts;
+    team_ctl(T, team)[kTeamLeft] = 1;
+  }
+}
+static_assert(sizeof(TeamState) <= kTeamHead * sizeof(u64));
+
+// Four workgroups a team: workgroup b is member (b / 8) % 4 of team
+// b % 8 + 8 (b / 32).
+template <int RPT>
+__global__ __launch_bounds__(kResThreads) void k_cocg_team(CocgTeams T, ResGraph G, int npad,
+                                                           int maxit, int max_refine,
+                                                           cpx<double>* __restrict__ xhi_all) {
+  extern __shared__ unsigned char smem_raw[];
+  cpx<float>* P = reinterpret_cast<cpx<float>*>(smem_raw);  // then the zero row and the trash row
+  const int zoff = npad, toff = zoff + 64;
+  double(*red)[kResWaves][4] =
+      reinterpret_cast<double(*)[kResWaves][4]>(smem_raw + (size_t)(npad + 128) * sizeof(cpx<float>));
+  const int team = (int)(blockIdx.x % 8 + blockIdx.x / 32 * 8), m = (int)(blockIdx.x / 8 % 4);
+  if (team >= T.nteam || team_ctl(T, team)[kTeamLeft] != 1) return;
+  const double tol2 = G.tol * G.tol;
+  TeamState ts = *reinterpret_cast<const TeamState*>(team_buf(T, team, npad));
+  cpx<double>* XH = xhi_all + (size_t)ts.owner * npad;
+  const double zr = G.zs[2 * ts.j], zi = G.zs[2 * ts.j + 1];
+  const int ocol = ts.j * G.kcols + ts.ci;
+  cpx<float>* D = reinterpret_cast<cpx<float>*>(G.D);
+  constexpr int NS = RPT / kTeamSize, NO = RPT - NS;
+  static_assert(NS == 2);
+  const int lane0 = threadIdx.x & 63;
+  int lane = lane0;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  u64* W = team_ctl(T, team);
+  u64* px = team_buf(T, team, npad) + kTeamHead;
+  u64* rx = px + npad;
+  const float* __restrict__ vals = reinterpret_cast<const float*>(G.ent);
+  const unsigned short* __restrict__ offs = reinterpret_cast<const unsigned short*>(vals + G.n32);
+  const double delta = 0.1;
+  unsigned seq = 0;
+  double last_res = 1.0;
+  int own[NS], oth[NO];  // slices (-1: none)
+#pragma unroll
+  for (int h = 0; h < NS; ++h)
+    own[h] = __builtin_amdgcn_readfirstlane(G.wave_slices[wv * RPT + team_slot<RPT>(m, h)]);
+#pragma unroll
+  for (int q = 0; q < NO; ++q)
+    oth[q] = __builtin_amdgcn_readfirstlane(
+        G.wave_slices[wv * RPT + team_slot<RPT>((m + 1 + q / NS) & (kTeamSize - 1), q % NS)]);
+  int bse[NS], wde[NS];
+  cpx<float> xr[NS], rr[NS];
+#pragma unroll
+  for (int h = 0; h < NS; ++h) {
+    bse[h] = own[h] >= 0 ? G.sbase[own[h]] : G.zero_base;
+    wde[h] = own[h] >= 0 ? (G.sbase[own[h] + 1] - bse[h]) >> 6 : 0;
+    xr[h] = own[h] >= 0 ? cpx_of(rx[npad + own[h] * 64 + lane]) : cpx<float>{0.0f, 0.0f};
+    rr[h] = own[h] >= 0 ? cpx_of(rx[own[h] * 64 + lane]) : cpx<float>{0.0f, 0.0f};
+  }
+#pragma unroll
+  for (int t = 0; t < RPT; ++t) {
+    const int slice = t < NS ? own[t] : oth[t - NS];
+    if (slice >= 0) P[slice * 64 + lane] = cpx_of(px[slice * 64 + lane]);
+  }
+  if (wv == 0) P[zoff + lane] = cpx<float>{0.0f, 0.0f};
+  __syncthreads();
+  auto same = [](const double* t, double* r) { r[0] = t[0]; };
+  // the first eight entries of the own rows stay in registers
+  float4 hv[NS][2];
+  uint4 ho[NS];
+#pragma unroll
+  for (int h = 0; h < NS; ++h) {
+    hv[h][0] = hv[h][1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    ho[h] = make_uint4(0u, 0u, 0u, 0u);
+    if (wde[h] >= 8) {
+      hv[h][0] = load_entry(reinterpret_cast<const float4*>(vals + bse[h]), (unsigned)lane);
+      hv[h][1] = load_entry(reinterpret_cast<const float4*>(vals + bse[h] + 256), (unsigned)lane);
+      ho[h] = load_entry(reinterpret_cast<const uint4*>(offs + bse[h]), (unsigned)lane);
+    } else if (wde[h] >= 4) {
+      hv[h][0] = load_entry(reinterpret_cast<const float4*>(vals + bse[h]), (unsigned)lane);
+      const uint2 o = load_entry(reinterpret_cast<const uint2*>(offs + bse[h]), (unsigned)lane);
+      ho[h] = make_uint4(o.x, o.y, 0u, 0u);
+    }
+  }
+  // acc += eight entries (0 times p's first past a row's end)
+  auto oct = [&](const float4 (&v)[2], const uint4& o, float& a_re, float& a_im) {
+    const unsigned w[4] = {o.x, o.y, o.z, o.w};
+    const float e[8] = {v[0].x, v[0].y, v[0].z, v[0].w, v[1].x, v[1].y, v[1].z, v[1].w};
+    cpx<float> g[8];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      g[2 * u] = lds_gather<float>((int)(w[u] & 0xffffu));
+      g[2 * u + 1] = lds_gather<float>((int)(w[u] >> 16));
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      a_re += e[u] * g[u].re;
+      a_im += e[u] * g[u].im;
+    }
+  };
+  // p = r + beta p of every slot (!keep: p = r), the others' r from the exchange
+  auto next_p = [&](float br, float bi, bool keep) {
+    u64 ro[NO];
+#pragma unroll
+    for (int q = 0; q < NO; ++q)
+      ro[q] = oth[q] >= 0 ? agent_get(at32(rx, oth[q] * 64 + lane)) : 0ull;
+    auto one = [&](int slice, cpx<float> r) {
+      const int s = (slice >= 0 ? slice * 64 : toff) + lane;
+      cpx<float> p = r;
+      if (keep) {
+        const cpx<float> o = P[slice >= 0 ? s : zoff + lane];
+        p = cpx<float>{r.re + br * o.re - bi * o.im, r.im + br * o.im + bi * o.re};
+      }
+      P[s] = p;
+    };
+#pragma unroll
+    for (int h = 0; h < NS; ++h) one(own[h], rr[h]);
+#pragma unroll
+    for (int q = 0; q < NO; ++q) one(oth[q], cpx_of(ro[q]));
+    __syncthreads();
+  };
+  for (;;) {
+    bool verify = false, restart = false;
+    // addresses are cheap to form again and too many to keep (as above)
+    lane = lane0;
+    asm volatile("" : "+v"(lane));
+    float ar[NS], ai[NS];
+#pragma unroll
+    for (int h = 0; h < NS; ++h) ar[h] = ai[h] = 0.0f;
+    // entries 8 to 15 are on their way while the held ones are used
+    float4 nv[NS][2];
+    uint4 no[NS];
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+      nv[h][0] = nv[h][1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      no[h] = make_uint4(0u, 0u, 0u, 0u);
+      const int b = bse[h] + 512;
+      if (wde[h] >= 16) {
+        nv[h][0] = load_entry(reinterpret_cast<const float4*>(vals + b), (unsigned)lane);
+        nv[h][1] = load_entry(reinterpret_cast<const float4*>(vals + b + 256), (unsigned)lane);
+        no[h] = load_entry(reinterpret_cast<const uint4*>(offs + b), (unsigned)lane);
+      } else if (wde[h] >= 12) {
+        nv[h][0] = load_entry(reinterpret_cast<const float4*>(vals + b), (unsigned)lane);
+        const uint2 o = load_entry(reinterpret_cast<const uint2*>(offs + b), (unsigned)lane);
+        no[h] = make_uint4(o.x, o.y, 0u, 0u);
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+      // unpacked each time: hoisted, the offsets would take twice the registers
+      asm volatile("" : "+v"(ho[h].x), "+v"(ho[h].y), "+v"(ho[h].z), "+v"(ho[h].w));
+      oct(hv[h], ho[h], ar[h], ai[h]);
+    }
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+      if (wde[h] >= 12) oct(nv[h], no[h], ar[h], ai[h]);
+      if (wde[h] > 16) {
+        const int b1[1] = {bse[h] + 1024}, w1[1] = {wde[h] - 16};
+        float r1[1] = {ar[h]}, i1[1] = {ai[h]};
+        spmv_f32<1>(vals, offs, b1, w1, lane, r1, i1);
+        ar[h] = r1[0];
+        ai[h] = i1[0];
+      }
+    }
+    const float zrt = (float)zr, zit = (float)zi;
+    float mu_t[2] = {0.0f, 0.0f};
+    cpx<float> pv[NS], w[NS];
+#pragma unroll
+    for (int h = 0; h < NS; ++h) {
+      pv[h] = P[(own[h] >= 0 ? own[h] * 64 : zoff) + lane];
+      w[h].re = zrt * pv[h].re - zit * pv[h].im - ar[h];
+      w[h].im = zrt * pv[h].im + zit * pv[h].re - ai[h];
+      mu_t[0] += pv[h].re * w[h].re - pv[h].im * w[h].im;
+      mu_t[1] += pv[h].re * w[h].im + pv[h].im * w[h].re;
+    }
+    double ms[4];
+    team_sum_fin<2, 4>(mu_t, ms, red, W, m, seq, [&](const double* t, double* r) {
+      const zd a = zdiv_fast(zd{ts.rho_re, ts.rho_im}, zd{t[0], t[1]});
+      r[0] = t[0];
+      r[1] = t[1];
+      r[2] = a.re;
+      r[3] = a.im;
+    });
+    if (!(isfinite(ms[2]) && isfinite(ms[3])) || (ms[0] == 0.0 && ms[1] == 0.0)) {
+      ++ts.nbd;
+      verify = true;
+      restart = true;
+    } else {
+      float s3_t[3] = {0.0f, 0.0f, 0.0f};
+      const float alr = (float)ms[2], ali = (float)ms[3];
+#pragma unroll
+      for (int h = 0; h < NS; ++h) {
+        xr[h].re += alr * pv[h].re - ali * pv[h].im;
+        xr[h].im += alr * pv[h].im + ali * pv[h].re;
+        rr[h].re -= alr * w[h].re - ali * w[h].im;
+        rr[h].im -= alr * w[h].im + ali * w[h].re;
+        if (own[h] >= 0) agent_put(at32(rx, own[h] * 64 + lane), bits_of(rr[h]));
+        s3_t[0] += rr[h].re * rr[h].re - rr[h].im * rr[h].im;
+        s3_t[1] += 2.0f * rr[h].re * rr[h].im;
+        s3_t[2] += rr[h].re * rr[h].re + rr[h].im * rr[h].im;
+      }
+      double so[5];
+      team_sum_fin<3, 5>(s3_t, so, red, W, m, seq, [&](const double* t, double* r) {
+        const zd b = zdiv_fast(zd{t[0], t[1]}, zd{ts.rho_re, ts.rho_im});
+        r[0] = t[0];
+        r[1] = t[1];
+        r[2] = t[2];
+        r[3] = b.re;
+        r[4] = b.im;
+      });
+      ++ts.it;
+      const bool stall =
+          ts.span > 0 && ts.it - ts.lastit > max(2 * max(ts.span, ts.span0), 256);
+      if (so[2] <= ts.cyc_tol2 || ts.it >= maxit || stall) {
+        verify = true;
+      } else {
+        ts.rho_re = so[0];
+        ts.rho_im = so[1];
+        next_p((float)so[3], (float)so[4], true);
+      }
+    }
+    if (!verify) continue;
+
+    // x_hi += x; true residual in FP64 on the own slots
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+      if (own[h] >= 0) {
+        cpx<double>* xp = at32(XH, own[h] * 64 + lane);
+        cpx<double> xh{0.0, 0.0};
+        if (!ts.first_cycle) xh = agent_get(xp);
+        xh.re += (double)xr[h].re;
+        xh.im += (double)xr[h].im;
+        agent_put(xp, xh);
+        xr[h] = cpx<float>{0.0f, 0.0f};
+      }
+    ts.first_cycle = 0;
+    const double none[1] = {0.0};
+    double all[1];
+    team_sum_fin<1, 1>(none, all, red, W, m, seq, same);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the members' x_hi
+    double s3p[3] = {0.0, 0.0, 0.0}, s3[3];
+    const char* XHb = reinterpret_cast<const char*>(XH);
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+      if (own[h] >= 0) {
+        const int s = own[h] * 64 + lane;
+        double sar = 0.0, sai = 0.0;
+        sell_dot<double, double>(G.ent64 + bse[h] + lane, wde[h], XHb, sar, sai);
+        const cpx<double> xh = agent_get(at32(XH, s));
+        const int row = G.perm[s];
+        const double b =
+            row >= 0 ? G.B[(unsigned)row * (unsigned)G.ldb + ts.ci] * ts.scale : 0.0;
+        const double sr = b - (zr * xh.re - zi * xh.im - sar);
+        const double si = -(zr * xh.im + zi * xh.re - sai);
+        rr[h] = cpx<float>{(float)sr, (float)si};
+        s3p[0] += sr * sr - si * si;
+        s3p[1] += 2.0 * sr * si;
+        s3p[2] += sr * sr + si * si;
+      }
+    team_sum_fin<3, 3>(s3p, s3, red, W, m, seq, [](const double* t, double* r) {
+      r[0] = t[0];
+      r[1] = t[1];
+      r[2] = t[2];
+    });
+    last_res = sqrt(s3[2]);
+    if (s3[2] <= tol2 || ts.nref >= max_refine || ts.it >= maxit || ts.nbd > 3) break;
+    ++ts.nref;
+    zd beta{0.0, 0.0};
+    if (!restart && s3[2] <= 0.25 * ts.sprev) {
+      beta = zdiv_fast(zd{s3[0], s3[1]}, zd{ts.rho_re, ts.rho_im});
+      if (!(isfinite(beta.re) && isfinite(beta.im))) beta = zd{0.0, 0.0};
+    }
+    const bool keep = beta.re != 0.0 || beta.im != 0.0;
+    ts.span = ts.it - ts.lastit;
+    if (ts.lastit == ts.rstart) ts.span0 = max(ts.span0, ts.span);
+    ts.lastit = ts.it;
+    if (!keep) ts.rstart = ts.it;
+    ts.sprev = s3[2];
+    ts.rho_re = s3[0];
+    ts.rho_im = s3[1];
+    ts.cyc_tol2 = fmax(tol2, delta * delta * s3[2]);
+#pragma unroll
+    for (int h = 0; h < NS; ++h)
+      if (own[h] >= 0) agent_put(at32(rx, own[h] * 64 + lane), bits_of(rr[h]));
+    team_sum_fin<1, 1>(none, all, red, W, m, seq, same);
+    next_p((float)beta.re, (float)beta.im, keep);
+  }
+#pragma unroll
+  for (int h = 0; h < NS; ++h)
+    if (own[h] >= 0) {
+      const int row = G.perm[own[h] * 64 + lane];
+      const cpx<double> xh = agent_get(at32(XH, own[h] * 64 + lane));
+      if (row >= 0)
+        D[(unsigned)row * (unsigned)G.ldd + ocol] =
+            cpx<float>{(float)(xh.re * ts.bn), (float)(xh.im * ts.bn)};
+    }
+  if (m == 0 && threadIdx.x == 0) {
+    G.iters[ocol] = ts.it;
+    if (G.resid) G.resid[ocol] = last_res;
+    if (ts.nref) atomicAdd(&G.stats[0], ts.nref);
+    if (ts.nbd > 3) atomicAdd(&G.stats[1], 1);
+  }
+}
+
 // MULTI false: every item belongs to the graph whose fields are the scalar
 // kernel arguments (scalar loads from the argument segment).  MULTI true:
 // item (g, j, i) reads graphs[g] at its start; the scalar graph arguments
-// are unused.
-template <typename T, int RPT, bool MULTI>
+// are unused.  TEAM: some items are
+// left to teams (above).
+template <typename T, int RPT, bool MULTI, bool TEAM>
 __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
     int a_nslices, const int* __restrict__ a_sbase, const int* __restrict__ a_perm,
     const void* __restrict__ a_ent, const SellEntry64* __restrict__ a_ent64, int a_n32, int nitems,
@@ -238,7 +790,7 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
     double tol, int maxit, int max_refine, int* __restrict__ counter, int* __restrict__ a_iters,
     int* __restrict__ a_stats, double* __restrict__ a_resid, cpx<double>* __restrict__ xhi_all,
     int a_zero_base, const int* __restrict__ a_wave_slices, const ResGraph* __restrict__ graphs,
-    int max_npad) {
+    int max_npad, CocgTeams teams) {
   // Dynamic LDS only (so p starts at address 0 and a gather address is the
   // entry's stored byte offset): p | r (sized for the graph of the current
   // item) ... | zero row | trash row | reduction slots | work item (after
@@ -335,6 +887,9 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
     if constexpr (MULTI) load_graph(*const_graph(graphs, g));
     const double zr = zs[2 * j], zi = zs[2 * j + 1];
     const int ocol = j * kcols + ci;
+    int team = -1;     // the item's team
+    bool left = false;  // and it is left to it
+    if constexpr (TEAM) team = __builtin_amdgcn_readfirstlane(teams.team_of[item]);
 
     // ---- right-hand side, scaled to unit norm ----
     double acc1[1] = {0.0};
@@ -420,81 +975,10 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
         wde[t] = slice >= 0 ? (sbase[slice + 1] - bse[t]) >> 6 : 0;
       }
       if constexpr (sizeof(T) == 4) {
-        // FP32: the SpMV issues few wide loads (the load instruction count,
-        // not the bytes, sets its pace): per lane and slot, eight entries
-        // take three 16-byte loads (eight values, eight 16-bit LDS offsets)
-        // and a trailing four take two; slots go in pairs so that the loads
-        // of two slots are in flight together; slots past their width load
-        // nothing (wave-uniform bounds).
         const float* __restrict__ vals = reinterpret_cast<const float*>(ent);
         const unsigned short* __restrict__ offs =
             reinterpret_cast<const unsigned short*>(vals + n32);
-#pragma unroll
-        for (int t = 0; t < RPT; t += 2) {
-          const int ta = t, tb = t + 1 < RPT ? t + 1 : t;
-          const int na = wde[ta] >> 3, nb = tb != ta ? wde[tb] >> 3 : 0;
-          for (int o = 0; o < na; ++o) {
-            const int ba = bse[ta] + o * 512;
-            const float4 va0 = load_entry(reinterpret_cast<const float4*>(vals + ba), (unsigned)ln);
-            const float4 va1 =
-                load_entry(reinterpret_cast<const float4*>(vals + ba + 256), (unsigned)ln);
-            const uint4 oa = load_entry(reinterpret_cast<const uint4*>(offs + ba), (unsigned)ln);
-            float4 vb0 = make_float4(0.f, 0.f, 0.f, 0.f), vb1 = vb0;
-            uint4 ob = make_uint4(0u, 0u, 0u, 0u);
-            const bool hb = o < nb;
-            if (hb) {
-              const int bb = bse[tb] + o * 512;
-              vb0 = load_entry(reinterpret_cast<const float4*>(vals + bb), (unsigned)ln);
-              vb1 = load_entry(reinterpret_cast<const float4*>(vals + bb + 256), (unsigned)ln);
-              ob = load_entry(reinterpret_cast<const uint4*>(offs + bb), (unsigned)ln);
-            }
-            const float va[8] = {va0.x, va0.y, va0.z, va0.w, va1.x, va1.y, va1.z, va1.w};
-            const unsigned oaw[4] = {oa.x, oa.y, oa.z, oa.w};
-            cpx<T> ga[8];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              ga[2 * u] = lds_gather<T>((int)(oaw[u] & 0xffffu));
-              ga[2 * u + 1] = lds_gather<T>((int)(oaw[u] >> 16));
-            }
-            if (hb) {
-              const float vbv[8] = {vb0.x, vb0.y, vb0.z, vb0.w, vb1.x, vb1.y, vb1.z, vb1.w};
-              const unsigned obw[4] = {ob.x, ob.y, ob.z, ob.w};
-              cpx<T> gb[8];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                gb[2 * u] = lds_gather<T>((int)(obw[u] & 0xffffu));
-                gb[2 * u + 1] = lds_gather<T>((int)(obw[u] >> 16));
-              }
-#pragma unroll
-              for (int u = 0; u < 8; ++u) {
-                acc_re[tb] += vbv[u] * gb[u].re;
-                acc_im[tb] += vbv[u] * gb[u].im;
-              }
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              acc_re[ta] += va[u] * ga[u].re;
-              acc_im[ta] += va[u] * ga[u].im;
-            }
-          }
-          // remaining octs of slot tb cannot exist (widths are non-increasing
-          // within a wave); trailing quads of both slots
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const int tq = q == 0 ? ta : tb;
-            if ((q == 0 || tb != ta) && (wde[tq] & 4)) {
-              const int bq = bse[tq] + (wde[tq] >> 3) * 512;
-              const float4 v = load_entry(reinterpret_cast<const float4*>(vals + bq), (unsigned)ln);
-              const uint2 oq = load_entry(reinterpret_cast<const uint2*>(offs + bq), (unsigned)ln);
-              const cpx<T> g0 = lds_gather<T>((int)(oq.x & 0xffffu));
-              const cpx<T> g1 = lds_gather<T>((int)(oq.x >> 16));
-              const cpx<T> g2 = lds_gather<T>((int)(oq.y & 0xffffu));
-              const cpx<T> g3 = lds_gather<T>((int)(oq.y >> 16));
-              acc_re[tq] += v.x * g0.re + v.y * g1.re + v.z * g2.re + v.w * g3.re;
-              acc_im[tq] += v.x * g0.im + v.y * g1.im + v.z * g2.im + v.w * g3.im;
-            }
-          }
-        }
+        spmv_f32<RPT>(vals, offs, bse, wde, ln, acc_re, acc_im);
       } else {
         // FP64: 16-byte entries, two per lane and slot per batch, the loads
         // of all slots issued before any gather
@@ -601,6 +1085,17 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
           __syncthreads();
         }
       }
+      if constexpr (TEAM) {
+        if (!verify && team >= 0 && it >= teams.leave_at) {
+          team_leave<RPT>(teams, team, max_npad,
+                          TeamState{it, nref, nbd, lastit, rstart, span, span0, first_cycle ? 1 : 0,
+                                    rho_re, rho_im, cyc_tol2, sprev, scale, sqrt(bn2), j, ci,
+                                    (int)blockIdx.x},
+                          P, R, xr, slc, ln);
+          left = true;
+          break;
+        }
+      }
       if (!verify) continue;
 
       // ---- x_hi += x; true residual s = b - (zI - A) x_hi in FP64 ----
@@ -681,17 +1176,19 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
     }
 
     const double bn = sqrt(bn2);
+    if (!left) {
 #pragma unroll
-    for (int t = 0; t < RPT; ++t) {
-      const int slice = slc[t];
-      if (slice >= 0) {
-        const int row = perm[slice * 64 + lane];
-        const cpx<double> xh = XH[slice * 64 + lane];
-        if (row >= 0)
-          D[(unsigned)row * (unsigned)ldd + ocol] = cpx<T>{T(xh.re * bn), T(xh.im * bn)};
+      for (int t = 0; t < RPT; ++t) {
+        const int slice = slc[t];
+        if (slice >= 0) {
+          const int row = perm[slice * 64 + lane];
+          const cpx<double> xh = XH[slice * 64 + lane];
+          if (row >= 0)
+            D[(unsigned)row * (unsigned)ldd + ocol] = cpx<T>{T(xh.re * bn), T(xh.im * bn)};
+        }
       }
     }
-    if (tid == 0) {
+    if (!left && tid == 0) {
       iters[ocol] = it;
       if (resid_out) resid_out[ocol] = last_res;
       if (nref) atomicAdd(&stats[0], nref);
@@ -752,6 +1249,81 @@ std::vector<int> cocg_resident_wave_table(const std::vector<int>& widths, int rp
   return tab;
 }
 
+size_t cocg_team_ctl_words(int nteam) { return (size_t)nteam * kTeamStride; }
+size_t cocg_team_buf_words(int n, int nteam) {
+  return (size_t)nteam * (kTeamHead + 3 * (size_t)((n + 63) / 64) * 64);
+}
+
+// Inversely proportional to the logarithm of the parameter of z's Bernstein
+// ellipse, |Im acos((2 z - lo - hi) / (hi - lo))| (knn n = 8000, 4 nodes: 6.5 :
+// 1.6 : 1.5 : 1 expected, 5.7 : 1.3 : 1.5 : 1 iterations).
+double cocg_expected_steps(double zr, double zi, double lo, double hi) {
+  if (!(hi > lo)) return 1.0;
+  const std::complex<double> w((2.0 * zr - lo - hi) / (hi - lo), 2.0 * zi / (hi - lo));
+  const double rate = std::fabs(std::acos(w).imag());
+  return rate > 1e-12 ? 1.0 / rate : 1e12;
+}
+
+// The bound is steps * ln(2 / tol); the systems of the easier shifts took 0.53
+// to 0.64 of it (knn n = 8000 and 3000, 4 nodes, tol = 1e-6).
+int cocg_team_iteration(double steps, double tol) {
+  const double it = 0.64 * steps * std::log(2.0 / tol);
+  return it > 1.0 ? (it < 1e9 ? (int)it : 1000000000) : 1;
+}
+
+// The first launch ends when the systems without teams are done; those with
+// teams hold a CU each until then.  Of the shifts, hardest first, as many get
+// teams as make the two launches shortest in expected steps, if that is at
+// least a tenth shorter than without.
+int cocg_plan_teams(const std::vector<int>& items, const double* zs, double lo, double hi,
+                    int num_cu, int rpt, std::vector<int>& team_of, double& done) {
+  const int nitems = (int)items.size() / 3;
+  team_of.clear();
+  done = 0.0;
+  if (rpt != 8 || num_cu < 64 || nitems < 1 || !(hi > lo)) return 0;
+  const double speed = 1.7;  // a team's against one workgroup's
+  std::vector<double> cost(nitems);
+  for (int i = 0; i < nitems; ++i) {
+    const int j = items[3 * i + 1];
+    cost[i] = cocg_expected_steps(zs[2 * j], zs[2 * j + 1], lo, hi);
+  }
+  // when items first .. nitems - 1 are done on c CUs
+  std::vector<double> cu;
+  auto alone = [&](int first, int c) {
+    cu.assign(c, 0.0);  // a heap: the earliest free first
+    double last = 0.0;
+    for (int i = first; i < nitems; ++i) {
+      std::pop_heap(cu.begin(), cu.end(), std::greater<double>());
+      cu.back() += cost[i];
+      last = std::max(last, cu.back());
+      std::push_heap(cu.begin(), cu.end(), std::greater<double>());
+    }
+    return last;
+  };
+  double best = 0.9 * alone(0, num_cu);
+  int nteam = 0;
+  for (int t = 0; t < nitems; ++t) {
+    // teams for items 0 .. t, whole shifts
+    if (t + 1 < nitems && items[3 * (t + 1) + 1] == items[3 * t + 1]) continue;
+    if (t + 1 > num_cu / 2) break;
+    const double first = alone(t + 1, num_cu - (t + 1));
+    const int at_once = num_cu / kTeamSize, rounds = (t + at_once) / at_once;
+    double second = 0.0;
+    for (int r = 0; r < rounds; ++r)
+      second += std::max(0.0, cost[r * at_once] - first) / speed;
+    if (first + second < best) {
+      best = first + second;
+      nteam = t + 1;
+      done = first;
+    }
+  }
+  if (nteam > 0) {
+    team_of.assign(nitems, -1);
+    for (int i = 0; i < nteam; ++i) team_of[i] = i;
+  }
+  return nteam;
+}
+
 size_t cocg_resident_lds(int n, bool fp32) {
   const size_t nsl = (size_t)(n + 63) / 64;
   // p and r, the zero and trash rows, the reduction slots, the work item
@@ -759,10 +1331,10 @@ size_t cocg_resident_lds(int n, bool fp32) {
          2 * kResWaves * 4 * sizeof(double) + 16;
 }
 
-template <typename T, int RPT, bool MULTI>
+template <typename T, int RPT, bool MULTI, bool TEAM>
 static hipError_t launch_res(hipStream_t st, const ResGraph& g0, const ResGraph* graphs, int max_n,
                              const CocgLaunch& L, int blocks) {
-  auto kern = k_cocg_resident<T, RPT, MULTI>;
+  auto kern = k_cocg_resident<T, RPT, MULTI, TEAM>;
   // the gathers address LDS absolutely: the kernel must own no static LDS
   hipFuncAttributes fa;
   hipError_t fe = hipFuncGetAttributes(&fa, (const void*)kern);
@@ -778,14 +1350,34 @@ static hipError_t launch_res(hipStream_t st, const ResGraph& g0, const ResGraph*
                      g0.kcols, g0.D, g0.ldd, L.tol, L.maxit, L.max_refine, L.counter, g0.iters,
                      g0.stats,
                      g0.resid, (cpx<double>*)L.xhi, g0.zero_base, g0.wave_slices, graphs,
-                     max_npad);
+                     max_npad, L.teams);
+  return hipGetLastError();
+}
+
+// The second launch: the systems that the first left to teams.
+template <int RPT>
+static hipError_t launch_team(hipStream_t st, const ResGraph& g0, int max_n, const CocgLaunch& L) {
+  auto kern = k_cocg_team<RPT>;
+  hipFuncAttributes fa;
+  hipError_t e = hipFuncGetAttributes(&fa, (const void*)kern);
+  if (e != hipSuccess) return e;
+  if (fa.sharedSizeBytes != 0) return hipErrorInvalidKernelFile;
+  const int npad = (max_n + 63) / 64 * 64;
+  const size_t lds =
+      (size_t)(npad + 128) * sizeof(cpx<float>) + 2 * kResWaves * 4 * sizeof(double);
+  e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  ResGraph g = g0;
+  g.tol = L.tol;
+  hipLaunchKernelGGL(kern, dim3((L.teams.nteam + 7) / 8 * 32), dim3(kResThreads), lds, st, L.teams,
+                     g, npad, L.maxit, L.max_refine, (cpx<double>*)L.xhi);
   return hipGetLastError();
 }
 
 template <typename T, int RPT, bool MULTI>
 static hipError_t prepare_res(int max_n) {
   const size_t lds = cocg_resident_lds(max_n, sizeof(T) == 4);
-  return hipFuncSetAttribute((const void*)k_cocg_resident<T, RPT, MULTI>,
+  return hipFuncSetAttribute((const void*)k_cocg_resident<T, RPT, MULTI, false>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
@@ -807,8 +1399,14 @@ hipError_t prepare_cocg_resident(int max_n, int rpt, bool fp32) {
 template <typename T, int RPT>
 static hipError_t launch_res2(hipStream_t st, const ResGraph* g0, const ResGraph* graphs,
                               int max_n, const CocgLaunch& L, int blocks) {
-  if (g0) return launch_res<T, RPT, false>(st, *g0, nullptr, max_n, L, blocks);
-  return launch_res<T, RPT, true>(st, ResGraph{}, graphs, max_n, L, blocks);
+  if constexpr (sizeof(T) == 4 && RPT == 8)
+    if (g0 && L.teams.nteam > 0) {
+      const hipError_t e = launch_res<T, RPT, false, true>(st, *g0, nullptr, max_n, L, blocks);
+      return e != hipSuccess ? e : launch_team<RPT>(st, *g0, max_n, L);
+    }
+  if (L.teams.nteam > 0) return hipErrorInvalidValue;
+  if (g0) return launch_res<T, RPT, false, false>(st, *g0, nullptr, max_n, L, blocks);
+  return launch_res<T, RPT, true, false>(st, ResGraph{}, graphs, max_n, L, blocks);
 }
 
 hipError_t launch_cocg_resident(hipStream_t st, const ResGraph* g0, const ResGraph* graphs,

@@ -152,6 +152,29 @@ struct ResGraph {
   double tol = 0.0;                     // relative residual tolerance of this graph's systems
 };
 
+// Teams of the resident engine (one graph, FP32, eight slots a thread):
+// the systems that are expected to run long after the others are continued by
+// four workgroups each from iteration leave_at on.
+constexpr int kTeamSize = 4;
+struct CocgTeams {
+  int nteam = 0;                      // 0: none
+  const int* team_of = nullptr;       // [nitems] team of an item (-1: none)
+  int leave_at = 0;                   // iteration
+  unsigned long long* ctl = nullptr;  // cocg_team_ctl_words(nteam) words, zero at the launch
+  unsigned long long* buf = nullptr;  // cocg_team_buf_words(max_n, nteam) words
+};
+size_t cocg_team_ctl_words(int nteam);
+size_t cocg_team_buf_words(int n, int nteam);
+// Steps that a Krylov method needs for z outside [lo, hi], up to a factor.
+double cocg_expected_steps(double zr, double zi, double lo, double hi);
+// Teams for the items (3 ints each, longest shift first) of shifts zs of a
+// matrix with its spectrum in [lo, hi], on num_cu CUs: team_of (empty: none),
+// and in expected steps when the others are done.  Returns the number of teams.
+int cocg_plan_teams(const std::vector<int>& items, const double* zs, double lo, double hi,
+                    int num_cu, int rpt, std::vector<int>& team_of, double& done);
+// The iteration that is expected after `steps` of a solve to tolerance tol.
+int cocg_team_iteration(double steps, double tol);
+
 struct CocgLaunch {
   int nitems = 0;
   const int* items = nullptr;   // [3*nitems] (graph g, shift j, column i), longest first
@@ -161,6 +184,7 @@ struct CocgLaunch {
   int* counter = nullptr;       // zeroed work counter
   void* xhi = nullptr;          // FP64 complex solution scratch, xhi_slots entries
   size_t xhi_slots = 0;         // >= blocks * (max_n rounded up to 64)
+  CocgTeams teams;
 };
 
 // FP64 scratch entries (complex) the resident engine needs for `blocks` workgroups.

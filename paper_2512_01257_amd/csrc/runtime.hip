@@ -160,7 +160,8 @@ struct rafeast_plan_s {
   double* d_part = nullptr;
   size_t part_doubles = 0;
   void* d_D = nullptr;       // n x (nc m0) complex
-  int* d_items = nullptr;    // 2 nc m0
+  int* d_items = nullptr;    // 3 nc m0
+  std::vector<int> h_items;  // the same
   int* d_counter = nullptr;  // 1
   int* d_iters = nullptr;    // nc m0
   int* d_stats = nullptr;    // 2
@@ -168,6 +169,12 @@ struct rafeast_plan_s {
   int* d_sel = nullptr;      // m0
   void* d_xhi = nullptr;     // FP64 solution scratch of the resident COCG engine
   size_t xhi_slots = 0;
+  // teams of the resident engine for a solve's systems (nteam 0: none); plans
+  // whose slot layout is forced never have any
+  bool teams_ok = true;
+  int nteam = 0;
+  double team_done = 0.0;    // expected steps of the systems without teams
+  int* d_team_of = nullptr;
   std::vector<int> sell_widths; // slice widths, for wave tables of other slot counts
   // autotuned launch shape (resident engine: slots per thread), candidates
   // and their measured times
@@ -542,7 +549,7 @@ void free_plan(rafeast_plan_s* P) {
                   P->d_G,      P->d_M,    P->d_S,     P->d_Ssel,  P->d_jw,   P->d_theta,
                   P->d_res,    P->d_qn,   P->d_gamma, P->d_info,  P->d_zw,   P->d_part,
                   P->d_D,      P->d_items, P->d_counter, P->d_iters, P->d_stats, P->d_flag,
-                  P->d_sel, P->d_xhi, P->d_srow, P->d_scol, P->d_sv32, P->d_sv64, P->d_sperm,
+                  P->d_sel, P->d_xhi, P->d_team_of, P->d_srow, P->d_scol, P->d_sv32, P->d_sv64, P->d_sperm,
                   P->d_k64, P->d_k32, P->d_t64, P->d_t32,
                   P->d_mtot, P->d_mtmp, P->d_pcW, P->d_pcWb, P->d_pcX, P->d_pcY, P->d_D64,
                   P->d_wrep, P->d_band, P->d_binfo};
@@ -996,7 +1003,8 @@ ResGraph resident_graph(const rafeast_plan_s* P, const double* d_zs, int k, cons
 // COCG over items (0, j, i) of the given shift table; outputs into D.
 rafeast_status run_cocg(rafeast_plan_s* P, int nitems, const int* d_items, const double* d_zs,
                         int k, const double* B, int ldb, void* D, int ldd, double tol,
-                        int* d_iters, double* d_resid = nullptr) {
+                        int* d_iters, double* d_resid, int nteam, const int* d_team_of,
+                        double team_done) {
   // 32-bit indexing of the RHS and output blocks inside the kernel
   if (P->n * (int64_t)ldb >= (int64_t(1) << 31) || P->n * (int64_t)ldd >= (int64_t(1) << 31))
     return fail(P, RAFEAST_UNSUPPORTED, "blocks too large for the resident engine");
@@ -1011,6 +1019,24 @@ rafeast_status run_cocg(rafeast_plan_s* P, int nitems, const int* d_items, const
   L.counter = P->d_counter;
   L.xhi = P->d_xhi;
   L.xhi_slots = P->xhi_slots;
+  DevBuf team_work(P);  // back to the plan's cache at the end: stream-ordered
+  if (nteam > 0) {
+    unsigned long long* ctl = nullptr;
+    unsigned long long* buf = nullptr;
+    hipError_t e = team_work.get(&ctl, cocg_team_ctl_words(nteam));
+    if (e == hipSuccess) e = team_work.get(&buf, cocg_team_buf_words((int)P->n, nteam));
+    if (e != hipSuccess) {
+      (void)hipGetLastError();  // no room: every system by one workgroup
+    } else {
+      L.teams.nteam = nteam;
+      L.teams.team_of = d_team_of;
+      L.teams.leave_at = cocg_team_iteration(team_done, tol);
+      L.teams.ctl = ctl;
+      L.teams.buf = buf;
+      HIPCHK(P, launch_fill_int(P->st, reinterpret_cast<int*>(ctl), 0,
+                                2 * (int)cocg_team_ctl_words(nteam)));
+    }
+  }
   HIPCHK(P, hipMemsetAsync(P->d_counter, 0, sizeof(int), P->st));
   HIPCHK(P, launch_cocg_resident(P->st, &gd, nullptr, (int)P->n, P->sell.wave_rpt, L, P->fp32,
                                  P->num_cu));
@@ -1110,18 +1136,19 @@ rafeast_status band_factor_shifts(rafeast_plan_s* P) {
   return RAFEAST_OK;
 }
 
-// Orders (shift, column) pairs longest-first: the smaller Im z, the more COCG
-// iterations a system needs.
-std::vector<int> make_items(int nz, const double* zs, int k, int g = 0) {
+// Orders (shift, column) pairs longest-first by the steps expected with the
+// spectrum in [lo, hi].
+std::vector<int> make_items(int nz, const double* zs, int k, double lo, double hi) {
   std::vector<int> js(nz);
   for (int j = 0; j < nz; ++j) js[j] = j;
-  std::stable_sort(js.begin(), js.end(),
-                   [&](int a, int b) { return std::fabs(zs[2 * a + 1]) < std::fabs(zs[2 * b + 1]); });
+  std::vector<double> steps(nz);
+  for (int j = 0; j < nz; ++j) steps[j] = cocg_expected_steps(zs[2 * j], zs[2 * j + 1], lo, hi);
+  std::stable_sort(js.begin(), js.end(), [&](int a, int b) { return steps[a] > steps[b]; });
   std::vector<int> items;
   items.reserve(3 * (size_t)nz * k);
   for (int j : js)
     for (int i = 0; i < k; ++i) {
-      items.push_back(g);
+      items.push_back(0);
       items.push_back(j);
       items.push_back(i);
     }
@@ -1431,7 +1458,8 @@ rafeast_status solve_shifted_systems(rafeast_plan_s* P, SolveRun& S) {
     return run_stream(P, P->swork, nc, m0, residual_form ? P->d_R : P->d_Q, ld, P->d_D, nc * m0,
                       P->tau, P->d_iters);
   return run_cocg(P, P->nitems, P->d_items, P->d_zw, m0, residual_form ? P->d_R : P->d_Q, ld,
-                  P->d_D, nc * m0, P->tau, P->d_iters);
+                  P->d_D, nc * m0, P->tau, P->d_iters, nullptr, P->nteam, P->d_team_of,
+                  P->team_done);
 }
 
 // After the solves (between events ev[2] and ev[3]): combination
@@ -1599,8 +1627,8 @@ void rafeast_destroy(rafeast_plan_t plan) { free_plan(plan); }
 // launch and then the best of two timed ones; the fastest count wins (ties
 // to fewer slots).  RAFEAST_TUNE=0 keeps the smallest count;
 // RAFEAST_RESIDENT_SLOTS=r takes candidate r untimed (plan creation fails if
-// r is not a candidate), so that two plans can be given the same layout and
-// hence the same summation order.
+// r is not a candidate) and gives no system a team, so that two plans can be
+// given the same layout and hence the same summation order.
 rafeast_status tune_resident(rafeast_plan_s* P) {
   const int maxr = P->fp32 ? 8 : 4;
   std::vector<std::vector<int>> tabs;
@@ -1625,6 +1653,7 @@ rafeast_status tune_resident(rafeast_plan_s* P) {
     HIPCHK(P, hipStreamSynchronize(P->st));
     P->tune_choice = P->tune_cand[c];
     P->sell.wave_rpt = P->tune_choice;
+    P->teams_ok = false;
     return RAFEAST_OK;
   }
   const char* env = std::getenv("RAFEAST_TUNE");
@@ -2182,10 +2211,22 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   }
   PCHK(hipMemcpy(P->d_zw, P->zw.data(), 4 * P->nc * sizeof(double), hipMemcpyHostToDevice));
   {
-    std::vector<int> items = make_items(P->nc, P->zw.data(), P->m0);
+    std::vector<int> items =
+        make_items(P->nc, P->zw.data(), P->m0, P->sig_lo, P->sig_hi);
+    P->h_items = items;
     PCHK(hipMemcpy(P->d_items, items.data(), items.size() * sizeof(int), hipMemcpyHostToDevice));
   }
-  if (P->engine == RAFEAST_ENGINE_RESIDENT) PRCHK(tune_resident(P));
+  if (P->engine == RAFEAST_ENGINE_RESIDENT) {
+    PRCHK(tune_resident(P));
+    std::vector<int> of;
+    if (P->teams_ok && P->fp32)
+      P->nteam = cocg_plan_teams(P->h_items, P->zw.data(), P->sig_lo, P->sig_hi, P->num_cu,
+                                 P->sell.wave_rpt, of, P->team_done);
+    if (P->nteam > 0) {
+      PRCHK(dalloc(P, &P->d_team_of, of.size(), "teams"));
+      PCHK(hipMemcpy(P->d_team_of, of.data(), of.size() * sizeof(int), hipMemcpyHostToDevice));
+    }
+  }
   if (P->engine == RAFEAST_ENGINE_DIRECT) PRCHK(band_factor_shifts(P));
   PCHK(hipMemset(P->d_stats, 0, 2 * sizeof(int)));
   PCHK(hipDeviceSynchronize());
@@ -2546,7 +2587,7 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
   int* d_items = nullptr;
   int* d_it = nullptr;
   double* d_rs = nullptr;
-  std::vector<int> items = make_items(nz, z, k);
+  std::vector<int> items = make_items(nz, z, k, P->sig_lo, P->sig_hi);
   const int nitems = nz * k;
   rafeast_status s = RAFEAST_OK;
   hipError_t e = buf.get(&d_z, 2 * (size_t)nz);
@@ -2634,7 +2675,27 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
       }
     } else {
-      s = run_cocg(P, nitems, d_items, d_z, k, B, ldb, X, nz * k, tol, d_it, d_rs);
+      std::vector<int> of;
+      double done = 0.0;
+      int* d_of = nullptr;
+      int nteam = 0;
+      if (P->teams_ok && P->fp32)
+        nteam = cocg_plan_teams(items, z, P->sig_lo, P->sig_hi, P->num_cu, P->sell.wave_rpt, of,
+                                done);
+      if (nteam > 0) {
+        e = buf.get(&d_of, of.size());
+        if (e == hipSuccess)
+          e = hipMemcpyAsync(d_of, of.data(), of.size() * sizeof(int), hipMemcpyHostToDevice,
+                             P->st);
+        if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve teams");
+      }
+      if (s == RAFEAST_OK)
+        s = run_cocg(P, nitems, d_items, d_z, k, B, ldb, X, nz * k, tol, d_it, d_rs, nteam, d_of,
+                     done);
+      if (s == RAFEAST_OK) {  // `of` is still being read
+        e = hipStreamSynchronize(P->st);
+        if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
+      }
     }
     if (s == RAFEAST_OK && iters) {
       e = hipMemcpyAsync(iters, d_it, nitems * sizeof(int), hipMemcpyDeviceToHost, P->st);
