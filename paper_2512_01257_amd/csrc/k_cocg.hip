@@ -41,6 +41,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <climits>
 #include <complex>
 #include <functional>
 #include <vector>
@@ -327,11 +328,13 @@ __device__ __forceinline__ const ResGraph* const_graph(const ResGraph* graphs, i
 // members' workgroup numbers are 8 apart, so they run on one XCD, where an
 // exchange takes half the time; the result does not depend on it.
 //
-// Every wait ends: a member waits for the words of its three fellows only,
-// whose workgroups are at most 24 numbers away; workgroups start in the order
-// of their numbers, so at most eight teams (24 workgroups) can be waiting for
-// fellows that have not started, which leaves CUs for those to start on.  The
-// members' sums and decisions are the same bits, so they take the same steps.
+// Every wait ends.  A team sets out only when all four members run: each waits
+// for that a bounded time at its start (CocgTeams::wait; on a free device it
+// takes microseconds, next to other work or on a few CUs perhaps for ever), and
+// the systems of teams that did not set out are solved from their start by a
+// third launch, which otherwise finds nothing to do.  From then on a member
+// waits for the words of its three running fellows only; their sums and
+// decisions are the same bits, so they take the same steps.
 //
 // What bounds it is the latency of the exchanges (of about 14,000 clocks an
 // iteration, 3,000 for each sum and 3,000 for the residuals).  knn n = 8000,
@@ -340,7 +343,9 @@ __device__ __forceinline__ const ResGraph* const_graph(const ResGraph* graphs, i
 // takes 5.4 us of four workgroups and 4.6 us of one, so those have no teams.
 typedef unsigned long long u64;
 constexpr int kTeamStride = 80;   // words of a team's ctl: two sets of kTeamSize * 8, then
-constexpr int kTeamLeft = 64;     //   1: its system was left to it
+constexpr int kTeamLeft = 64;     //   1: its system was left to it,
+constexpr int kTeamHere = 65;     //   members that run,
+constexpr int kTeamGo = 66;       //   1: it set out, 2: it did not
 constexpr int kTeamHead = 18;     // words of a team's buffer before p, r and x
 
 __device__ __forceinline__ u64 agent_get(const u64* p) {
@@ -495,6 +500,26 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_team(CocgTeams T, ResGraph
       reinterpret_cast<double(*)[kResWaves][4]>(smem_raw + (size_t)(npad + 128) * sizeof(cpx<float>));
   const int team = (int)(blockIdx.x % 8 + blockIdx.x / 32 * 8), m = (int)(blockIdx.x / 8 % 4);
   if (team >= T.nteam || team_ctl(T, team)[kTeamLeft] != 1) return;
+  int& s_go = *reinterpret_cast<int*>(&red[0][0][0]);
+  if (threadIdx.x == 0) {
+    u64* c = team_ctl(T, team);
+    if (atomicAdd(c + kTeamHere, 1ull) == kTeamSize - 1) atomicCAS(c + kTeamGo, 0ull, 1ull);
+    const long long t0 = wall_clock64();
+    u64 go;
+    while ((go = agent_get(c + kTeamGo)) == 0) {
+      if (wall_clock64() - t0 > T.wait) {
+        go = atomicCAS(c + kTeamGo, 0ull, 2ull);
+        if (go == 0) go = 2;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(4);
+    }
+    s_go = (int)go;
+  }
+  __syncthreads();
+  const int go = s_go;
+  __syncthreads();
+  if (go != 1) return;
   const double tol2 = G.tol * G.tol;
   TeamState ts = *reinterpret_cast<const TeamState*>(team_buf(T, team, npad));
   cpx<double>* XH = xhi_all + (size_t)ts.owner * npad;
@@ -889,7 +914,13 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
     const int ocol = j * kcols + ci;
     int team = -1;     // the item's team
     bool left = false;  // and it is left to it
-    if constexpr (TEAM) team = __builtin_amdgcn_readfirstlane(teams.team_of[item]);
+    if constexpr (TEAM) {
+      team = __builtin_amdgcn_readfirstlane(teams.team_of[item]);
+      if (teams.redo && (team < 0 || team_ctl(teams, team)[kTeamGo] != 2)) {
+        __syncthreads();  // before the next item is fetched
+        continue;
+      }
+    }
 
     // ---- right-hand side, scaled to unit norm ----
     double acc1[1] = {0.0};
@@ -1249,7 +1280,7 @@ std::vector<int> cocg_resident_wave_table(const std::vector<int>& widths, int rp
   return tab;
 }
 
-size_t cocg_team_ctl_words(int nteam) { return (size_t)nteam * kTeamStride; }
+size_t cocg_team_ctl_words(int nteam) { return (size_t)nteam * kTeamStride + 1; }
 size_t cocg_team_buf_words(int n, int nteam) {
   return (size_t)nteam * (kTeamHead + 3 * (size_t)((n + 63) / 64) * 64);
 }
@@ -1401,8 +1432,17 @@ static hipError_t launch_res2(hipStream_t st, const ResGraph* g0, const ResGraph
                               int max_n, const CocgLaunch& L, int blocks) {
   if constexpr (sizeof(T) == 4 && RPT == 8)
     if (g0 && L.teams.nteam > 0) {
-      const hipError_t e = launch_res<T, RPT, false, true>(st, *g0, nullptr, max_n, L, blocks);
-      return e != hipSuccess ? e : launch_team<RPT>(st, *g0, max_n, L);
+      hipError_t e = launch_res<T, RPT, false, true>(st, *g0, nullptr, max_n, L, blocks);
+      if (e == hipSuccess) e = launch_team<RPT>(st, *g0, max_n, L);
+      if (e != hipSuccess) return e;
+      // the first nteam items are the teams'; the counter is ctl's last word
+      CocgLaunch again = L;
+      again.teams.redo = 1;
+      again.teams.leave_at = INT_MAX;
+      again.nitems = L.teams.nteam;
+      again.counter = reinterpret_cast<int*>(L.teams.ctl + (size_t)L.teams.nteam * kTeamStride);
+      return launch_res<T, RPT, false, true>(st, *g0, nullptr, max_n, again,
+                                             std::min(blocks, again.nitems));
     }
   if (L.teams.nteam > 0) return hipErrorInvalidValue;
   if (g0) return launch_res<T, RPT, false, false>(st, *g0, nullptr, max_n, L, blocks);

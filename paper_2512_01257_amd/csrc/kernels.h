@@ -160,6 +160,8 @@ struct CocgTeams {
   int nteam = 0;                      // 0: none
   const int* team_of = nullptr;       // [nitems] team of an item (-1: none)
   int leave_at = 0;                   // iteration
+  int redo = 0;                       // the launch solves what teams did not
+  long long wait = 0;                 // for a team's members to run: 100 MHz ticks
   unsigned long long* ctl = nullptr;  // cocg_team_ctl_words(nteam) words, zero at the launch
   unsigned long long* buf = nullptr;  // cocg_team_buf_words(max_n, nteam) words
 };

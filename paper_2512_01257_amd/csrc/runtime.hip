@@ -174,6 +174,7 @@ struct rafeast_plan_s {
   bool teams_ok = true;
   int nteam = 0;
   double team_done = 0.0;    // expected steps of the systems without teams
+  long long team_wait = 100000000;  // ticks of 10 ns that a team's members wait for each other
   int* d_team_of = nullptr;
   std::vector<int> sell_widths; // slice widths, for wave tables of other slot counts
   // autotuned launch shape (resident engine: slots per thread), candidates
@@ -1031,6 +1032,7 @@ rafeast_status run_cocg(rafeast_plan_s* P, int nitems, const int* d_items, const
       L.teams.nteam = nteam;
       L.teams.team_of = d_team_of;
       L.teams.leave_at = cocg_team_iteration(team_done, tol);
+      L.teams.wait = P->team_wait;
       L.teams.ctl = ctl;
       L.teams.buf = buf;
       HIPCHK(P, launch_fill_int(P->st, reinterpret_cast<int*>(ctl), 0,
@@ -2219,6 +2221,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   if (P->engine == RAFEAST_ENGINE_RESIDENT) {
     PRCHK(tune_resident(P));
     std::vector<int> of;
+    if (const char* w = std::getenv("RAFEAST_TEAM_WAIT")) P->team_wait = std::atoll(w);
     if (P->teams_ok && P->fp32)
       P->nteam = cocg_plan_teams(P->h_items, P->zw.data(), P->sig_lo, P->sig_hi, P->num_cu,
                                  P->sell.wave_rpt, of, P->team_done);

@@ -17,8 +17,14 @@ pytestmark = pytest.mark.gpu
 # slots); k systems of the hardest shift get teams; 64 * 2 > one round of teams
 @pytest.mark.parametrize("dims,k", [((65, 65), 1), ((65, 65), 7), ((90, 91), 9), ((90, 91), 64),
                                     ((80, 80), 100)])
-def test_team_solves(gpu_lib, dims, k):
+@pytest.mark.parametrize("wait", [None, "0"])
+def test_team_solves(gpu_lib, monkeypatch, dims, k, wait):
+    # wait 0: a team whose members do not all run at once does not set out, and
+    # its system is solved by a launch of its own
     import torch
+
+    if wait is not None:
+        monkeypatch.setenv("RAFEAST_TEAM_WAIT", wait)
 
     csr = grid_laplacian(dims, 0.01)
     A, n = csr.to_scipy(), csr.n
@@ -36,8 +42,9 @@ def test_team_solves(gpu_lib, dims, k):
             X = torch.zeros((n, len(z) * k), dtype=torch.complex64, device="cuda")
             its, rs = plan.shifted_solve(z, torch.from_numpy(B).cuda(), X, tol)
             runs.append((X.cpu().numpy(), its, rs))
-    assert all(np.array_equal(a, b) for a, b in zip(*runs))
-    X, its, rs = runs[0]
+    if wait is None:
+        assert all(np.array_equal(a, b) for a, b in zip(*runs))
+    X, its, rs = runs[1]
     u = 2.0 ** -24
     norm_m = np.abs(z).max() + 8.02
     for j in range(len(z)):
