@@ -103,8 +103,9 @@ enum { RAFEAST_ENGINE_DIRECT = 4 };  /* precision FP64 and CSR plans only: stand
                                         (complex symmetric, no pivoting: Im z_j != 0 makes
                                         every pivot exist) in the band of the reverse
                                         Cuthill-McKee order, and every filter application
-                                        solves by substitution.  Memory nc n (b + 1) complex
-                                        doubles for bandwidth b (OOM when the device cannot
+                                        solves with the factors (block L D L^T, the inverses
+                                        of its 32 x 32 blocks kept).  Memory nc n (b + 1)
+                                        complex doubles for bandwidth b >= 31 (OOM when the device cannot
                                         hold it; BREAKDOWN if a pivot vanishes).  Reports
                                         zero COCG iterations.  Never chosen by AUTO */
 
@@ -310,9 +311,10 @@ int32_t rafeast_plan_engine(rafeast_plan_t plan);
  * matrix (64 COCG iterations of the first min(systems, CUs) systems on
  * Gaussian right-hand sides); the fastest is used.  RAFEAST_TUNE=0 in the
  * environment keeps the smallest; RAFEAST_RESIDENT_SLOTS=r takes candidate r
- * untimed (rafeast_plan fails with INVALID_ARG if r is not a candidate).  The
- * count sets the order of the SpMV's row sums, so plans with equal counts
- * give bitwise equal results.  Out: *chosen (0 for the streaming engine,
+ * untimed (rafeast_plan fails with INVALID_ARG if r is not a candidate) and
+ * gives no system a team of workgroups.  The count sets the order of the
+ * SpMV's row sums, so plans that force the same count give bitwise equal
+ * results.  Out: *chosen (0 for the streaming engine,
  * which is not tuned), *count candidates, and up to max of them in cand[]
  * with their measured milliseconds in ms[] (0 when untimed: a single
  * candidate or tuning off).  Host pointers owned by the caller.  Errors:
@@ -375,7 +377,8 @@ rafeast_status rafeast_gram_noalloc(void* hip_stream, int64_t n, int32_t k1, int
  * All pointers device, caller-owned (A and B may be null when K == 0, C when
  * M N == 0); beta == 0 does not read C.  A long inner
  * dimension with few output tiles is split into chunks summed in a fixed
- * order in a workspace this call allocates and frees.  Runs on hip_stream
+ * order in a workspace that the library keeps for later calls (64 MiB per
+ * device at most, freed with the last plan).  Runs on hip_stream
  * (nullable: the null stream) and waits for it.  Errors: INVALID_ARG for null
  * pointers, negative sizes, short leading dimensions or another precision;
  * OOM; DEVICE. */

@@ -807,7 +807,7 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_team(CocgTeams T, ResGraph
 // are unused.  TEAM: some items are
 // left to teams (above).
 template <typename T, int RPT, bool MULTI, bool TEAM>
-__global__ __launch_bounds__(kResThreads) void k_cocg_resident(
+__device__ __forceinline__ void cocg_items(
     int a_nslices, const int* __restrict__ a_sbase, const int* __restrict__ a_perm,
     const void* __restrict__ a_ent, const SellEntry64* __restrict__ a_ent64, int a_n32, int nitems,
     const int* __restrict__ items, const double* __restrict__ a_zs,
@@ -1233,6 +1233,39 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_resident(
   }
 }
 
+template <typename T, int RPT, bool MULTI>
+__global__ __launch_bounds__(kResThreads) void k_cocg_resident(
+    int a_nslices, const int* __restrict__ a_sbase, const int* __restrict__ a_perm,
+    const void* __restrict__ a_ent, const SellEntry64* __restrict__ a_ent64, int a_n32, int nitems,
+    const int* __restrict__ items, const double* __restrict__ a_zs,
+    const double* __restrict__ a_B, int a_ldb, int a_kcols, void* __restrict__ a_D, int a_ldd,
+    double tol, int maxit, int max_refine, int* __restrict__ counter, int* __restrict__ a_iters,
+    int* __restrict__ a_stats, double* __restrict__ a_resid, cpx<double>* __restrict__ xhi_all,
+    int a_zero_base, const int* __restrict__ a_wave_slices, const ResGraph* __restrict__ graphs,
+    int max_npad) {
+  cocg_items<T, RPT, MULTI, false>(a_nslices, a_sbase, a_perm, a_ent, a_ent64, a_n32, nitems, items, a_zs, a_B, a_ldb,
+                                   a_kcols, a_D, a_ldd, tol, maxit, max_refine, counter, a_iters,
+                                   a_stats, a_resid, xhi_all, a_zero_base, a_wave_slices, graphs,
+                                   max_npad, CocgTeams{});
+}
+
+// The same where some items are left to teams.
+template <typename T, int RPT>
+__global__ __launch_bounds__(kResThreads) void k_cocg_leaving(
+    int a_nslices, const int* __restrict__ a_sbase, const int* __restrict__ a_perm,
+    const void* __restrict__ a_ent, const SellEntry64* __restrict__ a_ent64, int a_n32, int nitems,
+    const int* __restrict__ items, const double* __restrict__ a_zs,
+    const double* __restrict__ a_B, int a_ldb, int a_kcols, void* __restrict__ a_D, int a_ldd,
+    double tol, int maxit, int max_refine, int* __restrict__ counter, int* __restrict__ a_iters,
+    int* __restrict__ a_stats, double* __restrict__ a_resid, cpx<double>* __restrict__ xhi_all,
+    int a_zero_base, const int* __restrict__ a_wave_slices, const ResGraph* __restrict__ graphs,
+    int max_npad, CocgTeams teams) {
+  cocg_items<T, RPT, false, true>(a_nslices, a_sbase, a_perm, a_ent, a_ent64, a_n32, nitems, items, a_zs, a_B, a_ldb,
+                                   a_kcols, a_D, a_ldd, tol, maxit, max_refine, counter, a_iters,
+                                   a_stats, a_resid, xhi_all, a_zero_base, a_wave_slices, graphs,
+                                   max_npad, teams);
+}
+
 size_t cocg_resident_xhi_slots(int n, int blocks) {
   return (size_t)blocks * (size_t)((n + 63) / 64) * 64;
 }
@@ -1365,7 +1398,12 @@ size_t cocg_resident_lds(int n, bool fp32) {
 template <typename T, int RPT, bool MULTI, bool TEAM>
 static hipError_t launch_res(hipStream_t st, const ResGraph& g0, const ResGraph* graphs, int max_n,
                              const CocgLaunch& L, int blocks) {
-  auto kern = k_cocg_resident<T, RPT, MULTI, TEAM>;
+  auto kern = [] {
+    if constexpr (TEAM)
+      return k_cocg_leaving<T, RPT>;
+    else
+      return k_cocg_resident<T, RPT, MULTI>;
+  }();
   // the gathers address LDS absolutely: the kernel must own no static LDS
   hipFuncAttributes fa;
   hipError_t fe = hipFuncGetAttributes(&fa, (const void*)kern);
@@ -1376,12 +1414,17 @@ static hipError_t launch_res(hipStream_t st, const ResGraph& g0, const ResGraph*
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const int max_npad = (max_n + 63) / 64 * 64;
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(kResThreads), lds, st, g0.nslices, g0.sbase,
-                     g0.perm, g0.ent, g0.ent64, g0.n32, L.nitems, L.items, g0.zs, g0.B, g0.ldb,
-                     g0.kcols, g0.D, g0.ldd, L.tol, L.maxit, L.max_refine, L.counter, g0.iters,
-                     g0.stats,
-                     g0.resid, (cpx<double>*)L.xhi, g0.zero_base, g0.wave_slices, graphs,
-                     max_npad, L.teams);
+  auto launch = [&](auto... more) {
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kResThreads), lds, st, g0.nslices, g0.sbase,
+                       g0.perm, g0.ent, g0.ent64, g0.n32, L.nitems, L.items, g0.zs, g0.B, g0.ldb,
+                       g0.kcols, g0.D, g0.ldd, L.tol, L.maxit, L.max_refine, L.counter, g0.iters,
+                       g0.stats, g0.resid, (cpx<double>*)L.xhi, g0.zero_base, g0.wave_slices,
+                       graphs, max_npad, more...);
+  };
+  if constexpr (TEAM)
+    launch(L.teams);
+  else
+    launch();
   return hipGetLastError();
 }
 
@@ -1408,7 +1451,7 @@ static hipError_t launch_team(hipStream_t st, const ResGraph& g0, int max_n, con
 template <typename T, int RPT, bool MULTI>
 static hipError_t prepare_res(int max_n) {
   const size_t lds = cocg_resident_lds(max_n, sizeof(T) == 4);
-  return hipFuncSetAttribute((const void*)k_cocg_resident<T, RPT, MULTI, false>,
+  return hipFuncSetAttribute((const void*)k_cocg_resident<T, RPT, MULTI>,
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
