@@ -346,7 +346,7 @@ constexpr int kTeamStride = 80;   // words of a team's ctl: two sets of kTeamSiz
 constexpr int kTeamLeft = 64;     //   1: its system was left to it,
 constexpr int kTeamHere = 65;     //   members that run,
 constexpr int kTeamGo = 66;       //   1: it set out, 2: it did not
-constexpr int kTeamHead = 18;     // words of a team's buffer before p, r and x
+constexpr int kTeamHead = 18;     // words of a team's buffer before p, r, x and x_hi
 
 __device__ __forceinline__ u64 agent_get(const u64* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -372,14 +372,14 @@ __device__ __forceinline__ u64* team_ctl(const CocgTeams& T, int t) {
   return T.ctl + (size_t)t * kTeamStride;
 }
 __device__ __forceinline__ u64* team_buf(const CocgTeams& T, int t, int npad) {
-  return T.buf + (size_t)t * (kTeamHead + 3 * (size_t)npad);
+  return T.buf + (size_t)t * (kTeamHead + 5 * (size_t)npad);
 }
 
 // A system's state, as in the solve of one workgroup.
 struct TeamState {
   int it, nref, nbd, lastit, rstart, span, span0, first_cycle;
   double rho_re, rho_im, cyc_tol2, sprev, scale, bn;
-  int j, ci, owner;  // the item; the workgroup whose x_hi buffer it uses
+  int j, ci;  // the item
 };
 
 // Slot h of member m: the widest with the narrowest.
@@ -463,15 +463,17 @@ __device__ __forceinline__ E* at32(E* base, unsigned i) {
   return reinterpret_cast<E*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(E));
 }
 
-// Leaves a system to its team: scalars, p, r, x (x_hi is in the workgroup's
-// global buffer).
+// Leaves a system to its team: scalars, p, r, x, x_hi (unless it is still zero;
+// the workgroup's own buffer XH is its next item's).
 template <int RPT>
 __device__ __forceinline__ void team_leave(const CocgTeams& T, int team, int npad,
                                            const TeamState& ts, const cpx<float>* P,
                                            const cpx<float>* R, const cpx<float> (&xr)[RPT],
-                                           const int (&slc)[RPT], int lane) {
+                                           cpx<double>* XH, const int (&slc)[RPT],
+                                           int lane) {
   u64* buf = team_buf(T, team, npad);
   cpx<float>* v = reinterpret_cast<cpx<float>*>(buf + kTeamHead);
+  cpx<double>* xh = reinterpret_cast<cpx<double>*>(buf + kTeamHead + 3 * (size_t)npad);
 #pragma unroll
   for (int t = 0; t < RPT; ++t)
     if (slc[t] >= 0) {
@@ -479,6 +481,7 @@ __device__ __forceinline__ void team_leave(const CocgTeams& T, int team, int npa
       *at32(v, s) = P[s];
       *at32(v + npad, s) = R[s];
       *at32(v + 2 * npad, s) = xr[t];
+      if (!ts.first_cycle) *at32(xh, s) = *at32(XH, s);
     }
   if (threadIdx.x == 0) {
     *reinterpret_cast<TeamState*>(buf) = ts;
@@ -491,8 +494,7 @@ static_assert(sizeof(TeamState) <= kTeamHead * sizeof(u64));
 // b % 8 + 8 (b / 32).
 template <int RPT>
 __global__ __launch_bounds__(kResThreads) void k_cocg_team(CocgTeams T, ResGraph G, int npad,
-                                                           int maxit, int max_refine,
-                                                           cpx<double>* __restrict__ xhi_all) {
+                                                           int maxit, int max_refine) {
   extern __shared__ unsigned char smem_raw[];
   cpx<float>* P = reinterpret_cast<cpx<float>*>(smem_raw);  // then the zero row and the trash row
   const int zoff = npad, toff = zoff + 64;
@@ -522,7 +524,8 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_team(CocgTeams T, ResGraph
   if (go != 1) return;
   const double tol2 = G.tol * G.tol;
   TeamState ts = *reinterpret_cast<const TeamState*>(team_buf(T, team, npad));
-  cpx<double>* XH = xhi_all + (size_t)ts.owner * npad;
+  cpx<double>* XH = reinterpret_cast<cpx<double>*>(team_buf(T, team, npad) + kTeamHead +
+                                                   3 * (size_t)npad);
   const double zr = G.zs[2 * ts.j], zi = G.zs[2 * ts.j + 1];
   const int ocol = ts.j * G.kcols + ts.ci;
   cpx<float>* D = reinterpret_cast<cpx<float>*>(G.D);
@@ -1120,9 +1123,8 @@ __device__ __forceinline__ void cocg_items(
         if (!verify && team >= 0 && it >= teams.leave_at) {
           team_leave<RPT>(teams, team, max_npad,
                           TeamState{it, nref, nbd, lastit, rstart, span, span0, first_cycle ? 1 : 0,
-                                    rho_re, rho_im, cyc_tol2, sprev, scale, sqrt(bn2), j, ci,
-                                    (int)blockIdx.x},
-                          P, R, xr, slc, ln);
+                                    rho_re, rho_im, cyc_tol2, sprev, scale, sqrt(bn2), j, ci},
+                          P, R, xr, XH, slc, ln);
           left = true;
           break;
         }
@@ -1315,7 +1317,7 @@ std::vector<int> cocg_resident_wave_table(const std::vector<int>& widths, int rp
 
 size_t cocg_team_ctl_words(int nteam) { return (size_t)nteam * kTeamStride + 1; }
 size_t cocg_team_buf_words(int n, int nteam) {
-  return (size_t)nteam * (kTeamHead + 3 * (size_t)((n + 63) / 64) * 64);
+  return (size_t)nteam * (kTeamHead + 5 * (size_t)((n + 63) / 64) * 64);
 }
 
 // Inversely proportional to the logarithm of the parameter of z's Bernstein
@@ -1444,7 +1446,7 @@ static hipError_t launch_team(hipStream_t st, const ResGraph& g0, int max_n, con
   ResGraph g = g0;
   g.tol = L.tol;
   hipLaunchKernelGGL(kern, dim3((L.teams.nteam + 7) / 8 * 32), dim3(kResThreads), lds, st, L.teams,
-                     g, npad, L.maxit, L.max_refine, (cpx<double>*)L.xhi);
+                     g, npad, L.maxit, L.max_refine);
   return hipGetLastError();
 }
 

@@ -59,3 +59,69 @@ def test_team_solves(gpu_lib, monkeypatch, dims, k, wait):
             dist = np.abs(z[j] - lam).min()
             assert np.linalg.norm(x) <= 1.01 * np.linalg.norm(b) / dist
     assert its[0] > 2 * its[k:].max() > 0  # the first shift's systems run on
+
+
+def test_two_plans_at_once(gpu_lib):
+    """Teams of two plans on two threads and streams share the device: each
+    solve ends and has the residuals it has alone."""
+    import threading
+
+    import torch
+
+    csr = grid_laplacian((70, 70), 0.01)
+    A, n, k = csr.to_scipy(), csr.n, 24
+    z = np.concatenate([[0.5 + 4e-3j], half_circle(0.0, 1.0, 4)[0]])
+    B = np.random.default_rng(5).standard_normal((n, k))
+    tol, out, errors = 1e-8, {}, []
+
+    def work(i):
+        try:
+            stream = torch.cuda.Stream()
+            with gpu_lib.Plan(csr, 0.0, 0.6, 8, nc=2, q=1, p=4, precision="fp32",
+                              stream=stream.cuda_stream) as plan:
+                b = torch.from_numpy(B).cuda()
+                X = torch.zeros((n, len(z) * k), dtype=torch.complex64, device="cuda")
+                torch.cuda.synchronize()
+                for _ in range(3):
+                    its, rs = plan.shifted_solve(z, b, X, tol)
+                torch.cuda.synchronize()
+                out[i] = (X.cpu().numpy().astype(complex), rs)
+        except Exception as e:  # the main thread reports it
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for X, rs in out.values():
+        assert rs.max() <= tol
+        for j in range(len(z)):
+            for c in (0, k - 1):
+                x, b = X[:, j * k + c], B[:, c]
+                bound = 1.01 * tol * np.linalg.norm(b) + 2 * 2.0 ** -24 * 30 * np.linalg.norm(x)
+                assert np.linalg.norm(b - (z[j] * x - A @ x)) <= bound
+
+
+def test_left_systems_keep_their_solution(gpu_lib):
+    """A workgroup that leaves a system to its team goes on with other items:
+    with more systems than workgroups the ones with teams take the iterations
+    that they take among few (a lost x_hi would cost them what they had)."""
+    import torch
+
+    csr = grid_laplacian((80, 80), 0.01)
+    n, k = csr.n, 100
+    z = np.concatenate([[0.5 + 4e-3j], half_circle(0.0, 1.0, 4)[0]])
+    B = np.random.default_rng(11).standard_normal((n, k))
+    its = {}
+    with gpu_lib.Plan(csr, 0.0, 0.6, 8, nc=2, q=1, p=4, precision="fp32") as plan:
+        for m in (k, 10):
+            X = torch.zeros((n, len(z) * m), dtype=torch.complex64, device="cuda")
+            b = torch.from_numpy(np.ascontiguousarray(B[:, :m])).cuda()
+            for rep in range(3):
+                its[m], rs = plan.shifted_solve(z, b, X, 1e-8)
+                assert rs.max() <= 1e-8
+    # one FP32 system's count varies by several percent with the rounding of its
+    # sums, the mean of ten by two or three
+    assert its[k][:10].mean() <= 1.15 * its[10][:10].mean()
