@@ -339,7 +339,7 @@ __device__ __forceinline__ const ResGraph* const_graph(const ResGraph* graphs, i
 // What bounds it is the latency of the exchanges (of about 14,000 clocks an
 // iteration, 3,000 for each sum and 3,000 for the residuals).  knn n = 8000,
 // FP32: an iteration takes 6.5 us of four workgroups, 9.6 us of one; 64
-// systems of 4 shifts 14.8 -> 12.0 ms.  With four slots a thread (n = 3000) it
+// systems of 4 shifts 14.8 -> 11.6 ms.  With four slots a thread (n = 3000) it
 // takes 5.4 us of four workgroups and 4.6 us of one, so those have no teams.
 typedef unsigned long long u64;
 constexpr int kTeamStride = 80;   // words of a team's ctl: two sets of kTeamSize * 8, then
