@@ -2695,7 +2695,7 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       if (s == RAFEAST_OK)
         s = run_cocg(P, nitems, d_items, d_z, k, B, ldb, X, nz * k, tol, d_it, d_rs, nteam, d_of,
                      done);
-      if (s == RAFEAST_OK) {  // `of` is still being read
+      if (s == RAFEAST_OK && nteam > 0) {  // `of` is still being read
         e = hipStreamSynchronize(P->st);
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
       }
