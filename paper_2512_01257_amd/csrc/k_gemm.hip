@@ -348,18 +348,22 @@ int gemm_tn(bool f64, int N) {
 }
 
 // Chunks of the inner dimension, given room for most of them: two workgroups
-// per CU, chunks at least 512 long.
+// per CU.  Chunks are at least 512 long, and at least 128 below 2,560: a short
+// product on few tiles otherwise leaves most CUs idle (us with 512 and 128:
+// FP64 602 x 350 x 1391 246 and 68, FP32 2000 x 480 x 2000 165 and 93), while
+// for long ones more chunks only add partial sums (3000 x 300 x 3000 167 and
+// 168, FP64 600 x 300 x 8000 110 and 121, FP32 4096 x 60 x 4096 48 and 50).
 int gemm_chunks(bool f64, int M, int N, int K, size_t most) {
-  if (K < 1024) return 1;
   const int BN = 32 * gemm_tn(f64, N);
   const int tiles = ((M + kBM - 1) / kBM) * ((N + BN - 1) / BN);
   const int want = (512 + tiles - 1) / tiles;
-  return std::max(1, std::min(want, std::min(K / 512, (int)std::min<size_t>(most, 64))));
+  const int fit = K / (K < 2560 ? 128 : 512);
+  return std::max(1, std::min(want, std::min(fit, (int)std::min<size_t>(most, 64))));
 }
 
 // C = alpha op(A) B + beta C.  work (nullable, work_elems elements) holds the
 // chunk slabs: the inner dimension is split when the output has fewer tiles
-// than two per CU and the chunks stay at least 512 long.
+// than two per CU and the chunks stay long enough.
 template <typename T>
 hipError_t gemm(hipStream_t st, bool acol, int M, int N, int K, const T* A, int64_t lda,
                 const T* B, int64_t ldb, T* C, int64_t ldc, T alpha, T beta, T* work,
@@ -412,22 +416,22 @@ hipError_t dense_apply(const DenseOp& A, hipStream_t st, int k, const T* X, int 
     return hipErrorInvalidValue;
   const int n = (int)A.n, rows = (int)A.rows;
   if (A.kind == 1) {
-    // K is symmetric: K(i, kk) = K[kk n + i], the column-major reading; the
+    // K is symmetric: K(i, kk) = K[kk lda + i], the column-major reading; the
     // workspace serves products up to tcols wide
     const size_t room = t && k <= A.tcols ? (size_t)A.wslabs * n * A.tcols : 0;
-    return gemm<T>(st, true, n, k, n, a, n, X, ldx, Y, ldy, alpha, beta, t, room);
+    return gemm<T>(st, true, n, k, n, a, A.lda, X, ldx, Y, ldy, alpha, beta, t, room);
   }
   if (A.kind != 2 || !t || k > A.tcols) return hipErrorInvalidValue;
-  // T (rows x k, ld kt) = Xd X: Xd(r, j) = a[j rows + r]; the chunk slabs
+  // T (rows x k, ld kt) = Xd X: Xd(r, j) = a[j lda + r]; the chunk slabs
   // follow T in the workspace.  kt rounds k up to a multiple of 4, so that
   // the second product reads T in whole vectors.
   const int kt = (k + 3) / 4 * 4 <= A.tcols ? (k + 3) / 4 * 4 : k;
   const size_t room = (size_t)(A.wslabs - 1) * rows * A.tcols;
-  hipError_t e = gemm<T>(st, true, rows, k, n, a, rows, X, ldx, t, kt, T(1), T(0),
+  hipError_t e = gemm<T>(st, true, rows, k, n, a, A.lda, X, ldx, t, kt, T(1), T(0),
                          t + (size_t)rows * A.tcols, room);
   if (e != hipSuccess) return e;
-  // Y = alpha scale Xd^T T + beta Y: Xd^T(i, r) = a[i rows + r]
-  return gemm<T>(st, false, n, k, rows, a, rows, t, kt, Y, ldy, alpha * T(A.scale), beta,
+  // Y = alpha scale Xd^T T + beta Y: Xd^T(i, r) = a[i lda + r]
+  return gemm<T>(st, false, n, k, rows, a, A.lda, t, kt, Y, ldy, alpha * T(A.scale), beta,
                  nullptr, 0);
 }
 

@@ -220,13 +220,13 @@ hipError_t launch_cocg_resident(hipStream_t st, const ResGraph* g0, const ResGra
 constexpr int kStreamMaxGroups = 128;
 // Dense symmetric operator of the statistical workloads: A = K (kind 1,
 // n x n) or A = scale X^T X (kind 2, X rows x n).  Device matrices are
-// column-major (leading dimension n for K, rows for X); the products run on
-// rocBLAS (MFMA GEMMs), the handle bound to the caller's stream per call.
+// column-major, the leading dimension lda a multiple of four (n for K, rows for
+// X, rounded up), so that the products read them in whole vectors.
 struct DenseOp {
   int kind = 0;
-  int64_t n = 0, rows = 0;
+  int64_t n = 0, rows = 0, lda = 0;
   double scale = 1.0;
-  const double* a64 = nullptr;     // K or Xd (column-major, ld rows), FP64
+  const double* a64 = nullptr;     // K or Xd (column-major), FP64
   const float* a32 = nullptr;      // the same, FP32
   double* t64 = nullptr;           // workspace of wslabs slabs of rows x tcols: kind 2,
   float* t32 = nullptr;            // Xd X in the first and the inner-dimension chunks of

@@ -1848,23 +1848,24 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   }
 
   if (D) {
-    // dense operator: device copies (FP64, FP32) compacted to leading
-    // dimension rows, scratch for the covariance form's X V, the BLAS handle,
-    // and the identity row order of the streaming engine
+    // dense operator: device copies (FP64, FP32) with a leading dimension of
+    // rows rounded up to whole vectors, scratch for the covariance form's X V
+    // and chunk sums, and the identity row order of the streaming engine
     DenseOp& op = P->dop;
     op.kind = D->kind;
     op.n = n;
     op.rows = D->kind == 2 ? D->rows : n;
     op.scale = D->kind == 2 ? D->scale : 1.0;
-    const size_t cnt = (size_t)op.rows * n;
+    op.lda = (op.rows + 3) / 4 * 4;
+    const size_t cnt = (size_t)op.lda * n;
     {
-      std::vector<double> h64(cnt);
-      std::vector<float> h32(cnt);
+      std::vector<double> h64(cnt, 0.0);
+      std::vector<float> h32(cnt, 0.0f);
       for (int64_t j = 0; j < n; ++j)
         for (int64_t i = 0; i < op.rows; ++i) {
           const double v = D->M[i + j * D->ld];
-          h64[(size_t)j * op.rows + i] = v;
-          h32[(size_t)j * op.rows + i] = (float)v;
+          h64[(size_t)j * op.lda + i] = v;
+          h32[(size_t)j * op.lda + i] = (float)v;
         }
       PRCHK(dalloc(P, &P->d_k64, cnt, "dense operator"));
       PRCHK(dalloc(P, &P->d_k32, cnt, "dense operator fp32"));
@@ -1878,9 +1879,11 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     const int Bp = stream_padded_columns(P->m0, P->nc * P->m0, fp32);
     op.tcols = std::max<int64_t>(2 * (int64_t)Bp, kMaxSmallK);
     // covariance: X V (rows x tcols) and chunk slabs of its long inner
-    // dimension n (chunks of at least 512, at most 32); kernel: up to four
-    // chunk slabs of K X (n x tcols) for products with few output tiles
-    op.wslabs = op.kind == 2 ? 1 + (int)std::min<int64_t>(32, std::max<int64_t>(1, n / 512)) : 4;
+    // dimension n (at most 32); kernel: chunk slabs of K X (n x tcols) for
+    // products with few output tiles, eight where K is small
+    op.wslabs = op.kind == 2 ? 1 + (int)std::min<int64_t>(32, std::max<int64_t>(1, n / 512))
+                : n <= 1024  ? 8
+                             : 4;
     const size_t wrows = op.kind == 2 ? (size_t)op.rows : (size_t)n;
     PRCHK(dalloc(P, &P->d_t64, (size_t)op.wslabs * wrows * op.tcols, "dense workspace"));
     PRCHK(dalloc(P, &P->d_t32, (size_t)op.wslabs * wrows * op.tcols, "dense workspace fp32"));
