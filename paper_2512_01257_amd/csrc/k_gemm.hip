@@ -107,7 +107,9 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
   const int b = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
   const int l = (RAFEAST_GEMM_XCD && G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
   const int tn = l % gx, tm = (l / gx) % gy, tz = l / (gx * gy);
-  const int i0 = tm * kBM, j0 = tn * BN;
+  // the tile's first row and column, and the first ones it stores
+  const int is = tm * kBM, js = tn * BN;
+  const int i0 = M >= kBM ? min(is, M - kBM) : is, j0 = N >= BN ? min(js, N - BN) : js;
   const int kbeg = tz * kc;
   const int kend = min(K, kbeg + kc);
   const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
@@ -176,17 +178,49 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
     }
   };
 
-  // The fast path needs whole steps of the inner dimension.  Rows of op(A)
-  // past M and columns of B past N feed only outputs that are never stored,
-  // so a vector that starts past the edge is simply read from the tile's
-  // first row or column instead; a vector may not straddle the edge (M, N a
-  // multiple of VEC when the tile is cut there).
-  const bool a_fast = !ACOL || i0 + kBM <= M || M % VEC == 0;
-  const bool b_fast = j0 + BN <= N || N % VEC == 0;
-  if (a_fast && b_fast && (kend - kbeg) % BK == 0) {
+  // Element loads from addresses clamped into the matrix, the elements outside
+  // it zeroed: tiles that are cut inside a vector, and a last step of the inner
+  // dimension that is not whole.
+  auto load_any = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < NVA; ++q) {
+      const int e = (tid + q * kGT) * VEC;
+      const int ca = e % CA, oa = e / CA;
+#pragma unroll
+      for (int u = 0; u < VEC; ++u) {
+        const int gi = i0 + (ACOL ? ca + u : oa), gk = k0 + (ACOL ? oa : ca + u);
+        const int ci = min(gi, M - 1), ck = min(gk, kend - 1);
+        const T va = A[ACOL ? (int64_t)ck * lda + ci : (int64_t)ci * lda + ck];
+        ra[q][u] = (gi < M && gk < kend) ? va : T(0);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NVB; ++q) {
+      const int e = (tid + q * kGT) * VEC;
+#pragma unroll
+      for (int u = 0; u < VEC; ++u) {
+        const int gj = j0 + e % BN + u, gb = k0 + e / BN;
+        const int cj = min(gj, N - 1), cb = min(gb, kend - 1);
+        const T vb = B[(int64_t)cb * ldb + cj];
+        rb[q][u] = (gj < N && gb < kend) ? vb : T(0);
+      }
+    }
+  };
+
+  // The fast path takes the whole steps of the inner dimension.  A tile cut by
+  // the edge of C is moved back to end there (its first rows or columns are the
+  // tile's before it, and only that one stores them), so its loads stay inside
+  // the matrix.  Where C is smaller than a tile, rows and columns past it feed
+  // only outputs that are never stored: a vector that starts there is read from
+  // the tile's first row or column instead, but none may straddle the edge (M, N
+  // a multiple of VEC).  Vectors need not start on a 16-byte boundary.
+  const bool a_fast = !ACOL || M >= kBM || M % VEC == 0;
+  const bool b_fast = N >= BN || N % VEC == 0;
+  const int nf = a_fast && b_fast ? (kend - kbeg) / BK : 0;  // whole steps
+  if (nf > 0) {
     // Per-thread operand pointers advanced by one step each time,
     // whole-vector loads, no bounds tests in the loop.
-    typedef T VT __attribute__((ext_vector_type(VEC)));
+    typedef T VT __attribute__((ext_vector_type(VEC), aligned(sizeof(T))));
     const T* pa[NVA];
     const T* pb[NVB];
 #pragma unroll
@@ -221,54 +255,24 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
         pb[q] += db;
       }
     };
-    if (nk > 0) {
-      load();
-      store(0);
-    }
+    load();
+    store(0);
     __syncthreads();
-    for (int t = 0; t < nk; ++t) {
+    for (int t = 0; t < nf; ++t) {
       const int cur = t & 1;
-      if (t + 1 < nk) load();
-      mfma_step(cur, t + 1 < nk);
-      if (!kStoreInStep && t + 1 < nk) store(cur ^ 1);
+      if (t + 1 < nf) load();
+      mfma_step(cur, t + 1 < nf);
+      if (!kStoreInStep && t + 1 < nf) store(cur ^ 1);
       __syncthreads();
     }
-  } else {
-    // Other edge tiles: element loads from addresses clamped into the
-    // matrix, the elements outside it zeroed.
-    auto load = [&](int k0) {
-#pragma unroll
-      for (int q = 0; q < NVA; ++q) {
-        const int e = (tid + q * kGT) * VEC;
-        const int ca = e % CA, oa = e / CA;
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-          const int gi = i0 + (ACOL ? ca + u : oa), gk = k0 + (ACOL ? oa : ca + u);
-          const int ci = min(gi, M - 1), ck = min(gk, kend - 1);
-          const T va = A[ACOL ? (int64_t)ck * lda + ci : (int64_t)ci * lda + ck];
-          ra[q][u] = (gi < M && gk < kend) ? va : T(0);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < NVB; ++q) {
-        const int e = (tid + q * kGT) * VEC;
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) {
-          const int gj = j0 + e % BN + u, gb = k0 + e / BN;
-          const int cj = min(gj, N - 1), cb = min(gb, kend - 1);
-          const T vb = B[(int64_t)cb * ldb + cj];
-          rb[q][u] = (gj < N && gb < kend) ? vb : T(0);
-        }
-      }
-    };
-    if (nk > 0) {
-      load(kbeg);
-      store(0);
-    }
+  }
+  if (nf < nk) {
+    load_any(kbeg + nf * BK);
+    store(0);
     __syncthreads();
-    for (int t = 0; t < nk; ++t) {
-      const int cur = t & 1;
-      if (t + 1 < nk) load(kbeg + (t + 1) * BK);
+    for (int t = nf; t < nk; ++t) {
+      const int cur = (t - nf) & 1;
+      if (t + 1 < nk) load_any(kbeg + (t + 1) * BK);
       mfma_step(cur, t + 1 < nk);
       if (!kStoreInStep && t + 1 < nk) store(cur ^ 1);
       __syncthreads();
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
       for (int v = 0; v < 4; ++v) {
         const int gi = i0 + wm * 64 + mt * 16 + Mfma<T>::row(lane, v);
         const int gj = j0 + wn * 16 * TN + nt * 16 + fc;
-        if (gi >= M || gj >= N) continue;
+        if (gi < is || gi >= M || gj < js || gj >= N) continue;
         if (slab) {
           slab[(size_t)gi * N + gj] = acc[mt][nt][v];
         } else {
@@ -383,11 +387,16 @@ hipError_t gemm(hipStream_t st, bool acol, int M, int N, int K, const T* A, int6
   S = K > 0 ? (K + kc - 1) / kc : 1;
   T* part = S > 1 ? work : nullptr;
   dim3 grid((N + BN - 1) / BN, (M + kBM - 1) / kBM, S);
-  // vector loads when every operand row starts on a vector boundary
+  // Vector loads, also of rows that start between 16-byte boundaries (us with
+  // element and vector loads: FP32 8191 x 480 x 8191 1850 and 609, 883 x 101 x 883
+  // 43 and 39; FP64 5003 x 334 x 4002 912 and 462), unless C is smaller than a
+  // tile and cuts vectors.
   constexpr int V = kGemmVecBytes / (int)sizeof(T) > 0 ? kGemmVecBytes / (int)sizeof(T) : 1;
-  const bool vec = V > 1 && lda % V == 0 && ldb % V == 0 &&
-                   reinterpret_cast<uintptr_t>(A) % (V * sizeof(T)) == 0 &&
-                   reinterpret_cast<uintptr_t>(B) % (V * sizeof(T)) == 0;
+  const bool aligned = lda % V == 0 && ldb % V == 0 &&
+                       reinterpret_cast<uintptr_t>(A) % (V * sizeof(T)) == 0 &&
+                       reinterpret_cast<uintptr_t>(B) % (V * sizeof(T)) == 0;
+  const bool whole = (N >= BN || N % V == 0) && (!acol || M >= kBM || M % V == 0);
+  const bool vec = V > 1 && (aligned || whole);
   hipError_t e;
   if (TN == 1)
     e = launch_tiles<T, BK, 1>(st, acol, vec, grid, M, N, K, kc, A, lda, B, ldb, C, ldc, alpha,
