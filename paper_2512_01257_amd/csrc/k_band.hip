@@ -122,16 +122,38 @@ __device__ __forceinline__ void tile_product(const Plane& A, const Plane& Bm, in
   }
 }
 
-// 1 / d: from |d|^2 where that is far from the ends of the range (one
-// reciprocal in the chain), else with the larger component scaled out.
-__device__ __forceinline__ zc crcp(zc d) {
-  const double m = d.re * d.re + d.im * d.im;
+// The inverse (i11, i12, i22) of two pivots (p11, p12, p22).  From the
+// determinant (one reciprocal in the chain) where its square is far from the
+// ends of the range, else by the scalar pivots p11 and p22 - p12^2 / p11, whose
+// products stay in range whatever the scale of the matrix.  Returns 0, or 1 or 2
+// for a vanishing or non-finite first or second pivot.  The branch is uniform;
+// the second form is out of the chain.
+__device__ __forceinline__ int inverse2(zc p11, zc p12, zc p22, zc& i11, zc& i12, zc& i22) {
+  zc det{0.0, 0.0};
+  cfma(det, p11, p22);
+  cfma(det, zc{-p12.re, -p12.im}, p12);
+  const double m = det.re * det.re + det.im * det.im;
+  i11 = i12 = i22 = zc{0.0, 0.0};
   if (m > 0x1.0p-900 && m < 0x1.0p+900) {
     const double x = rcp_nr(m);
-    return zc{d.re * x, -d.im * x};
+    const zc q{det.re * x, -det.im * x};
+    cfma(i11, p22, q);
+    cfma(i12, zc{-p12.re, -p12.im}, q);
+    cfma(i22, p11, q);
+    return p11.re != 0.0 || p11.im != 0.0 ? 0 : 1;
   }
-  const zd i = zdiv_fast(zd{1.0, 0.0}, zd{d.re, d.im});
-  return zc{i.re, i.im};
+  if (!(cfinite(p11) && (p11.re != 0.0 || p11.im != 0.0))) return 1;
+  const zd one{1.0, 0.0}, l = zdiv_fast(zd{p12.re, p12.im}, zd{p11.re, p11.im});
+  zc d2 = p22;
+  cfma(d2, zc{-l.re, -l.im}, p12);
+  if (!(cfinite(d2) && (d2.re != 0.0 || d2.im != 0.0))) return 2;
+  const zd r1 = zdiv_fast(one, zd{p11.re, p11.im}), r2 = zdiv_fast(one, zd{d2.re, d2.im});
+  const zd lr = zmul(l, r2);
+  i22 = zc{r2.re, r2.im};
+  i12 = zc{-lr.re, -lr.im};
+  i11 = zc{r1.re, r1.im};
+  cfma(i11, zc{lr.re, lr.im}, zc{l.re, l.im});
+  return 0;
 }
 
 // The 32 x 32 symmetric block held in the waves' tiles (wave w: rows 16 (w /
@@ -168,16 +190,9 @@ __device__ __forceinline__ int sweep_block(v4d& cr, v4d& ci, zc (*rowbuf)[2][kBB
         b0[v] = rows[0][r0 + lk + 4 * v];
         b1[v] = rows[1][r0 + lk + 4 * v];
       }
-      zc det{0.0, 0.0};
-      cfma(det, p11, p22);
-      cfma(det, zc{-p12.re, -p12.im}, p12);
-      if (!fail && !(cfinite(p11) && (p11.re != 0.0 || p11.im != 0.0))) fail = k + 1;
-      if (!fail && !(cfinite(det) && (det.re != 0.0 || det.im != 0.0))) fail = k + 2;
-      const zc q = crcp(det);
-      zc i11{0.0, 0.0}, i12{0.0, 0.0}, i22{0.0, 0.0};
-      cfma(i11, p22, q);
-      cfma(i12, zc{-p12.re, -p12.im}, q);
-      cfma(i22, p11, q);
+      zc i11, i12, i22;
+      const int vanished = inverse2(p11, p12, p22, i11, i12, i22);
+      if (!fail && vanished) fail = k + vanished;
       // t = P^{-1} A_Kj; in a column of K, -P^{-1}'s own and a = 0, so that the
       // one update below gives A_iK P^{-1}
       const bool ck0 = col == k, ck1 = col == k + 1;
@@ -255,8 +270,10 @@ __global__ __launch_bounds__(kStepThreads) void k_band_first(int n, int b, zc* _
 // workgroup, once per panel.  A scalar L D L^T needed two launches a panel, one
 // workgroup a shift for the block, its inverse triangle and all multipliers
 // (90 us) and the window after it (22 us); this launch takes 17.5 us
-// (knn n = 8000, band 258, 8 shifts).
-__global__ __launch_bounds__(kStepThreads) void k_band_step(int n, int b, int c, int nz,
+// (knn n = 8000, band 258, 8 shifts).  Two workgroups a CU are asked for: the
+// pivots' second form otherwise takes the registers of one of them (band 3000,
+// 4 shifts: 50 -> 63 ms).
+__global__ __launch_bounds__(kStepThreads, 2) void k_band_step(int n, int b, int c, int nz,
                                                             zc* __restrict__ Wall, size_t stride,
                                                             int* __restrict__ info) {
   __shared__ Plane Pi, Ri, Ci;  // Pi: the inverse, then -(rows' M21) M11^{-1}
