@@ -675,6 +675,14 @@ int ms_blocks(int n, int num_cu) {
   if (nb > need) nb = (need + 7) / 8 * 8;
   return nb < 8 ? 8 : nb;
 }
+// k_ms_shift's row blocks: as many workgroups as are resident at once, always a
+// multiple of the eight stripes that its rows are cut into.
+int ms_shift_blocks(int n, int num_cu, int shifts) {
+  const int most = num_cu * (shifts <= 4 ? 2 : 1) / 8 * 8;
+  const int need = (n + kSR * kSW - 1) / (kSR * kSW);
+  const int nb = need < most ? (need + 7) / 8 * 8 : most;
+  return nb < 8 ? 8 : nb;
+}
 
 namespace {
 
@@ -687,10 +695,7 @@ hipError_t launch_shift(hipStream_t st, int n, int ns, const MsWork& W, int nz, 
   hipError_t e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return e;
-  // as many workgroups as are resident at once, a multiple of the eight XCDs
-  const int most = W.num_cu * (NZ <= 4 ? 2 : 1);
-  const int need = (n + kSR * kSW - 1) / (kSR * kSW);
-  const int nb = need < most ? (need + 7) / 8 * 8 : most;
+  const int nb = ms_shift_blocks(n, W.num_cu, NZ);
   hipLaunchKernelGGL(fn, dim3(nb, W.kp / 64), dim3(64 * kSW), lds, st, n, W.kp, nz, j0, ns, W.cols,
                      W.r, W.y, W.X, W.P);
   return hipGetLastError();

@@ -424,6 +424,7 @@ struct MsLaunch {
 int ms_cpl(int k);
 int ms_padded(int k);
 int ms_blocks(int n, int num_cu);
+int ms_shift_blocks(int n, int num_cu, int shifts);
 // Runs to completion; synchronises st once per chunk of iterations.
 hipError_t run_mshift(hipStream_t st, const StreamMatrix& A, const MsWork& W, const MsLaunch& L);
 
