@@ -280,7 +280,12 @@ rafeast_status rafeast_warmstart(rafeast_plan_t plan, const double* omega, doubl
  * iteration goes to stderr. */
 rafeast_status rafeast_solve(rafeast_plan_t plan, const double* Q_init, rafeast_result* res);
 
-/* Releases the plan and all its device memory.  NULL is a no-op. */
+/* Releases the plan and all its device memory.  NULL is a no-op.
+ *
+ * The step-level calls below keep their device workspaces in the plan for the
+ * next call.  All plans of the process and rafeast_gemm together keep at most
+ * 1 GiB (the blocks unused for longest are freed first), and give everything
+ * idle back before an allocation of the library's fails for want of memory. */
 void rafeast_destroy(rafeast_plan_t plan);
 
 /* Text of the last error on this plan (or of the last failed rafeast_plan when
@@ -378,7 +383,7 @@ rafeast_status rafeast_gram_noalloc(void* hip_stream, int64_t n, int32_t k1, int
  * M N == 0); beta == 0 does not read C.  A long inner
  * dimension with few output tiles is split into chunks summed in a fixed
  * order in a workspace that the library keeps for later calls (64 MiB per
- * device at most, freed with the last plan).  Runs on hip_stream
+ * device at most; see rafeast_destroy).  Runs on hip_stream
  * (nullable: the null stream) and waits for it.  Errors: INVALID_ARG for null
  * pointers, negative sizes, short leading dimensions or another precision;
  * OOM; DEVICE. */

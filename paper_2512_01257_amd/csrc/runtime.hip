@@ -13,7 +13,6 @@
 #include <cstring>
 #include <limits>
 #include <map>
-#include <memory>
 #include <mutex>
 #include <string>
 #include <thread>
@@ -22,6 +21,7 @@
 
 #include "../../include/rafeast.h"
 #include "kernels.h"
+#include "work_cache.h"
 
 using namespace rafeast;
 
@@ -40,75 +40,37 @@ constexpr double kSpuriousGain = 0.25;
 // Host workers driving streaming-engine members of a batch concurrently.
 constexpr size_t kBatchWorkers = 8;
 
+// What the step-level calls keep between them is bounded for the process; the
+// pool outlives every static object (a plan may be destroyed at exit).
+constexpr size_t kIdleBytes = size_t(1) << 30;
+constexpr size_t kGemmIdleBytes = size_t(64) << 20;
+
+WorkPool& work_pool() {
+  static WorkPool* pool = new WorkPool(
+      {[](void** q, size_t bytes) {
+         const hipError_t e = hipMalloc(q, bytes);
+         if (e != hipSuccess) (void)hipGetLastError();
+         return (int)e;
+       },
+       [](void* q) { (void)hipFree(q); }, (int)hipErrorOutOfMemory},
+      kIdleBytes);
+  return *pool;
+}
+
+// Device memory for whoever owns it (released by hipFree).
+hipError_t dev_alloc(void** q, size_t bytes) {
+  return (hipError_t)work_pool().alloc(q, bytes ? bytes : 1);
+}
+
 }  // namespace
 
-// Device workspaces of finished calls, kept for the next one: hipMalloc and
-// hipFree of a step-level call's blocks cost more than its kernels (a product
-// of 8192 x 480 x 8192 in FP32: 7.1 ms, of which 0.64 ms in kernels).  A block
-// goes back only when the call that used it has waited for its work, or to a
-// caller on the same stream.  At most `most` bytes are kept, the rest is freed;
-// an allocation that fails is tried again with everything kept given back.
-class WorkCache {
- public:
-  explicit WorkCache(size_t most) : most_(most) {}
-  ~WorkCache() { clear(); }
-  // bytes in: wanted, out: the block's size
-  hipError_t get(void** q, size_t& bytes) {
-    bytes = (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
-    {
-      std::lock_guard<std::mutex> lock(mu_);
-      size_t best = idle_.size();
-      for (size_t i = 0; i < idle_.size(); ++i)
-        if (idle_[i].bytes >= bytes && idle_[i].bytes <= 2 * bytes &&
-            (best == idle_.size() || idle_[i].bytes < idle_[best].bytes))
-          best = i;
-      if (best < idle_.size()) {
-        *q = idle_[best].p;
-        bytes = idle_[best].bytes;
-        held_ -= bytes;
-        idle_.erase(idle_.begin() + best);
-        return hipSuccess;
-      }
-    }
-    hipError_t e = hipMalloc(q, bytes);
-    if (e == hipErrorOutOfMemory) {
-      (void)hipGetLastError();
-      clear();
-      e = hipMalloc(q, bytes);
-    }
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      *q = nullptr;
-    }
-    return e;
-  }
-  void put(void* q, size_t bytes) {
-    {
-      std::lock_guard<std::mutex> lock(mu_);
-      if (held_ + bytes <= most_) {
-        idle_.push_back({q, bytes});
-        held_ += bytes;
-        return;
-      }
-    }
-    (void)hipFree(q);
-  }
-  void clear() {
-    std::lock_guard<std::mutex> lock(mu_);
-    for (const Block& b : idle_) (void)hipFree(b.p);
-    idle_.clear();
-    held_ = 0;
-  }
-
- private:
-  struct Block {
-    void* p;
-    size_t bytes;
-  };
-  std::mutex mu_;
-  std::vector<Block> idle_;
-  size_t held_ = 0;
-  const size_t most_;
+// Teams of a resident launch and the device memory they need.
+struct TeamWork {
+  int nteam = 0;
+  double done = 0.0;         // expected steps of the systems without teams
+  int* of = nullptr;         // [systems] team of a system
+  unsigned long long* ctl = nullptr;
+  unsigned long long* buf = nullptr;
 };
 
 struct rafeast_plan_s {
@@ -172,10 +134,8 @@ struct rafeast_plan_s {
   // teams of the resident engine for a solve's systems (nteam 0: none); plans
   // whose slot layout is forced never have any
   bool teams_ok = true;
-  int nteam = 0;
-  double team_done = 0.0;    // expected steps of the systems without teams
   long long team_wait = 100000000;  // ticks of 10 ns that a team's members wait for each other
-  int* d_team_of = nullptr;
+  TeamWork team;             // of a solve
   std::vector<int> sell_widths; // slice widths, for wave tables of other slot counts
   // autotuned launch shape (resident engine: slots per thread), candidates
   // and their measured times
@@ -224,7 +184,7 @@ struct rafeast_plan_s {
   std::vector<double> last_theta;
   std::string err;
   hipEvent_t ev[8] = {};
-  WorkCache cache{size_t(1) << 30};  // step-level calls' workspaces
+  WorkCache cache{work_pool(), kIdleBytes};  // step-level calls' workspaces
 };
 
 // A batch: member plans sharing one stream, and the state of the shared
@@ -503,7 +463,7 @@ struct DevBuf {
   hipError_t get(T** p, size_t count) {
     void* q = nullptr;
     size_t bytes = count * sizeof(T);
-    const hipError_t e = cache.get(&q, bytes);
+    const hipError_t e = (hipError_t)cache.get(&q, bytes);
     if (e == hipSuccess) blocks.emplace_back(q, bytes);
     *p = (T*)q;
     return e;
@@ -511,30 +471,20 @@ struct DevBuf {
 };
 
 // Workspaces of rafeast_gemm, which takes no plan: per device, shared by all
-// threads (a block is one call's at a time), at most 64 MiB kept, given back
-// when the process's last plan goes.
-std::mutex g_gemm_mu;
-std::map<int, std::shared_ptr<WorkCache>> g_gemm_cache;
-int g_plans = 0;
-
-std::shared_ptr<WorkCache> gemm_cache(int dev) {
-  std::lock_guard<std::mutex> lock(g_gemm_mu);
-  std::shared_ptr<WorkCache>& c = g_gemm_cache[dev];
-  if (!c) c = std::make_shared<WorkCache>(size_t(64) << 20);
-  return c;
-}
-
-void count_plan(int d) {
-  std::lock_guard<std::mutex> lock(g_gemm_mu);
-  g_plans += d;
-  if (g_plans == 0)
-    for (auto& c : g_gemm_cache) c.second->clear();
+// threads (a block is one call's at a time).
+WorkCache& gemm_cache(int dev) {
+  static std::mutex mu;
+  static auto* caches = new std::map<int, WorkCache*>;
+  std::lock_guard<std::mutex> lock(mu);
+  WorkCache*& c = (*caches)[dev];
+  if (!c) c = new WorkCache(work_pool(), kGemmIdleBytes);
+  return *c;
 }
 
 template <typename T>
 rafeast_status dalloc(rafeast_plan_s* P, T** p, size_t count, const char* what) {
   if (count == 0) count = 1;
-  hipError_t e = hipMalloc((void**)p, count * sizeof(T));
+  hipError_t e = dev_alloc((void**)p, count * sizeof(T));
   if (e != hipSuccess) {
     *p = nullptr;
     return hip_fail(P, e, what);
@@ -550,7 +500,7 @@ void free_plan(rafeast_plan_s* P) {
                   P->d_G,      P->d_M,    P->d_S,     P->d_Ssel,  P->d_jw,   P->d_theta,
                   P->d_res,    P->d_qn,   P->d_gamma, P->d_info,  P->d_zw,   P->d_part,
                   P->d_D,      P->d_items, P->d_counter, P->d_iters, P->d_stats, P->d_flag,
-                  P->d_sel, P->d_xhi, P->d_team_of, P->d_srow, P->d_scol, P->d_sv32, P->d_sv64, P->d_sperm,
+                  P->d_sel, P->d_xhi, P->team.of, P->team.ctl, P->team.buf, P->d_srow, P->d_scol, P->d_sv32, P->d_sv64, P->d_sperm,
                   P->d_k64, P->d_k32, P->d_t64, P->d_t32,
                   P->d_mtot, P->d_mtmp, P->d_pcW, P->d_pcWb, P->d_pcX, P->d_pcY, P->d_D64,
                   P->d_wrep, P->d_band, P->d_binfo};
@@ -562,7 +512,6 @@ void free_plan(rafeast_plan_s* P) {
     if (e) (void)hipEventDestroy(e);
   if (P->own_stream && P->st) (void)hipStreamDestroy(P->st);
   delete P;
-  count_plan(-1);
 }
 
 // A dense operator handed to rafeast_plan_dense (kind 1: K, n x n) or
@@ -737,7 +686,7 @@ std::vector<int> rcm_order(int64_t n, const std::vector<int>& rp, const std::vec
 rafeast_status work_alloc(rafeast_plan_s* P, DevBuf* tmp, void** ptr, size_t bytes,
                           const char* what) {
   const hipError_t e =
-      tmp ? tmp->get((char**)ptr, bytes) : hipMalloc(ptr, bytes ? bytes : 1);
+      tmp ? tmp->get((char**)ptr, bytes) : dev_alloc(ptr, bytes);
   if (e != hipSuccess) {
     *ptr = nullptr;
     return hip_fail(P, e, what);
@@ -1004,8 +953,7 @@ ResGraph resident_graph(const rafeast_plan_s* P, const double* d_zs, int k, cons
 // COCG over items (0, j, i) of the given shift table; outputs into D.
 rafeast_status run_cocg(rafeast_plan_s* P, int nitems, const int* d_items, const double* d_zs,
                         int k, const double* B, int ldb, void* D, int ldd, double tol,
-                        int* d_iters, double* d_resid, int nteam, const int* d_team_of,
-                        double team_done) {
+                        int* d_iters, double* d_resid, const TeamWork& team) {
   // 32-bit indexing of the RHS and output blocks inside the kernel
   if (P->n * (int64_t)ldb >= (int64_t(1) << 31) || P->n * (int64_t)ldd >= (int64_t(1) << 31))
     return fail(P, RAFEAST_UNSUPPORTED, "blocks too large for the resident engine");
@@ -1020,24 +968,15 @@ rafeast_status run_cocg(rafeast_plan_s* P, int nitems, const int* d_items, const
   L.counter = P->d_counter;
   L.xhi = P->d_xhi;
   L.xhi_slots = P->xhi_slots;
-  DevBuf team_work(P);  // back to the plan's cache at the end: stream-ordered
-  if (nteam > 0) {
-    unsigned long long* ctl = nullptr;
-    unsigned long long* buf = nullptr;
-    hipError_t e = team_work.get(&ctl, cocg_team_ctl_words(nteam));
-    if (e == hipSuccess) e = team_work.get(&buf, cocg_team_buf_words((int)P->n, nteam));
-    if (e != hipSuccess) {
-      (void)hipGetLastError();  // no room: every system by one workgroup
-    } else {
-      L.teams.nteam = nteam;
-      L.teams.team_of = d_team_of;
-      L.teams.leave_at = cocg_team_iteration(team_done, tol);
-      L.teams.wait = P->team_wait;
-      L.teams.ctl = ctl;
-      L.teams.buf = buf;
-      HIPCHK(P, launch_fill_int(P->st, reinterpret_cast<int*>(ctl), 0,
-                                2 * (int)cocg_team_ctl_words(nteam)));
-    }
+  if (team.nteam > 0) {
+    L.teams.nteam = team.nteam;
+    L.teams.team_of = team.of;
+    L.teams.leave_at = cocg_team_iteration(team.done, tol);
+    L.teams.wait = P->team_wait;
+    L.teams.ctl = team.ctl;
+    L.teams.buf = team.buf;
+    HIPCHK(P, launch_fill_int(P->st, reinterpret_cast<int*>(team.ctl), 0,
+                              2 * (int)cocg_team_ctl_words(team.nteam)));
   }
   HIPCHK(P, hipMemsetAsync(P->d_counter, 0, sizeof(int), P->st));
   HIPCHK(P, launch_cocg_resident(P->st, &gd, nullptr, (int)P->n, P->sell.wave_rpt, L, P->fp32,
@@ -1460,8 +1399,7 @@ rafeast_status solve_shifted_systems(rafeast_plan_s* P, SolveRun& S) {
     return run_stream(P, P->swork, nc, m0, residual_form ? P->d_R : P->d_Q, ld, P->d_D, nc * m0,
                       P->tau, P->d_iters);
   return run_cocg(P, P->nitems, P->d_items, P->d_zw, m0, residual_form ? P->d_R : P->d_Q, ld,
-                  P->d_D, nc * m0, P->tau, P->d_iters, nullptr, P->nteam, P->d_team_of,
-                  P->team_done);
+                  P->d_D, nc * m0, P->tau, P->d_iters, nullptr, P->team);
 }
 
 // After the solves (between events ev[2] and ev[3]): combination
@@ -1672,7 +1610,7 @@ rafeast_status tune_resident(rafeast_plan_s* P) {
   L.xhi = P->d_xhi;
   L.xhi_slots = P->xhi_slots;
   int* d_tab = nullptr;
-  HIPCHK(P, hipMalloc(&d_tab, (size_t)cocg_resident_waves() * maxr * sizeof(int)));
+  HIPCHK(P, dev_alloc((void**)&d_tab, (size_t)cocg_resident_waves() * maxr * sizeof(int)));
   hipError_t e = hipSuccess;
   size_t best = 0;
   for (size_t c = 0; c < P->tune_cand.size() && e == hipSuccess; ++c) {
@@ -1771,7 +1709,6 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     return fail(nullptr, RAFEAST_DEVICE, "no HIP device available");
 
   rafeast_plan_s* P = new rafeast_plan_s();
-  count_plan(1);
   P->prm = *prm;
   P->n = n;
   P->nnz = nnz;
@@ -2126,13 +2063,14 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
         const size_t bytes = (size_t)P->nc * (size_t)n * (size_t)(b + 1) * sizeof(cpx<double>);
         size_t fr = 0, tot = 0;
         PCHK(hipMemGetInfo(&fr, &tot));
+        if (bytes > fr / 10 * 9 && work_pool().give_back()) PCHK(hipMemGetInfo(&fr, &tot));
         if (bytes > fr / 10 * 9)
           return bail(fail(P, RAFEAST_OOM,
                            "the band factors need " + std::to_string(bytes >> 20) +
                                " MiB (bandwidth " + std::to_string(b) + ", " +
                                std::to_string(P->nc) + " shifts); " +
                                std::to_string(fr >> 20) + " MiB free"));
-        hipError_t e = hipMalloc(&P->d_band, bytes);
+        hipError_t e = dev_alloc((void**)&P->d_band, bytes);
         if (e != hipSuccess) return bail(hip_fail(P, e, "band factors"));
         PRCHK(dalloc(P, &P->d_binfo, (size_t)P->nc, "band pivot report"));
       }
@@ -2167,7 +2105,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   // the solutions of one filter step (the multi-shift engine combines them
   // as it goes and needs no such block unless the learned solver runs)
   if (P->engine != RAFEAST_ENGINE_MULTISHIFT || prm->precond == RAFEAST_PC_LEARNED) {
-    hipError_t e = hipMalloc(&P->d_D, (size_t)n * P->nc * P->m0 * cs);
+    hipError_t e = dev_alloc(&P->d_D, (size_t)n * P->nc * P->m0 * cs);
     if (e != hipSuccess) return bail(hip_fail(P, e, "solve block"));
   }
   if (prm->precond == RAFEAST_PC_LEARNED) {
@@ -2179,7 +2117,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     if (!fp32) {
       P->d_D64 = P->d_D;  // the plan's solve block is FP64 already
     } else {
-      hipError_t e = hipMalloc(&P->d_D64, (size_t)n * P->nc * P->m0 * 2 * sizeof(double));
+      hipError_t e = dev_alloc(&P->d_D64, (size_t)n * P->nc * P->m0 * 2 * sizeof(double));
       if (e != hipSuccess) return bail(hip_fail(P, e, "FP64 solve block"));
     }
   }
@@ -2192,7 +2130,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   PRCHK(dalloc(P, &P->d_sel, P->m0, "sel"));
   if (P->engine == RAFEAST_ENGINE_RESIDENT) {
     P->xhi_slots = cocg_resident_xhi_slots((int)n, P->num_cu);
-    hipError_t e = hipMalloc(&P->d_xhi, P->xhi_slots * 2 * sizeof(double));
+    hipError_t e = dev_alloc(&P->d_xhi, P->xhi_slots * 2 * sizeof(double));
     if (e != hipSuccess) return bail(hip_fail(P, e, "solution scratch"));
   } else if (P->engine == RAFEAST_ENGINE_DIRECT) {
     // the factors are the whole workspace
@@ -2225,12 +2163,21 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     PRCHK(tune_resident(P));
     std::vector<int> of;
     if (const char* w = std::getenv("RAFEAST_TEAM_WAIT")) P->team_wait = std::atoll(w);
+    TeamWork& T = P->team;
     if (P->teams_ok && P->fp32)
-      P->nteam = cocg_plan_teams(P->h_items, P->zw.data(), P->sig_lo, P->sig_hi, P->num_cu,
-                                 P->sell.wave_rpt, of, P->team_done);
-    if (P->nteam > 0) {
-      PRCHK(dalloc(P, &P->d_team_of, of.size(), "teams"));
-      PCHK(hipMemcpy(P->d_team_of, of.data(), of.size() * sizeof(int), hipMemcpyHostToDevice));
+      T.nteam = cocg_plan_teams(P->h_items, P->zw.data(), P->sig_lo, P->sig_hi, P->num_cu,
+                                P->sell.wave_rpt, of, T.done);
+    if (T.nteam > 0) {
+      // without room for them every system is one workgroup's
+      hipError_t e = dev_alloc((void**)&T.of, of.size() * sizeof(int));
+      if (e == hipSuccess)
+        e = dev_alloc((void**)&T.ctl, cocg_team_ctl_words(T.nteam) * sizeof(*T.ctl));
+      if (e == hipSuccess)
+        e = dev_alloc((void**)&T.buf, cocg_team_buf_words((int)n, T.nteam) * sizeof(*T.buf));
+      if (e != hipSuccess)
+        T.nteam = 0;
+      else
+        PCHK(hipMemcpy(T.of, of.data(), of.size() * sizeof(int), hipMemcpyHostToDevice));
     }
   }
   if (P->engine == RAFEAST_ENGINE_DIRECT) PRCHK(band_factor_shifts(P));
@@ -2541,8 +2488,7 @@ rafeast_status rafeast_gemm(void* hip_stream, int32_t precision, int32_t a_cols,
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm: device");
-  const std::shared_ptr<WorkCache> cache = gemm_cache(dev);
-  DevBuf buf(*cache);
+  DevBuf buf(gemm_cache(dev));
   char* work = nullptr;
   if (room) {
     e = buf.get(&work, room * es);
@@ -2682,23 +2628,25 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       }
     } else {
       std::vector<int> of;
-      double done = 0.0;
-      int* d_of = nullptr;
-      int nteam = 0;
+      TeamWork T;
       if (P->teams_ok && P->fp32)
-        nteam = cocg_plan_teams(items, z, P->sig_lo, P->sig_hi, P->num_cu, P->sell.wave_rpt, of,
-                                done);
-      if (nteam > 0) {
-        e = buf.get(&d_of, of.size());
-        if (e == hipSuccess)
-          e = hipMemcpyAsync(d_of, of.data(), of.size() * sizeof(int), hipMemcpyHostToDevice,
+        T.nteam = cocg_plan_teams(items, z, P->sig_lo, P->sig_hi, P->num_cu, P->sell.wave_rpt, of,
+                                  T.done);
+      if (T.nteam > 0) {
+        e = buf.get(&T.of, of.size());
+        if (e == hipSuccess) e = buf.get(&T.ctl, cocg_team_ctl_words(T.nteam));
+        if (e == hipSuccess) e = buf.get(&T.buf, cocg_team_buf_words((int)P->n, T.nteam));
+        if (e != hipSuccess) {
+          T.nteam = 0;  // no room: every system by one workgroup
+        } else {
+          e = hipMemcpyAsync(T.of, of.data(), of.size() * sizeof(int), hipMemcpyHostToDevice,
                              P->st);
-        if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve teams");
+          if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve teams");
+        }
       }
       if (s == RAFEAST_OK)
-        s = run_cocg(P, nitems, d_items, d_z, k, B, ldb, X, nz * k, tol, d_it, d_rs, nteam, d_of,
-                     done);
-      if (s == RAFEAST_OK && nteam > 0) {  // `of` is still being read
+        s = run_cocg(P, nitems, d_items, d_z, k, B, ldb, X, nz * k, tol, d_it, d_rs, T);
+      if (s == RAFEAST_OK && T.nteam > 0) {  // `of` is still being read
         e = hipStreamSynchronize(P->st);
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
       }
@@ -2940,7 +2888,7 @@ rafeast_status rafeast_plan_batch(int32_t count, const rafeast_csr* A, const raf
       if (tab.empty())
         return bail(batch_fail(B, RAFEAST_UNSUPPORTED, "wave table of member " + std::to_string(g)));
       int* d = nullptr;
-      BPCHK(hipMalloc(&d, tab.size() * sizeof(int)));
+      BPCHK(dev_alloc((void**)&d, tab.size() * sizeof(int)));
       B->own_wtab.push_back(d);
       BPCHK(hipMemcpy(d, tab.data(), tab.size() * sizeof(int), hipMemcpyHostToDevice));
       B->wtab[g] = d;
@@ -2949,11 +2897,11 @@ rafeast_status rafeast_plan_batch(int32_t count, const rafeast_csr* A, const raf
     for (int g = 0; g < count; ++g)
       if (B->res_idx[g] >= 0) items += 3 * (size_t)B->plans[g]->nitems;
     B->h_graphs.resize(B->nres);
-    BPCHK(hipMalloc(&B->d_graphs, B->nres * sizeof(ResGraph)));
-    BPCHK(hipMalloc(&B->d_items, items * sizeof(int)));
-    BPCHK(hipMalloc(&B->d_counter, sizeof(int)));
+    BPCHK(dev_alloc((void**)&B->d_graphs, B->nres * sizeof(ResGraph)));
+    BPCHK(dev_alloc((void**)&B->d_items, items * sizeof(int)));
+    BPCHK(dev_alloc((void**)&B->d_counter, sizeof(int)));
     B->xhi_slots = (size_t)B->num_cu * ((size_t)(B->max_n + 63) / 64 * 64);
-    BPCHK(hipMalloc(&B->d_xhi, B->xhi_slots * 2 * sizeof(double)));
+    BPCHK(dev_alloc(&B->d_xhi, B->xhi_slots * 2 * sizeof(double)));
   }
 #undef BPCHK
   *out = B;
@@ -3278,10 +3226,10 @@ rafeast_status rafeast_pc_attach(rafeast_plan_t P, const float* W) {
   P->err.clear();
   const int npar = mlp_param_count();
   if (!P->d_pcW) {  // plans made with precond NONE get the buffers on first attach
-    HIPCHK(P, hipMalloc(&P->d_pcW, npar * sizeof(float)));
-    HIPCHK(P, hipMalloc(&P->d_pcWb, npar * sizeof(float)));
-    HIPCHK(P, hipMalloc(&P->d_pcX, 4 * (size_t)P->nc * sizeof(double)));
-    HIPCHK(P, hipMalloc(&P->d_pcY, 16 * (size_t)P->nc * sizeof(float)));
+    HIPCHK(P, dev_alloc((void**)&P->d_pcW, npar * sizeof(float)));
+    HIPCHK(P, dev_alloc((void**)&P->d_pcWb, npar * sizeof(float)));
+    HIPCHK(P, dev_alloc((void**)&P->d_pcX, 4 * (size_t)P->nc * sizeof(double)));
+    HIPCHK(P, dev_alloc((void**)&P->d_pcY, 16 * (size_t)P->nc * sizeof(float)));
   }
   HIPCHK(P, hipMemcpyAsync(P->d_pcW, W, npar * sizeof(float), hipMemcpyDeviceToDevice, P->st));
   HIPCHK(P, launch_mlp_bf16(P->st, P->d_pcW, P->d_pcWb));
