@@ -448,23 +448,37 @@ rafeast_status validate_csr(const rafeast_csr* A, int64_t& nnz, double& anorm, d
   return RAFEAST_OK;
 }
 
-// A call's device workspaces, given back to the plan's cache together.
+// A call's device workspaces, given back to the plan's cache together once the
+// call's work is done: calls end with wait(), and where one ends early, with an
+// error, the destructor waits (declare it after the host arrays that the work
+// reads or writes, which then outlive it).
 struct DevBuf {
   WorkCache& cache;
+  hipStream_t st;
   std::vector<std::pair<void*, size_t>> blocks;
-  explicit DevBuf(rafeast_plan_s* P) : cache(P->cache) {}
-  explicit DevBuf(WorkCache& c) : cache(c) {}
+  bool waited = true;  // nothing is in use yet
+  explicit DevBuf(rafeast_plan_s* P) : cache(P->cache), st(P->st) {}
+  DevBuf(WorkCache& c, hipStream_t s) : cache(c), st(s) {}
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
   ~DevBuf() {
+    if (!waited) (void)hipStreamSynchronize(st);
     for (const auto& b : blocks) cache.put(b.first, b.second);
+  }
+  hipError_t wait() {
+    const hipError_t e = hipStreamSynchronize(st);
+    waited = e == hipSuccess;
+    return e;
   }
   template <typename T>
   hipError_t get(T** p, size_t count) {
     void* q = nullptr;
     size_t bytes = count * sizeof(T);
     const hipError_t e = (hipError_t)cache.get(&q, bytes);
-    if (e == hipSuccess) blocks.emplace_back(q, bytes);
+    if (e == hipSuccess) {
+      blocks.emplace_back(q, bytes);
+      waited = false;
+    }
     *p = (T*)q;
     return e;
   }
@@ -1128,6 +1142,8 @@ rafeast_status pc_solve_run(rafeast_plan_s* P, int nz, const double* z, int k, c
                             double* resid, int maxit = -1, void* r_out = nullptr) {
   const int64_t n = P->n;
   const int Bc = nz * k;
+  std::vector<double> hz(2 * (size_t)Bc), hc, hres(Bc);
+  std::vector<int> hit(Bc);
   DevBuf buf(P);
   PcSolve S;
   S.n = n;
@@ -1165,7 +1181,6 @@ rafeast_status pc_solve_run(rafeast_plan_s* P, int nz, const double* z, int k, c
   HIPCHK(P, buf.get(&S.cols.rhon, 2 * (size_t)Bc));
   HIPCHK(P, buf.get(&S.cols.alpha, 2 * (size_t)Bc));
   HIPCHK(P, buf.get(&S.cols.beta, 2 * (size_t)Bc));
-  std::vector<double> hz(2 * (size_t)Bc), hc;
   for (int c = 0; c < Bc; ++c) {
     hz[2 * c] = z[2 * (c / k)];
     hz[2 * c + 1] = z[2 * (c / k) + 1];
@@ -1189,12 +1204,10 @@ rafeast_status pc_solve_run(rafeast_plan_s* P, int nz, const double* z, int k, c
   if (r_out)
     HIPCHK(P, hipMemcpyAsync(r_out, S.r, blk * sizeof(cpx<double>), hipMemcpyDeviceToDevice,
                              P->st));
-  std::vector<int> hit(Bc);
-  std::vector<double> hres(Bc);
   HIPCHK(P, hipMemcpyAsync(hit.data(), S.cols.it, Bc * sizeof(int), hipMemcpyDeviceToHost, P->st));
   HIPCHK(P, hipMemcpyAsync(hres.data(), S.cols.res, Bc * sizeof(double), hipMemcpyDeviceToHost,
                            P->st));
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  HIPCHK(P, buf.wait());
   if (iters) std::memcpy(iters, hit.data(), Bc * sizeof(int));
   if (resid) std::memcpy(resid, hres.data(), Bc * sizeof(double));
   return RAFEAST_OK;
@@ -1361,7 +1374,7 @@ rafeast_status solve_learned(rafeast_plan_s* P, SolveRun& S) {
                                  (size_t)n, hipMemcpyDeviceToDevice, P->st));
       S.iters[c] += it[t];
     }
-    HIPCHK(P, hipStreamSynchronize(P->st));
+    HIPCHK(P, fb.wait());
     S.pc_fallbacks += kf;
     if (verbose_log())
       std::fprintf(stderr, "rafeast: node %d: %d systems solved again without the preconditioner\n",
@@ -2404,7 +2417,7 @@ rafeast_status rafeast_gram(rafeast_plan_t P, int64_t n, int32_t k1, int32_t k2,
   double* part = nullptr;
   HIPCHK(P, buf.get(&part, gram_partial_doubles(n, k1, k2)));
   HIPCHK(P, launch_gram(P->st, n, k1, k2, X, ldx, Y, ldy, G, ldg, part));
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  HIPCHK(P, buf.wait());
   return RAFEAST_OK;
 }
 
@@ -2488,7 +2501,7 @@ rafeast_status rafeast_gemm(void* hip_stream, int32_t precision, int32_t a_cols,
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm: device");
-  DevBuf buf(gemm_cache(dev));
+  DevBuf buf(gemm_cache(dev), st);
   char* work = nullptr;
   if (room) {
     e = buf.get(&work, room * es);
@@ -2499,8 +2512,8 @@ rafeast_status rafeast_gemm(void* hip_stream, int32_t precision, int32_t a_cols,
                             (double*)C, ldc, alpha, beta, (double*)work, room)
           : launch_gemm_f32(st, a_cols, M, N, K, (const float*)A, lda, (const float*)B, ldb,
                             (float*)C, ldc, (float)alpha, (float)beta, (float*)work, room);
-  const hipError_t es2 = hipStreamSynchronize(st);  // before the workspace goes back
-  if (e == hipSuccess) e = es2;
+  const hipError_t ew = buf.wait();
+  if (e == hipSuccess) e = ew;
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm");
   return RAFEAST_OK;
 }
@@ -2517,7 +2530,7 @@ rafeast_status rafeast_cholqr2(rafeast_plan_t P, int64_t n, int32_t k, double* Y
   std::swap(P->d_part, part);
   if (info) *info = ci;
   RCHK(s);
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  HIPCHK(P, buf.wait());
   return RAFEAST_OK;
 }
 
@@ -2534,12 +2547,14 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
                                      int32_t* iters, double* resid) {
   if (!P || !z || !B || !X || nz < 1 || k < 1 || ldb < k || !(tol > 0.0) || !(tol < 1.0))
     return RAFEAST_INVALID_ARG;
-  DevBuf buf(P);
   double* d_z = nullptr;
   int* d_items = nullptr;
   int* d_it = nullptr;
   double* d_rs = nullptr;
   std::vector<int> items = make_items(nz, z, k, P->sig_lo, P->sig_hi);
+  std::vector<int> of, info(nz);
+  std::vector<double> zc;
+  DevBuf buf(P);
   const int nitems = nz * k;
   rafeast_status s = RAFEAST_OK;
   hipError_t e = buf.get(&d_z, 2 * (size_t)nz);
@@ -2567,7 +2582,6 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       if (s == RAFEAST_OK) {
         e = band_assemble(P->st, n, b, P->d_srow, P->d_scol, P->d_sv64, nz, d_z, Wb);
         if (e == hipSuccess) e = band_factor(P->st, n, b, nz, Wb, d_info);
-        std::vector<int> info(nz);
         if (e == hipSuccess)
           e = hipMemcpyAsync(info.data(), d_info, nz * sizeof(int), hipMemcpyDeviceToHost, P->st);
         if (e == hipSuccess) e = hipStreamSynchronize(P->st);
@@ -2602,10 +2616,6 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       else
         s = alloc_ms_work(P, nz, k, W, false, &buf);
       if (s == RAFEAST_OK) s = run_ms(P, W, nz, z, k, B, ldb, X, nz * k, tol, d_it, d_rs);
-      if (s == RAFEAST_OK) {
-        e = hipStreamSynchronize(P->st);
-        if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
-      }
     } else if (P->engine == RAFEAST_ENGINE_STREAM) {
       // a workspace of this call's width
       const int gw = 64 * stream_cpl(k, nitems, P->fp32);
@@ -2616,18 +2626,13 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       else
         s = alloc_stream_work(P, Bp, W, &buf);
       if (s == RAFEAST_OK) {
-        const std::vector<double> zc = stream_shifts(nz, z, k, Bp);
+        zc = stream_shifts(nz, z, k, Bp);
         e = hipMemcpyAsync(W.zc, zc.data(), zc.size() * sizeof(double), hipMemcpyHostToDevice,
                            P->st);
         if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve shifts");
       }
       if (s == RAFEAST_OK) s = run_stream(P, W, nz, k, B, ldb, X, nz * k, tol, d_it, d_rs);
-      if (s == RAFEAST_OK) {
-        e = hipStreamSynchronize(P->st);
-        if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
-      }
     } else {
-      std::vector<int> of;
       TeamWork T;
       if (P->teams_ok && P->fp32)
         T.nteam = cocg_plan_teams(items, z, P->sig_lo, P->sig_hi, P->num_cu, P->sell.wave_rpt, of,
@@ -2646,10 +2651,6 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       }
       if (s == RAFEAST_OK)
         s = run_cocg(P, nitems, d_items, d_z, k, B, ldb, X, nz * k, tol, d_it, d_rs, T);
-      if (s == RAFEAST_OK && T.nteam > 0) {  // `of` is still being read
-        e = hipStreamSynchronize(P->st);
-        if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
-      }
     }
     if (s == RAFEAST_OK && iters) {
       e = hipMemcpyAsync(iters, d_it, nitems * sizeof(int), hipMemcpyDeviceToHost, P->st);
@@ -2660,7 +2661,7 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
       if (e != hipSuccess) s = hip_fail(P, e, "copy residuals");
     }
     if (s == RAFEAST_OK) {
-      e = hipStreamSynchronize(P->st);
+      e = buf.wait();
       if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve");
     }
   }
@@ -3065,7 +3066,7 @@ rafeast_status rafeast_pc_samples(rafeast_plan_t P, int32_t nz, const double* z,
               -1.0));
   HIPCHK(P, launch_pc_gram_assemble(P->st, n, k, T, nz, dz, a, b, theta_lo, theta_hi, part,
                                     nchunks, X, G, h, rr));
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  HIPCHK(P, buf.wait());
   return RAFEAST_OK;
 }
 
@@ -3077,7 +3078,7 @@ rafeast_status rafeast_pc_forward(rafeast_plan_t P, int32_t ns, const double* X,
   HIPCHK(P, buf.get(&wb, mlp_param_count()));
   HIPCHK(P, launch_mlp_bf16(P->st, W, wb));
   HIPCHK(P, launch_mlp_forward(P->st, ns, X, wb, Y));
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  HIPCHK(P, buf.wait());
   return RAFEAST_OK;
 }
 
@@ -3085,6 +3086,9 @@ rafeast_status rafeast_pc_gradient(rafeast_plan_t P, int32_t ns, const double* X
                                    const double* h, const double* rr, const float* W, float* grad,
                                    double* loss) {
   if (!P || !X || !G || !h || !rr || !W || !grad || ns < 1) return RAFEAST_INVALID_ARG;
+  std::vector<int> order(ns);
+  for (int i = 0; i < ns; ++i) order[i] = i;
+  double hl = 0.0;
   DevBuf buf(P);
   float *wb = nullptr, *part = nullptr;
   double *lpart = nullptr, *dl = nullptr;
@@ -3095,14 +3099,11 @@ rafeast_status rafeast_pc_gradient(rafeast_plan_t P, int32_t ns, const double* X
   HIPCHK(P, buf.get(&lpart, waves));
   HIPCHK(P, buf.get(&dl, 1));
   HIPCHK(P, buf.get(&idx, ns));
-  std::vector<int> order(ns);
-  for (int i = 0; i < ns; ++i) order[i] = i;
   HIPCHK(P, hipMemcpyAsync(idx, order.data(), ns * sizeof(int), hipMemcpyHostToDevice, P->st));
   HIPCHK(P, launch_mlp_bf16(P->st, W, wb));
   HIPCHK(P, launch_mlp_grad(P->st, ns, idx, X, G, h, rr, wb, part, lpart, grad, dl));
-  double hl = 0.0;
   HIPCHK(P, hipMemcpyAsync(&hl, dl, sizeof(double), hipMemcpyDeviceToHost, P->st));
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  HIPCHK(P, buf.wait());
   if (loss) *loss = hl;
   return RAFEAST_OK;
 }
@@ -3140,7 +3141,7 @@ rafeast_status rafeast_pc_train(rafeast_plan_t P, int32_t ns, const double* X, c
   }
   if (loss)
     HIPCHK(P, hipMemcpyAsync(loss, dl, steps * sizeof(double), hipMemcpyDeviceToHost, P->st));
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  HIPCHK(P, buf.wait());
   return RAFEAST_OK;
 }
 
@@ -3187,6 +3188,7 @@ rafeast_status rafeast_pc_harvest(rafeast_plan_t P, int32_t nsteps, const int32_
       s0 += 2 * m0;
     }
   }
+  HIPCHK(P, buf.wait());
   *count = (int32_t)s0;
   return RAFEAST_OK;
 }
