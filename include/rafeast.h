@@ -383,7 +383,8 @@ rafeast_status rafeast_gram_noalloc(void* hip_stream, int64_t n, int32_t k1, int
  * M N == 0); beta == 0 does not read C.  A long inner
  * dimension with few output tiles is split into chunks summed in a fixed
  * order in a workspace that the library keeps for later calls (64 MiB per
- * device at most; see rafeast_destroy).  Runs on hip_stream
+ * device at most; see rafeast_destroy); without memory for it the product
+ * runs in one piece.  Runs on hip_stream
  * (nullable: the null stream) and waits for it.  Errors: INVALID_ARG for null
  * pointers, negative sizes, short leading dimensions or another precision;
  * OOM; DEVICE. */

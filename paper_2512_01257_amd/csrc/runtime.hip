@@ -2497,7 +2497,7 @@ rafeast_status rafeast_gemm(void* hip_stream, int32_t precision, int32_t a_cols,
   const bool f64 = precision == RAFEAST_FP64;
   const size_t es = f64 ? sizeof(double) : sizeof(float);
   // room for the chunk slabs the launcher will choose
-  const size_t room = gemm_work_elems(f64, M, N, K);
+  size_t room = gemm_work_elems(f64, M, N, K);
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm: device");
@@ -2505,7 +2505,10 @@ rafeast_status rafeast_gemm(void* hip_stream, int32_t precision, int32_t a_cols,
   char* work = nullptr;
   if (room) {
     e = buf.get(&work, room * es);
-    if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gemm: workspace");
+    if (e == hipErrorOutOfMemory)
+      room = 0;  // the inner dimension in one piece
+    else if (e != hipSuccess)
+      return hip_fail(nullptr, e, "rafeast_gemm: workspace");
   }
   e =
       f64 ? launch_gemm_f64(st, a_cols, M, N, K, (const double*)A, lda, (const double*)B, ldb,

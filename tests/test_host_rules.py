@@ -12,16 +12,19 @@ from tests.test_kernel_structure import _hipcc
 pytestmark = pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
 
 
-def run(tmp_path, body):
-    """Compiles body as main's text, links the library and returns its output lines."""
+def run(tmp_path, body, before=""):
+    """Compiles body as main's text, links the library and returns its output lines.
+    before: definitions, of HIP functions among others: the program's own take
+    the place of the runtime's in the library, too."""
     from paper_2512_01257_amd import build
 
     src = tmp_path / "rule.cpp"
-    src.write_text('#include "kernels.h"\n#include <cstdio>\n#include <vector>\n'
-                   "using namespace rafeast;\nint main() {\n" + body + "\nreturn 0;\n}\n")
+    src.write_text('#include "kernels.h"\n#include "../../include/rafeast.h"\n#include <cstdio>\n'
+                   "#include <vector>\nusing namespace rafeast;\n" + before +
+                   "\nint main() {\n" + body + "\nreturn 0;\n}\n")
     exe = str(tmp_path / "rule")
     cmd = [_hipcc(), "--offload-arch=gfx950", "--offload-host-only", "-std=c++17", "-I", build.CSRC,
-           "-x", "hip", str(src), "-o", exe, "-L", build.HERE, "-l:librafeast.so",
+           "-x", "hip", str(src), "-o", exe, "-rdynamic", "-L", build.HERE, "-l:librafeast.so",
            "-Wl,-rpath," + build.HERE]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-3000:]
@@ -51,3 +54,39 @@ def test_shifted_updates_take_every_row_once(tmp_path):
                 for r in range(r0, min(hi, r0 + rows_of_step)):
                     count[r] += 1
         assert count == [1] * n, (n, grid)
+
+
+# a device without memory on which every launch succeeds and does nothing
+NO_MEMORY = """
+static std::vector<dim3> grids;
+static dim3 next_grid;
+extern "C" {
+hipError_t hipMalloc(void** p, size_t) { *p = nullptr; return hipErrorOutOfMemory; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 g, dim3, size_t, hipStream_t) {
+  next_grid = g;
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+  grids.push_back(next_grid);
+  return hipSuccess;
+}
+}
+"""
+
+
+@pytest.mark.parametrize("m,n,k", [(602, 350, 1391), (300, 24, 4096), (64, 32, 300)])
+def test_gemm_runs_unsplit_without_memory(tmp_path, m, n, k):
+    # split for speed where there is room, in one launch of one chunk where not
+    out = run(tmp_path, f"""
+  std::printf("%zu\\n", gemm_work_elems(true, {m}, {n}, {k}));
+  double* p = reinterpret_cast<double*>(4096);
+  int s = rafeast_gemm(nullptr, RAFEAST_FP64, 1, {m}, {n}, {k}, p, {m}, p, {n}, p, {n}, 1.0, 0.0);
+  std::printf("%d %zu %u\\n", s, grids.size(), grids.empty() ? 0 : grids[0].z);
+""", NO_MEMORY)
+    assert int(out[0]) > 0
+    assert out[1] == "0 1 1"  # OK, one launch, one chunk
