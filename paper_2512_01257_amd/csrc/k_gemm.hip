@@ -9,8 +9,8 @@
 // waves own 64 x 16 TN quarters, 4 x TN MFMA tiles of 16 x 16 each, so every
 // operand fragment read from LDS feeds several MFMAs (TN = 4 in FP32, 2 in
 // FP64).  The inner dimension advances in
-// steps of 16: the step's A (128 x 16) and B (16 x 128) panels are staged in
-// LDS (two buffers; the next step's global loads are issued before the
+// steps of BK, 32 in FP32 and 16 in FP64: the step's A (128 x BK) and B (BK x
+// 32 TN) panels are staged in LDS (two buffers; the next step's global loads are issued before the
 // current step's MFMAs and stored after them, one barrier per step).  A may
 // be stored by rows or by columns (op(A)(i, k) at A[i lda + k] or
 // A[k lda + i]); B and C by rows.  Products with a long inner dimension and
@@ -71,8 +71,8 @@ struct Mfma<float> {
 
 // ACOL: op(A)(i, k) = A[k lda + i] (else A[i lda + k]).  BK: inner indices
 // per LDS step.  VEC: elements per global load along each operand's
-// contiguous dimension (the host takes VEC > 1 only when the operands'
-// addresses and leading dimensions are multiples of VEC elements).  part != nullptr:
+// contiguous dimension (VEC > 1 asks for no alignment of the operands; the host
+// takes it unless C is smaller than a tile and cuts vectors).  part != nullptr:
 // chunk z covers inner indices [z kc, min(K, (z + 1) kc)) and its
 // raw product goes to part + z M N (row-major, ld N); otherwise C is written.
 template <typename T, bool ACOL, int BK, int VEC, int TN>
@@ -388,15 +388,13 @@ hipError_t gemm(hipStream_t st, bool acol, int M, int N, int K, const T* A, int6
   T* part = S > 1 ? work : nullptr;
   dim3 grid((N + BN - 1) / BN, (M + kBM - 1) / kBM, S);
   // Vector loads, also of rows that start between 16-byte boundaries (us with
-  // element and vector loads: FP32 8191 x 480 x 8191 1850 and 609, 883 x 101 x 883
-  // 43 and 39; FP64 5003 x 334 x 4002 912 and 462), unless C is smaller than a
-  // tile and cuts vectors.
+  // element and vector loads: FP32 8191 x 480 x 8191 1850 and 609; FP64 5003 x
+  // 334 x 4002 912 and 425), unless C is smaller than a tile and cuts vectors:
+  // no step of the vector form is whole then (us with vector and element form,
+  // aligned operands: FP32 4096 x 30 x 4096 78 and 43, 4096 x 126 x 4096 130 and
+  // 75; FP64 3000 x 17 x 1500 53 and 43).
   constexpr int V = kGemmVecBytes / (int)sizeof(T) > 0 ? kGemmVecBytes / (int)sizeof(T) : 1;
-  const bool aligned = lda % V == 0 && ldb % V == 0 &&
-                       reinterpret_cast<uintptr_t>(A) % (V * sizeof(T)) == 0 &&
-                       reinterpret_cast<uintptr_t>(B) % (V * sizeof(T)) == 0;
-  const bool whole = (N >= BN || N % V == 0) && (!acol || M >= kBM || M % V == 0);
-  const bool vec = V > 1 && (aligned || whole);
+  const bool vec = V > 1 && (N >= BN || N % V == 0) && (!acol || M >= kBM || M % V == 0);
   hipError_t e;
   if (TN == 1)
     e = launch_tiles<T, BK, 1>(st, acol, vec, grid, M, N, K, kc, A, lda, B, ldb, C, ldc, alpha,

@@ -59,6 +59,7 @@ def test_shifted_updates_take_every_row_once(tmp_path):
 # a device without memory on which every launch succeeds and does nothing
 NO_MEMORY = """
 static std::vector<dim3> grids;
+static std::vector<const void*> kernels;
 static dim3 next_grid;
 extern "C" {
 hipError_t hipMalloc(void** p, size_t) { *p = nullptr; return hipErrorOutOfMemory; }
@@ -71,7 +72,8 @@ hipError_t __hipPushCallConfiguration(dim3 g, dim3, size_t, hipStream_t) {
   return hipSuccess;
 }
 hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
+  kernels.push_back(f);
   grids.push_back(next_grid);
   return hipSuccess;
 }
@@ -90,3 +92,21 @@ def test_gemm_runs_unsplit_without_memory(tmp_path, m, n, k):
 """, NO_MEMORY)
     assert int(out[0]) > 0
     assert out[1] == "0 1 1"  # OK, one launch, one chunk
+
+
+@pytest.mark.parametrize("f64", [0, 1])
+@pytest.mark.parametrize("m,n,a_cols", [(512, 29, 0), (512, 29, 1), (97, 64, 1), (97, 27, 1)])
+def test_gemm_takes_vectors_only_where_none_is_cut(tmp_path, f64, m, n, a_cols):
+    # C is smaller than a tile and cuts a vector: the vector form has no whole
+    # step, and alignment of the operands does not change that
+    prec = "RAFEAST_FP64" if f64 else "RAFEAST_FP32_REFINED"
+    out = run(tmp_path, f"""
+  const int lda[2] = {{600, 601}}, ldb[2] = {{128, 129}};
+  for (int i = 0; i < 2; ++i) {{
+    void* p = reinterpret_cast<void*>(4096 + i * {8 if f64 else 4});
+    std::printf("%d\\n", rafeast_gemm(nullptr, {prec}, {a_cols}, {m}, {n}, 100, p, lda[i], p,
+                                       ldb[i], p, {n}, 1.0, 0.0));
+  }}
+  std::printf("%zu %d\\n", kernels.size(), kernels.size() == 2 && kernels[0] == kernels[1]);
+""", NO_MEMORY)
+    assert out == ["0", "0", "2 1"]
