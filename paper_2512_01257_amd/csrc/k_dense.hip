@@ -345,23 +345,42 @@ int gram_chunks(int64_t n) {
 // Largest k of the symmetric kernel (its tiles: 12 x 13 / 2).
 constexpr int kSymMaxK = 192;
 
-size_t gram_chunk_doubles(int k1, int k2) {
-  const size_t all = (size_t)k1 * (size_t)k2;
-  if (k1 != k2 || k1 > kSymMaxK) return all;
-  const size_t nt = (k1 + 15) / 16, tiles = nt * (nt + 1) / 2 * 256;
-  return all > tiles ? all : tiles;
+// Whether the Gram of one block (same: X is Y) takes the symmetric kernel.  It
+// reads X once and computes half the tiles, but has one workgroup a row chunk: up
+// to two tiles a row its waves have too little to do on many rows, and from five
+// on a chunk's tiles one after the other take longer than the general kernel's
+// side by side while those leave CUs idle.  us, general and symmetric, at
+// k = 1: n = 16,000 28, 28; 64,000 32, 36; 1e6 73, 139
+// k = 16: n = 128,000 44, 42; 250,000 55, 56; 1e6 93, 134
+// k = 64: n = 3,000 27, 28; 32,000 51, 37; 1e6 259, 148
+// k = 84: n = 1,000 26, 28; 4,000 29, 30; 8,000 34, 32; 1e6 585, 247
+// k = 128: n = 1,000 26, 33; 8,000 36, 38; 16,000 50, 39; 1e6 1126, 460
+// k = 192: n = 500 29, 41; 8,000 48, 50; 16,000 70, 58; 500,000 951, 484
+static bool gram_symmetric(int64_t n, int k1, int k2, bool same) {
+  if (!same || k1 != k2 || k1 > kSymMaxK) return false;
+  if (k1 <= 32) return n <= (k1 <= 3 ? 1 << 14 : 1 << 17);
+  return k1 <= 64 || n > (k1 <= 96 ? 4096 : 8192);
 }
 
-// Row chunks of X^T Y, or of X^T X (sym), whose workgroups hold all tiles of
-// a chunk: two per CU, from chunks of 64 rows on.
-int gram_chunks_of(int64_t n, int k1, int k2, bool sym) {
-  if (!sym || k1 != k2 || k1 > kSymMaxK) return gram_chunks(n);
+// Partial doubles of one row chunk: the symmetric kernel's tiles, or the product.
+size_t gram_chunk_doubles(int64_t n, int k1, int k2, bool same) {
+  const size_t nt = (k1 + 15) / 16;
+  return gram_symmetric(n, k1, k2, same) ? nt * (nt + 1) / 2 * 256 : (size_t)k1 * (size_t)k2;
+}
+
+// Row chunks: of the symmetric kernel, whose workgroups hold all tiles of a
+// chunk, two per CU, from chunks of 64 rows on.
+int gram_chunks_of(int64_t n, int k1, int k2, bool same) {
+  if (!gram_symmetric(n, k1, k2, same)) return gram_chunks(n);
   const int64_t c = (n + 63) / 64;
   return (int)(c > 512 ? 512 : c < 1 ? 1 : c);
 }
 
+// Enough for X^T Y and for X^T X.
 size_t gram_partial_doubles(int64_t n, int k1, int k2) {
-  return (size_t)gram_chunks_of(n, k1, k2, true) * gram_chunk_doubles(k1, k2);
+  const size_t two = gram_chunks_of(n, k1, k2, false) * gram_chunk_doubles(n, k1, k2, false);
+  const size_t one = gram_chunks_of(n, k1, k2, true) * gram_chunk_doubles(n, k1, k2, true);
+  return two > one ? two : one;
 }
 
 // A workgroup owns a TA x TB block of 16 x 16 output tiles of one row chunk;
@@ -676,15 +695,15 @@ hipError_t launch_gram_chunks(hipStream_t st, int64_t n, int k1, int k2, const d
                               int chunks) {
   if (k1 <= 0 || k2 <= 0) return hipSuccess;
   if (chunks < 1) chunks = 1;
-  const int most = gram_chunks_of(n, k1, k2, X == Y && ldx == ldy);
+  const bool same = X == Y && ldx == ldy;
+  const int most = gram_chunks_of(n, k1, k2, same);
   if (chunks > most) chunks = most;
   int64_t rpc = (n + chunks - 1) / chunks;
   rpc = (rpc + 3) & ~int64_t(3);
   // a chunk's rows are addressed through 32-bit buffer offsets
   if (rpc * (int64_t)(ldx > ldy ? ldx : ldy) * 8 > (int64_t)INT32_MAX) return hipErrorInvalidValue;
   const int ta_n = (k1 + 15) / 16, tb_n = (k2 + 15) / 16;
-  if (X == Y && ldx == ldy && k1 == k2 && k1 <= kSymMaxK &&
-      rpc * (int64_t)ldx * 8 < (int64_t)kOutside) {
+  if (gram_symmetric(n, k1, k2, same)) {
     // waves and tiles per wave by the tile count: 10, 21, 45, 78 at k = 64, 96,
     // 144, 192; shorter stages where a row is long, so that two workgroups fit
     hipError_t e;

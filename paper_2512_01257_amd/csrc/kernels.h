@@ -22,14 +22,15 @@ hipError_t launch_spmm_f64(hipStream_t st, int n, int k, const int* rowptr, cons
 // ---- tall-skinny products (FP64 MFMA) ----------------------------------------
 // Number of row chunks the Gram splits n into, and the partial buffer it needs.
 int gram_chunks(int64_t n);
-int gram_chunks_of(int64_t n, int k1, int k2, bool sym);
-size_t gram_chunk_doubles(int k1, int k2);  // of one row chunk
+// The same for X^T Y, or for X^T X (same), and the partial doubles of one chunk.
+int gram_chunks_of(int64_t n, int k1, int k2, bool same);
+size_t gram_chunk_doubles(int64_t n, int k1, int k2, bool same);
 size_t gram_partial_doubles(int64_t n, int k1, int k2);
 // G = X^T Y; `part` holds gram_partial_doubles(n, k1, k2) doubles.
 hipError_t launch_gram(hipStream_t st, int64_t n, int k1, int k2, const double* X, int ldx,
                        const double* Y, int ldy, double* G, int ldg, double* part);
 // The same with an explicit number of row chunks (clamped to [1, gram_chunks_of()]);
-// `part` holds chunks * gram_chunk_doubles(k1, k2) doubles.
+// `part` holds chunks * gram_chunk_doubles() doubles.
 hipError_t launch_gram_chunks(hipStream_t st, int64_t n, int k1, int k2, const double* X,
                               int ldx, const double* Y, int ldy, double* G, int ldg, double* part,
                               int chunks);

@@ -2112,7 +2112,9 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   PRCHK(dalloc(P, &P->d_gamma, 2 * (size_t)P->nc * P->m0, "gamma"));
   PRCHK(dalloc(P, &P->d_info, 4, "info"));
   PRCHK(dalloc(P, &P->d_zw, 4 * P->nc, "zw"));
-  P->part_doubles = std::max(gram_partial_doubles(n, w, w), (size_t)2 * w * gram_chunks(n));
+  P->part_doubles = std::max(std::max(gram_partial_doubles(n, w, w),
+                                      gram_partial_doubles(n, P->m0, P->m0)),
+                             (size_t)2 * w * gram_chunks(n));
   PRCHK(dalloc(P, &P->d_part, P->part_doubles, "partials"));
   const size_t cs = fp32 ? 2 * sizeof(float) : 2 * sizeof(double);
   // the solutions of one filter step (the multi-shift engine combines them
@@ -2429,7 +2431,11 @@ rafeast_status rafeast_gram(rafeast_plan_t P, int64_t n, int32_t k1, int32_t k2,
 // its own address, which hipGetSymbolAddress returns once per device (in host
 // code the array's name is not a device address).
 // ----------------------------------------------------------------------------
-constexpr size_t kGramScratchDoubles = size_t(1) << 21;  // 16 MiB per device
+constexpr size_t kGramMostDoubles = size_t(1) << 21;  // of a product, and of X^T Y's chunks
+// X^T X needs room for 512 chunks of 21 tiles to have rafeast_gram's chunks up to
+// 96 columns (21 MiB per device)
+constexpr size_t kGramScratchDoubles = 512 * 21 * 256;
+static_assert(kGramScratchDoubles >= kGramMostDoubles);
 static __device__ __align__(256) double scratch[kGramScratchDoubles];
 
 namespace {
@@ -2466,18 +2472,19 @@ rafeast_status rafeast_gram_noalloc(void* hip_stream, int64_t n, int32_t k1, int
   if (!X || !Y || !G || n < 1 || k1 < 1 || k2 < 1 || ldx < k1 || ldy < k2 || ldg < k2)
     return fail(nullptr, RAFEAST_INVALID_ARG, "rafeast_gram_noalloc: bad argument");
   const size_t tile = (size_t)k1 * (size_t)k2;
-  if (tile > kGramScratchDoubles)
+  if (tile > kGramMostDoubles)
     return fail(nullptr, RAFEAST_INVALID_ARG,
                 "rafeast_gram_noalloc: k1 * k2 = " + std::to_string(tile) +
-                    " exceeds the scratch of " + std::to_string(kGramScratchDoubles) +
+                    " exceeds the scratch of " + std::to_string(kGramMostDoubles) +
                     " doubles");
   double* part = nullptr;
   hipError_t e = gram_scratch(&part);
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gram_noalloc: scratch address");
   // as many row chunks as rafeast_gram uses when they fit, fewer otherwise
-  const int chunks = (int)std::min<size_t>(
-      (size_t)gram_chunks_of(n, k1, k2, X == Y && ldx == ldy),
-      kGramScratchDoubles / gram_chunk_doubles(k1, k2));
+  const bool same = X == Y && ldx == ldy;
+  const size_t chunk = gram_chunk_doubles(n, k1, k2, same);
+  const int chunks = (int)std::min<size_t>((size_t)gram_chunks_of(n, k1, k2, same),
+                                           (same ? kGramScratchDoubles : kGramMostDoubles) / chunk);
   e = launch_gram_chunks(static_cast<hipStream_t>(hip_stream), n, k1, k2, X, ldx, Y, ldy, G, ldg,
                          part, chunks);
   if (e != hipSuccess) return hip_fail(nullptr, e, "rafeast_gram_noalloc: launch");
