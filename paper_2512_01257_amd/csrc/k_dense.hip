@@ -275,19 +275,35 @@ __global__ __launch_bounds__(256) void k_spmm_f64_x2(int n, int k, int rbx, int 
 hipError_t launch_spmm_f64(hipStream_t st, int n, int k, const int* rowptr, const int* col,
                            const double* val, int64_t nnz, const double* X, int ldx, double* Y,
                            int ldy, double alpha, double beta, const double* X2, int ldx2,
-                           double gamma) {
+                           double gamma, int64_t span) {
   if (n <= 0 || k <= 0) return hipSuccess;
-  // Odd widths of 33 to 63, and above 128 on few rows: a pass over column pairs
-  // has half its lanes or more idle, and the rows start between 16-byte
-  // boundaries; one column per lane is as fast or faster (us, pairs and single
-  // columns: 3D neighbour graph of 9,402 points, k = 63: 28.7, 26.1; k = 147:
-  // 47.3, 45.3; of 50,000, k = 33: 60.8, 56.3; 2D of 30,000, k = 63: 44.3, 43.0;
-  // 40^3 grid, k = 33: 37.5, 39.1; but 2D of 30,000, k = 147: 84.6, 90.4, and 3D
-  // of 50,000: 200, 211).
-  const bool single = k % 2 == 1 && ((k > 32 && k < 64) || (k > 128 && n < 16384));
+  // Column pairs, or one column a lane.  With odd k the rows of pairs start
+  // between 16-byte boundaries and a pass may have half its lanes idle, and one
+  // column a lane is as fast or faster (us, pairs and single columns)
+  // - for widths of 33 to 63: 3D neighbour graph of 50,000 points, k = 33: 60.8,
+  //   56.3; 2D of 30,000, k = 63: 44.3, 43.0; 40^3 grid, k = 33: 37.5, 39.1;
+  // - above 64 and 128 on rows of a few entries: tridiagonal n = 64,000, k = 65:
+  //   50, 45; k = 119: 54, 52; k = 129: 68, 58; k = 161: 71, 64 (seven entries:
+  //   55, 59; 62, 72; 79, 83; 83, 92); n = 250,000, k = 73: 135, 133; k = 81:
+  //   138, 146;
+  // - above 128 on fewer than 16,384 rows (3D neighbour graph of 9,402 points,
+  //   k = 147: 47.3, 45.3), and on long rows whose gathers stay in an XCD's L2,
+  //   the longer the rows the wider: n = 64,000, k = 137: 13 entries within 40 of
+  //   the diagonal 119, 108; 40 within 120 266, 236; in random order 451, 477;
+  //   k = 191: 20 entries 178, 191; 70 470, 427.
+  const int64_t len = nnz / n;  // entries a row
+  const bool near = (2 * span + 1) * k * 8 <= (3 << 20);  // of 4 MiB
+  const bool single =
+      k % 2 == 1 &&
+      ((k > 32 && k < 64) || (k > 64 && k < (n <= 1 << 17 ? 120 : 80) && len < 4) ||
+       (k > 128 && n < 16384) || (k > 128 && k < 192 && len < 4) ||
+       (k > 128 && k < 160 + (len < 32 ? len : 32) && len > 10 && near));
   if (nnz > 0 && k >= 2 && !single) {
-    // lanes per row: the power of two covering the column pairs (<= 64)
-    int L = 1;
+    // lanes per row: the power of two covering the column pairs (<= 64); on few
+    // rows eight at least, which take eight entries a round (us with as few as
+    // cover the pairs and with eight, k = 3: 4,000 rows of 70 entries 43, 29;
+    // 16,000 rows of 7 23, 22)
+    int L = n <= 16384 ? 8 : 1;
     while (L < 64 && 2 * L < k) L *= 2;
     const int rw = 64 / L;
     const int rblocks = (n + 4 * rw - 1) / (4 * rw);

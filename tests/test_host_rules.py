@@ -110,3 +110,34 @@ def test_gemm_takes_vectors_only_where_none_is_cut(tmp_path, f64, m, n, a_cols):
   std::printf("%zu %d\\n", kernels.size(), kernels.size() == 2 && kernels[0] == kernels[1]);
 """, NO_MEMORY)
     assert out == ["0", "0", "2 1"]
+
+
+def test_spmm_form(tmp_path):
+    # the one-column form (the kernel that a single column takes) or the number of
+    # workgroups of the two-column one, for (rows, entries a row, span, columns)
+    cases = {(20000, 3, 1, 65): "one", (20000, 3, 1, 119): "one", (20000, 3, 1, 121): "pairs",
+             (20000, 5, 2, 65): "pairs", (20000, 3, 1, 129): "one", (20000, 3, 1, 66): "pairs",
+             (250000, 3, 1, 73): "one", (250000, 3, 1, 81): "pairs", (20000, 3, 1, 193): "pairs",
+             (64000, 40, 120, 137): "one", (64000, 40, 60000, 137): "pairs",
+             (64000, 40, 120, 191): "one", (64000, 40, 120, 193): "pairs",
+             (64000, 20, 60, 191): "pairs", (64000, 7, 1600, 147): "pairs",
+             (9402, 19, 9000, 147): "one", (50000, 19, 49000, 33): "one",
+             # eight lanes a row on few rows: 32 rows a workgroup
+             (4000, 67, 3900, 3): 128, (4000, 67, 3900, 2): 128, (16384, 70, 200, 5): 512,
+             (16385, 70, 200, 5): 264, (16385, 70, 200, 9): 520}
+    calls = "".join(f"""
+  launch_spmm_f64(nullptr, {n}, {k}, nullptr, nullptr, nullptr, {n * d}LL, nullptr, {k}, nullptr,
+                  {k}, 1.0, 0.0, nullptr, 0, 0.0, {s});""" for n, d, s, k in cases)
+    out = run(tmp_path, """
+  launch_spmm_f64(nullptr, 100, 1, nullptr, nullptr, nullptr, 100, nullptr, 1, nullptr, 1, 1.0,
+                  0.0, nullptr, 0, 0.0, 0);""" + calls + """
+  for (size_t i = 1; i < kernels.size(); ++i)
+    std::printf("%d %u\\n", kernels[i] == kernels[0], grids[i].x);
+""", NO_MEMORY)
+    assert len(out) == len(cases)
+    for line, (case, want) in zip(out, cases.items()):
+        one, grid = map(int, line.split())
+        if want in ("one", "pairs"):
+            assert bool(one) == (want == "one"), case
+        else:
+            assert not one and grid == want, (case, grid)
