@@ -308,12 +308,17 @@ hipError_t launch_spmm_f64(hipStream_t st, int n, int k, const int* rowptr, cons
     const int rw = 64 / L;
     const int rblocks = (n + 4 * rw - 1) / (4 * rw);
     const int rbx = (rblocks + 7) / 8;
-    // Few row blocks: one to a workgroup, so that the chip is full; many: the
-    // pipeline over several saves the start of each.  us with 1, 2 and 4 row
-    // blocks: 2,000 points of a 3D neighbour graph, k = 64: 19.4, 20.9, 24.5;
-    // 30,000 of a 2D one, k = 147: 87, 89, 93; 40^3 grid, k = 147 (16,000 row
-    // blocks): 78, 76, 79.
-    const int rpb = rblocks >= (1 << 16) ? 4 : rblocks >= (1 << 13) ? 2 : 1;
+    // Few row blocks: one to a workgroup, so that the chip is full; more: the
+    // pipeline over several saves the start of each, the sooner the shorter the
+    // rows.  us with 1, 2 and 4 row blocks: rows of 3 entries, 125 blocks
+    // (4,000 rows, k = 16) 21, 22, 23; 8,000 blocks (64,000 rows, k = 48) 41, 37,
+    // 36; 31,250 (250,000 rows, k = 34) 100, 86, 83; of 13 entries, 8,000 blocks
+    // 53, 51, 50; of 70, 2,000 blocks (8,000 rows, k = 148) 86, 96, 117; 3D
+    // neighbour graph of 2,000 points, k = 64 (250 blocks): 19.4, 20.9, 24.5;
+    // 40^3 grid, k = 147 (16,000 blocks): 78, 76, 79.
+    const int rpb = rblocks >= (1 << (len < 10 ? 15 : 16))   ? 4
+                    : rblocks >= (1 << (len < 32 ? 10 : 12)) ? 2
+                                                             : 1;
     const dim3 grid((unsigned)(8 * ((rbx + rpb - 1) / rpb)));
 #define RAFEAST_SPMM_X2(LL)                                                                     \
   hipLaunchKernelGGL(k_spmm_f64_x2<LL>, grid, dim3(256), 0, st, n, k, rbx, rpb, rowptr, col,     \

@@ -124,6 +124,7 @@ def test_spmm_form(tmp_path):
              (9402, 19, 9000, 147): "one", (50000, 19, 49000, 33): "one",
              # eight lanes a row on few rows: 32 rows a workgroup
              (4000, 67, 3900, 3): 128, (4000, 67, 3900, 2): 128, (16384, 70, 200, 5): 512,
+             (16384, 13, 200, 64): 1024, (16384, 40, 200, 64): 2048, (70000, 3, 1, 128): 8752,
              (16385, 70, 200, 5): 264, (16385, 70, 200, 9): 520}
     calls = "".join(f"""
   launch_spmm_f64(nullptr, {n}, {k}, nullptr, nullptr, nullptr, {n * d}LL, nullptr, {k}, nullptr,
