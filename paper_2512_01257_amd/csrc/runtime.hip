@@ -108,7 +108,7 @@ struct rafeast_plan_s {
   double* d_M = nullptr;     // kmax^2
   double* d_S = nullptr;     // kmax^2
   double* d_Ssel = nullptr;  // kmax * m0
-  double* d_jw = nullptr;    // jacobi_work_doubles(kmax)
+  double* d_jw = nullptr;    // jacobi_work_doubles(w)
   double* d_theta = nullptr; // kmax
   double* d_res = nullptr;   // kmax
   double* d_qn = nullptr;    // kmax
@@ -2107,7 +2107,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   PRCHK(dalloc(P, &P->d_M, kk2, "M"));
   PRCHK(dalloc(P, &P->d_S, kk2, "S"));
   PRCHK(dalloc(P, &P->d_Ssel, (size_t)kMaxSmallK * P->m0, "Ssel"));
-  PRCHK(dalloc(P, &P->d_jw, jacobi_work_doubles(kMaxSmallK), "jacobi work"));
+  PRCHK(dalloc(P, &P->d_jw, jacobi_work_doubles(w), "jacobi work"));
   PRCHK(dalloc(P, &P->d_theta, kMaxSmallK, "theta"));
   PRCHK(dalloc(P, &P->d_res, kMaxSmallK, "res"));
   PRCHK(dalloc(P, &P->d_qn, kMaxSmallK, "qn"));
@@ -2551,8 +2551,13 @@ rafeast_status rafeast_cholqr2(rafeast_plan_t P, int64_t n, int32_t k, double* Y
 rafeast_status rafeast_syev(rafeast_plan_t P, int32_t k, const double* H, double* theta,
                             double* S) {
   if (!P || !H || !theta || !S || k < 1 || k > kMaxSmallK) return RAFEAST_INVALID_ARG;
-  HIPCHK(P, launch_jacobi(P->st, k, H, k, theta, S, k, P->d_jw));
-  HIPCHK(P, hipStreamSynchronize(P->st));
+  // the plan's list of rotations is as long as its own reduced problems need
+  double* jw = P->d_jw;
+  DevBuf buf(P);
+  if (jacobi_work_doubles(k) > jacobi_work_doubles(P->w))
+    HIPCHK(P, buf.get(&jw, jacobi_work_doubles(k)));
+  HIPCHK(P, launch_jacobi(P->st, k, H, k, theta, S, k, jw));
+  HIPCHK(P, buf.wait());
   return RAFEAST_OK;
 }
 
