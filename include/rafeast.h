@@ -105,9 +105,10 @@ enum { RAFEAST_ENGINE_DIRECT = 4 };  /* precision FP64 and CSR plans only: stand
                                         Cuthill-McKee order, and every filter application
                                         solves with the factors (block L D L^T, the inverses
                                         of its 32 x 32 blocks kept).  Memory nc n (b + 1)
-                                        complex doubles for bandwidth b >= 31 (OOM when the device cannot
-                                        hold it; BREAKDOWN if a pivot vanishes).  Reports
-                                        zero COCG iterations.  Never chosen by AUTO */
+                                        complex doubles for bandwidth b (OOM when the device
+                                        cannot hold it; BREAKDOWN if a pivot vanishes); bands
+                                        below 31 are widened to 31 where that takes at most
+                                        32 GiB and fits.  Reports zero COCG iterations.  Never chosen by AUTO */
 
 /* rafeast_params.precond: preconditioner of the shifted solves. */
 enum { RAFEAST_PC_NONE = 0,       /* unpreconditioned COCG on the plan's engine */

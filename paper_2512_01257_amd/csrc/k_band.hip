@@ -14,7 +14,9 @@
 // positive definite real and imaginary parts, Math. Comp. 1998).
 //
 // Storage: per shift an n x (b + 1) complex array W, row r holding M(r, r - d)
-// in W[r][d], d = 0..b (d = 0 the diagonal; the plan keeps b >= 31).
+// in W[r][d], d = 0..b (d = 0 the diagonal).  Bands below 31 are kept at b = 31,
+// which the blocks below need, as long as that takes no more than 32 GiB and
+// fits, and at their own width, with the scalar factors, above.
 //
 // Factorization: block L D L^T in block columns (panels) of 32.  With the
 // window's rows below panel c, M21 (b x 32) and the panel's own block M11 (both
@@ -671,6 +673,190 @@ __global__ __launch_bounds__(256) void k_band_resid_fin(int nsys, int nb,
   resid[sys] = s[1] > 0.0 ? sqrt(s[0] / s[1]) : 0.0;
 }
 
+// ---------------------------------------------------------------------------
+// Bands below 31 kept at their own width (large n: at b = 31 a tridiagonal
+// matrix takes 16 times the memory): the scalar L D L^T, W[r][0] = D(r) and
+// W[r][d] = L(r, r - d), one wave a shift, and solves by substitution, a lane a
+// right-hand side.  Both are serial in the rows, so the wider form is the faster
+// one (n = 262,145, 64 shifts, 2 columns, factors and solves: 189, 196 and 234 ms
+// at b = 1, 8 and 29, this 320, 436 and 998) and is left for memory only.
+// ---------------------------------------------------------------------------
+constexpr int kRing = 32;  // rows of a ring, more than b + 1
+
+// One column a step: the window's rows c .. c + b in LDS, the update of its
+// b (b + 1) / 2 entries over the lanes, rows read eight steps ahead.
+__global__ __launch_bounds__(64) void k_narrow_factor(int n, int b, zc* __restrict__ Wall,
+                                                      size_t stride, int* __restrict__ info) {
+  __shared__ zc win[kRing][kRing + 1];  // row r in r % 32
+  __shared__ zc ms[kRing], ls[kRing];   // column c: M(c + i, c) and L(c + i, c)
+  constexpr int kAhead = 8, kPairs = 8;  // 30 * 31 / 2 entries of 64 lanes
+  const int lane = threadIdx.x, ldw = b + 1;
+  zc* __restrict__ W = Wall + (size_t)blockIdx.x * stride;
+  // this lane's entries (c + pi, c + pk), 1 <= pk <= pi <= b (pi = 0: none)
+  int pi[kPairs], pk[kPairs];
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    int e = lane + 64 * u, i = 1;
+    while (i <= b && e >= i) e -= i++;
+    pi[u] = i <= b ? i : 0;
+    pk[u] = e + 1;
+  }
+  for (int e = lane; e < kRing * (kRing + 1); e += 64) (&win[0][0])[e] = zc{0.0, 0.0};
+  __syncthreads();
+  const int first = min(n, b + 1);
+  for (int e = lane; e < first * ldw; e += 64) win[e / ldw][e % ldw] = W[e];
+  zc next[kAhead], cur[kAhead];
+  auto load = [&](int r0) {  // rows past the matrix are zeros
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      next[u] = zc{0.0, 0.0};
+      if (lane <= b && r0 + u < n) next[u] = W[(size_t)(r0 + u) * ldw + lane];
+    }
+  };
+  load(b + 1);
+  __syncthreads();
+  for (int c0 = 0; c0 < n; c0 += kAhead) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) cur[u] = next[u];
+    load(c0 + kAhead + b + 1);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int c = c0 + u;
+      if (c >= n) break;
+      const zc d = win[c % kRing][0];
+      if (!(cfinite(d) && (d.re != 0.0 || d.im != 0.0))) {
+        if (lane == 0) info[blockIdx.x] = 1 + c;
+        return;  // the same pivot in every lane
+      }
+      const zd inv = zdiv(zd{1.0, 0.0}, zd{d.re, d.im});
+      if (lane <= b) W[(size_t)c * ldw + lane] = win[c % kRing][lane];
+      if (lane >= 1 && lane <= b) {
+        zc& w = win[(c + lane) % kRing][lane];
+        const zc m = w;
+        zc l{0.0, 0.0};
+        cfma(l, m, zc{inv.re, inv.im});
+        ms[lane] = m;
+        ls[lane] = l;
+        w = l;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kPairs; ++q)
+        if (pi[q]) {
+          const zc l = ls[pi[q]];
+          cfma(win[(c + pi[q]) % kRing][pi[q] - pk[q]], zc{-l.re, -l.im}, ms[pk[q]]);
+        }
+      if (lane <= b) win[(c + b + 1) % kRing][lane] = cur[u];
+      __syncthreads();
+    }
+  }
+}
+
+// L y = b in dot products with the ring of the last rows' y, then, from the last
+// row on, x = y / D - s with s the sums L^T x that the later rows have left in
+// the ring.  Band rows go through LDS sixteen at a time, read a block ahead.
+__global__ __launch_bounds__(64) void k_narrow_solve(int n, int b, int nz,
+                                                     const zc* __restrict__ Wall, size_t stride,
+                                                     const int* __restrict__ perm,
+                                                     const double* __restrict__ B, int ldb, int k,
+                                                     zc* __restrict__ X, int64_t ldx) {
+  constexpr int kRows = 16, kPer = kRows * kRing / 64;
+  __shared__ zc ring[kRing][64];
+  __shared__ zc band[kRows][kRing];
+  const int lane = threadIdx.x, ldw = b + 1;
+  const int j = (int)blockIdx.x % nz, c = (int)blockIdx.x / nz * 64 + lane;
+  const bool on = c < k;
+  const int cc = min(c, k - 1);
+  const zc* __restrict__ W = Wall + (size_t)j * stride;
+  zc* __restrict__ Xc = X + (size_t)j * k + cc;
+  zc st[kPer];
+  int pr[kRows], pn[kRows];
+  auto load_band = [&](int r0) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = lane + 64 * u, r = r0 + e / kRing, d = e % kRing;
+      st[u] = zc{0.0, 0.0};
+      if (d <= b && r >= 0 && r < n) st[u] = W[(size_t)r * ldw + d];
+    }
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) pn[i] = perm[min(max(r0 + i, 0), n - 1)];
+  };
+  auto put_band = [&](bool inverse) {
+    __syncthreads();  // the block before has been read
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int e = lane + 64 * u;
+      zc v = st[u];
+      if (inverse && e % kRing == 0) {
+        const zd i = zdiv(zd{1.0, 0.0}, zd{v.re, v.im});  // rows past n: not used
+        v = zc{i.re, i.im};
+      }
+      band[e / kRing][e % kRing] = v;
+    }
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) pr[i] = pn[i];
+    __syncthreads();
+  };
+  auto clear = [&] {
+    for (int r = 0; r < kRing; ++r) ring[r][lane] = zc{0.0, 0.0};
+  };
+  clear();
+  double bn[kRows], bv[kRows];
+  auto load_rhs = [&] {
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) bn[i] = B[(size_t)pn[i] * ldb + cc];
+  };
+  load_band(0);
+  load_rhs();
+  for (int r0 = 0; r0 < n; r0 += kRows) {
+    put_band(false);
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) bv[i] = bn[i];
+    load_band(r0 + kRows);
+    load_rhs();
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+      const int r = r0 + i;
+      if (r >= n) break;
+      zc s[2] = {zc{0.0, 0.0}, zc{0.0, 0.0}};
+      for (int d = 1; d <= b; d += 2) {  // past b the band row is zero
+        cfma(s[0], band[i][d], ring[(r - d) & (kRing - 1)][lane]);
+        cfma(s[1], band[i][d + 1], ring[(r - d - 1) & (kRing - 1)][lane]);
+      }
+      const zc y{bv[i] - (s[0].re + s[1].re), -(s[0].im + s[1].im)};
+      ring[r & (kRing - 1)][lane] = y;
+      if (on) Xc[(size_t)pr[i] * ldx] = y;
+    }
+  }
+  clear();
+  zc yn[kRows], yv[kRows];
+  auto load_y = [&] {
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) yn[i] = on ? Xc[(size_t)pn[i] * ldx] : zc{0.0, 0.0};
+  };
+  const int last = (n - 1) / kRows * kRows;
+  load_band(last);
+  load_y();
+  for (int r0 = last; r0 >= 0; r0 -= kRows) {
+    put_band(true);
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) yv[i] = yn[i];
+    load_band(r0 - kRows);
+    load_y();
+#pragma unroll
+    for (int i = kRows - 1; i >= 0; --i) {
+      const int r = r0 + i;
+      if (r >= n) continue;
+      const zc s = ring[r & (kRing - 1)][lane];
+      zc x{-s.re, -s.im};
+      cfma(x, yv[i], band[i][0]);
+      ring[r & (kRing - 1)][lane] = zc{0.0, 0.0};
+      if (on) Xc[(size_t)pr[i] * ldx] = x;
+      for (int d = 1; d <= b; ++d) cfma(ring[(r - d) & (kRing - 1)][lane], band[i][d], x);
+    }
+  }
+}
+
 }  // namespace
 
 int band_solve_ring_rows(int b) {
@@ -679,7 +865,10 @@ int band_solve_ring_rows(int b) {
   return rows;
 }
 
-int band_width(int b) { return b < kBB - 1 ? kBB - 1 : b; }
+int band_width(int64_t n, int nz, int b) {
+  const int64_t padded = (int64_t)nz * n * kBB * (int64_t)sizeof(zc);
+  return b < kBB - 1 && padded <= (int64_t(32) << 30) ? kBB - 1 : b;
+}
 
 bool band_supported(int b) {
   return (size_t)band_solve_ring_rows(b) * kSolveCols * sizeof(zc) <= kBandSolveRingBytes;
@@ -696,10 +885,14 @@ hipError_t band_assemble(hipStream_t st, int n, int b, const int* rowptr, const 
 
 hipError_t band_factor(hipStream_t st, int n, int b, int nz, cpx<double>* W, int* info) {
   if (n <= 0 || nz <= 0) return hipSuccess;
-  if (b < kBB - 1) return hipErrorInvalidValue;
+  if (b < 0) return hipErrorInvalidValue;
   hipError_t e = hipMemsetAsync(info, 0, nz * sizeof(int), st);
   if (e != hipSuccess) return e;
   const size_t stride = (size_t)n * (b + 1);
+  if (b < kBB - 1) {
+    hipLaunchKernelGGL(k_narrow_factor, dim3(nz), dim3(64), 0, st, n, b, W, stride, info);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_band_first, dim3(nz), dim3(kStepThreads), 0, st, n, b, W, stride, info);
   // shift j of workgroup id % nz: with eight shifts a window stays in one XCD's L2
   for (int c = 0; c + kBB < n; c += kBB) {
@@ -713,6 +906,11 @@ hipError_t band_factor(hipStream_t st, int n, int b, int nz, cpx<double>* W, int
 hipError_t band_solve(hipStream_t st, int n, int b, int nz, const cpx<double>* W, const int* perm,
                       const double* B, int ldb, int k, cpx<double>* X, int64_t ldx) {
   if (n <= 0 || nz <= 0 || k <= 0) return hipSuccess;
+  if (b < kBB - 1) {
+    hipLaunchKernelGGL(k_narrow_solve, dim3((k + 63) / 64 * nz), dim3(64), 0, st, n, b, nz, W,
+                       (size_t)n * (b + 1), perm, B, ldb, k, X, ldx);
+    return hipGetLastError();
+  }
   const int ring = band_solve_ring_rows(b);
   const size_t lds = (size_t)ring * kSolveCols * sizeof(zc);
   if (lds > kBandSolveRingBytes) return hipErrorInvalidValue;

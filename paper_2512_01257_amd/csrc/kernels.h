@@ -260,11 +260,12 @@ hipError_t launch_gemm_f32(hipStream_t st, bool acol, int M, int N, int K, const
 // Band LDL^T of the shifted matrices (standard FEAST with exact solves).
 // W: nz blocks of n x (b + 1) complex, row r of block j holding
 // (z_j I - A)(r, r - d) in column d, A in engine (reverse Cuthill-McKee)
-// order; factorized in place (block columns of 32, see k_band.hip), b =
-// band_width(lower bandwidth).  info: device [nz], 0 or 1 + the row of a
-// vanishing pivot.
+// order; factorized in place: in block columns of 32 from b = 31 on, scalar
+// below.  info: device [nz], 0 or 1 + the row of a vanishing pivot.
 int band_solve_ring_rows(int b);
-int band_width(int b);  // the bandwidth the factors are stored with
+// The bandwidth that the factors of lower bandwidth b are stored with: 31 at
+// least, unless that takes more than 32 GiB.
+int band_width(int64_t n, int nz, int b);
 // whether bandwidth b fits the solve's LDS ring
 bool band_supported(int b);
 hipError_t band_assemble(hipStream_t st, int n, int b, const int* rowptr, const int* col,

@@ -156,7 +156,8 @@ struct rafeast_plan_s {
   // direct engine: band LDL^T factors of the nc shifted matrices (engine
   // order), the lower bandwidth, and the factorization's pivot report
   cpx<double>* d_band = nullptr;
-  int band_b = 0;
+  int band_lb = 0;                // the lower bandwidth
+  int band_b = 0;                 // the bandwidth the factors are stored with
   int* d_binfo = nullptr;
   float factor_ms = 0.0f;
   DenseOp dop;                    // dense operator (kind 0: A is the CSR matrix)
@@ -2070,23 +2071,30 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
         int b = 0;
         for (int64_t r = 0; r < n; ++r)
           if (srp[r + 1] > srp[r]) b = std::max<int>(b, (int)r - scl[srp[r]]);
-        b = band_width(b);
-        P->band_b = b;
+        P->band_lb = b;
         if (!band_supported(b))
           return bail(fail(P, RAFEAST_UNSUPPORTED,
                            "bandwidth " + std::to_string(b) +
                                " of the reordered matrix exceeds the direct engine's LDS "
                                "(the solve's ring of b + 32 rows)"));
-        const size_t bytes = (size_t)P->nc * (size_t)n * (size_t)(b + 1) * sizeof(cpx<double>);
+        b = band_width(n, P->nc, b);
+        auto factor_bytes = [&](int bw) {
+          return (size_t)P->nc * (size_t)n * (size_t)(bw + 1) * sizeof(cpx<double>);
+        };
         size_t fr = 0, tot = 0;
         PCHK(hipMemGetInfo(&fr, &tot));
-        if (bytes > fr / 10 * 9 && work_pool().give_back()) PCHK(hipMemGetInfo(&fr, &tot));
+        if (factor_bytes(b) > fr / 10 * 9 && work_pool().give_back())
+          PCHK(hipMemGetInfo(&fr, &tot));
+        // a narrow band at its own width where there is no room for the wider one
+        if (factor_bytes(b) > fr / 10 * 9) b = P->band_lb;
+        const size_t bytes = factor_bytes(b);
         if (bytes > fr / 10 * 9)
           return bail(fail(P, RAFEAST_OOM,
                            "the band factors need " + std::to_string(bytes >> 20) +
                                " MiB (bandwidth " + std::to_string(b) + ", " +
                                std::to_string(P->nc) + " shifts); " +
                                std::to_string(fr >> 20) + " MiB free"));
+        P->band_b = b;
         hipError_t e = dev_alloc((void**)&P->d_band, bytes);
         if (e != hipSuccess) return bail(hip_fail(P, e, "band factors"));
         PRCHK(dalloc(P, &P->d_binfo, (size_t)P->nc, "band pivot report"));
@@ -2590,11 +2598,16 @@ rafeast_status rafeast_shifted_solve(rafeast_plan_t P, int32_t nz, const double*
   } else {
     if (P->engine == RAFEAST_ENGINE_DIRECT) {
       // factorize the requested shifts into a band workspace of this call
-      const int n = (int)P->n, b = P->band_b;
+      const int n = (int)P->n;
+      int b = band_width(n, nz, P->band_lb);
       cpx<double>* Wb = nullptr;
       int* d_info = nullptr;
       double* d_part = nullptr;
       e = buf.get(&Wb, (size_t)nz * n * (b + 1));
+      if (e == hipErrorOutOfMemory && b > P->band_lb) {
+        b = P->band_lb;
+        e = buf.get(&Wb, (size_t)nz * n * (b + 1));
+      }
       if (e == hipSuccess) e = buf.get(&d_info, nz);
       if (e == hipSuccess) e = buf.get(&d_part, band_resid_doubles(n, nitems));
       if (e != hipSuccess) s = hip_fail(P, e, "shifted_solve band workspace");

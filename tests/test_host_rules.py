@@ -142,3 +142,13 @@ def test_spmm_form(tmp_path):
             assert bool(one) == (want == "one"), case
         else:
             assert not one and grid == want, (case, grid)
+
+
+def test_band_width(tmp_path):
+    # 64 shifts: widened up to 2^20 rows (32 GiB), at its own width above
+    got = run(tmp_path, """
+  for (long long n : {100LL, 1048576LL, 1048577LL, 70000000LL})
+    for (int b : {0, 1, 30, 31, 500}) std::printf("%d\\n", band_width(n, 64, b));
+""")
+    wide, own = ["31", "31", "31", "31", "500"], ["0", "1", "30", "31", "500"]
+    assert got == wide + wide + own + own
