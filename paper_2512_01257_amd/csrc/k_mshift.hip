@@ -34,7 +34,8 @@
 // iterates follow it kMsDefer iterations at a time: the seed residuals and the
 // scalars of those iterations are kept, and one pass over the directions
 // applies them all, in the same order and with the same results as a pass per
-// iteration at a quarter of its traffic.
+// iteration at a quarter of its traffic.  Where there is no memory for so many
+// residuals, a pass per iteration it is.
 //
 // Layout: engine rows in the streaming engine's reverse Cuthill-McKee order,
 // blocks n x kp row-major (kp = 64 CPL, column c of lane c / CPL); the seed
@@ -335,8 +336,9 @@ __global__ __launch_bounds__(kFT) void k_ms_fin_alpha(int kp, int k, int nz, int
   }
 }
 
-// r_{k+1} = r_k - alpha w into the next slot, partials of its r^T r.
-template <int CPL>
+// r_{k+1} = r_k - alpha w into the next slot, or over r_k (INPLACE: there is one
+// slot, and rnext is it), partials of its r^T r.
+template <int CPL, bool INPLACE>
 __global__ __launch_bounds__(kMT) void k_ms_rupd(int n, int kp, MsCols cols,
                                                  const double* __restrict__ r,
                                                  double* __restrict__ rnext,
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(kMT) void k_ms_rupd(int n, int kp, MsCols cols,
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
       if (!on[q]) continue;
-      const double rn = r[o + q] - alpha[q] * w[o + q];
+      const double rn = (INPLACE ? rnext : r)[o + q] - alpha[q] * w[o + q];
       rnext[o + q] = rn;
       acc[q] += rn * rn;
     }
@@ -764,22 +766,26 @@ hipError_t run_ms_t(hipStream_t st, const StreamMatrix& A, const MsWork& W, cons
   };
   int live = 0, it = 0;
   MCHK(census(live));
-  // seed residual r_k in slot k mod kMsDefer of W.r
+  // seed residual r_k in slot k mod W.defer of W.r
   for (; it < L.maxit && live > 0; ++it) {
-    const int slot = it % kMsDefer;
+    const int slot = it % W.defer;
     double* r = W.r + slot * rblk;
     MLAUNCH((k_ms_pupd<CPL>), grid, blk, 0, st, n, kp, W.cols, r, W.p);
     MLAUNCH((k_ms_spmv<CPL>), grid, blk, 0, st, n, kp, A.rowptr, A.col, A.val64, L.seed,
             W.cols.colive, W.p, W.w, W.part);
     MLAUNCH(k_ms_fin_alpha, fg, fb, 0, st, kp, k, nz, nb, slot, W.part, W.sig, L.g, W.cols);
-    if (slot == kMsDefer - 1) MCHK(shift_pass(st, n, kMsDefer, W, nz, comb));
-    MLAUNCH((k_ms_rupd<CPL>), grid, blk, 0, st, n, kp, W.cols, r,
-            W.r + (it + 1) % kMsDefer * rblk, W.w, W.part);
+    if (slot == W.defer - 1) MCHK(shift_pass(st, n, W.defer, W, nz, comb));
+    if (W.defer > 1)
+      MLAUNCH((k_ms_rupd<CPL, false>), grid, blk, 0, st, n, kp, W.cols, r,
+              W.r + (it + 1) % W.defer * rblk, W.w, W.part);
+    else
+      MLAUNCH((k_ms_rupd<CPL, true>), grid, blk, 0, st, n, kp, W.cols, (const double*)nullptr, r,
+              W.w, W.part);
     MLAUNCH(k_ms_fin_beta, fg, fb, 0, st, kp, nz, nb, W.part, L.tol, L.maxit, W.cols);
     if ((it + 1) % L.chunk == 0 || it + 1 == L.maxit) MCHK(census(live));
   }
   // iterations since the last pass: their residuals are still in slots 0, 1, ...
-  if (it % kMsDefer) MCHK(shift_pass(st, n, it % kMsDefer, W, nz, comb));
+  if (it % W.defer) MCHK(shift_pass(st, n, it % W.defer, W, nz, comb));
   if (comb) {
     MLAUNCH((k_ms_out_y<CPL>), grid, blk, 0, st, n, k, kp, nz, A.perm, yb, L.g, L.Qin, L.ldqin,
             L.Qt, L.ldq);
@@ -810,6 +816,7 @@ hipError_t run_ms_t(hipStream_t st, const StreamMatrix& A, const MsWork& W, cons
 
 hipError_t run_mshift(hipStream_t st, const StreamMatrix& A, const MsWork& W, const MsLaunch& L) {
   if (L.k < 1 || L.nz < 1 || L.k > W.kp || W.kp != ms_padded(L.k) || L.nz > W.nz || !A.val64 ||
+      W.defer < 1 || W.defer > kMsDefer ||
       W.nb != ms_blocks(A.n, W.num_cu) || L.chunk < 1)
     return hipErrorInvalidValue;
   if (L.g ? (!W.y || !L.Qt || L.ldq < L.k || (L.Qin && L.ldqin < L.k))

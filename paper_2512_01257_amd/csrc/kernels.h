@@ -384,11 +384,12 @@ struct MsCols {                  // per column kp entries; per (j, c) nz x kp en
   cpx<double>* sc = nullptr;
   int* on = nullptr;
 };
-// Seed iterations whose shifted updates are applied in one pass.
+// Seed iterations whose shifted updates are applied in one pass, at most.
 constexpr int kMsDefer = 4;
 struct MsWork {
   int kp = 0, nz = 0, nb = 0, num_cu = 0;  // nz: the most shifts this workspace holds
-  double* r = nullptr;           // kMsDefer n x kp blocks: the last seed residuals
+  int defer = kMsDefer;          // iterations a pass (kMsDefer, or 1)
+  double* r = nullptr;           // defer n x kp blocks: the last seed residuals
   double* p = nullptr;           // n x kp seed blocks
   double* w = nullptr;
   cpx<double>* X = nullptr;      // nz blocks n x kp: shifted iterates

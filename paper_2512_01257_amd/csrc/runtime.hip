@@ -778,7 +778,6 @@ rafeast_status alloc_ms_work(rafeast_plan_s* P, int nz, int k, MsWork& W,
   W.num_cu = P->num_cu;
   W.nb = ms_blocks((int)n, P->num_cu);
   const size_t blk = (size_t)n * W.kp, cs = (size_t)nz * W.kp;
-  RCHK(get((void**)&W.r, kMsDefer * blk * sizeof(double), "multi-shift r"));
   RCHK(get((void**)&W.p, blk * sizeof(double), "multi-shift p"));
   RCHK(get((void**)&W.w, blk * sizeof(double), "multi-shift w"));
   if (combining)
@@ -805,7 +804,11 @@ rafeast_status alloc_ms_work(rafeast_plan_s* P, int nz, int k, MsWork& W,
   RCHK(get((void**)&c.est, cs * sizeof(double), "ms est"));
   RCHK(get((void**)&c.sc, 3 * kMsDefer * cs * sizeof(cpx<double>), "ms deferred scalars"));
   RCHK(get((void**)&c.on, kMsDefer * cs * sizeof(int), "ms deferred flags"));
-  return RAFEAST_OK;
+  // the deferred residuals last: without room for them the engine runs with one
+  const rafeast_status s = get((void**)&W.r, kMsDefer * blk * sizeof(double), "multi-shift r");
+  if (s != RAFEAST_OOM) return s;
+  W.defer = 1;
+  return get((void**)&W.r, blk * sizeof(double), "multi-shift r");
 }
 
 // The multi-shift seed: A - s I is positive definite for s below the
