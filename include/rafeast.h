@@ -329,6 +329,22 @@ int32_t rafeast_plan_engine(rafeast_plan_t plan);
 rafeast_status rafeast_plan_tuning(rafeast_plan_t plan, int32_t* chosen, int32_t* count,
                                    int32_t* cand, float* ms, int32_t max);
 
+/* Teams of the resident engine (FP32_REFINED plans with eight slots a thread):
+ * the systems that are expected to run long after the others are finished by
+ * four workgroups each.  Out: *planned, the systems of a rafeast_solve's filter
+ * step that have a team (0: none); *set_out and *redone, over all solves and
+ * rafeast_shifted_solve calls since the plan was made, the systems that teams
+ * have continued, and those whose team did not set out (its workgroups did not
+ * all run at once, on a device busy with other work) and which one workgroup
+ * solved from their start instead.  A team's sums are formed in another order
+ * than one workgroup's, so a system's solution depends on which solved it, within
+ * its tolerance.  RAFEAST_TEAM_WAIT=t in the environment when the plan is made
+ * is how long a team's workgroups wait for each other, in units of 10 ns (10^8
+ * by default; negative: no team sets out).  Errors: INVALID_ARG for a null
+ * pointer. */
+rafeast_status rafeast_plan_teams(rafeast_plan_t plan, int32_t* planned, int32_t* set_out,
+                                  int32_t* redone);
+
 /* Reverse Cuthill-McKee order of the graph of A (host only, needs no
  * device): per connected component, breadth-first search from a
  * pseudo-peripheral vertex (George-Liu), neighbours by increasing degree, the
@@ -440,8 +456,11 @@ rafeast_status rafeast_gaussian(rafeast_plan_t plan, int32_t w, uint64_t seed, d
  * Members too large for the resident engine whose engine is AUTO run the
  * multi-shift engine in FP64 (others the engine they name), after that
  * launch, concurrently with each other.  The Rayleigh-Ritz,
- * combination and CholQR2 steps run per member.  Each member computes
- * exactly what rafeast_solve computes for it.
+ * combination and CholQR2 steps run per member.  Each member's results are
+ * those of rafeast_solve up to the rounding of its shifted solves: the shared
+ * launch has one workgroup a system, where rafeast_solve gives some systems a
+ * team (rafeast_plan_teams; with RAFEAST_RESIDENT_SLOTS set it does not, and the
+ * sums are the same for equal slot counts).
  * ------------------------------------------------------------------------- */
 
 /* Plans count >= 1 problems: A[g] with prm[g] (host arrays of count).  All

@@ -338,8 +338,8 @@ __device__ __forceinline__ const ResGraph* const_graph(const ResGraph* graphs, i
 //
 // What bounds it is the latency of the exchanges (of about 14,000 clocks an
 // iteration, 3,000 for each sum and 3,000 for the residuals).  knn n = 8000,
-// FP32: an iteration takes 6.5 us of four workgroups, 9.6 us of one; 64
-// systems of 4 shifts 14.8 -> 11.6 ms.  With four slots a thread (n = 3000) it
+// FP32: an iteration takes 5.65 us of four workgroups (64 teams), 9.3 us of one
+// (64 systems and 256 alike); 64 systems of 4 shifts 14.1 -> 11.2 ms.  With four slots a thread (n = 3000) it
 // takes 5.4 us of four workgroups and 4.6 us of one, so those have no teams.
 typedef unsigned long long u64;
 constexpr int kTeamStride = 80;   // words of a team's ctl: two sets of kTeamSize * 8, then
@@ -505,7 +505,8 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_team(CocgTeams T, ResGraph
   int& s_go = *reinterpret_cast<int*>(&red[0][0][0]);
   if (threadIdx.x == 0) {
     u64* c = team_ctl(T, team);
-    if (atomicAdd(c + kTeamHere, 1ull) == kTeamSize - 1) atomicCAS(c + kTeamGo, 0ull, 1ull);
+    if (atomicAdd(c + kTeamHere, 1ull) == kTeamSize - 1 && T.wait >= 0)
+      atomicCAS(c + kTeamGo, 0ull, 1ull);
     const long long t0 = wall_clock64();
     u64 go;
     while ((go = agent_get(c + kTeamGo)) == 0) {
@@ -522,6 +523,7 @@ __global__ __launch_bounds__(kResThreads) void k_cocg_team(CocgTeams T, ResGraph
   const int go = s_go;
   __syncthreads();
   if (go != 1) return;
+  if (m == 0 && threadIdx.x == 0) atomicAdd(&G.stats[2], 1);
   const double tol2 = G.tol * G.tol;
   TeamState ts = *reinterpret_cast<const TeamState*>(team_buf(T, team, npad));
   cpx<double>* XH = reinterpret_cast<cpx<double>*>(team_buf(T, team, npad) + kTeamHead +
@@ -1226,6 +1228,8 @@ __device__ __forceinline__ void cocg_items(
       if (resid_out) resid_out[ocol] = last_res;
       if (nref) atomicAdd(&stats[0], nref);
       if (nbd > 3) atomicAdd(&stats[1], 1);
+      if constexpr (TEAM)
+        if (teams.redo) atomicAdd(&stats[3], 1);
     }
     // A barrier between this thread-0 block and the thread-0 fetch of the
     // next item: without it the compiler may merge the two blocks and send
@@ -1347,7 +1351,7 @@ int cocg_plan_teams(const std::vector<int>& items, const double* zs, double lo, 
   team_of.clear();
   done = 0.0;
   if (rpt != 8 || num_cu < 64 || nitems < 1 || !(hi > lo)) return 0;
-  const double speed = 1.7;  // a team's against one workgroup's
+  const double speed = 9.3 / 5.65;  // a team's against one workgroup's (above)
   std::vector<double> cost(nitems);
   for (int i = 0; i < nitems; ++i) {
     const int j = items[3 * i + 1];

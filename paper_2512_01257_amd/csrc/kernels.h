@@ -150,7 +150,8 @@ struct ResGraph {
   const double* zs = nullptr;           // shifts (re, im)
   int* iters = nullptr;                 // [nz kcols] iterations per system
   double* resid = nullptr;              // nullable [nz kcols] final relative true residual
-  int* stats = nullptr;                 // [2]: continued checks, breakdowns (accumulated)
+  int* stats = nullptr;                 // accumulated: [0] continued checks, [1] breakdowns, and
+                                        //   [2] teams that set out, [3] their systems solved without
   double tol = 0.0;                     // relative residual tolerance of this graph's systems
 };
 
@@ -163,7 +164,8 @@ struct CocgTeams {
   const int* team_of = nullptr;       // [nitems] team of an item (-1: none)
   int leave_at = 0;                   // iteration
   int redo = 0;                       // the launch solves what teams did not
-  long long wait = 0;                 // for a team's members to run: 100 MHz ticks
+  long long wait = 0;                 // for a team's members to run: 100 MHz ticks (negative:
+                                      //   none sets out)
   unsigned long long* ctl = nullptr;  // cocg_team_ctl_words(nteam) words, zero at the launch
   unsigned long long* buf = nullptr;  // cocg_team_buf_words(max_n, nteam) words
 };

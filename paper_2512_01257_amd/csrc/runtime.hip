@@ -127,7 +127,7 @@ struct rafeast_plan_s {
   std::vector<int> h_items;  // the same
   int* d_counter = nullptr;  // 1
   int* d_iters = nullptr;    // nc m0
-  int* d_stats = nullptr;    // 2
+  int* d_stats = nullptr;    // 2 of a solve, 2 of the plan's teams
   int* d_flag = nullptr;     // 3: one Cholesky status per CholQR pass
   int* d_sel = nullptr;      // m0
   void* d_xhi = nullptr;     // FP64 solution scratch of the resident COCG engine
@@ -2155,7 +2155,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
   PRCHK(dalloc(P, &P->d_items, 3 * (size_t)P->nitems, "items"));
   PRCHK(dalloc(P, &P->d_counter, 1, "counter"));
   PRCHK(dalloc(P, &P->d_iters, (size_t)P->nitems, "iters"));
-  PRCHK(dalloc(P, &P->d_stats, 2, "stats"));
+  PRCHK(dalloc(P, &P->d_stats, 4, "stats"));
   PRCHK(dalloc(P, &P->d_flag, 3, "flag"));
   PRCHK(dalloc(P, &P->d_sel, P->m0, "sel"));
   if (P->engine == RAFEAST_ENGINE_RESIDENT) {
@@ -2211,7 +2211,7 @@ static rafeast_status plan_create(const rafeast_csr* A, const DenseSpec* D,
     }
   }
   if (P->engine == RAFEAST_ENGINE_DIRECT) PRCHK(band_factor_shifts(P));
-  PCHK(hipMemset(P->d_stats, 0, 2 * sizeof(int)));
+  PCHK(hipMemset(P->d_stats, 0, 4 * sizeof(int)));
   PCHK(hipDeviceSynchronize());
 #undef PCHK
 #undef PRCHK
@@ -2262,6 +2262,18 @@ rafeast_status rafeast_plan_tuning(rafeast_plan_t P, int32_t* chosen, int32_t* c
     cand[i] = P->tune_cand[i];
     ms[i] = P->tune_ms[i];
   }
+  return RAFEAST_OK;
+}
+
+rafeast_status rafeast_plan_teams(rafeast_plan_t P, int32_t* planned, int32_t* set_out,
+                                  int32_t* redone) {
+  if (!P || !planned || !set_out || !redone) return RAFEAST_INVALID_ARG;
+  int counts[2] = {0, 0};
+  HIPCHK(P, hipMemcpyAsync(counts, P->d_stats + 2, sizeof(counts), hipMemcpyDeviceToHost, P->st));
+  HIPCHK(P, hipStreamSynchronize(P->st));
+  *planned = P->team.nteam;
+  *set_out = counts[0];
+  *redone = counts[1];
   return RAFEAST_OK;
 }
 

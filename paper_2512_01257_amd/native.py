@@ -116,6 +116,8 @@ def lib():
     L.rafeast_plan_tuning.argtypes = [P, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                       C.POINTER(C.c_int32), C.POINTER(C.c_float), C.c_int32]
     L.rafeast_plan_tuning.restype = C.c_int
+    L.rafeast_plan_teams.argtypes = [P] + [C.POINTER(C.c_int32)] * 3
+    L.rafeast_plan_teams.restype = C.c_int
     L.rafeast_rcm_order.argtypes = [C.POINTER(Csr), C.POINTER(C.c_int32)]
     L.rafeast_rcm_order.restype = C.c_int
     L.rafeast_pc_param_count.argtypes = []
@@ -416,6 +418,14 @@ class Plan:
         ms = (C.c_float * 8)()
         self._check(lib().rafeast_plan_tuning(self._h, C.byref(ch), C.byref(cnt), cand, ms, 8))
         return dict(chosen=ch.value, candidates=[(cand[i], ms[i]) for i in range(min(cnt.value, 8))])
+
+    @property
+    def teams(self):
+        """rafeast_plan_teams: systems of a solve with a team, and of all calls so
+        far those that teams continued and those solved without their team."""
+        n = [C.c_int32() for _ in range(3)]
+        self._check(lib().rafeast_plan_teams(self._h, *(C.byref(x) for x in n)))
+        return dict(zip(("planned", "set_out", "redone"), (x.value for x in n)))
 
     @property
     def engine(self):

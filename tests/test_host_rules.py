@@ -152,3 +152,55 @@ def test_band_width(tmp_path):
 """)
     wide, own = ["31", "31", "31", "31", "500"], ["0", "1", "30", "31", "500"]
     assert got == wide + wide + own + own
+
+
+def test_team_planning(tmp_path):
+    # shifts of a half circle around the low end of [0, 20]: the one nearest the
+    # spectrum takes four times the others' steps
+    out = run(tmp_path, """
+  const double zs[] = {0.0567, 0.0062, 0.0007, 0.0062, 0.0141, 0.0247, 0.0433, 0.0247};
+  const int order[] = {0, 1, 3, 2};
+  auto plan = [&](int shifts, int k, int cu, int rpt, bool same) {
+    std::vector<int> items, of;
+    for (int j = 0; j < shifts; ++j)
+      for (int i = 0; i < k; ++i) {
+        items.push_back(0);
+        items.push_back(same ? 0 : order[j]);
+        items.push_back(i);
+      }
+    double done = -1.0;
+    const int n = cocg_plan_teams(items, zs, 0.001, 19.76, cu, rpt, of, done);
+    int bad = n > 0 && (int)of.size() != shifts * k;
+    for (size_t i = 0; i < of.size(); ++i) bad += of[i] != ((int)i < n ? (int)i : -1);
+    std::printf("%d %d %d %d\\n", n, bad, done > 0.0,
+                done > 0.0 ? cocg_team_iteration(done, 1e-6) : 0);
+  };
+  plan(4, 64, 256, 8, false);
+  plan(4, 10, 256, 8, false);
+  plan(4, 64, 256, 4, false);
+  plan(4, 64, 32, 8, false);
+  plan(4, 64, 256, 8, true);
+  plan(4, 200, 256, 8, false);
+  plan(1, 1, 256, 8, false);
+""")
+    rows = [tuple(map(int, ln.split())) for ln in out]
+    assert all(bad == 0 for _, bad, _, _ in rows)
+    full, few, slots, small, alike, many, single = rows
+    # the hardest shift's systems, left when the others are done (343 to 377 steps)
+    assert full[0] == 64 and 300 <= full[3] <= 420
+    # few systems: CUs for teams of all at once
+    assert few[0] == 40
+    # four slots a thread, a small device, equal shifts: no teams; more systems of
+    # the hardest shift than half the CUs: none either; one system: its team starts
+    # at once or there is none
+    assert slots[0] == small[0] == alike[0] == many[0] == 0
+    assert single[0] in (0, 1)
+
+
+def test_plan_teams_refuses_null_pointers():
+    import ctypes as C
+
+    from paper_2512_01257_amd import native
+
+    n = C.c_int32()
+    assert native.lib().rafeast_plan_teams(None, C.byref(n), C.byref(n), C.byref(n)) == 1
