@@ -213,9 +213,11 @@ __device__ __forceinline__ int sweep_block(v4d& cr, v4d& ci, zc (*rowbuf)[2][kBB
       }
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
+        zc u{0.0, 0.0};
+        cfma(u, b0[v], t0);
+        cfma(u, b1[v], t1);
         zc a{ck0 || ck1 ? 0.0 : cr[v], ck0 || ck1 ? 0.0 : ci[v]};
-        cfma(a, zc{-b0[v].re, -b0[v].im}, t0);
-        cfma(a, zc{-b1[v].re, -b1[v].im}, t1);
+        a = csub(a, u);
         if (v == vk && mine) a = (lk & 1) ? t1 : t0;
         cr[v] = a.re;
         ci[v] = a.im;
