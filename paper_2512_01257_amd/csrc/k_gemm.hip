@@ -10,8 +10,9 @@
 // operand fragment read from LDS feeds several MFMAs (TN = 4 in FP32, 2 in
 // FP64).  The inner dimension advances in
 // steps of BK, 32 in FP32 and 16 in FP64: the step's A (128 x BK) and B (BK x
-// 32 TN) panels are staged in LDS (two buffers; the next step's global loads are issued before the
-// current step's MFMAs and stored after them, one barrier per step).  A may
+// 32 TN) panels are staged in LDS (two buffers; the next step's global loads are
+// issued before the current step's MFMAs and stored before or after the last of
+// them, one barrier per step).  A may
 // be stored by rows or by columns (op(A)(i, k) at A[i lda + k] or
 // A[k lda + i]); B and C by rows.  Products with a long inner dimension and
 // few output tiles are split into chunks of the inner dimension (grid.z), each
@@ -75,12 +76,21 @@ struct Mfma<float> {
 // takes it unless C is smaller than a tile and cuts vectors).  part != nullptr:
 // chunk z covers inner indices [z kc, min(K, (z + 1) kc)) and its
 // raw product goes to part + z M N (row-major, ld N); otherwise C is written.
+// Two waves a SIMD are asked for (LDS allows two or three): told so, the compiler
+// keeps the accumulators in the VGPRs that the MFMAs write; else it splits them
+// over AGPRs, with copies in every step, and the element form of A by rows took
+// more than half of a SIMD's registers, one wave (us before and with it: FP64
+// 8192 x 480 x 8192 A by rows 1301 and 1157, by columns 1207 and 1140, 5003 x 334
+// x 4002 374 and 313; FP32 65536 x 117 x 1024 187 and 167).  The widest vector
+// form of A by rows in FP32 is faster as the compiler lays it out (8192 x 1024 x
+// 8192 1070 and 1103).
 template <typename T, bool ACOL, int BK, int VEC, int TN>
-__global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
-                                              const T* __restrict__ A, int64_t lda,
-                                              const T* __restrict__ B, int64_t ldb,
-                                              T* __restrict__ C, int64_t ldc, T alpha, T beta,
-                                              T* __restrict__ part) {
+constexpr int kGemmWaves = sizeof(T) == 4 && !ACOL && VEC > 1 && TN == 4 ? 1 : 2;
+
+template <typename T, bool ACOL, int BK, int VEC, int TN>
+__global__ __launch_bounds__(kGT, (kGemmWaves<T, ACOL, BK, VEC, TN>)) void k_gemm(
+    int M, int N, int K, int kc, const T* __restrict__ A, int64_t lda, const T* __restrict__ B,
+    int64_t ldb, T* __restrict__ C, int64_t ldc, T alpha, T beta, T* __restrict__ part) {
   // Rows are padded so that the four rows a fragment read touches start 16
   // elements apart modulo the banks (every bank pair once), and by a whole
   // number of 16-byte words, so that a panel stored along its rows is stored
@@ -150,10 +160,11 @@ __global__ __launch_bounds__(kGT) void k_gemm(int M, int N, int K, int kc,
   // The fragments of sub-step ks + 4 are read from LDS while the MFMAs of
   // sub-step ks issue (two register sets), so LDS latency overlaps the
   // matrix work.
-  // FP32 stores the next step's panels before the last sub-step's MFMAs, which
-  // cover them (8192 x 480 x 8192, A by columns: 640 -> 624 us; in FP64 4%
-  // slower, so it stores after them).
-  constexpr bool kStoreInStep = sizeof(T) == 4;
+  // The next step's panels are stored before the last sub-step's MFMAs, which
+  // cover them (8192 x 480 x 8192, us after and before: FP64 A by columns 1143
+  // and 1105, by rows 1159 and 1109; FP32 by rows 602 and 600), but after them in
+  // FP32 with A by columns (580 and 594).
+  constexpr bool kStoreInStep = sizeof(T) == 8 || !ACOL;
   auto mfma_step = [&](int cur, bool next) {
     T a[2][4], b[2][TN];
     auto frag = [&](int set, int ks) {
@@ -388,11 +399,11 @@ hipError_t gemm(hipStream_t st, bool acol, int M, int N, int K, const T* A, int6
   T* part = S > 1 ? work : nullptr;
   dim3 grid((N + BN - 1) / BN, (M + kBM - 1) / kBM, S);
   // Vector loads, also of rows that start between 16-byte boundaries (us with
-  // element and vector loads: FP32 8191 x 480 x 8191 1850 and 609; FP64 5003 x
-  // 334 x 4002 912 and 425), unless C is smaller than a tile and cuts vectors:
+  // element and vector loads: FP32 8191 x 480 x 8191 678 and 600; FP64 5003 x
+  // 334 x 4002 358 and 312), unless C is smaller than a tile and cuts vectors:
   // no step of the vector form is whole then (us with vector and element form,
-  // aligned operands: FP32 4096 x 30 x 4096 78 and 43, 4096 x 126 x 4096 130 and
-  // 75; FP64 3000 x 17 x 1500 53 and 43).
+  // aligned operands: FP32 4096 x 30 x 4096 60 and 24, 4096 x 126 x 4096 110 and
+  // 54; FP64 3000 x 17 x 1500 35 and 23).
   constexpr int V = kGemmVecBytes / (int)sizeof(T) > 0 ? kGemmVecBytes / (int)sizeof(T) : 1;
   const bool vec = V > 1 && (N >= BN || N % V == 0) && (!acol || M >= kBM || M % V == 0);
   hipError_t e;
