@@ -91,7 +91,7 @@ def spmm_rate(reps=20):
     plan.close()
     nbytes = 12.0 * csr.nnz + 4.0 * (csr.n + 1) + 16.0 * csr.n * k
     gbs = nbytes / (ms * 1e-3) / 1e9
-    return {"kernel": "k_spmm_f64", "matrix": "7-point Laplacian of a 100^3 grid, n=1e6",
+    return {"kernel": "k_spmm_f64_x2<32>", "matrix": "7-point Laplacian of a 100^3 grid, n=1e6",
             "nnz": int(csr.nnz), "k": k, "avg_ms": round(ms, 4), "bytes_per_call": nbytes,
             "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(gbs / HBM_PEAK_GBS, 4)}
@@ -147,7 +147,7 @@ def gemm_shapes(reps=6):
     full width: the kernel matrix's K P (8192 x 8192 times 1024 columns) and
     the covariance's X V (1024 x 65536 data, 512 columns; the inner dimension
     split in chunks) and X^T T, in FP32 and FP64.  Wall-clock per call
-    (includes the call's workspace allocation and its synchronisation); the
+    (includes the call's synchronisation); the
     kernels' own durations come from rocprofv3."""
     import torch
 
@@ -1056,9 +1056,10 @@ def main():
         best = max(fp64["stream"]["value"], fp64["multishift"]["value"])
         fp64["fp32_speedup_over_best_fp64"] = round(value / best, 3)
 
-    # dominant kernel: the resident COCG engine (one launch per FEAST
-    # iteration), timed by the library with HIP events on its own stream.  It
-    # keeps every vector of a system in one CU's LDS and registers, so what
+    # dominant kernels: the resident COCG engine (three launches per FEAST
+    # iteration: all systems, the slowest ones by four workgroups each, and
+    # normally nothing left), timed together by the library with HIP events on
+    # its own stream.  It keeps every vector of a system on chip, so what
     # bounds it is on chip: each COCG iteration of a system streams the whole
     # matrix (FP32 value + 16-bit LDS offset per nonzero) from L2 into the CU.
     # Roof: 256 CUs x 64 B/clk L2->vL1D x 2.4 GHz.  The HBM-equivalent figure
@@ -1134,7 +1135,7 @@ def main():
         "cocg_iters_per_step": int(coliters / args.steps),
         "max_eig_error_vs_reference": err,
         "roofline": {
-            "kernel": "k_cocg_resident<float>",
+            "kernel": "k_cocg_leaving<float> + k_cocg_team (a filter step's launches)",
             "bound": "l2",
             "achieved": round(l2_achieved, 1),
             "peak": L2_PEAK_GBS,
@@ -1142,9 +1143,10 @@ def main():
             "frac": round(l2_achieved / L2_PEAK_GBS, 4),
             "traffic": traffic,
             "basis": "achieved = 6 B per nonzero (FP32 value, 16-bit LDS offset) per COCG "
-                     "column-iteration, streamed from L2 by the CU that owns the system, over "
-                     "the mean launch; peak = 256 CUs x 64 B/clk x 2.4 GHz; traffic = HBM "
-                     "bytes per launch (FETCH_SIZE + WRITE_SIZE)",
+                     "column-iteration, streamed from L2 by the CUs that hold the system, over "
+                     "a filter step's three launches, which launch figures here mean; peak = "
+                     "256 CUs x 64 B/clk x 2.4 GHz; traffic = bytes between L2 and the "
+                     "memory side (FETCH_SIZE + WRITE_SIZE)",
             "avg_launch_ms": round(avg_launch_s * 1e3, 4),
             "column_iterations_per_launch": round(coliters_per_launch, 1),
             "l2_bytes_per_launch": l2_bytes_per_launch,

@@ -108,7 +108,8 @@ enum { RAFEAST_ENGINE_DIRECT = 4 };  /* precision FP64 and CSR plans only: stand
                                         complex doubles for bandwidth b (OOM when the device
                                         cannot hold it; BREAKDOWN if a pivot vanishes); bands
                                         below 31 are widened to 31 where that takes at most
-                                        32 GiB and fits.  Reports zero COCG iterations.  Never chosen by AUTO */
+                                        32 GiB and fits.  Reports zero COCG iterations.
+                                        Never chosen by AUTO */
 
 /* rafeast_params.precond: preconditioner of the shifted solves. */
 enum { RAFEAST_PC_NONE = 0,       /* unpreconditioned COCG on the plan's engine */
@@ -380,10 +381,10 @@ rafeast_status rafeast_gram(rafeast_plan_t plan, int64_t n, int32_t k1, int32_t 
  * must not exceed 2^21 (INVALID_ARG otherwise, text in
  * rafeast_last_error(NULL)); it uses as many row chunks as rafeast_gram when
  * they fit, which they do for 256 k1 k2 <= 2^21 and, with Y = X, for k1 = k2
- * <= 96 (then the results are identical), fewer otherwise.  Every call on a device shares that device's scratch, so calls
- * that overlap on one device (concurrent streams or threads) race; serialise
- * them.  Errors: INVALID_ARG for null pointers, n < 1, k1 < 1, k2 < 1 or
- * ld < k; DEVICE for a HIP error. */
+ * <= 96 (then the results are identical), fewer otherwise.  Every call on a
+ * device shares that device's scratch, so calls that overlap on one device
+ * (concurrent streams or threads) race; serialise them.  Errors: INVALID_ARG
+ * for null pointers, n < 1, k1 < 1, k2 < 1 or ld < k; DEVICE for a HIP error. */
 rafeast_status rafeast_gram_noalloc(void* hip_stream, int64_t n, int32_t k1, int32_t k2,
                                     const double* X, int32_t ldx, const double* Y, int32_t ldy,
                                     double* G, int32_t ldg);

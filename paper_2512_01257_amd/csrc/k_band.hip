@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kStepThreads) void k_band_first(int n, int b, zc* _
 // What bounds it: the chain load - product - product - 32 pivots of that
 // workgroup, once per panel.  A scalar L D L^T needed two launches a panel, one
 // workgroup a shift for the block, its inverse triangle and all multipliers
-// (90 us) and the window after it (22 us); this launch takes 17.5 us
+// (90 us) and the window after it (22 us); this launch takes 16.4 us
 // (knn n = 8000, band 258, 8 shifts).  Two workgroups a CU are asked for: the
 // pivots' second form otherwise takes the registers of one of them (band 3000,
 // 4 shifts: 50 -> 63 ms).

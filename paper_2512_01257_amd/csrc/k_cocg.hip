@@ -339,8 +339,9 @@ __device__ __forceinline__ const ResGraph* const_graph(const ResGraph* graphs, i
 // What bounds it is the latency of the exchanges (of about 14,000 clocks an
 // iteration, 3,000 for each sum and 3,000 for the residuals).  knn n = 8000,
 // FP32: an iteration takes 5.65 us of four workgroups (64 teams), 9.3 us of one
-// (64 systems and 256 alike); 64 systems of 4 shifts 14.1 -> 11.2 ms.  With four slots a thread (n = 3000) it
-// takes 5.4 us of four workgroups and 4.6 us of one, so those have no teams.
+// (64 systems and 256 alike); 64 systems of 4 shifts 14.1 -> 11.2 ms.  With four
+// slots a thread (n = 3000) it takes 5.4 us of four workgroups and 4.6 us of one,
+// so those have no teams.
 typedef unsigned long long u64;
 constexpr int kTeamStride = 80;   // words of a team's ctl: two sets of kTeamSize * 8, then
 constexpr int kTeamLeft = 64;     //   1: its system was left to it,

@@ -19,7 +19,7 @@ def test_small_plans_are_small(gpu_lib):
         plans.append(gpu_lib.Plan(csr, 0.0, 0.5, 4, nc=1, q=0, p=4, engine="stream"))
     used = (before - torch.cuda.mem_get_info()[0]) / 16
     # three matrices of 192 x 192 doubles and small arrays, each rounded up by the
-    # driver; the list of rotations for 192 columns alone would be 11.7 MB
+    # runtime; the list of rotations for 192 columns alone would be 11.7 MB
     assert used <= 6e6, used
     # the reduced eigenproblem takes any k <= 192 all the same, also after smaller ones
     for k in (192, 9, 192):
