@@ -97,9 +97,13 @@ __global__ __launch_bounds__(kGT, (kGemmWaves<T, ACOL, BK, VEC, TN>)) void k_gem
   // in vectors; a transposed A is padded by four more, which spreads its stores
   // (eight rows of a vector's column over four banks) at two passes a read.
   // A pad of one element cost four passes a read (FP32, 8192 x 480 x 8192, A by
-  // columns: 654 -> 640 us; FP64 the same).
+  // columns: 654 -> 640 us; FP64 the same).  FP32 blocks of 64 columns with A by
+  // rows are padded less, so that three workgroups share a CU's LDS (65536 x 64 x
+  // 1024 84 -> 79 us, 8192 x 64 x 8192 90 -> 85; by columns the same).
   constexpr int BN = 32 * TN;                   // block tile width
-  constexpr int PA = kBM + 16 + (ACOL ? 0 : sizeof(T) == 4 ? 4 : 2), PB = BN + 16;
+  constexpr bool kLess = sizeof(T) == 4 && !ACOL && TN == 2;
+  constexpr int PA = kBM + (kLess ? 10 : ACOL ? 16 : sizeof(T) == 4 ? 20 : 18);
+  constexpr int PB = BN + (kLess ? 8 : 16);
   __shared__ __align__(16) T As[2][BK][PA];
   __shared__ __align__(16) T Bs[2][BK][PB];
   typedef typename Mfma<T>::Acc Acc;
